@@ -2,6 +2,8 @@
 // (FlowPrefill Eq. (2) with the causal mask and KV-cache reuse of Section 3.1; operator `attn`
 // of Section 5.1).  bf16 path: flash-style tiling, MFMA 32x32x16 for both contractions, fp32
 // online softmax.  fp32 path: one wave per (token, head), plain FMAs (debug).
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -50,7 +52,7 @@ namespace fp {
 //                            16 rows one read phase touches fall on 16 distinct bank groups
 //   V tile [4 blocks][D][16] the two 16-byte halves of channel row d swapped when d & 8
 // ------------------------------------------------------------------------------------------
-constexpr int kKT = 64;   // keys per tile
+constexpr int kKT = kAttnKeyTile;   // keys per tile
 
 __device__ __forceinline__ float xhalf_max(float v) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -112,12 +114,15 @@ __device__ __forceinline__ void dma_kv_tile(int j0, int tile, int total, const i
   }
 }
 
+// Floats of one (part, query head): 256 rows of unnormalised output, then {reference, sum} of every row.
+template <int D> __host__ __device__ constexpr int part_head_floats() { return 256 * (D + 2); }
+
 template <int D, int NW>
 __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ k_pool, const bf16* __restrict__ v_pool,
-    bf16* __restrict__ o, int n_q_heads, int n_kv_heads, int64_t kv_num_blocks, int layer,
-    const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ cached_lens,
-    const int32_t* __restrict__ block_tables, int max_blocks,
+    bf16* __restrict__ o, float* __restrict__ part_out, int n_q_heads, int n_kv_heads,
+    int64_t kv_num_blocks, int layer, const int32_t* __restrict__ cu_seqlens,
+    const int32_t* __restrict__ cached_lens, const int32_t* __restrict__ block_tables, int max_blocks,
     const int32_t* __restrict__ attn_items, float scale_log2) {
   static_assert(NW == 8, "work split assumes 8 waves");
   constexpr int BQW = NW * 32;
@@ -148,8 +153,11 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(
   const int rest = w / n_kv_heads;
   const int head = kvh * group + rest % group;
   const int item = rest / group;
-  const int s = attn_items[2 * item];
-  const int qt = attn_items[2 * item + 1];
+  const int s = attn_items[kAttnItemInts * item];
+  const int qt = attn_items[kAttnItemInts * item + 1];
+  const int t_first = attn_items[kAttnItemInts * item + 2];
+  const int n_tiles = attn_items[kAttnItemInts * item + 3];   // end of this item's key tiles
+  const int part = attn_items[kAttnItemInts * item + 4];
 
   const int seq_lo = cu_seqlens[s];
   const int n_new = cu_seqlens[s + 1] - seq_lo;
@@ -157,8 +165,6 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(
   const int total = cached + n_new;
   const int q_row0 = qt * BQW;
   const int wq0 = q_row0 + wave * 32;
-  const int kv_len = cached + min(n_new, q_row0 + BQW);
-  const int n_tiles = (kv_len + kKT - 1) / kKT;
   const int64_t width = (int64_t)(n_q_heads + 2 * n_kv_heads) * D;
   const int32_t* bt = block_tables + (int64_t)s * max_blocks;
   const int64_t block_elems = (int64_t)n_kv_heads * kKvBlock * D;           // one block, all kv heads
@@ -261,7 +267,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(
         mx1 = max3(mx1, sacc[1][r], sacc[1][r + 1]);
       }
       const float mx = xhalf_max(fmaxf(mx0, mx1));
-      // Key 0 is visible to every query, so mx is finite from the first tile on.
+      // The item's first key is visible to every query of the tile, so mx is finite from the first tile on.
       if (__any(m_use == -INFINITY || mx > lazy_gap)) {
         const float shift = m_use == -INFINITY ? mx : fmaxf(mx, 0.f);   // new reference - old reference
         const float base = m_use == -INFINITY ? 0.f : m_use;
@@ -320,15 +326,34 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(
   };
 
   if (loader) {
-    dma_tile(0, sK0, sV0);
-    if (1 < n_tiles) dma_tile(1, sK1, sV1);
+    dma_tile(t_first, sK0, sV0);
+    if (t_first + 1 < n_tiles) dma_tile(t_first + 1, sK1, sV1);
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
   tile_barrier();
-  for (int t = 0; t < n_tiles; t += 3) {
+  for (int t = t_first; t < n_tiles; t += 3) {
     tile_step(t, sK0, sV0, sK2, sV2);
     if (t + 1 < n_tiles) tile_step(t + 1, sK1, sV1, sK0, sV0);
     if (t + 2 < n_tiles) tile_step(t + 2, sK2, sV2, sK1, sV1);
+  }
+
+  if (part >= 0) {
+    // One part of the query tile's keys: the accumulators as they lie in the registers (whole 1 KB
+    // segments per store), then every row's exponent reference and sum; attn_merge_kernel reads the
+    // same layout.
+    if (wave_valid) {
+      float* dst = part_out + ((int64_t)part * n_q_heads + head) * part_head_floats<D>() + wave * (32 * D);
+#pragma unroll
+      for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+          *reinterpret_cast<f32x4*>(dst + ((i * 4 + a) * 64 + lane) * 4) =
+              f32x4{oacc[i][4 * a], oacc[i][4 * a + 1], oacc[i][4 * a + 2], oacc[i][4 * a + 3]};
+      const float l_tot = xhalf_sum(l_run + l_run2);
+      float* ml = part_out + ((int64_t)part * n_q_heads + head) * part_head_floats<D>() + BQW * D + (wave * 32 + lq) * 2;
+      ml[lh] = lh ? l_tot : m_use;
+    }
+    return;
   }
 
   // ---- normalise, stage through LDS, store rows with 16-byte accesses ----
@@ -358,6 +383,66 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(
       u32x4 v = *reinterpret_cast<const u32x4*>(stage + row * D + ((dch ^ (row & 7)) << 3));
       *reinterpret_cast<u32x4*>(o + (int64_t)(seq_lo + wq0 + row) * o_width + head * D + dch * 8) = v;
     }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Combines the parts of the query tiles that were cut over their keys (attention_part_tiles): with
+// reference m_i, sum l_i and unnormalised output O_i of part i, M = max m_i and w_i = 2^(m_i - M), the
+// output is sum_i w_i O_i / sum_i w_i l_i, parts in index order.  One workgroup per (query tile, head, 32
+// rows); the parts come back in the register layout they were left in, 1 KB per load instruction, and
+// the rows leave through LDS in whole 16-byte pieces.  Bound by reading the parts.
+// ------------------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ parts, bf16* __restrict__ o,
+                                                         int n_q_heads, const int32_t* __restrict__ cu_seqlens,
+                                                         const int32_t* __restrict__ merges) {
+  constexpr int CPR = D / 8;
+  __shared__ __attribute__((aligned(16))) bf16 stage[32 * D];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lq = lane & 31, lh = lane >> 5;
+  const int rows32 = blockIdx.x & 7;
+  const int head = (blockIdx.x >> 3) % n_q_heads;
+  const int32_t* mg = merges + kAttnMergeInts * ((blockIdx.x >> 3) / n_q_heads);
+  const int s = mg[0], q_row0 = mg[1] * 256 + rows32 * 32, first = mg[2], n_parts = mg[3];
+  const int seq_lo = cu_seqlens[s], n_new = cu_seqlens[s + 1] - seq_lo;
+  if (q_row0 >= n_new) return;                      // whole workgroup
+  const int64_t stride = (int64_t)n_q_heads * part_head_floats<D>();
+  const float* base = parts + first * stride + (int64_t)head * part_head_floats<D>();
+  const float* ml = base + 256 * D + (rows32 * 32 + lq) * 2;
+  float m_all = ml[0];
+  for (int p = 1; p < n_parts; ++p) m_all = fmaxf(m_all, ml[p * stride]);
+  float l_all = 0.f;
+  constexpr int NV = D / 32;                        // 16-byte pieces of the row block per thread: one 32 x 8 block each
+  f32x4 acc[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int p = 0; p < n_parts; ++p) {
+    const float w = __builtin_amdgcn_exp2f(ml[p * stride] - m_all);
+    l_all += w * ml[p * stride + 1];
+    const float* src = base + p * stride + rows32 * (32 * D);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(src + ((j * 4 + wave) * 64 + lane) * 4);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[j][b] += w * v[b];
+    }
+  }
+  const float inv = 1.0f / l_all;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int d = j * 32 + 8 * wave + 4 * lh;
+    bf16x4 v4;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) v4[b] = static_cast<bf16>(acc[j][b] * inv);
+    *reinterpret_cast<bf16x4*>(stage + lq * D + (((d >> 3) ^ (lq & 7)) << 3) + (d & 7)) = v4;
+  }
+  __syncthreads();
+  for (int idx = tid; idx < 32 * CPR; idx += 256) {
+    const int row = idx / CPR, dch = idx % CPR;
+    if (q_row0 + row < n_new)
+      *reinterpret_cast<u32x4*>(o + (int64_t)(seq_lo + q_row0 + row) * n_q_heads * D + head * D + dch * 8) =
+          *reinterpret_cast<const u32x4*>(stage + row * D + ((dch ^ (row & 7)) << 3));
   }
 }
 
@@ -416,6 +501,45 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(
 
 int attention_q_tile_rows(int head_dim) { (void)head_dim; return 8 * 32; }
 
+size_t attn_part_floats(const Geometry& g) { return (size_t)g.n_q_heads * 256 * (g.head_dim + 2); }
+
+// A workgroup walks its keys one tile after the other and a CU holds one workgroup, so a launch of few
+// query tiles over many keys -- a chunk of a long prompt -- keeps most CUs idle for the whole walk.  Cut
+// over the keys it ends when its longest part does, plus the merge.  Times in key tiles (about 1.4 us): a
+// part pays kPartCost on top of its keys (prologue, first loads, storing its output), the merge kMergeCost.
+// All heads of a query tile take equally long, so the 256 CUs count as 256 / heads places that each
+// take one (query tile, every head) at a time, longest first.  More than four such rounds balance
+// themselves.  No part is shorter than kMinPart tiles (its first key must be visible to all 256 queries
+// of the tile, which five tiles ensure).  512 tokens behind 15872 cached ones, 32 heads of 128: 365 us
+// whole (64 workgroups of 256 tiles), 130 + 8 us in four parts per query tile.
+int attention_part_tiles(const std::vector<int32_t>& tiles, int n_q_heads) {
+  constexpr int kPlaces = 256, kMaxPlaces = 64, kRounds = 4, kMinPart = 8, kPartCost = 3, kMergeCost = 6, kMaxParts = 16;
+  const int places = std::min(kMaxPlaces, std::max(1, kPlaces / n_q_heads));
+  if (tiles.empty() || (int)tiles.size() > kRounds * places || tiles[0] < 2 * kMinPart) return 0;
+  auto end_of = [&](int limit) {                    // when the last part of at most `limit` tiles is done
+    int at[kMaxPlaces] = {};
+    for (int32_t n : tiles) {
+      const int parts = limit ? (n + limit - 1) / limit : 1;
+      for (int p = 0; p < parts; ++p) {
+        int* soonest = std::min_element(at, at + places);
+        *soonest += (n + parts - 1) / parts + kPartCost;
+      }
+    }
+    return *std::max_element(at, at + places) + (limit ? kMergeCost : 0);
+  };
+  int best = 0, best_end = end_of(0);
+  best_end -= best_end / 16;                        // worth it from about a sixteenth on
+  int last = 0;
+  for (int parts = 2; parts <= kMaxParts; ++parts) {
+    const int limit = std::max(2 * kMinPart - 1, (tiles[0] + parts - 1) / parts);   // (then no part is below kMinPart)
+    if (limit == last || limit >= tiles[0]) continue;
+    last = limit;
+    const int end = end_of(limit);
+    if (end < best_end) { best_end = end; best = limit; }
+  }
+  return best;
+}
+
 template <int D>
 static void launch_attn_bf16(const void* qkv, const void* k_pool, const void* v_pool, void* o,
                              const Geometry& g, const BatchMeta& m, int layer, hipStream_t s) {
@@ -423,9 +547,12 @@ static void launch_attn_bf16(const void* qkv, const void* k_pool, const void* v_
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)D);
   dim3 grid((unsigned)((int64_t)m.n_attn_items * g.n_q_heads));
   attn_bf16_kernel<D, NW><<<grid, NW * 64, 0, s>>>(
-      (const bf16*)qkv, (const bf16*)k_pool, (const bf16*)v_pool, (bf16*)o, g.n_q_heads,
+      (const bf16*)qkv, (const bf16*)k_pool, (const bf16*)v_pool, (bf16*)o, m.attn_part, g.n_q_heads,
       g.n_kv_heads, g.kv_num_blocks, layer, m.cu_seqlens, m.cached_lens, m.block_tables,
       m.max_blocks, m.attn_items, scale_log2);
+  if (m.n_attn_merges > 0)
+    attn_merge_kernel<D><<<dim3((unsigned)((int64_t)m.n_attn_merges * g.n_q_heads * 8)), 256, 0, s>>>(
+        m.attn_part, (bf16*)o, g.n_q_heads, m.cu_seqlens, m.attn_merges);
 }
 
 template <int D>

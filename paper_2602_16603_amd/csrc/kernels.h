@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace fp {
 
 // Static geometry of the model that the kernels need.
@@ -25,13 +27,28 @@ struct BatchMeta {
   const int32_t* block_tables;  // device [n_seqs, max_blocks]
   const int32_t* kv_items;      // device [n_kv_items][2]  (seq, logical block) touched by new tokens
   int32_t n_kv_items;
-  const int32_t* attn_items;    // device [n_attn_items][2] (seq, query tile), longest first
+  const int32_t* attn_items;    // device [n_attn_items][kAttnItemInts], most keys first (bf16 path)
   int32_t n_attn_items;
+  const int32_t* attn_merges;   // device [n_attn_merges][kAttnMergeInts]: the query tiles cut over their keys
+  int32_t n_attn_merges;
+  float* attn_part;             // device: unnormalised outputs of the parts, attn_part_floats() per part
 };
+
+// An attention item is the work of one workgroup per query head: {sequence, query tile, first key tile, end key
+// tile, part}.  part < 0: the item covers every key of its query tile and writes the output; else it
+// leaves its unnormalised output as part number `part`, and the merge {sequence, query tile, first part,
+// number of parts} combines the parts of its query tile.
+constexpr int kAttnItemInts = 5, kAttnMergeInts = 4;
+constexpr int kAttnKeyTile = 64;
 
 // Rows of queries one attention workgroup owns on the bf16 path (the runtime sizes attn_items
 // with it).
 int attention_q_tile_rows(int head_dim);
+// Number of key tiles a part of a query tile should hold so that the launch ends soonest: `tiles` =
+// key tiles of every query tile, most first.  0: leave the query tiles whole.
+int attention_part_tiles(const std::vector<int32_t>& tiles, int n_q_heads);
+// Floats one part takes (all query heads).
+size_t attn_part_floats(const Geometry& g);
 
 void launch_to_residual(int dtype, const void* in, float* x, int64_t n_elems, hipStream_t s);
 void launch_rmsnorm(int dtype, const float* x, const void* gain, void* out, int64_t t, int64_t d,

@@ -576,7 +576,7 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
 
   // ---- host-side work lists ----
   const int bqw = fp::attention_q_tile_rows(sh.head_dim);
-  std::vector<int32_t> tok_seq((size_t)T), tok_pos((size_t)T), kv_items, attn_items;
+  std::vector<int32_t> tok_seq((size_t)T), tok_pos((size_t)T), kv_items, attn_items, attn_merges;
   struct Item { int32_t seq, qt, work; };
   std::vector<Item> items;
   for (int s = 0; s < n_seqs; ++s) {
@@ -589,13 +589,25 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
     }
     for (int32_t qt = 0; qt * bqw < n; ++qt) {
       const int32_t kv_len = c + std::min(n, (qt + 1) * bqw);
-      items.push_back(Item{s, qt, (kv_len + 63) / 64});
+      items.push_back(Item{s, qt, (kv_len + fp::kAttnKeyTile - 1) / fp::kAttnKeyTile});
     }
   }
   // Longest first: workgroups are dispatched in index order, so the heaviest causal tiles
   // start first and the short ones fill the tail.
   std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.work > b.work; });
-  for (const Item& it : items) { attn_items.push_back(it.seq); attn_items.push_back(it.qt); }
+  std::vector<int32_t> tiles;
+  if (sh.dtype == FP_DTYPE_BF16)
+    for (const Item& it : items) tiles.push_back(it.work);
+  const int part_tiles = fp::attention_part_tiles(tiles, sh.n_q_heads);
+  int32_t n_parts = 0;
+  for (const Item& it : items) {
+    const int parts = part_tiles ? (it.work + part_tiles - 1) / part_tiles : 1;
+    if (parts > 1) attn_merges.insert(attn_merges.end(), {it.seq, it.qt, n_parts, parts});
+    for (int p = 0; p < parts; ++p)
+      attn_items.insert(attn_items.end(), {it.seq, it.qt, (int32_t)((int64_t)it.work * p / parts),
+                                           (int32_t)((int64_t)it.work * (p + 1) / parts), parts > 1 ? n_parts + p : -1});
+    if (parts > 1) n_parts += parts;
+  }
 
   // ---- workspace layout ----
   const size_t e = m->elem;
@@ -628,8 +640,9 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
                o_mh = carve(moe ? pairs * 4 : 0), o_ma = carve(moe ? pairs * F * e : 0),
                o_my = carve(moe ? pairs * d * e : 0);
   const size_t o_sk = carve(sk_bytes);
+  const size_t o_ap = carve((size_t)n_parts * fp::attn_part_floats(m->geo) * 4);
   const size_t n_int = tok_seq.size() + tok_pos.size() + t->cu.size() + t->cached.size() +
-                       t->tables.size() + kv_items.size() + attn_items.size();
+                       t->tables.size() + kv_items.size() + attn_items.size() + attn_merges.size();
   const size_t o_int = carve((n_int + 16) * 4);
   fp_status st = acquire_workspace(m, off, (n_int + 16) * 4, &t->ws);
   if (st != FP_OK) {
@@ -659,7 +672,7 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
     return at;
   };
   const size_t a_seq = put(tok_seq), a_pos = put(tok_pos), a_cu = put(t->cu), a_cached = put(t->cached),
-               a_tab = put(t->tables), a_kv = put(kv_items), a_attn = put(attn_items);
+               a_tab = put(t->tables), a_kv = put(kv_items), a_attn = put(attn_items), a_merge = put(attn_merges);
   int32_t* dints = reinterpret_cast<int32_t*>(base + o_int);
   auto bail = [&](fp_status code) {
     (void)hipStreamSynchronize(m->stream);      // nothing of this task may still be in flight
@@ -684,7 +697,10 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
   t->meta.kv_items = dints + a_kv;
   t->meta.n_kv_items = (int32_t)(kv_items.size() / 2);
   t->meta.attn_items = dints + a_attn;
-  t->meta.n_attn_items = (int32_t)(attn_items.size() / 2);
+  t->meta.n_attn_items = (int32_t)(attn_items.size() / fp::kAttnItemInts);
+  t->meta.attn_merges = dints + a_merge;
+  t->meta.n_attn_merges = (int32_t)(attn_merges.size() / fp::kAttnMergeInts);
+  t->meta.attn_part = n_parts ? reinterpret_cast<float*>(base + o_ap) : nullptr;
 
   fp::launch_to_residual(sh.dtype, hidden_in, t->x, (int64_t)T * sh.hidden, m->stream);
   if ((he = hipGetLastError()) != hipSuccess)
