@@ -1,8 +1,8 @@
 // Dense projections of the prefill layer: C[M,N] = A[M,K] * W[N,K]^T (both operands K-major),
 // FlowPrefill Eq. (1) and the operators qkv_proj / o_proj / gate_up_proj / down_proj of
 // Section 5.1.  bf16 path: MFMA tiles with fp32 accumulation, LDS-staged and double-buffered (the
-// fast kernel on 16x16x32, the small-problem kernel on 32x32x16).  fp32 path: a plain LDS-tiled
-// FMA kernel (debug).
+// fast kernel on 16x16x32, the small-problem kernel on 32x32x16).  fp32 path (debug): MFMA tiles in
+// fp32 throughout.
 #include <algorithm>
 
 #include "common.h"
@@ -869,7 +869,156 @@ static void launch_bf16_cfg(const bf16* a, const bf16* w, void* c, int m, int n,
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 debug GEMM: 64x64 tile, 256 threads, 4x4 outputs per thread, K step 16, plain FMAs.
+// fp32 GEMM (debug path) on v_mfma_f32_16x16x4_f32: products and sums in fp32, 256 FLOP per clock and
+// CU.  256 threads = 2 x 2 waves, wave tile (16 TM) x (16 TN), K consumed 32 at a time through a ring
+// of three LDS stages filled by DMA two k-tiles ahead (128-byte rows, chunk c of row r at position
+// c ^ ((r >> 1) & 7): conflict-free for the 16-row fragment reads, as in the bf16 kernel).  The
+// instruction takes one k per lane quarter; a lane reads four consecutive k of its row with one
+// ds_read_b128 and step j of four multiplies the j-th of each quarter -- A and W are permuted over k
+// alike.  Chunks past K are fetched from outside the descriptor, so they read as zero (K % 4 == 0).
+// The matrix pipes bound it (157 TFLOP/s): 300 rows of the 8B shape's gate_up projection 2040 -> 630 us
+// (119 TFLOP/s, row padding included), down 2476 -> 381 us, against the plain FMA kernel below.
+// ------------------------------------------------------------------------------------------
+constexpr int kFK = 32;
+
+__device__ __forceinline__ void f32_dma(const float* panel, uint32_t bytes, float* lds_rows, uint32_t voff, int kbyte) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(panel_rsrc(panel, bytes), (__attribute__((address_space(3))) void*)lds_rows, 16,
+                                           voff, kbyte, 0, 0);
+}
+
+template <int TM, int TN, bool RESID>
+__global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restrict__ A,
+                                                            const float* __restrict__ W,
+                                                            float* __restrict__ C, int M, int N, int K,
+                                                            int tiles_m, int tiles_n) {
+  constexpr int BM = 32 * TM, BN = 32 * TN;
+  constexpr int IA = BM / 32, IW = BN / 32;          // DMA instructions (8 rows of 128 bytes) per wave and k-tile
+  constexpr int kWaitNewest = 0x0F70 | (IA + IW);    // vmcnt: all but the newest k-tile's
+  __shared__ __attribute__((aligned(1024))) float s0[(BM + BN) * kFK];
+  __shared__ __attribute__((aligned(1024))) float s1[(BM + BN) * kFK];
+  __shared__ __attribute__((aligned(1024))) float s2[(BM + BN) * kFK];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave & 1, wn = wave >> 1;
+  int tile_m, tile_n;
+  tile_of_workgroup(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+
+  const float* const panel_a = A + (int64_t)m0 * K;
+  const float* const panel_w = W + (int64_t)n0 * K;
+  const uint32_t bytes_a = (uint32_t)(min(BM, M - m0) * K * 4), bytes_w = (uint32_t)(min(BN, N - n0) * K * 4);
+  // Instruction i of this wave fills rows 8 (wave * IA + i) .. + 7; lane: row lane/8, chunk position lane%8.
+  uint32_t off_a[IA], off_w[IW];
+  int k_a[IA], k_w[IW];
+#pragma unroll
+  for (int i = 0; i < IA; ++i) {
+    const int row = 8 * (wave * IA + i) + (lane >> 3);
+    k_a[i] = 4 * ((lane & 7) ^ ((row >> 1) & 7));
+    off_a[i] = (uint32_t)((row * K + k_a[i]) * 4);
+  }
+#pragma unroll
+  for (int i = 0; i < IW; ++i) {
+    const int row = 8 * (wave * IW + i) + (lane >> 3);
+    k_w[i] = 4 * ((lane & 7) ^ ((row >> 1) & 7));
+    off_w[i] = (uint32_t)((row * K + k_w[i]) * 4);
+  }
+  const int kt_count = (K + kFK - 1) / kFK;
+  auto fetch = [&](int t, float* s) __attribute__((always_inline)) {
+    const int left = K - t * kFK;                    // past the last k-tile every chunk is outside: nothing to fetch
+#pragma unroll
+    for (int i = 0; i < IA; ++i)
+      f32_dma(panel_a, bytes_a, s + 8 * (wave * IA + i) * kFK, k_a[i] < left ? off_a[i] : kOffOutOfRange, t * kFK * 4);
+#pragma unroll
+    for (int i = 0; i < IW; ++i)
+      f32_dma(panel_w, bytes_w, s + (BM + 8 * (wave * IW + i)) * kFK, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * kFK * 4);
+  };
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int frag_row = lane & 15, quad = lane >> 4;
+  const int key = (frag_row >> 1) & 7;               // (16-row blocks: the block's first row does not change it)
+  auto step = [&](int t, const float* s, float* next) __attribute__((always_inline)) {
+    fetch(t + 2, next);                              // the stage every wave finished before the last barrier
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const int at = ((kk * 4 + quad) ^ key) * 4;
+      f32x4 fa[TM], fw[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        fa[i] = *reinterpret_cast<const f32x4*>(s + (wm * 16 * TM + i * 16 + frag_row) * kFK + at);
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        fw[j] = *reinterpret_cast<const f32x4*>(s + (BM + wn * 16 * TN + j * 16 + frag_row) * kFK + at);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[j][e], fa[i][e], acc[i][j], 0, 0, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);          // this wave is done with the stage ...
+    __builtin_amdgcn_s_waitcnt(kWaitNewest);         // ... and its share of the next one has landed
+    w4_barrier();
+  };
+  fetch(0, s0);
+  fetch(1, s1);
+  __builtin_amdgcn_s_waitcnt(kWaitNewest);
+  w4_barrier();
+  for (int t = 0; t < kt_count; t += 3) {
+    // Always three: up to two k-tiles of zeros at the end.  (With a branch between them the compiler
+    // waits for all DMA before it reads a stage.)
+    step(t, s0, s2);
+    step(t + 1, s1, s0);
+    step(t + 2, s2, s1);
+  }
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);              // the last (empty) fetches
+
+  // W is the row operand: accumulator [i][j] of a lane holds row m = 16 i + lane % 16 and the four
+  // consecutive columns 16 j + 4 (lane / 16) + (0..3).
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = m0 + wm * 16 * TM + i * 16 + frag_row;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + wn * 16 * TN + j * 16 + 4 * quad;
+      if (m < M && n < N) {                          // N % 8 == 0: all four or none
+        float* c = C + (int64_t)m * N + n;
+        f32x4 v = acc[i][j];
+        if (RESID) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(c);
+#pragma unroll
+          for (int b = 0; b < 4; ++b) v[b] = x[b] + v[b];
+        }
+        *reinterpret_cast<f32x4*>(c) = v;
+      }
+    }
+  }
+}
+
+template <int TM, int TN, bool RESID>
+static void launch_f32_mfma(const float* a, const float* w, float* c, int m, int n, int k, hipStream_t s) {
+  const int tiles_m = (m + 32 * TM - 1) / (32 * TM), tiles_n = (n + 32 * TN - 1) / (32 * TN);
+  gemm_f32_mfma_kernel<TM, TN, RESID><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(a, w, c, m, n, k, tiles_m, tiles_n);
+}
+
+template <bool RESID>
+static void launch_f32(const float* a, const float* w, float* c, int64_t m, int64_t n, int64_t k, hipStream_t s) {
+  // A CU's tiles share its matrix pipes, so what counts is how many outputs the busiest of 256 CUs
+  // has, padding included; on a tie the larger tile, which reads its operands less often.
+  auto outputs = [&](int64_t bm, int64_t bn) { return (((m + bm - 1) / bm) * ((n + bn - 1) / bn) + 255) / 256 * bm * bn; };
+  const int64_t large = outputs(128, 128), middle = outputs(64, 64), small = outputs(32, 64);
+  if (large <= middle && large <= small) launch_f32_mfma<4, 4, RESID>(a, w, c, (int)m, (int)n, (int)k, s);
+  else if (middle <= small) launch_f32_mfma<2, 2, RESID>(a, w, c, (int)m, (int)n, (int)k, s);
+  else launch_f32_mfma<1, 2, RESID>(a, w, c, (int)m, (int)n, (int)k, s);
+}
+
+// ------------------------------------------------------------------------------------------
+// fp32 GEMM for operands that are not 16-byte aligned or too long for 32-bit offsets: 64x64 tile, 256 threads, 4x4 outputs per thread, K step 16, plain FMAs.
 // ------------------------------------------------------------------------------------------
 template <bool RESID>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A,
@@ -942,6 +1091,12 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
                  const GemmTail* tail) {
   if (m == 0 || n == 0) return;
   if (dtype == 0) {
+    const uintptr_t address = reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(c);
+    if (address % 16 == 0 && n % 4 == 0 && k % 4 == 0 && k <= (1 << 20) && (m + 31) / 32 * ((n + 63) / 64) <= INT32_MAX) {
+      if (residual) launch_f32<true>((const float*)a, (const float*)w, (float*)c, m, n, k, s);
+      else launch_f32<false>((const float*)a, (const float*)w, (float*)c, m, n, k, s);
+      return;
+    }
     dim3 grid((unsigned)((n + 63) / 64), (unsigned)((m + 63) / 64));
     if (residual)
       gemm_f32_kernel<true><<<grid, 256, 0, s>>>((const float*)a, (const float*)w, (float*)c,

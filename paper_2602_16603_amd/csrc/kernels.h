@@ -27,7 +27,7 @@ struct BatchMeta {
   const int32_t* block_tables;  // device [n_seqs, max_blocks]
   const int32_t* kv_items;      // device [n_kv_items][2]  (seq, logical block) touched by new tokens
   int32_t n_kv_items;
-  const int32_t* attn_items;    // device [n_attn_items][kAttnItemInts], most keys first (bf16 path)
+  const int32_t* attn_items;    // device [n_attn_items][kAttnItemInts], most keys first
   int32_t n_attn_items;
   const int32_t* attn_merges;   // device [n_attn_merges][kAttnMergeInts]: the query tiles cut over their keys
   int32_t n_attn_merges;

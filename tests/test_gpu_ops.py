@@ -341,3 +341,37 @@ def test_mfma_ceiling_diagnostic_reports_a_plausible_rate():
     assert 800.0 < rate < 2600.0
     with pytest.raises(B.FlowPrefillError):
         B.fp_diag_mfma_ceiling(0)
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("m,n,k", [(1, 8, 8), (31, 72, 40), (33, 64, 32), (300, 4096, 96), (65, 520, 72), (1024, 2056, 104), (1153, 5128, 136)])
+def test_fp32_gemm_tiles_and_alignment(m, n, k, residual, offset):
+    """The fp32 MFMA kernel on its three tiles (32x64, 64x64, 128x128: one row, one row more than a tile,
+    eight columns more; one, two, three and more k-tiles with tails of 8 to 32), and, one float off the
+    16-byte alignment, the plain kernel.  Rows before and behind the output stay untouched."""
+    B = _binding()
+
+    def put(t):
+        buf = torch.empty(t.numel() + 4, device="cuda")
+        view = buf[offset:offset + t.numel()].view(t.shape)
+        view.copy_(t)
+        return view
+
+    a = put(I.normal_tensor((m, k), 1.0, 51, torch.float32, "cuda"))
+    w = put(I.normal_tensor((n, k), 0.05, 52, torch.float32, "cuda"))
+    c = put(torch.full((m + 2, n), 7.0, device="cuda"))
+    if residual:
+        c[1:m + 1] = I.normal_tensor((m, n), 1.0, 53, torch.float32, "cuda")
+    x0 = c[1:m + 1].cpu().double()
+    print(f"fp32 gemm m={m} n={n} k={k} residual={residual} offset={offset}", flush=True)
+    torch.cuda.synchronize()
+    B.fp_op_gemm(0, a.data_ptr(), w.data_ptr(), c[1:].data_ptr(), m, n, k, residual)
+    torch.cuda.synchronize()
+    ref = O.linear(a.cpu(), w.cpu())
+    if residual:
+        ref = ref + x0
+    # k <= 136 fp32 products and sums: at most (k + 1) roundings of 2^-24 of the sum of magnitudes, itself
+    # under 12 sqrt(k) times an element's spread (about 1e-4 of the largest result); observed 1e-7 .. 5e-7.
+    assert max_rel_err(c[1:m + 1], ref) <= 1e-5
+    assert torch.all(c[0] == 7.0) and torch.all(c[m + 1] == 7.0)
