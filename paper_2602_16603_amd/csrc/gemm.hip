@@ -203,7 +203,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
 // ------------------------------------------------------------------------------------------
 constexpr int kWaitVm0 = 0x0F70;   // s_waitcnt vmcnt(0)           (expcnt/lgkmcnt untouched)
 constexpr int kWaitVm1 = 0x0F71;   // s_waitcnt vmcnt(1)
-constexpr int kWaitVm13 = 0x0F7D;  // s_waitcnt vmcnt(13)
+constexpr int kWaitVm12 = 0x0F7C;  // s_waitcnt vmcnt(12)
+constexpr int kWaitVm24 = 0x4F78;  // s_waitcnt vmcnt(24)
 constexpr int kWaitVm17 = 0x4F71;  // s_waitcnt vmcnt(17)
 constexpr int kWaitLgkm0 = 0xC07F; // s_waitcnt lgkmcnt(0)         (vmcnt/expcnt untouched)
 constexpr int kWarmAhead = 3;      // k-tiles between the L2 warm-up load and the DMA of the same lines
@@ -297,7 +298,11 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // the chip is occupied with half as many K ranges -- half the fp32 partial sums through memory,
 // and the fused gate_up projection of a 256-token request needs no K ranges at all (measured: a
 // 256-token request through the 8B-shaped stack 7.3 -> 6.5 ms; from three row tiles on the MFMAs
-// bound the launch and the wide tile's operand reuse wins).
+// bound the launch and the wide tile's operand reuse wins).  Such a launch streams its weights from
+// HBM, every line for one or two workgroups only, and what a CU gets is its bytes in flight per
+// latency: the narrow tile's stages are three (144 KB, filled two k-tiles ahead) instead of two with
+// L2 warm-up.  Cold weights, 256 tokens of the 8B shape: gate_up 79 -> 66 us, down 49 -> 45; 50 tokens:
+// 74 -> 55, 40 -> 31; 512 tokens: down 76 -> 67.  (The wide tile's three stages would take 192 KB.)
 template <int EPI, bool GROUPED = false, int NJ = 8>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restrict__ A,
                                                            const bf16* __restrict__ W,
@@ -313,9 +318,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   constexpr int BM = 256, BN = SWIGLU ? WR / 2 : WR; // output columns per tile
   __shared__ __attribute__((aligned(1024))) bf16 sA0[BM * kBK];
   __shared__ __attribute__((aligned(1024))) bf16 sA1[BM * kBK];
-  __shared__ __attribute__((aligned(1024))) bf16 sB0[256 * kBK];   // (32 KB each also when WR = 128: the epilogue
-  __shared__ __attribute__((aligned(1024))) bf16 sB1[256 * kBK];   //  stages 32 KB per wave through them)
-  __shared__ __attribute__((aligned(256))) uint32_t sWarm[4 * 64];   // landing pad of the L2 warm-up loads
+  __shared__ __attribute__((aligned(1024))) bf16 sB0[256 * kBK];   // (32 KB also when WR = 128: the epilogue
+  __shared__ __attribute__((aligned(1024))) bf16 sB1[(NJ == 8 ? 256 : WR) * kBK];   //  stages 32 KB per wave through the first four)
+  __shared__ __attribute__((aligned(1024))) bf16 sA2[NJ == 8 ? 8 : BM * kBK];      // third stage of the narrow tile
+  __shared__ __attribute__((aligned(1024))) bf16 sB2[NJ == 8 ? 8 : WR * kBK];
+  __shared__ __attribute__((aligned(256))) uint32_t sWarm[NJ == 8 ? 4 * 64 : 4];   // landing pad of the L2 warm-up loads
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -394,8 +401,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const __amdgpu_buffer_rsrc_t rsrc_none = panel_rsrc(A, 0u);
   bf16* const dA0 = sA0 + 64 * wave * kBK;
   bf16* const dA1 = sA1 + 64 * wave * kBK;
+  bf16* const dA2 = sA2 + 64 * wave * kBK;
   bf16* const dB0 = sB0 + Q * wave * kBK;
   bf16* const dB1 = sB1 + Q * wave * kBK;
+  bf16* const dB2 = sB2 + Q * wave * kBK;
 
   // L2 warm-up sources: wave 0 lane l -> A row 4l + share, wave 1 lane l < 32 -> W-stage row 8l +
   // share (SwiGLU: stage row r is gate row n0 + Q*(r/2Q) + r%Q, or the up row N + that, for
@@ -427,6 +436,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const int pch0 = ((0 + quad) ^ key) << 3, pch1 = ((4 + quad) ^ key) << 3;
   const bf16* const rA0 = sA0 + (wm * 128 + frag_row) * kBK;
   const bf16* const rA1 = sA1 + (wm * 128 + frag_row) * kBK;
+  const bf16* const rA2 = sA2 + (wm * 128 + frag_row) * kBK;
+  const bf16* const rB2 = sB2 + (wn * (WR / 2) + frag_row) * kBK;
   const bf16* const rB0 = sB0 + (wn * (WR / 2) + frag_row) * kBK;
   const bf16* const rB1 = sB1 + (wn * (WR / 2) + frag_row) * kBK;
 
@@ -434,49 +445,50 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   __builtin_amdgcn_raw_ptr_buffer_load_lds((u) < kt_count ? rsrc_warm : rsrc_none,                            \
                                            (__attribute__((address_space(3))) void*)warm, 4, voff_warm,       \
                                            kbyte0 + (u) * kBK * 2 + ((warm_id - (u)) & warm_mask) * K * 2, 0, 0)
-  // Prologue: k-tile 0 into stage 0 (awaited), k-tile 1 into stage 1 (in flight), then one warm-up
-  // load, so that "all but one" is the right wait from the first barrier on.
-#pragma unroll
-  for (int s = 0; s < 8; ++s) w4_dma(rsrc_a, dA0 + s * 8 * kBK, voff_a[s], kbyte0);
-#pragma unroll
-  for (int s = 0; s < NJ; ++s) w4_dma(rsrc_w, dB0 + s * 8 * kBK, voff[s], kbyte0);
-  {
-    const __amdgpu_buffer_rsrc_t ra1 = kt_count > 1 ? rsrc_a : rsrc_none, rw1 = kt_count > 1 ? rsrc_w : rsrc_none;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) w4_dma(ra1, dA1 + s * 8 * kBK, voff_a[s], kbyte0 + kBK * 2);
-#pragma unroll
-    for (int s = 0; s < NJ; ++s) w4_dma(rw1, dB1 + s * 8 * kBK, voff[s], kbyte0 + kBK * 2);
-  }
-  W4_WARM(kWarmAhead - 1);
-  __builtin_amdgcn_sched_barrier(0);
-  // Cleared while the first k-tile is on its way.
   f32x4_acc acc[8][NJ];
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));   // materialise the zeros here, not at first use
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(NJ == 8 ? kWaitVm17 : kWaitVm13);   // all but k-tile 1 (8 + NJ) and the warm-up load
-  w4_barrier();
   W4Frags<NJ> f0, f1;
+  if constexpr (NJ == 8) {
+    // Prologue: k-tile 0 into stage 0 (awaited), k-tile 1 into stage 1 (in flight), then one warm-up
+    // load, so that "all but one" is the right wait from the first barrier on.
 #pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    if (s < NJ) f0.b[s] = *reinterpret_cast<const bf16x8*>(rB0 + s * 16 * kBK + pch0);
-    f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
-  }
-  __builtin_amdgcn_sched_barrier(0);
+    for (int s = 0; s < 8; ++s) w4_dma(rsrc_a, dA0 + s * 8 * kBK, voff_a[s], kbyte0);
+#pragma unroll
+    for (int s = 0; s < NJ; ++s) w4_dma(rsrc_w, dB0 + s * 8 * kBK, voff[s], kbyte0);
+    {
+      const __amdgpu_buffer_rsrc_t ra1 = kt_count > 1 ? rsrc_a : rsrc_none, rw1 = kt_count > 1 ? rsrc_w : rsrc_none;
+#pragma unroll
+      for (int s = 0; s < 8; ++s) w4_dma(ra1, dA1 + s * 8 * kBK, voff_a[s], kbyte0 + kBK * 2);
+#pragma unroll
+      for (int s = 0; s < NJ; ++s) w4_dma(rw1, dB1 + s * 8 * kBK, voff[s], kbyte0 + kBK * 2);
+    }
+    W4_WARM(kWarmAhead - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    // Cleared while the first k-tile is on its way.
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));   // materialise the zeros here, not at first use
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(kWaitVm17);   // all but k-tile 1 (8 + NJ) and the warm-up load
+    w4_barrier();
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      if (s < NJ) f0.b[s] = *reinterpret_cast<const bf16x8*>(rB0 + s * 16 * kBK + pch0);
+      f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 
-  // k-tile t on stage c (the other stage: o).  On entry f0 holds k-step 0 of tile t and tile t+1 is
-  // in flight to stage o.  k-step 0 reads k-step 1's fragments; then everything but the last
-  // warm-up load must have landed; the barrier tells all waves that tile t+1 is complete and stage
-  // c is free; k-step 1 (fed from registers) refills stage c with tile t+2, asks for the wave's
-  // share of tile t+3's lines, and starts reading tile t+1.
+    // k-tile t on stage c (the other stage: o).  On entry f0 holds k-step 0 of tile t and tile t+1 is
+    // in flight to stage o.  k-step 0 reads k-step 1's fragments; then everything but the last
+    // warm-up load must have landed; the barrier tells all waves that tile t+1 is complete and stage
+    // c is free; k-step 1 (fed from registers) refills stage c with tile t+2, asks for the wave's
+    // share of tile t+3's lines, and starts reading tile t+1.
 #define W4_TILE(t, c, o)                                                                                      \
   {                                                                                                           \
     const int t2_ = (t) + 2;                                                                                  \
@@ -488,25 +500,87 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
                       t2_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte0 + t2_ * kBK * 2); \
     W4_WARM((t) + kWarmAhead);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
+    }
+    // Eight k-tiles per trip: the taken branch at the end of a trip costs the matrix pipe about 200
+    // cycles.
+    int t = 0;
+    for (; t + 7 < kt_count; t += 8) {
+      W4_TILE(t, 0, 1);
+      W4_TILE(t + 1, 1, 0);
+      W4_TILE(t + 2, 0, 1);
+      W4_TILE(t + 3, 1, 0);
+      W4_TILE(t + 4, 0, 1);
+      W4_TILE(t + 5, 1, 0);
+      W4_TILE(t + 6, 0, 1);
+      W4_TILE(t + 7, 1, 0);
+    }
+    for (; t + 1 < kt_count; t += 2) {
+      W4_TILE(t, 0, 1);
+      W4_TILE(t + 1, 1, 0);
+    }
+    if (t < kt_count) W4_TILE(t, 0, 1);
+#undef W4_TILE
+  } else {
+    // Three stages, filled two k-tiles ahead: k-tiles 0, 1 and 2 are requested here and k-tile 0 awaited.
+#define W4_FETCH(u, c)                                                                                        \
+  {                                                                                                           \
+    const __amdgpu_buffer_rsrc_t ra_ = (u) < kt_count ? rsrc_a : rsrc_none, rw_ = (u) < kt_count ? rsrc_w : rsrc_none; \
+    _Pragma("unroll") for (int s = 0; s < 8; ++s) w4_dma(ra_, dA##c + s * 8 * kBK, voff_a[s], kbyte0 + (u) * kBK * 2); \
+    _Pragma("unroll") for (int s = 0; s < NJ; ++s) w4_dma(rw_, dB##c + s * 8 * kBK, voff[s], kbyte0 + (u) * kBK * 2); \
   }
-  // Eight k-tiles per trip: the taken branch at the end of a trip costs the matrix pipe about 200
-  // cycles.
-  int t = 0;
-  for (; t + 7 < kt_count; t += 8) {
-    W4_TILE(t, 0, 1);
-    W4_TILE(t + 1, 1, 0);
-    W4_TILE(t + 2, 0, 1);
-    W4_TILE(t + 3, 1, 0);
-    W4_TILE(t + 4, 0, 1);
-    W4_TILE(t + 5, 1, 0);
-    W4_TILE(t + 6, 0, 1);
-    W4_TILE(t + 7, 1, 0);
+    W4_FETCH(0, 0);
+    W4_FETCH(1, 1);
+    W4_FETCH(2, 2);
+#undef W4_FETCH
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(kWaitVm24);       // all but k-tiles 1 and 2
+    w4_barrier();
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      if (s < NJ) f0.b[s] = *reinterpret_cast<const bf16x8*>(rB0 + s * 16 * kBK + pch0);
+      f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // As above, but at the barrier k-tile t + 2 may still be in flight, and k-step 1 asks for t + 3.
+#define W4_TILE(t, c, o)                                                                                      \
+  {                                                                                                           \
+    const int t3_ = (t) + 3;                                                                                  \
+    w4_block<4, false, NJ>(acc, f0, f1, rA##c, rB##c, pch1, rsrc_none, rsrc_none, dA##c, dB##c, voff_a, voff, 0); \
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                                                                   \
+    __builtin_amdgcn_s_waitcnt(kWaitVm12);                                                                    \
+    w4_barrier();                                                                                             \
+    w4_block<2, true, NJ>(acc, f1, f0, rA##o, rB##o, pch0, t3_ < kt_count ? rsrc_a : rsrc_none,                   \
+                      t3_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte0 + t3_ * kBK * 2); \
+    __builtin_amdgcn_sched_barrier(0);                                                                        \
   }
-  for (; t + 1 < kt_count; t += 2) {
-    W4_TILE(t, 0, 1);
-    W4_TILE(t + 1, 1, 0);
+    int t = 0;
+    for (; t + 5 < kt_count; t += 6) {
+      W4_TILE(t, 0, 1);
+      W4_TILE(t + 1, 1, 2);
+      W4_TILE(t + 2, 2, 0);
+      W4_TILE(t + 3, 0, 1);
+      W4_TILE(t + 4, 1, 2);
+      W4_TILE(t + 5, 2, 0);
+    }
+    for (; t + 2 < kt_count; t += 3) {
+      W4_TILE(t, 0, 1);
+      W4_TILE(t + 1, 1, 2);
+      W4_TILE(t + 2, 2, 0);
+    }
+    if (t < kt_count) W4_TILE(t, 0, 1);
+    if (t + 1 < kt_count) W4_TILE(t + 1, 1, 2);
   }
-  if (t < kt_count) W4_TILE(t, 0, 1);
 #undef W4_TILE
 #undef W4_WARM
   __builtin_amdgcn_s_waitcnt(kWaitVm0);      // the trailing (empty) DMA writes have landed
@@ -525,7 +599,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   // fall outside it, columns past N get an out-of-range offset): no branches, so the stores -- and
   // the residual reads, 16 row segments at a time -- are in flight together instead of one after
   // the other.
-  bf16* region = wave == 0 ? sA0 : wave == 1 ? sA1 : wave == 2 ? sB0 : sB1;
+  bf16* region = wave == 0 ? sA0 : wave == 1 ? sA1 : wave == 2 ? sB0 : NJ == 8 ? sB1 : sA2;
   const int rows_valid = __builtin_amdgcn_readfirstlane(min(128, max(0, M - m0 - wm * 128)));
   if (SWIGLU) {
     // Accumulators [i][0..NJ/2-1] are gate, [i][NJ/2..NJ-1] up of outputs n0 + (WR/4)*wn + (0..WR/4-1):
