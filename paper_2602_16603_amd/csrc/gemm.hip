@@ -4,6 +4,7 @@
 // fast kernel on 16x16x32, the small-problem kernel on 32x32x16).  fp32 path (debug): MFMA tiles in
 // fp32 throughout.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -716,6 +717,197 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// bf16 MFMA GEMM for few rows (up to 16 MI = 32, 64 or 128; K % 64 == 0): a launch that reads every weight
+// once from HBM for a handful of MFMAs, so the weights' stream is all there is to it.
+// 256 threads = 4 waves side by side along N; every wave multiplies all rows by its 16 NJ columns with
+// v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits).  K is consumed KT at a
+// time through a ring of S LDS stages, separate arrays filled by DMA S - 1 k-tiles ahead; the loop body has no
+// branch and always runs a multiple of S k-tiles (behind the last one there is nothing to fetch and
+// zeros to multiply), since with a branch between stages the compiler waits for all DMA before a read.
+// LDS rows hold KT bf16, 16-byte chunk c of row r at c ^ ((r >> 1) & 7) (KT = 64) or c ^ (r & 15)
+// (KT = 128): a half-wave's 16 rows x 2 chunks put two lanes on every bank group.
+// ------------------------------------------------------------------------------------------
+template <int N> constexpr int wait_vm() { return 0x0F70 | (N & 15) | ((N >> 4) << 14); }
+
+template <int KT> __device__ __forceinline__ int few_chunk(int chunk, int row) {
+  return KT == 128 ? chunk ^ (row & 15) : chunk ^ ((row >> 1) & 7);
+}
+
+__device__ __forceinline__ void few_dma(const bf16* base, uint32_t bytes, bf16* lds, uint32_t voff, int kbyte) {
+  w4_dma(panel_rsrc(base, bytes), lds, voff, kbyte);
+}
+
+template <int MI, int NJ, int KT, int S, int EPI, bool GROUPED>
+__global__ __launch_bounds__(256) void gemm_bf16_few_rows_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
+                                                                 void* __restrict__ Cout, int M, int N, int K,
+                                                                 int tiles_n, int kt_per_split,
+                                                                 const int32_t* __restrict__ groups,
+                                                                 const int32_t* __restrict__ a_rows) {
+  constexpr bool SWIGLU = EPI == kEpiSwiGLU;
+  constexpr int BM = 16 * MI, WR = 64 * NJ;          // rows of A and of W per stage
+  constexpr int BN = SWIGLU ? WR / 2 : WR;           // output columns per tile
+  constexpr int CPR = KT / 8;                        // 16-byte chunks per LDS row
+  constexpr int RPI = 64 / CPR;                      // rows per DMA instruction
+  constexpr int IA = BM / RPI / 4, IW = WR / RPI / 4;   // DMA instructions per wave and stage
+  constexpr int STAGE = (BM + WR) * KT;
+  static_assert(BM % (4 * RPI) == 0 && S >= 2 && S <= 6 && (!SWIGLU || NJ % 2 == 0));
+  __shared__ __attribute__((aligned(1024))) bf16 s0[STAGE];
+  __shared__ __attribute__((aligned(1024))) bf16 s1[STAGE];
+  __shared__ __attribute__((aligned(1024))) bf16 s2[S > 2 ? STAGE : 8];
+  __shared__ __attribute__((aligned(1024))) bf16 s3[S > 3 ? STAGE : 8];
+  __shared__ __attribute__((aligned(1024))) bf16 s4[S > 4 ? STAGE : 8];
+  __shared__ __attribute__((aligned(1024))) bf16 s5[S > 5 ? STAGE : 8];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tile_n, a_total_rows = M;
+  const int split = GROUPED ? 0 : blockIdx.x / tiles_n;
+  if (GROUPED) {                                     // (the order of gemm_bf16_w4_kernel)
+    const int n_row_tiles = groups[0];
+    const int quota = (n_row_tiles + kXcds - 1) / kXcds;
+    const int in_xcd = blockIdx.x / kXcds;
+    const int ti = (blockIdx.x % kXcds) * quota + in_xcd / tiles_n;
+    if (in_xcd / tiles_n >= quota || ti >= n_row_tiles) return;   // whole workgroup, before any barrier
+    const int expert = groups[1 + 3 * ti], first = groups[2 + 3 * ti];
+    M = groups[3 + 3 * ti];
+    if (a_rows) a_rows += first;
+    else A += (int64_t)first * K;
+    W += (int64_t)expert * (SWIGLU ? 2 : 1) * N * K;
+    Cout = reinterpret_cast<char*>(Cout) + (int64_t)first * N * 2;
+    tile_n = in_xcd % tiles_n;
+  } else {
+    tile_n = blockIdx.x - split * tiles_n;
+  }
+  const int n0 = tile_n * BN;
+  const int k_first = split * kt_per_split * kBK;    // (K ranges are counted in k-tiles of 64)
+  const int k_count = min(kt_per_split * kBK, K - k_first);
+  const bool gathered = GROUPED && a_rows != nullptr;
+
+  // DMA sources: instruction i of this wave fills LDS rows RPI (IA wave + i) .. (A), RPI (IW wave + i) .. (W).
+  // W stage row r is row n0 + r; SwiGLU: rows 32 u .. + 15 of a wave's share are gate rows, the next 16 the up
+  // rows of the same outputs (unit u = r / 32 covers outputs n0 + 16 u ..).
+  uint32_t off_a[IA], off_w[IW];
+  int k_a[IA], k_w[IW];
+#pragma unroll
+  for (int i = 0; i < IA; ++i) {
+    const int row = RPI * (IA * wave + i) + lane / CPR;
+    k_a[i] = few_chunk<KT>(lane % CPR, row) * 8;
+    int src = row < M ? row : -1;
+    if (gathered && src >= 0) src = a_rows[row];
+    off_a[i] = src >= 0 ? (uint32_t)((src * K + k_a[i]) * 2) : kOffOutOfRange;
+  }
+#pragma unroll
+  for (int i = 0; i < IW; ++i) {
+    const int row = RPI * (IW * wave + i) + lane / CPR;
+    k_w[i] = few_chunk<KT>(lane % CPR, row) * 8;
+    const int col = n0 + (SWIGLU ? (row >> 5) * 16 + (row & 15) : row);
+    const int src = SWIGLU ? ((row >> 4) & 1) * N + col : col;
+    off_w[i] = col < N ? (uint32_t)(((src - n0) * K + k_w[i]) * 2) : kOffOutOfRange;
+  }
+  const bf16* const panel_a = A + k_first;
+  const bf16* const panel_w = W + (int64_t)n0 * K + k_first;
+  const uint32_t bytes_a = (uint32_t)(((gathered ? a_total_rows : M) * K - k_first) * 2);
+  const uint32_t bytes_w = (uint32_t)((((SWIGLU ? N : 0) + min(BN, N - n0)) * K - k_first) * 2);
+  auto fetch = [&](int t, bf16* s) __attribute__((always_inline)) {
+    const int left = k_count - t * KT;               // behind the last k-tile every chunk is out of range
+#pragma unroll
+    for (int i = 0; i < IA; ++i)
+      few_dma(panel_a, bytes_a, s + RPI * (IA * wave + i) * KT, k_a[i] < left ? off_a[i] : kOffOutOfRange, t * KT * 2);
+#pragma unroll
+    for (int i = 0; i < IW; ++i)
+      few_dma(panel_w, bytes_w, s + (BM + RPI * (IW * wave + i)) * KT, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * KT * 2);
+  };
+
+  f32x4 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int frag_row = lane & 15, quad = lane >> 4;
+  auto step = [&](int t, const bf16* s, bf16* next) __attribute__((always_inline)) {
+    fetch(t + S - 1, next);                          // the stage every wave finished before the last barrier
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < KT / 32; ++ks) {
+      bf16x8 fa[MI], fw[NJ];
+      const int at = few_chunk<KT>(4 * ks + quad, frag_row) * 8;   // (16-row blocks: the block's first row does not change it)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        fw[j] = *reinterpret_cast<const bf16x8*>(s + (BM + 16 * (NJ * wave + j) + frag_row) * KT + at);
+#pragma unroll
+      for (int i = 0; i < MI; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(s + (16 * i + frag_row) * KT + at);
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j], fa[i], acc[i][j], 0, 0, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);          // this wave is done with the stage ...
+    __builtin_amdgcn_s_waitcnt(wait_vm<(S - 2) * (IA + IW)>());   // ... and its share of the next one has landed
+    w4_barrier();
+  };
+  fetch(0, s0);
+  if (S > 2) fetch(1, s1);
+  if (S > 3) fetch(2, s2);
+  if (S > 4) fetch(3, s3);
+  if (S > 5) fetch(4, s4);
+  __builtin_amdgcn_s_waitcnt(wait_vm<(S - 2) * (IA + IW)>());
+  w4_barrier();
+  for (int t = 0; t * KT < k_count; t += S) {
+    step(t, s0, S == 2 ? s1 : S == 3 ? s2 : S == 4 ? s3 : S == 5 ? s4 : s5);
+    step(t + 1, s1, s0);
+    if (S > 2) step(t + 2, s2, s1);
+    if (S > 3) step(t + 3, s3, s2);
+    if (S > 4) step(t + 4, s4, s3);
+    if (S > 5) step(t + 5, s5, s4);
+  }
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);              // the last (empty) fetches
+
+  // Accumulator [i][j] of a lane holds output row 16 i + lane % 16 and the four columns 4 (lane / 16) +
+  // (0..3) of the wave's j-th 16: stored as they are, 32 to 64 bytes of a row at a time (few rows: the output is
+  // a small part of what moves).
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    const int m = 16 * i + frag_row;
+    if (m >= M) continue;
+    if (SWIGLU) {
+#pragma unroll
+      for (int j = 0; j < NJ / 2; ++j) {
+        const int n = n0 + 16 * (NJ / 2 * wave + j) + 4 * quad;
+        if (n >= N) continue;                        // N % 8 == 0: all four or none
+        bf16x4 v;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          v[b] = static_cast<bf16>(silu_mul_f32(static_cast<float>(static_cast<bf16>(acc[i][2 * j][b])),
+                                                static_cast<float>(static_cast<bf16>(acc[i][2 * j + 1][b]))));
+        *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(Cout) + (int64_t)m * N + n) = v;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int n = n0 + 16 * (NJ * wave + j) + 4 * quad;
+        if (n >= N) continue;
+        if (EPI == kEpiBf16) {
+          bf16x4 v;
+#pragma unroll
+          for (int b = 0; b < 4; ++b) v[b] = static_cast<bf16>(acc[i][j][b]);
+          *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(Cout) + (int64_t)m * N + n) = v;
+        } else {
+          float* c = reinterpret_cast<float*>(Cout) + (EPI == kEpiPartial ? (int64_t)split * M * N : 0) + (int64_t)m * N + n;
+          f32x4 v = acc[i][j];
+          if (EPI == kEpiResidual) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(c);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) v[b] += x[b];
+          }
+          *reinterpret_cast<f32x4*>(c) = v;
+        }
+      }
+    }
+  }
+}
+
 // Split-K reduction: out[m][n] = sum over splits (in index order: deterministic) of the fp32
 // partials, added into the fp32 residual or rounded to bf16.  One thread per 8 outputs.
 template <bool RESID>
@@ -851,6 +1043,36 @@ static W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
   return {narrow ? 4 : 8, s};
 }
 
+// Few rows: up to kFewRows of them.  Columns per tile, k-tile and stages by row count and epilogue, as measured on
+// cold weights of the 8B shape (us, start -> now): up to 64 rows 64-column tiles of 128 k (256 bytes of a
+// weight row at a time: HBM gives 4.9 TB/s to such pieces where 128-byte pieces get 4.2) -- 50 rows: qkv
+// 22 -> 17, o 17.5 -> 12.7, down 40 -> 27; from 65 rows on the A tile weighs more and 128-column tiles of 64 k
+// read it half as often -- 128 rows: qkv 23, down 34 (26, 41 on the former).  SwiGLU: 128 W rows of 64 k, 74 ->
+// 48 at 50 rows, 56 at 128.
+constexpr int kFewRows = 128;
+template <int MI, bool SWIGLU> struct FewRowsTile {
+  static constexpr bool kWide = SWIGLU || MI > 4;
+  static constexpr int NJ = kWide ? 2 : 1, KT = kWide ? 64 : 128, S = 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
+};
+template <int MI, int EPI>
+static int launch_few_rows_of(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
+  using T = FewRowsTile<MI, EPI == kEpiSwiGLU>;
+  const int tiles_n = (n + T::BN - 1) / T::BN, kt = k / kBK;
+  // A CU holds one of these workgroups: no more K ranges than it takes to occupy the 256 once.
+  if (EPI == kEpiPartial) splits = std::max(2, std::min(splits, 256 / tiles_n));
+  const int per = (kt + splits - 1) / splits, used = (kt + per - 1) / per;   // every range has at least one k-tile
+  gemm_bf16_few_rows_kernel<MI, T::NJ, T::KT, T::S, EPI, false><<<dim3((unsigned)(tiles_n * used)), 256, 0, s>>>(
+      a, w, c, m, n, k, tiles_n, per, nullptr, nullptr);
+  return used;
+}
+// Returns the number of K ranges launched (at most `splits`).
+template <int EPI>
+static int launch_few_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
+  if (m <= 32) return launch_few_rows_of<2, EPI>(a, w, c, m, n, k, splits, s);
+  if (m <= 64) return launch_few_rows_of<4, EPI>(a, w, c, m, n, k, splits, s);
+  return launch_few_rows_of<8, EPI>(a, w, c, m, n, k, splits, s);
+}
+
 // Tile of the fused gate_up projection: 128 FFN columns when that occupies the chip or the
 // request has more than two row tiles, else 64.
 static int swiglu_nj(int64_t m, int64_t f) {
@@ -867,6 +1089,10 @@ bool gemm_swiglu_fusable(int dtype, int64_t m, int64_t f, int64_t k) {
 
 void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f,
                         int64_t k, hipStream_t s) {
+  if (m <= kFewRows) {
+    launch_few_rows<kEpiSwiGLU>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, 1, s);
+    return;
+  }
   const int nj = swiglu_nj(m, f);
   const int tiles_m = (int)((m + 255) / 256), tiles_n = (int)((f + nj * 16 - 1) / (nj * 16));
   const dim3 grid((unsigned)(tiles_m * tiles_n));
@@ -879,9 +1105,49 @@ void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t
                                                                    nullptr, nullptr);
 }
 
+size_t gemm_workspace_bytes(int dtype, int64_t m, int64_t n, int64_t k) {
+  if (dtype != 1 || k % kBK != 0) return 0;
+  const int s = w4_shape(m, n, k).splits;
+  return s > 1 ? (size_t)s * m * n * sizeof(float) : 0;
+}
+
+// tail: what follows the split-K reduction in the same kernel (kTailNone: nothing).
+// Row tile of a grouped launch whose experts receive `mean_rows` rows on average: the smallest that holds most
+// experts in one tile, up to 128 rows of the few-rows kernel; from about 100 rows on the matrix pipes bound the
+// launch and the 256-row tile is ahead.  experts_up / experts_down (with the combine) of the 30B-A3B shape, us, with tiles
+// of 256, 128, 64 and 32 rows: 6 rows per expert 214/110, 186/97, 170/82, 159/80; 37 rows 224/121, 198/99,
+// 187/99, 192/108; 64 rows 235/126, 204/110, 209/117, -; 125 rows 247/140, 254/150, -, -.
+int moe_tile_rows(int64_t mean_rows) { return mean_rows <= 18 ? 32 : mean_rows <= 44 ? 64 : mean_rows <= 100 ? 128 : 256; }
+
+template <int MI, int EPI>
+static void launch_grouped_few_rows(const bf16* a, const bf16* w, void* c, int n, int k, const int32_t* groups,
+                                    int max_row_tiles, const int32_t* a_rows, int m_arg, hipStream_t s) {
+  // The down projection's K is short: two workgroups per CU, so that one's prologue and stores lie under the
+  // other's k-tiles, are worth more than the stages they cost (37 rows per expert: 102 -> 99 us with three
+  // stages; 64 rows: 117 -> 110 with two).
+  constexpr bool SWIGLU = EPI == kEpiSwiGLU;
+  constexpr int NJ = 2, KT = 64, S = SWIGLU ? 4 : MI == 8 ? 2 : 3, BN = SWIGLU ? 32 * NJ : 64 * NJ;
+  const int tiles_n = (n + BN - 1) / BN;
+  gemm_bf16_few_rows_kernel<MI, NJ, KT, S, EPI, true>
+      <<<dim3((unsigned)((max_row_tiles + kXcds - 1) / kXcds * kXcds * tiles_n)), 256, 0, s>>>(
+          a, w, c, m_arg, n, k, tiles_n, k / kBK, groups, a_rows);
+}
+
 void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64_t k, int swiglu,
-                         const int32_t* groups, int max_row_tiles, const int32_t* a_rows, int64_t a_total_rows,
-                         hipStream_t s) {
+                         const int32_t* groups, int max_row_tiles, int tile_rows,
+                         const int32_t* a_rows, int64_t a_total_rows, hipStream_t s) {
+  if (tile_rows < 256) {
+    auto few = [&](auto mi) {
+      constexpr int MI = decltype(mi)::value;
+      const int m = a_rows ? (int)a_total_rows : 0;
+      if (swiglu) launch_grouped_few_rows<MI, kEpiSwiGLU>((const bf16*)a, (const bf16*)w, c, (int)n, (int)k, groups, max_row_tiles, a_rows, m, s);
+      else launch_grouped_few_rows<MI, kEpiBf16>((const bf16*)a, (const bf16*)w, c, (int)n, (int)k, groups, max_row_tiles, a_rows, m, s);
+    };
+    if (tile_rows == 32) few(std::integral_constant<int, 2>{});
+    else if (tile_rows == 64) few(std::integral_constant<int, 4>{});
+    else few(std::integral_constant<int, 8>{});
+    return;
+  }
   const int tiles_n = (int)(swiglu ? (n + 127) / 128 : (n + 255) / 256);
   const dim3 grid((unsigned)((max_row_tiles + kXcds - 1) / kXcds * kXcds * tiles_n));   // a whole number of row tiles per XCD
   const int m_arg = a_rows ? (int)a_total_rows : 0;
@@ -893,28 +1159,28 @@ void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64
                                                             (int)k, max_row_tiles, tiles_n, (int)(k / kBK), groups, a_rows);
 }
 
-size_t gemm_workspace_bytes(int dtype, int64_t m, int64_t n, int64_t k) {
-  if (dtype != 1 || k % kBK != 0) return 0;
-  const int s = w4_shape(m, n, k).splits;
-  return s > 1 ? (size_t)s * m * n * sizeof(float) : 0;
-}
-
-// tail: what follows the split-K reduction in the same kernel (kTailNone: nothing).
 template <bool RESID, int NJ>
 static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits,
                            float* workspace, const GemmTail& tail, hipStream_t s) {
   constexpr int BN = 32 * NJ;
   const int tiles_m = (m + 255) / 256, tiles_n = (n + BN - 1) / BN;
   const int kt = k / kBK;
+  if (splits <= 1 && m <= kFewRows) {
+    launch_few_rows<RESID ? kEpiResidual : kEpiBf16>(a, w, c, m, n, k, 1, s);
+    return;
+  }
   if (splits <= 1) {
     gemm_bf16_w4_kernel<RESID ? kEpiResidual : kEpiBf16, false, NJ>
         <<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(a, w, c, m, n, k, tiles_m, tiles_n, kt, nullptr, nullptr);
     return;
   }
   const int per = (kt + splits - 1) / splits;
-  const int used = (kt + per - 1) / per;             // every launched split has at least one k-tile
-  gemm_bf16_w4_kernel<kEpiPartial, false, NJ><<<dim3((unsigned)(tiles_m * tiles_n * used)), 256, 0, s>>>(
-      a, w, workspace, m, n, k, tiles_m, tiles_n, per, nullptr, nullptr);
+  int used = (kt + per - 1) / per;                   // every launched split has at least one k-tile
+  if (m <= kFewRows)
+    used = launch_few_rows<kEpiPartial>(a, w, workspace, m, n, k, splits, s);
+  else
+    gemm_bf16_w4_kernel<kEpiPartial, false, NJ><<<dim3((unsigned)(tiles_m * tiles_n * used)), 256, 0, s>>>(
+        a, w, workspace, m, n, k, tiles_m, tiles_n, per, nullptr, nullptr);
   const int64_t mn = (int64_t)m * n;
   if (RESID && tail.kind == kTailRmsNorm)
     splitk_reduce_norm_kernel<<<dim3((unsigned)m), 256, 0, s>>>(workspace, (float*)c, (const bf16*)tail.gain,

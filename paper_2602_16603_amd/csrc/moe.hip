@@ -105,11 +105,11 @@ __global__ __launch_bounds__(1024) void moe_route_kernel(const float* __restrict
 
 // One workgroup: per-expert totals and row offsets, the route workgroups' counts turned into
 // their first row inside each expert's range (in place), and the grouped GEMMs' row-tile table.
-//   plan[0 .. E) offsets;   groups[0] = row tiles, then {expert, first row, rows} per 256-row tile
+//   plan[0 .. E) offsets;   groups[0] = row tiles, then {expert, first row, rows} per tile of tile_rows rows
 __global__ __launch_bounds__(256) void moe_plan_kernel(int32_t* __restrict__ plan,
                                                        int32_t* __restrict__ block_counts,
                                                        int32_t* __restrict__ groups, int n_experts,
-                                                       int n_blocks) {
+                                                       int n_blocks, int tile_rows) {
   __shared__ int s_cnt[256], s_off[257], s_tile[257];
   const int e = threadIdx.x;
   int total = 0;
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256) void moe_plan_kernel(int32_t* __restrict__ pla
       s_off[i] = off;
       s_tile[i] = tiles;
       off += s_cnt[i];
-      tiles += (s_cnt[i] + 255) >> 8;
+      tiles += (s_cnt[i] + tile_rows - 1) / tile_rows;
     }
     groups[0] = tiles;
   }
@@ -142,10 +142,10 @@ __global__ __launch_bounds__(256) void moe_plan_kernel(int32_t* __restrict__ pla
     plan[e] = s_off[e];
     const int c = s_cnt[e];
     int n = s_tile[e];
-    for (int m = 0; m < c; m += 256, ++n) {
+    for (int m = 0; m < c; m += tile_rows, ++n) {
       groups[1 + 3 * n] = e;
       groups[2 + 3 * n] = s_off[e] + m;
-      groups[3 + 3 * n] = min(256, c - m);
+      groups[3 + 3 * n] = min(tile_rows, c - m);
     }
   }
 }
@@ -192,11 +192,11 @@ int moe_route_blocks(int64_t n_tokens) { return (int)((n_tokens + kRouteTokensPe
 
 void launch_moe_route(const float* logits, int32_t* ids, float* wts, int32_t* slot_of, int32_t* plan,
                       int32_t* block_counts, int32_t* groups, int64_t n_tokens, int n_experts, int top_k,
-                      hipStream_t s) {
+                      int tile_rows, hipStream_t s) {
   const int n_blocks = moe_route_blocks(n_tokens);
   moe_route_kernel<<<dim3((unsigned)n_blocks), 1024, 0, s>>>(logits, ids, wts, slot_of, block_counts, (int)n_tokens,
                                                            n_experts, top_k);
-  moe_plan_kernel<<<1, 256, 0, s>>>(plan, block_counts, groups, n_experts, n_blocks);
+  moe_plan_kernel<<<1, 256, 0, s>>>(plan, block_counts, groups, n_experts, n_blocks, tile_rows);
 }
 
 void launch_moe_index(const int32_t* ids, const int32_t* plan, const int32_t* block_counts,

@@ -103,7 +103,7 @@ struct fp_prefill : fp::OpBackend {
   int32_t *moe_ids = nullptr, *moe_slot = nullptr, *moe_plan = nullptr, *moe_groups = nullptr, *moe_blocks = nullptr;
   int32_t* moe_rows = nullptr;         // token of every row of the experts' row space (gather index)
   void *moe_act = nullptr, *moe_y = nullptr;
-  int32_t moe_max_row_tiles = 0;
+  int32_t moe_max_row_tiles = 0, moe_tile_rows = 0;
   bool swiglu_fused = false;   // op 6 writes act directly (fused GEMM epilogue, or fused split-K reduction); op 7 then has no work and gu is not allocated
   bool swiglu_epilogue = false;   // ... by the GEMM epilogue (the problem fills the chip); else by the split-K reduction
   bool norm_after_o = false;   // short requests: op 4's split-K reduction also normalises the row (op 5 has no work)
@@ -152,15 +152,16 @@ fp_status launch_op(fp_prefill* t, int32_t index) {
       case 6:   // gate: router logits (fp32, accumulated into zeros), selection, row plan
         fp::launch_fill_zero(t->moe_logits, T * E, s);
         fp::launch_gemm(dt, t->h, w.w_router, t->moe_logits, T, E, d, 1, t->splitk, t->splitk_bytes, s);
-        fp::launch_moe_route(t->moe_logits, ids, wts, t->moe_slot, t->moe_plan, t->moe_blocks, t->moe_groups, T, E, k, s);
+        fp::launch_moe_route(t->moe_logits, ids, wts, t->moe_slot, t->moe_plan, t->moe_blocks, t->moe_groups, T, E, k,
+                             t->moe_tile_rows, s);
         break;
       case 7:   // experts, first half: gather per expert, gate/up projection + SiLU*up
         fp::launch_moe_index(ids, t->moe_plan, t->moe_blocks, t->moe_slot, t->moe_rows, T, k, E, s);
-        fp::launch_gemm_grouped(t->h, w.w_gate_up, t->moe_act, F, d, 1, t->moe_groups, t->moe_max_row_tiles,
+        fp::launch_gemm_grouped(t->h, w.w_gate_up, t->moe_act, F, d, 1, t->moe_groups, t->moe_max_row_tiles, t->moe_tile_rows,
                                 t->moe_rows, T, s);
         break;
       case 8:   // experts, second half: down projection, weighted sum into the residual stream
-        fp::launch_gemm_grouped(t->moe_act, w.w_down, t->moe_y, d, F, 0, t->moe_groups, t->moe_max_row_tiles,
+        fp::launch_gemm_grouped(t->moe_act, w.w_down, t->moe_y, d, F, 0, t->moe_groups, t->moe_max_row_tiles, t->moe_tile_rows,
                                 nullptr, 0, s);
         fp::launch_moe_combine(t->x, t->moe_y, t->moe_slot, wts, T, k, (int)d, s);
         break;
@@ -633,7 +634,8 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
                o_o = carve(Tn * qd * e), o_gu = carve(t->swiglu_fused || moe ? 0 : Tn * 2 * F * e),
                o_act = carve(moe ? 0 : Tn * F * e);
   // Mixture-of-experts scratch: every (token, choice) pair owns one row of the gathered buffers.
-  t->moe_max_row_tiles = moe ? (int32_t)(pairs / 256 + E) : 0;
+  t->moe_tile_rows = moe ? fp::moe_tile_rows((int64_t)(pairs / E)) : 0;
+  t->moe_max_row_tiles = moe ? (int32_t)(pairs / t->moe_tile_rows + E) : 0;
   const size_t o_ml = carve(moe ? Tn * E * 4 : 0), o_mw = carve(moe ? pairs * 4 * sh.n_layers : 0),
                o_mi = carve(moe ? pairs * 4 * sh.n_layers : 0), o_ms = carve(moe ? pairs * 4 : 0),
                o_mp = carve(moe ? E * 4 : 0), o_mb = carve(moe ? (size_t)fp::moe_route_blocks(T) * E * 4 : 0), o_mg = carve(moe ? (1 + 3 * (size_t)t->moe_max_row_tiles) * 4 : 0),

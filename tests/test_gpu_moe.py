@@ -157,3 +157,12 @@ def test_moe_shape_validation():
         t.moe_routing(0)
     t.end()
     dense.close()
+
+
+@pytest.mark.parametrize("tokens", [40, 150, 300, 500])
+def test_expert_row_tiles_of_every_size(tokens):
+    """10, 37, 75 and 125 rows per expert on average: the experts' GEMMs run on row tiles of 32, 64, 128
+    and 256; the routing is uneven, so some experts open a second tile."""
+    model, task, _, _ = run_and_check(I.TINY_MOE, [tokens], 56, pool_blocks=64)
+    task.end()
+    model.close()

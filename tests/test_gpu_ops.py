@@ -375,3 +375,57 @@ def test_fp32_gemm_tiles_and_alignment(m, n, k, residual, offset):
     # under 12 sqrt(k) times an element's spread (about 1e-4 of the largest result); observed 1e-7 .. 5e-7.
     assert max_rel_err(c[1:m + 1], ref) <= 1e-5
     assert torch.all(c[0] == 7.0) and torch.all(c[m + 1] == 7.0)
+
+
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("m", [1, 31, 33, 64, 65, 128])
+@pytest.mark.parametrize("n,k", [(12296, 64), (12296, 192), (4104, 1088), (2056, 4096)])
+def test_gemm_of_few_rows(m, n, k, residual):
+    """The kernel of up to 128 rows on its three row tiles (one row, a row less, a row more, all), uncut
+    where the columns alone occupy the chip and cut over K otherwise, k-tiles behind the end of K (one and
+    three of 64: the ring holds more) and a last column tile of eight columns: against the definition, and
+    the uncut form bit for bit against the kernel of larger requests (the same sums in the same order)."""
+    B = _binding()
+    print(f"few rows m={m} n={n} k={k} residual={residual}", flush=True)
+    a = torch.zeros((200, k), dtype=torch.bfloat16, device="cuda")
+    a[:m] = I.normal_tensor((m, k), 1.0, 61, torch.bfloat16, "cuda")
+    w = I.normal_tensor((n, k), 0.05, 62, torch.bfloat16, "cuda")
+    td = torch.float32 if residual else torch.bfloat16
+    buf = torch.full((m + 200, n), 7.0, dtype=td, device="cuda")
+    if residual:
+        buf[:m] = I.normal_tensor((m, n), 1.0, 63, torch.float32, "cuda")
+    x0 = buf[:m].clone()
+    large = torch.zeros((200, n), dtype=td, device="cuda")
+    large[:m] = x0 if residual else 0
+    ws_bytes = B.fp_op_gemm_workspace_bytes(1, m, n, k)
+    ws = torch.full((ws_bytes + 256,), 0x5A, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    B.fp_op_gemm_ws(1, a.data_ptr(), w.data_ptr(), buf.data_ptr(), m, n, k, residual, ws.data_ptr(), ws_bytes)
+    B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), large.data_ptr(), 200, n, k, residual)
+    torch.cuda.synchronize()
+    ref = O.linear(a[:m].cpu(), w.cpu())
+    if residual:
+        ref = ref + x0.cpu().double()
+    assert max_rel_err(buf[:m], ref) <= TOL["bf16"]
+    assert torch.all(buf[m:] == 7.0) and torch.all(ws[ws_bytes:] == 0x5A)
+    if ws_bytes == 0:
+        assert torch.equal(buf[:m], large[:m])
+
+
+@pytest.mark.parametrize("m", [1, 32, 64, 127])
+@pytest.mark.parametrize("f,k", [(6152, 128), (7176, 704)])
+def test_fused_gate_up_swiglu_of_few_rows(m, f, k):
+    """SiLU(gate)*up in the epilogue of the few-rows kernel: the bits of the two operators."""
+    B = _binding()
+    a = I.normal_tensor((m, k), 1.0, 64, torch.bfloat16, "cuda")
+    w = I.normal_tensor((2 * f, k), 0.02, 65, torch.bfloat16, "cuda")
+    gu = torch.empty((m, 2 * f), dtype=torch.bfloat16, device="cuda")
+    two = torch.empty((m, f), dtype=torch.bfloat16, device="cuda")
+    fused = torch.full((m + 1, f), 7.0, dtype=torch.bfloat16, device="cuda")
+    torch.cuda.synchronize()
+    B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), gu.data_ptr(), m, 2 * f, k, False)
+    B.fp_op_silu_mul(1, gu.data_ptr(), two.data_ptr(), m, f)
+    B.fp_op_gemm_swiglu(a.data_ptr(), w.data_ptr(), fused.data_ptr(), m, f, k)
+    torch.cuda.synchronize()
+    assert torch.equal(fused[:m], two) and torch.all(fused[m] == 7.0)
+    assert max_rel_err(fused[:m], O.silu_mul(O.linear(a.cpu(), w.cpu()))) <= TOL["bf16"]
