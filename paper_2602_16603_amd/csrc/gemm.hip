@@ -718,8 +718,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16 MFMA GEMM for few rows (up to 16 MI = 32, 64 or 128; K % 64 == 0): a launch that reads every weight
-// once from HBM for a handful of MFMAs, so the weights' stream is all there is to it.
+// bf16 MFMA GEMM on small tiles (16 MI = 32, 64 or 128 rows, 64 NJ columns; any K % 8 == 0).  Its main use is a
+// launch of few rows, which reads every weight once from HBM for a handful of MFMAs, so the weights'
+// stream is all there is to it; it also takes what has too few 256-row tiles to occupy the chip, and
+// odd K.
 // 256 threads = 4 waves side by side along N; every wave multiplies all rows by its 16 NJ columns with
 // v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits).  K is consumed KT at a
 // time through a ring of S LDS stages, separate arrays filled by DMA S - 1 k-tiles ahead; the loop body has no
@@ -730,18 +732,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // ------------------------------------------------------------------------------------------
 template <int N> constexpr int wait_vm() { return 0x0F70 | (N & 15) | ((N >> 4) << 14); }
 
-template <int KT> __device__ __forceinline__ int few_chunk(int chunk, int row) {
+template <int KT> __device__ __forceinline__ int ring_chunk(int chunk, int row) {
   return KT == 128 ? chunk ^ (row & 15) : chunk ^ ((row >> 1) & 7);
 }
 
-__device__ __forceinline__ void few_dma(const bf16* base, uint32_t bytes, bf16* lds, uint32_t voff, int kbyte) {
+__device__ __forceinline__ void ring_dma(const bf16* base, uint32_t bytes, bf16* lds, uint32_t voff, int kbyte) {
   w4_dma(panel_rsrc(base, bytes), lds, voff, kbyte);
 }
 
 template <int MI, int NJ, int KT, int S, int EPI, bool GROUPED>
-__global__ __launch_bounds__(256) void gemm_bf16_few_rows_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
+__global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
                                                                  void* __restrict__ Cout, int M, int N, int K,
-                                                                 int tiles_n, int kt_per_split,
+                                                                 int tiles_m, int tiles_n, int kt_per_split,
                                                                  const int32_t* __restrict__ groups,
                                                                  const int32_t* __restrict__ a_rows) {
   constexpr bool SWIGLU = EPI == kEpiSwiGLU;
@@ -761,8 +763,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_rows_kernel(const bf16* __r
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  int tile_n, a_total_rows = M;
-  const int split = GROUPED ? 0 : blockIdx.x / tiles_n;
+  int tile_m = 0, tile_n, a_total_rows = M;
+  const int split = GROUPED ? 0 : blockIdx.x / (tiles_m * tiles_n);
+  const int64_t slab = (int64_t)split * M * N;       // of the partial sums
   if (GROUPED) {                                     // (the order of gemm_bf16_w4_kernel)
     const int n_row_tiles = groups[0];
     const int quota = (n_row_tiles + kXcds - 1) / kXcds;
@@ -777,7 +780,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_rows_kernel(const bf16* __r
     Cout = reinterpret_cast<char*>(Cout) + (int64_t)first * N * 2;
     tile_n = in_xcd % tiles_n;
   } else {
-    tile_n = blockIdx.x - split * tiles_n;
+    tile_n = blockIdx.x - split * (tiles_m * tiles_n);
+    if (tiles_m > 1) tile_of_workgroup(tile_n, tiles_m, tiles_n, tile_m, tile_n);
+    const int m0 = tile_m * BM;
+    A += (int64_t)m0 * K;
+    Cout = reinterpret_cast<char*>(Cout) + ((int64_t)m0 * N + slab) * (EPI == kEpiBf16 || SWIGLU ? 2 : 4);
+    M = min(BM, M - m0);
   }
   const int n0 = tile_n * BN;
   const int k_first = split * kt_per_split * kBK;    // (K ranges are counted in k-tiles of 64)
@@ -792,7 +800,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_rows_kernel(const bf16* __r
 #pragma unroll
   for (int i = 0; i < IA; ++i) {
     const int row = RPI * (IA * wave + i) + lane / CPR;
-    k_a[i] = few_chunk<KT>(lane % CPR, row) * 8;
+    k_a[i] = ring_chunk<KT>(lane % CPR, row) * 8;
     int src = row < M ? row : -1;
     if (gathered && src >= 0) src = a_rows[row];
     off_a[i] = src >= 0 ? (uint32_t)((src * K + k_a[i]) * 2) : kOffOutOfRange;
@@ -800,7 +808,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_rows_kernel(const bf16* __r
 #pragma unroll
   for (int i = 0; i < IW; ++i) {
     const int row = RPI * (IW * wave + i) + lane / CPR;
-    k_w[i] = few_chunk<KT>(lane % CPR, row) * 8;
+    k_w[i] = ring_chunk<KT>(lane % CPR, row) * 8;
     const int col = n0 + (SWIGLU ? (row >> 5) * 16 + (row & 15) : row);
     const int src = SWIGLU ? ((row >> 4) & 1) * N + col : col;
     off_w[i] = col < N ? (uint32_t)(((src - n0) * K + k_w[i]) * 2) : kOffOutOfRange;
@@ -813,10 +821,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_rows_kernel(const bf16* __r
     const int left = k_count - t * KT;               // behind the last k-tile every chunk is out of range
 #pragma unroll
     for (int i = 0; i < IA; ++i)
-      few_dma(panel_a, bytes_a, s + RPI * (IA * wave + i) * KT, k_a[i] < left ? off_a[i] : kOffOutOfRange, t * KT * 2);
+      ring_dma(panel_a, bytes_a, s + RPI * (IA * wave + i) * KT, k_a[i] < left ? off_a[i] : kOffOutOfRange, t * KT * 2);
 #pragma unroll
     for (int i = 0; i < IW; ++i)
-      few_dma(panel_w, bytes_w, s + (BM + RPI * (IW * wave + i)) * KT, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * KT * 2);
+      ring_dma(panel_w, bytes_w, s + (BM + RPI * (IW * wave + i)) * KT, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * KT * 2);
   };
 
   f32x4 acc[MI][NJ];
@@ -831,7 +839,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_rows_kernel(const bf16* __r
 #pragma unroll
     for (int ks = 0; ks < KT / 32; ++ks) {
       bf16x8 fa[MI], fw[NJ];
-      const int at = few_chunk<KT>(4 * ks + quad, frag_row) * 8;   // (16-row blocks: the block's first row does not change it)
+      const int at = ring_chunk<KT>(4 * ks + quad, frag_row) * 8;   // (16-row blocks: the block's first row does not change it)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
         fw[j] = *reinterpret_cast<const bf16x8*>(s + (BM + 16 * (NJ * wave + j) + frag_row) * KT + at);
@@ -894,7 +902,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_rows_kernel(const bf16* __r
           for (int b = 0; b < 4; ++b) v[b] = static_cast<bf16>(acc[i][j][b]);
           *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(Cout) + (int64_t)m * N + n) = v;
         } else {
-          float* c = reinterpret_cast<float*>(Cout) + (EPI == kEpiPartial ? (int64_t)split * M * N : 0) + (int64_t)m * N + n;
+          float* c = reinterpret_cast<float*>(Cout) + (int64_t)m * N + n;
           f32x4 v = acc[i][j];
           if (EPI == kEpiResidual) {
             const f32x4 x = *reinterpret_cast<const f32x4*>(c);
@@ -1050,27 +1058,46 @@ static W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
 // read it half as often -- 128 rows: qkv 23, down 34 (26, 41 on the former).  SwiGLU: 128 W rows of 64 k, 74 ->
 // 48 at 50 rows, 56 at 128.
 constexpr int kFewRows = 128;
-template <int MI, bool SWIGLU> struct FewRowsTile {
+template <int MI, bool SWIGLU> struct RingTile {
   static constexpr bool kWide = SWIGLU || MI > 4;
   static constexpr int NJ = kWide ? 2 : 1, KT = kWide ? 64 : 128, S = 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
 };
 template <int MI, int EPI>
-static int launch_few_rows_of(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
-  using T = FewRowsTile<MI, EPI == kEpiSwiGLU>;
-  const int tiles_n = (n + T::BN - 1) / T::BN, kt = k / kBK;
+static int launch_ring(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
+  using T = RingTile<MI, EPI == kEpiSwiGLU>;
+  const int tiles_m = (m + 16 * MI - 1) / (16 * MI), tiles_n = (n + T::BN - 1) / T::BN, kt = (k + kBK - 1) / kBK;
   // A CU holds one of these workgroups: no more K ranges than it takes to occupy the 256 once.
-  if (EPI == kEpiPartial) splits = std::max(2, std::min(splits, 256 / tiles_n));
+  if (splits > 1) splits = std::max(2, std::min(splits, 256 / tiles_n));
   const int per = (kt + splits - 1) / splits, used = (kt + per - 1) / per;   // every range has at least one k-tile
-  gemm_bf16_few_rows_kernel<MI, T::NJ, T::KT, T::S, EPI, false><<<dim3((unsigned)(tiles_n * used)), 256, 0, s>>>(
-      a, w, c, m, n, k, tiles_n, per, nullptr, nullptr);
+  gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, EPI, false><<<dim3((unsigned)(tiles_m * tiles_n * used)), 256, 0, s>>>(
+      a, w, c, m, n, k, tiles_m, tiles_n, per, nullptr, nullptr);
   return used;
 }
 // Returns the number of K ranges launched (at most `splits`).
 template <int EPI>
 static int launch_few_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
-  if (m <= 32) return launch_few_rows_of<2, EPI>(a, w, c, m, n, k, splits, s);
-  if (m <= 64) return launch_few_rows_of<4, EPI>(a, w, c, m, n, k, splits, s);
-  return launch_few_rows_of<8, EPI>(a, w, c, m, n, k, splits, s);
+  if (m <= 32) return launch_ring<2, EPI>(a, w, c, m, n, k, splits, s);
+  if (m <= 64) return launch_ring<4, EPI>(a, w, c, m, n, k, splits, s);
+  return launch_ring<8, EPI>(a, w, c, m, n, k, splits, s);
+}
+
+// Problems with too few 256-row tiles to occupy the chip, and odd K.  A CU works off its tiles one after
+// the other: the tile for which the busiest of 256 CUs has the fewest outputs, padding included; on a tie the
+// larger one, which reads its operands less often.  Against the register-staged kernel on 128x128 tiles, us: 200 x 256
+// x 704 19 -> 6, 256 x 512 x 8192 105 -> 20, 50 x 4096 x 4104 69 -> 18, 2048 x 1024 x 1024 18.7 -> 14.7.
+template <int EPI>
+static void launch_small_problem(const bf16* a, const bf16* w, void* c, int64_t m, int64_t n, int64_t k, hipStream_t s) {
+  auto outputs = [&](int64_t bm, int64_t bn) { return (((m + bm - 1) / bm) * ((n + bn - 1) / bn) + 255) / 256 * bm * bn; };
+  const int64_t large = outputs(128, 128), middle = outputs(64, 64), small = outputs(32, 64);
+  if (large <= middle && large <= small) launch_ring<8, EPI>(a, w, c, (int)m, (int)n, (int)k, 1, s);
+  else if (middle <= small) launch_ring<4, EPI>(a, w, c, (int)m, (int)n, (int)k, 1, s);
+  else launch_ring<2, EPI>(a, w, c, (int)m, (int)n, (int)k, 1, s);
+}
+
+// The router has few outputs and as many rows as the task: 32-row tiles, logits stored in fp32 as they come (590
+// x 128 x 2048: 52 -> 8 us).
+void launch_router_gemm(const void* a, const void* w, float* logits, int64_t m, int64_t n, int64_t k, hipStream_t s) {
+  launch_ring<2, kEpiPartial>((const bf16*)a, (const bf16*)w, logits, (int)m, (int)n, (int)k, 1, s);
 }
 
 // Tile of the fused gate_up projection: 128 FFN columns when that occupies the chip or the
@@ -1120,7 +1147,7 @@ size_t gemm_workspace_bytes(int dtype, int64_t m, int64_t n, int64_t k) {
 int moe_tile_rows(int64_t mean_rows) { return mean_rows <= 18 ? 32 : mean_rows <= 44 ? 64 : mean_rows <= 100 ? 128 : 256; }
 
 template <int MI, int EPI>
-static void launch_grouped_few_rows(const bf16* a, const bf16* w, void* c, int n, int k, const int32_t* groups,
+static void launch_grouped_ring(const bf16* a, const bf16* w, void* c, int n, int k, const int32_t* groups,
                                     int max_row_tiles, const int32_t* a_rows, int m_arg, hipStream_t s) {
   // The down projection's K is short: two workgroups per CU, so that one's prologue and stores lie under the
   // other's k-tiles, are worth more than the stages they cost (37 rows per expert: 102 -> 99 us with three
@@ -1128,9 +1155,9 @@ static void launch_grouped_few_rows(const bf16* a, const bf16* w, void* c, int n
   constexpr bool SWIGLU = EPI == kEpiSwiGLU;
   constexpr int NJ = 2, KT = 64, S = SWIGLU ? 4 : MI == 8 ? 2 : 3, BN = SWIGLU ? 32 * NJ : 64 * NJ;
   const int tiles_n = (n + BN - 1) / BN;
-  gemm_bf16_few_rows_kernel<MI, NJ, KT, S, EPI, true>
+  gemm_bf16_ring_kernel<MI, NJ, KT, S, EPI, true>
       <<<dim3((unsigned)((max_row_tiles + kXcds - 1) / kXcds * kXcds * tiles_n)), 256, 0, s>>>(
-          a, w, c, m_arg, n, k, tiles_n, k / kBK, groups, a_rows);
+          a, w, c, m_arg, n, k, max_row_tiles, tiles_n, k / kBK, groups, a_rows);
 }
 
 void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64_t k, int swiglu,
@@ -1140,8 +1167,8 @@ void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64
     auto few = [&](auto mi) {
       constexpr int MI = decltype(mi)::value;
       const int m = a_rows ? (int)a_total_rows : 0;
-      if (swiglu) launch_grouped_few_rows<MI, kEpiSwiGLU>((const bf16*)a, (const bf16*)w, c, (int)n, (int)k, groups, max_row_tiles, a_rows, m, s);
-      else launch_grouped_few_rows<MI, kEpiBf16>((const bf16*)a, (const bf16*)w, c, (int)n, (int)k, groups, max_row_tiles, a_rows, m, s);
+      if (swiglu) launch_grouped_ring<MI, kEpiSwiGLU>((const bf16*)a, (const bf16*)w, c, (int)n, (int)k, groups, max_row_tiles, a_rows, m, s);
+      else launch_grouped_ring<MI, kEpiBf16>((const bf16*)a, (const bf16*)w, c, (int)n, (int)k, groups, max_row_tiles, a_rows, m, s);
     };
     if (tile_rows == 32) few(std::integral_constant<int, 2>{});
     else if (tile_rows == 64) few(std::integral_constant<int, 4>{});
@@ -1461,6 +1488,12 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   } else if (splits >= 1) {
     if (residual) launch_bf16_w4<true, 4>(pa, pw, c, (int)m, (int)n, (int)k, splits, (float*)workspace, tl, s);
     else launch_bf16_w4<false, 4>(pa, pw, c, (int)m, (int)n, (int)k, splits, (float*)workspace, tl, s);
+  } else if ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(c)) % 16 == 0 &&
+             k <= (1 << 21) && ((m + 127) / 128) * ((n + 127) / 128) <= 512) {
+    // (more tiles than two per CU: odd K only, where the register-staged kernel is ahead -- 8192 x 8192 x 2056
+    // 440 us against 512, while 513 x 776 x 1000 takes 5.8 us here and 18 there)
+    if (residual) launch_small_problem<kEpiResidual>(pa, pw, c, m, n, k, s);
+    else launch_small_problem<kEpiBf16>(pa, pw, c, m, n, k, s);
   } else {
     if (residual) launch_bf16_cfg<128, 128, 2, 2, true>(pa, pw, c, (int)m, (int)n, (int)k, s);
     else launch_bf16_cfg<128, 128, 2, 2, false>(pa, pw, c, (int)m, (int)n, (int)k, s);

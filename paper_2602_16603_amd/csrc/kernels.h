@@ -83,6 +83,8 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
                  int64_t k, int residual, void* workspace, size_t workspace_bytes, hipStream_t s,
                  const GemmTail* tail = nullptr);
 size_t gemm_workspace_bytes(int dtype, int64_t m, int64_t n, int64_t k);
+// Mixture-of-experts router: logits[m][n] (fp32) = a[m][k] w[n][k]^T, bf16 operands.
+void launch_router_gemm(const void* a, const void* w, float* logits, int64_t m, int64_t n, int64_t k, hipStream_t s);
 // Fused gate_up projection + SiLU(gate)*up (bf16): out[m][f] from a[m][k] and w_gate_up[2f][k]
 // (gate rows first), bit-identical to launch_gemm into [m][2f] followed by launch_silu_mul.
 // Only for problems gemm_swiglu_fusable accepts (K % 64 == 0, f % 8 == 0, enough tiles to fill the
@@ -113,7 +115,6 @@ void launch_kv_gather(int dtype, const void* k_pool, const void* v_pool, void* k
 // [T*top_k] (rank inside the route workgroup after launch_moe_route, final row after
 // launch_moe_gather); groups = device int32 [1 + 3 * (T*top_k/tile_rows + n_experts)]: the row-tile
 // table launch_gemm_grouped reads.
-void launch_fill_zero(void* p, int64_t n_dwords, hipStream_t s);
 int moe_route_blocks(int64_t n_tokens);
 void launch_moe_route(const float* logits, int32_t* ids, float* wts, int32_t* slot_of, int32_t* plan,
                       int32_t* block_counts, int32_t* groups, int64_t n_tokens, int n_experts, int top_k,

@@ -11,23 +11,30 @@
 
 namespace fp {
 
-__global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* __restrict__ p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0u;
-}
-
-void launch_fill_zero(void* p, int64_t n_dwords, hipStream_t s) {
-  if (n_dwords <= 0) return;
-  fill_zero_kernel<<<dim3((unsigned)((n_dwords + 255) / 256)), 256, 0, s>>>((uint32_t*)p, n_dwords);
-}
-
-// Router: one wave per token (16 waves per workgroup, 4 tokens per wave): probabilities, top_k
-// selection, renormalised weights.  n_experts <= 256 (lane l holds experts l, l+64, l+128, l+192),
-// top_k <= 8.  Every chosen (token, expert) pair also takes a rank among the workgroup's pairs of
+// Router: 64 tokens per workgroup, 16 waves of four tokens: probabilities, top_k selection, renormalised
+// weights.  n_experts <= 256 (lane l holds experts l, l+64, l+128, l+192), top_k <= 8.  A selection step is
+// a chain -- the wave's maximum by DPP, then the first lane that holds it by ballot (ties: lower index) -- so a
+// wave runs the chains of its four tokens side by side (29 us with one after the other on LDS-shuffle reductions).
+// Every chosen (token, expert) pair also takes a rank among the workgroup's pairs of
 // that expert (an LDS counter), and the workgroup leaves its per-expert counts in
 // block_counts[block][expert]: the row plan below needs no global atomics (65536 of them on 128
 // addresses cost more than the rest of the operator).
 constexpr int kRouteTokensPerBlock = 64;
+constexpr int kRouteTokensPerWave = 4;
+
+template <int CTRL, int ROWS> __device__ __forceinline__ float max_dpp(float v) {   // lanes without a source keep v
+  const int u = __builtin_bit_cast(int, v);
+  return fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(u, u, CTRL, ROWS, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max_dpp(float v) {
+  v = max_dpp<0x111, 0xf>(v);                       // row_shr 1, 2, 4, 8: lane 15 of each row of 16 has the row's maximum
+  v = max_dpp<0x112, 0xf>(v);
+  v = max_dpp<0x114, 0xf>(v);
+  v = max_dpp<0x118, 0xf>(v);
+  v = max_dpp<0x142, 0xa>(v);                       // row_bcast 15 into rows 1 and 3, row_bcast 31 into rows 2 and 3
+  v = max_dpp<0x143, 0xc>(v);
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
 
 __global__ __launch_bounds__(1024) void moe_route_kernel(const float* __restrict__ logits,
                                                          int32_t* __restrict__ ids,
@@ -35,70 +42,68 @@ __global__ __launch_bounds__(1024) void moe_route_kernel(const float* __restrict
                                                          int32_t* __restrict__ rank_in_block,
                                                          int32_t* __restrict__ block_counts,
                                                          int n_tokens, int n_experts, int top_k) {
+  constexpr int Q = kRouteTokensPerWave;
   __shared__ int hist[256];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (threadIdx.x < 256) hist[threadIdx.x] = 0;
   __syncthreads();
-  for (int q = 0; q < 4; ++q) {
-    const int t = blockIdx.x * kRouteTokensPerBlock + wave * 4 + q;
-    if (t >= n_tokens) break;                       // wave-uniform
-    float p[4];
+  const int t0 = blockIdx.x * kRouteTokensPerBlock + wave * Q;   // (a token past the end repeats the last one and is not written)
+  float p[Q][4];
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int e = lane + 64 * i;
-      p[i] = e < n_experts ? logits[(int64_t)t * n_experts + e] : -INFINITY;
+      p[q][i] = e < n_experts ? logits[(int64_t)min(t0 + q, n_tokens - 1) * n_experts + e] : -INFINITY;
     }
-    float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+  for (int q = 0; q < Q; ++q) {
+    const float mx = wave_max_dpp(fmaxf(fmaxf(p[q][0], p[q][1]), fmaxf(p[q][2], p[q][3])));
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      p[i] = lane + 64 * i < n_experts ? expf(p[i] - mx) : -1.0f;   // -1: never selected
-      sum += fmaxf(p[i], 0.f);
+      p[q][i] = lane + 64 * i < n_experts ? expf(p[q][i] - mx) : -1.0f;   // -1: never selected
+      sum += fmaxf(p[q][i], 0.f);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    sum = wave_sum(sum);
     const float inv = 1.0f / sum;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) p[i] = p[i] >= 0.f ? p[i] * inv : -1.0f;
-
-    float chosen_p[8];
-    int chosen_e[8];
-    float total = 0.f;
+    for (int i = 0; i < 4; ++i) p[q][i] = p[q][i] >= 0.f ? p[q][i] * inv : -1.0f;
+  }
+  // Lane j (< 8) of the wave keeps choice j of every token.
+  float my_p[Q], total[Q];
+  int my_e[Q];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if (j < top_k) {
-        float bv = p[0];
-        int be = lane;
+  for (int q = 0; q < Q; ++q) { my_p[q] = 0.f; my_e[q] = 0; total[q] = 0.f; }
 #pragma unroll
-        for (int i = 1; i < 4; ++i)
-          if (p[i] > bv) { bv = p[i]; be = lane + 64 * i; }        // own experts ascend with i: ties keep the lower
+  for (int j = 0; j < 8; ++j) {
+    if (j >= top_k) break;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-          const float ov = __shfl_xor(bv, o);
-          const int oe = __shfl_xor(be, o);
-          if (ov > bv || (ov == bv && oe < be)) { bv = ov; be = oe; }
-        }
-        chosen_p[j] = bv;
-        chosen_e[j] = be;
-        total += bv;
+    for (int q = 0; q < Q; ++q) {
+      const float best = wave_max_dpp(fmaxf(fmaxf(p[q][0], p[q][1]), fmaxf(p[q][2], p[q][3])));
+      int e = -1;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (be == lane + 64 * i) p[i] = -1.0f;                    // taken
+      for (int i = 3; i >= 0; --i) {
+        const uint64_t holds = __ballot(p[q][i] == best);
+        e = holds ? 64 * i + __ffsll((unsigned long long)holds) - 1 : e;
       }
-    }
-    if (lane == 0) {
-      const float norm = 1.0f / total;
+      if (e < 0 || e >= n_experts) e = 0;             // (only infinities or NaN among the logits leave none in range)
+      total[q] += best;
+      if (lane == j) { my_p[q] = best; my_e[q] = e; }
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (j < top_k) {
-          ids[(int64_t)t * top_k + j] = chosen_e[j];
-          wts[(int64_t)t * top_k + j] = chosen_p[j] * norm;
-          rank_in_block[(int64_t)t * top_k + j] = atomicAdd(&hist[chosen_e[j]], 1);
-        }
+      for (int i = 0; i < 4; ++i)
+        if (lane + 64 * i == e) p[q][i] = -1.0f;                    // taken
     }
   }
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (t0 + q < n_tokens && lane < top_k) {
+      const int64_t at = (int64_t)(t0 + q) * top_k + lane;
+      const float norm = 1.0f / total[q];
+      ids[at] = my_e[q];
+      wts[at] = my_p[q] * norm;
+      rank_in_block[at] = atomicAdd(&hist[my_e[q]], 1);
+    }
   __syncthreads();
   if (threadIdx.x < n_experts) block_counts[(int64_t)blockIdx.x * n_experts + threadIdx.x] = hist[threadIdx.x];
 }

@@ -149,9 +149,8 @@ fp_status launch_op(fp_prefill* t, int32_t index) {
     int32_t* ids = t->moe_ids + (int64_t)layer * T * k;      // kept per layer for inspection
     float* wts = t->moe_wts + (int64_t)layer * T * k;
     switch (op) {
-      case 6:   // gate: router logits (fp32, accumulated into zeros), selection, row plan
-        fp::launch_fill_zero(t->moe_logits, T * E, s);
-        fp::launch_gemm(dt, t->h, w.w_router, t->moe_logits, T, E, d, 1, t->splitk, t->splitk_bytes, s);
+      case 6:   // gate: router logits (fp32), selection, row plan
+        fp::launch_router_gemm(t->h, w.w_router, t->moe_logits, T, E, d, s);
         fp::launch_moe_route(t->moe_logits, ids, wts, t->moe_slot, t->moe_plan, t->moe_blocks, t->moe_groups, T, E, k,
                              t->moe_tile_rows, s);
         break;
@@ -624,7 +623,7 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
                                    fp::gemm_workspace_bytes(sh.dtype, T, (int64_t)d, (int64_t)F));
   const size_t sk_bytes = std::max(
       std::max(fp::gemm_workspace_bytes(sh.dtype, T, (int64_t)W, (int64_t)d), fp::gemm_workspace_bytes(sh.dtype, T, (int64_t)d, (int64_t)qd)),
-      moe ? fp::gemm_workspace_bytes(sh.dtype, T, (int64_t)E, (int64_t)d) : sk_dense);
+      moe ? (size_t)0 : sk_dense);
   t->swiglu_epilogue = !moe && fp::gemm_swiglu_fusable(sh.dtype, T, (int64_t)F, (int64_t)d);
   t->swiglu_fused = t->swiglu_epilogue ||
                     (!moe && fp::gemm_tail_fusable(sh.dtype, T, 2 * (int64_t)F, (int64_t)d, sk_bytes, fp::kTailSwiGLU));
