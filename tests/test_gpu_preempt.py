@@ -256,3 +256,32 @@ def test_model_destroy_is_refused_while_a_task_is_alive():
     assert torch.equal(again.hidden(), first)
     again.end()
     model.close()
+
+
+@pytest.mark.parametrize("name,head_dim", [("fp32", 16), ("fp32", 32), ("fp32", 128), ("bf16", 64), ("bf16", 128)])
+def test_kv_gather_copies_every_slot_and_no_other(name, head_dim):
+    """K and V of one sequence out of the scattered pools, for every head size, a last block of one, fifteen
+    and sixteen tokens: the bits of the pools, and nothing behind the last token."""
+    import numpy as np
+    from paper_2602_16603_amd import binding as B, runner as R
+    code, td = (0, torch.float32) if name == "fp32" else (1, torch.bfloat16)
+    spec = I.ShapeSpec(1, 64, 6, 3, head_dim, 64, 1e-5, 10000.0)
+    model = R.PrefillModel(spec, I.make_weights(spec, 71, td, "cuda"), code, 64, 64)
+    lengths = [33, 16, 47]
+    table, _ = I.permuted_block_tables(lengths, None, 16, 64, seed=9)
+    task = model.begin(I.make_hidden(sum(lengths), spec.hidden, 71, td, "cuda"), lengths, [0] * 3, table)
+    task.run_to_completion()
+    k_ptr, v_ptr, tables = task.kv_pools(0)
+    pool_k = R.copy_from_device_ptr(k_ptr, (64, 3, 16, head_dim), td)
+    pool_v = R.copy_from_device_ptr(v_ptr, (64, 3, head_dim, 16), td)
+    for s, n in enumerate(lengths):
+        out = [torch.full((n + 16, 3, head_dim), 7.0, dtype=td, device="cuda") for _ in range(2)]
+        torch.cuda.synchronize()
+        B.fp_prefill_kv_gather(task.handle, 0, s, out[0].data_ptr(), out[1].data_ptr())
+        blocks = torch.from_numpy(np.ascontiguousarray(tables[s][:(n + 15) // 16])).long().cuda()
+        k_ref = pool_k[blocks].permute(0, 2, 1, 3).reshape(-1, 3, head_dim)[:n]
+        v_ref = pool_v[blocks].permute(0, 3, 1, 2).reshape(-1, 3, head_dim)[:n]
+        assert torch.equal(out[0][:n], k_ref) and torch.equal(out[1][:n], v_ref)
+        assert torch.all(out[0][n:] == 7.0) and torch.all(out[1][n:] == 7.0)
+    task.end()
+    model.close()
