@@ -1,4 +1,4 @@
-// HBM-bound operators of the prefill layer: residual initialisation, RMSNorm, rotary embedding
+// HBM-bound operators of the prefill layer: the start of a task, RMSNorm, rotary embedding
 // with paged KV-cache write, SiLU(gate)*up.  All are coalesced, 16-byte-vectorised and do their
 // arithmetic in fp32 (FlowPrefill Section 2.1: "FFN and residual connections"; the operators
 // between the five core operators of Section 5.1).
@@ -10,42 +10,19 @@ namespace fp {
 template <typename T> using vec8 = T __attribute__((ext_vector_type(8)));
 
 // ------------------------------------------------------------------------------------------
-// hidden_in (storage dtype) -> fp32 residual stream
-// ------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void to_residual_kernel(const T* __restrict__ in,
-                                                          float* __restrict__ x, int64_t n8) {
-  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n8) return;
-  f32x8 v = Vec8<T>::load(in + i * 8);
-  Vec8<float>::store(x + i * 8, v);
-}
-
-void launch_to_residual(int dtype, const void* in, float* x, int64_t n_elems, hipStream_t s) {
-  int64_t n8 = n_elems / 8;
-  if (n8 == 0) return;
-  dim3 grid((unsigned)((n8 + 255) / 256));
-  if (dtype == 1)
-    to_residual_kernel<bf16><<<grid, 256, 0, s>>>((const bf16*)in, x, n8);
-  else
-    to_residual_kernel<float><<<grid, 256, 0, s>>>((const float*)in, x, n8);
-}
-
-// ------------------------------------------------------------------------------------------
 // RMSNorm: out = x * rsqrt(mean(x^2) + eps) * gain.  One 256-thread workgroup per token row;
 // the row stays in registers between the sum-of-squares pass and the scaling pass (one HBM
 // read), for rows up to 256*8*kMaxVec elements; longer rows are re-read.
 // ------------------------------------------------------------------------------------------
 constexpr int kNormMaxVec = 4;   // 256 threads * 8 elems * 4 = 8192 columns held in registers
 
-template <typename T>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ x,
-                                                      const T* __restrict__ gain,
-                                                      T* __restrict__ out, int64_t d, float eps) {
+// One row by one workgroup.  START: `row` is the task's input in the storage type, and the widened row
+// goes to `x`, the fp32 residual stream.
+template <typename T, typename IN, bool START>
+__device__ __forceinline__ void rmsnorm_row(const IN* __restrict__ row, const T* __restrict__ gain, T* __restrict__ orow,
+                                            float* __restrict__ x, int64_t d, float eps) {
   __shared__ float partial[4];
   const int tid = threadIdx.x;
-  const float* row = x + (int64_t)blockIdx.x * d;
-  T* orow = out + (int64_t)blockIdx.x * d;
   const int64_t n8 = d / 8;
   f32x8 held[kNormMaxVec];
   float ss = 0.f;
@@ -53,13 +30,15 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   for (int i = 0; i < kNormMaxVec; ++i) {
     int64_t c = tid + (int64_t)i * 256;
     if (c < n8) {
-      held[i] = Vec8<float>::load(row + c * 8);
+      held[i] = Vec8<IN>::load(row + c * 8);
+      if (START) Vec8<float>::store(x + c * 8, held[i]);
 #pragma unroll
       for (int e = 0; e < 8; ++e) ss += held[i][e] * held[i][e];
     }
   }
   for (int64_t c = tid + (int64_t)kNormMaxVec * 256; c < n8; c += 256) {
-    f32x8 v = Vec8<float>::load(row + c * 8);
+    f32x8 v = Vec8<IN>::load(row + c * 8);
+    if (START) Vec8<float>::store(x + c * 8, v);
 #pragma unroll
     for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
   }
@@ -80,13 +59,20 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
     }
   }
   for (int64_t c = tid + (int64_t)kNormMaxVec * 256; c < n8; c += 256) {
-    f32x8 v = Vec8<float>::load(row + c * 8);
+    f32x8 v = Vec8<IN>::load(row + c * 8);
     f32x8 g = Vec8<T>::load(gain + c * 8);
     f32x8 o;
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = v[e] * inv * g[e];
     Vec8<T>::store(orow + c * 8, o);
   }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ x,
+                                                      const T* __restrict__ gain,
+                                                      T* __restrict__ out, int64_t d, float eps) {
+  rmsnorm_row<T, float, false>(x + (int64_t)blockIdx.x * d, gain, out + (int64_t)blockIdx.x * d, nullptr, d, eps);
 }
 
 void launch_rmsnorm(int dtype, const float* x, const void* gain, void* out, int64_t t, int64_t d,
@@ -97,6 +83,41 @@ void launch_rmsnorm(int dtype, const float* x, const void* gain, void* out, int6
     rmsnorm_kernel<bf16><<<grid, 256, 0, s>>>(x, (const bf16*)gain, (bf16*)out, d, eps);
   else
     rmsnorm_kernel<float><<<grid, 256, 0, s>>>(x, (const float*)gain, (float*)out, d, eps);
+}
+
+// ------------------------------------------------------------------------------------------
+// Everything a task needs on the device before its first GEMM, in one launch: the batch's metadata from pinned host
+// memory (16 bytes per thread, the first workgroups), hidden_in widened into the fp32 residual stream, and
+// the first layer's attention RMSNorm of the same rows (one workgroup per token), with the bits of the separate
+// operator.  Separately these are an upload and two kernels, the second re-reading the residual: 67 us of kernels
+// at 8192 x 4096, 49 here, and two launches fewer for a short request.
+// ------------------------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(256) void task_start_kernel(const T* __restrict__ in, float* __restrict__ x,
+                                                         const T* __restrict__ gain, T* __restrict__ out, int64_t d,
+                                                         float eps, const u32x4* __restrict__ meta_in,
+                                                         u32x4* __restrict__ meta_out, int64_t n_meta, int meta_blocks) {
+  if ((int)blockIdx.x < meta_blocks) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n_meta) meta_out[i] = meta_in[i];
+    return;
+  }
+  const int64_t at = (int64_t)(blockIdx.x - meta_blocks) * d;
+  rmsnorm_row<T, T, true>(in + at, gain, out + at, x + at, d, eps);
+}
+
+void launch_task_start(int dtype, const void* in, float* x, const void* gain, void* out, int64_t t, int64_t d, float eps,
+                       const int32_t* meta_in, int32_t* meta_out, int64_t n_ints, hipStream_t s) {
+  const int64_t n_meta = (n_ints + 3) / 4;
+  const int meta_blocks = (int)((n_meta + 255) / 256);
+  dim3 grid((unsigned)(meta_blocks + t));
+  if (grid.x == 0) return;
+  if (dtype == 1)
+    task_start_kernel<bf16><<<grid, 256, 0, s>>>((const bf16*)in, x, (const bf16*)gain, (bf16*)out, d, eps,
+                                                 (const u32x4*)meta_in, (u32x4*)meta_out, n_meta, meta_blocks);
+  else
+    task_start_kernel<float><<<grid, 256, 0, s>>>((const float*)in, x, (const float*)gain, (float*)out, d, eps,
+                                                  (const u32x4*)meta_in, (u32x4*)meta_out, n_meta, meta_blocks);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -50,7 +50,10 @@ int attention_part_tiles(const std::vector<int32_t>& tiles, int n_q_heads);
 // Floats one part takes (all query heads).
 size_t attn_part_floats(const Geometry& g);
 
-void launch_to_residual(int dtype, const void* in, float* x, int64_t n_elems, hipStream_t s);
+// x (fp32) = in, out = rmsnorm(in) * gain (the first operator of the first layer), and the batch's
+// metadata from pinned host memory to the device: n_ints rounded up to four, both sides 16-byte aligned.
+void launch_task_start(int dtype, const void* in, float* x, const void* gain, void* out, int64_t t, int64_t d, float eps,
+                       const int32_t* meta_in, int32_t* meta_out, int64_t n_ints, hipStream_t s);
 void launch_rmsnorm(int dtype, const float* x, const void* gain, void* out, int64_t t, int64_t d,
                     float eps, hipStream_t s);
 void launch_silu_mul(int dtype, const void* gu, void* out, int64_t t, int64_t f, hipStream_t s);

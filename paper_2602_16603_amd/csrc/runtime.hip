@@ -172,7 +172,8 @@ fp_status launch_op(fp_prefill* t, int32_t index) {
   }
   switch (op) {
     case 0:
-      if (!(layer > 0 && t->norm_after_down)) fp::launch_rmsnorm(dt, t->x, w.attn_norm, t->h, T, d, sh.rms_eps, s);
+      // (the first layer's norm is done when the task starts, a later one's may ride on the layer before)
+      if (layer > 0 && !t->norm_after_down) fp::launch_rmsnorm(dt, t->x, w.attn_norm, t->h, T, d, sh.rms_eps, s);
       break;
     case 1: fp::launch_gemm(dt, t->h, w.w_qkv, t->qkv, T, m->geo.qkv_width(), d, 0, t->splitk, t->splitk_bytes, s); break;
     case 2:
@@ -316,7 +317,7 @@ void fp_prefill::begin_call() {
 int fp_prefill::launch(int32_t index, bool* launched) {
   const int op = index % FP_OPS_PER_LAYER;
   *launched = !((swiglu_fused && op == 7) || (norm_after_o && op == 5) ||
-                (norm_after_down && op == 0 && index >= FP_OPS_PER_LAYER));
+                index == 0 || (norm_after_down && op == 0));
   return launch_op(this, index) == FP_OK ? 0 : -1;
 }
 
@@ -662,8 +663,8 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
     t->moe_rows = reinterpret_cast<int32_t*>(base + o_mh); t->moe_act = base + o_ma; t->moe_y = base + o_my;
   }
 
-  // Metadata goes through the workspace's pinned staging buffer, so the upload is asynchronous
-  // and nothing here waits for the stream.
+  // Metadata goes through the workspace's pinned staging buffer, which the task's first kernel reads: nothing
+  // here waits for the stream.
   int32_t* ints = static_cast<int32_t*>(t->ws.staging);
   size_t n_put = 0;
   auto put = [&](const std::vector<int32_t>& v) {
@@ -683,10 +684,6 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
     delete t;
     return code;
   };
-  hipError_t he;
-  if (n_put &&
-      (he = hipMemcpyAsync(dints, ints, n_put * 4, hipMemcpyHostToDevice, m->stream)) != hipSuccess)
-    return bail(fail(FP_ERR_DEVICE, "metadata upload: %s", hipGetErrorString(he)));
   t->meta.n_tokens = T;
   t->meta.n_seqs = n_seqs;
   t->meta.max_blocks = t->max_blocks;
@@ -703,9 +700,10 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
   t->meta.n_attn_merges = (int32_t)(attn_merges.size() / fp::kAttnMergeInts);
   t->meta.attn_part = n_parts ? reinterpret_cast<float*>(base + o_ap) : nullptr;
 
-  fp::launch_to_residual(sh.dtype, hidden_in, t->x, (int64_t)T * sh.hidden, m->stream);
-  if ((he = hipGetLastError()) != hipSuccess)
-    return bail(fail(FP_ERR_DEVICE, "residual initialisation: %s", hipGetErrorString(he)));
+  fp::launch_task_start(sh.dtype, hidden_in, t->x, m->layers[0].attn_norm, t->h, T, sh.hidden, sh.rms_eps, ints, dints,
+                        (int64_t)n_put, m->stream);
+  const hipError_t he = hipGetLastError();
+  if (he != hipSuccess) return bail(fail(FP_ERR_DEVICE, "start of the task: %s", hipGetErrorString(he)));
   if ((st = acquire_events(m, false, kMarkRing, t->ring)) != FP_OK) return bail(st);
   {
     std::lock_guard<std::mutex> lk(m->mu);
