@@ -60,6 +60,13 @@ class PrefillModel:
               boundary_mask: int = B.FP_BOUNDARY_EVERY_OP) -> "PrefillTask":
         return PrefillTask(self, hidden, lengths, cached, block_tables, boundary_mask)
 
+    def wait_for_torch(self) -> None:
+        """What torch has enqueued on its current stream comes before what the library enqueues next: nothing
+        to do where both use the same stream."""
+        current = torch.cuda.current_stream()
+        if current.cuda_stream != (self.stream.cuda_stream if self.stream is not None else 0):
+            current.synchronize()
+
     def close(self) -> None:
         if self.handle:
             B.fp_model_destroy(self.handle)
@@ -85,7 +92,7 @@ class PrefillTask:
             self.cu.append(self.cu[-1] + n)
         assert hidden.is_cuda and hidden.dtype == model.torch_dtype and hidden.is_contiguous()
         assert tuple(hidden.shape) == (self.cu[-1], model.spec.hidden)
-        torch.cuda.current_stream().synchronize()   # hidden was produced on torch's stream
+        model.wait_for_torch()                      # hidden was produced on torch's stream
         self._hidden_in = hidden                    # read asynchronously by the library: keep it alive
         self.handle = B.fp_prefill_begin(model.handle, hidden.data_ptr(), self.cu,
                                          None if cached is None else self.cached, block_tables,
@@ -119,7 +126,7 @@ class PrefillTask:
         sp = self.model.spec
         k = torch.empty((n, sp.n_kv_heads, sp.head_dim), dtype=self.model.torch_dtype, device="cuda")
         v = torch.empty_like(k)
-        torch.cuda.synchronize()
+        self.model.wait_for_torch()                 # (torch may still be using the memory these came from)
         if n:
             B.fp_prefill_kv_gather(self.handle, layer, seq, k.data_ptr(), v.data_ptr())
         return k, v
@@ -129,7 +136,7 @@ class PrefillTask:
         k = self.model.spec.top_k
         ids = torch.empty((self.cu[-1], k), dtype=torch.int32, device="cuda")
         wts = torch.empty((self.cu[-1], k), dtype=torch.float32, device="cuda")
-        torch.cuda.synchronize()
+        self.model.wait_for_torch()
         B.fp_prefill_moe_routing(self.handle, layer, ids.data_ptr(), wts.data_ptr())
         return ids, wts
 
