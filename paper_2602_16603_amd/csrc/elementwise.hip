@@ -222,7 +222,6 @@ __global__ __launch_bounds__(256) void rope_kvwrite_kernel(
   const int64_t blk = block_tables[(int64_t)s * max_blocks + lb];
   const int p_lo = max(lb * kKvBlock, cached);
   const int p_hi = min(lb * kKvBlock + kKvBlock, cached + n_new);
-  const bool full = (p_hi - p_lo) == kKvBlock;
   const int units = n_kv_heads * head_dim / 8;
   const int64_t v_off = (int64_t)(n_q_heads + n_kv_heads) * head_dim;
   for (int u = tid; u < units; u += 256) {
@@ -230,30 +229,33 @@ __global__ __launch_bounds__(256) void rope_kvwrite_kernel(
     const int d0 = (u - kh * (head_dim / 8)) * 8;
     T* dst = v_pool + (((int64_t)layer * kv_num_blocks + blk) * n_kv_heads + kh) *
                           ((int64_t)head_dim * kKvBlock) + (int64_t)d0 * kKvBlock;
-    if (full) {
-      vec8<T> v[kKvBlock];
+    // All tokens' loads are in flight together.  A half of the block's 16 slots leaves as whole 16-byte pieces
+    // where all of it is new; slots of tokens that are not new keep what they hold.
+    vec8<T> v[kKvBlock];
 #pragma unroll
-      for (int tk = 0; tk < kKvBlock; ++tk) {
-        const int64_t trow = seq_lo + (p_lo + tk - cached);
-        v[tk] = *reinterpret_cast<const vec8<T>*>(qkv + trow * width + v_off + kh * head_dim + d0);
-      }
+    for (int tk = 0; tk < kKvBlock; ++tk) {
+      const int p = min(max(lb * kKvBlock + tk, p_lo), p_hi - 1);
+      const int64_t trow = seq_lo + (p - cached);
+      v[tk] = *reinterpret_cast<const vec8<T>*>(qkv + trow * width + v_off + kh * head_dim + d0);
+    }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        vec8<T> lo, hi;
+    for (int h = 0; h < 2; ++h) {
+      const int first = lb * kKvBlock + 8 * h;
+      if (first >= p_lo && first + 8 <= p_hi) {
 #pragma unroll
-        for (int tk = 0; tk < 8; ++tk) {
-          lo[tk] = v[tk][e];
-          hi[tk] = v[tk + 8][e];
+        for (int e = 0; e < 8; ++e) {
+          vec8<T> piece;
+#pragma unroll
+          for (int tk = 0; tk < 8; ++tk) piece[tk] = v[8 * h + tk][e];
+          *reinterpret_cast<vec8<T>*>(dst + e * kKvBlock + 8 * h) = piece;
         }
-        *reinterpret_cast<vec8<T>*>(dst + e * kKvBlock) = lo;
-        *reinterpret_cast<vec8<T>*>(dst + e * kKvBlock + 8) = hi;
-      }
-    } else {
-      for (int p = p_lo; p < p_hi; ++p) {
-        const int64_t trow = seq_lo + (p - cached);
-        vec8<T> v = *reinterpret_cast<const vec8<T>*>(qkv + trow * width + v_off + kh * head_dim + d0);
+      } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) dst[e * kKvBlock + (p % kKvBlock)] = v[e];
+        for (int tk = 0; tk < 8; ++tk)
+          if (first + tk >= p_lo && first + tk < p_hi) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dst[e * kKvBlock + 8 * h + tk] = v[8 * h + tk][e];
+          }
       }
     }
   }
