@@ -1446,6 +1446,18 @@ static W4Shape w4_plan(int dtype, int64_t m, int64_t n, int64_t k, size_t worksp
   return p;
 }
 
+// What a problem that w4_plan cuts over K runs as.  Three or four row tiles and a short K: the 128-column
+// tile in fewer ranges (possibly one: nothing is cut then), if that occupies the chip -- fewer partial sums
+// against more operand reads per MFMA, which a long K would pay for too often.  With the reduction, us:
+// 777 x 6144 x 4096 59 -> 51, 777 x 4096 x 4096 48 -> 45, 590 x 5120 x 2048 31 -> 25, but x 14336 110 -> 115; 600 x 6144 x
+// 4096 has 144 tiles and stays (47.7, 49).  Residual projections stay cut (their tail rides on the reduction).
+static W4Shape w4_cut(int64_t m, int64_t n, int64_t k, bool residual, W4Shape p) {
+  const int64_t tiles_m = (m + 255) / 256, tiles = tiles_m * ((n + 127) / 128);
+  if (p.nj != 8 || tiles_m > 4 || k > 6144 || tiles > 256) return p;
+  const int s = (int)std::min<int64_t>(p.splits, 256 / tiles);
+  return tiles * s >= 184 && s >= (residual ? 2 : 1) ? W4Shape{4, s} : p;
+}
+
 bool gemm_tail_fusable(int dtype, int64_t m, int64_t n, int64_t k, size_t workspace_bytes, int tail_kind) {
   if (w4_plan(dtype, m, n, k, workspace_bytes).splits <= 1) return false;   // tails ride on the split-K reduction
   if (tail_kind == kTailRmsNorm) return n <= kTailNormCols;
@@ -1478,10 +1490,15 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   // K a multiple of 64 and enough 256x256 tiles (or enough K to split) to occupy the chip: the
   // one-wave-per-SIMD DMA kernel, split over K when the caller's workspace allows.  Otherwise (tiny or
   // odd-K problems): the register-staged kernel on 128x128 tiles.
-  const W4Shape plan = w4_plan(dtype, m, n, k, workspace_bytes);
-  const int splits = plan.splits;
+  W4Shape plan = w4_plan(dtype, m, n, k, workspace_bytes);
   const GemmTail none{};
   const GemmTail& tl = tail && gemm_tail_fusable(dtype, m, n, k, workspace_bytes, tail->kind) ? *tail : none;
+  if (plan.splits > 1) plan = w4_cut(m, n, k, residual, plan);
+  const int splits = plan.splits;
+  if (splits == 1 && tl.kind == kTailSwiGLU) {       // not cut after all: the fused epilogue gives the same bits
+    launch_gemm_swiglu(a, w, tl.out, m, n / 2, k, s);
+    return;
+  }
   if (splits >= 1 && plan.nj == 8) {
     if (residual) launch_bf16_w4<true, 8>(pa, pw, c, (int)m, (int)n, (int)k, splits, (float*)workspace, tl, s);
     else launch_bf16_w4<false, 8>(pa, pw, c, (int)m, (int)n, (int)k, splits, (float*)workspace, tl, s);

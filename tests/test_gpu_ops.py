@@ -429,3 +429,41 @@ def test_fused_gate_up_swiglu_of_few_rows(m, f, k):
     torch.cuda.synchronize()
     assert torch.equal(fused[:m], two) and torch.all(fused[m] == 7.0)
     assert max_rel_err(fused[:m], O.silu_mul(O.linear(a.cpu(), w.cpu()))) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("m,n,k", [(777, 6144, 1088), (513, 7824, 2048), (1024, 4096, 1600), (600, 5136, 1024)])
+@pytest.mark.parametrize("residual", [False, True])
+def test_three_and_four_row_tiles_on_the_narrow_tile(m, n, k, residual):
+    """Problems of three and four row tiles with a short K run on the 128-column tile in fewer K ranges,
+    or uncut: against the definition; uncut, the bits of the call without a workspace.  The workspace
+    asked for is still enough and its guard stays untouched."""
+    B = _binding()
+    ws_bytes = B.fp_op_gemm_workspace_bytes(1, m, n, k)
+    assert ws_bytes > 0
+    a = I.normal_tensor((m, k), 1.0, 66, torch.bfloat16, "cuda")
+    w = I.normal_tensor((n, k), 0.05, 67, torch.bfloat16, "cuda")
+    td = torch.float32 if residual else torch.bfloat16
+    x0 = I.normal_tensor((m, n), 1.0, 68, td, "cuda")
+    buf = torch.full((m + 2, n), 7.0, dtype=td, device="cuda")
+    buf[1:m + 1] = x0
+    plain = x0.clone()
+    ws = torch.full((ws_bytes + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    print(f"narrow cut m={m} n={n} k={k} residual={residual}", flush=True)
+    torch.cuda.synchronize()
+    B.fp_op_gemm_ws(1, a.data_ptr(), w.data_ptr(), buf[1:].data_ptr(), m, n, k, residual, ws.data_ptr(), ws_bytes)
+    B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), plain.data_ptr(), m, n, k, residual)
+    torch.cuda.synchronize()
+    ref = O.linear(a.cpu(), w.cpu())
+    if residual:
+        ref = ref + x0.cpu().double()
+    assert max_rel_err(buf[1:m + 1], ref) <= TOL["bf16"]
+    assert torch.all(buf[0] == 7.0) and torch.all(buf[m + 1] == 7.0) and torch.all(ws[ws_bytes:] == 0x5A)
+    if not residual and 184 <= ((m + 255) // 256) * ((n + 127) // 128) <= 256:       # the tiles alone occupy the chip: one range
+        assert torch.equal(buf[1:m + 1], plain)
+    if not residual:                                              # the SwiGLU tail, cut or not: the two operators' bits
+        two = torch.empty((m, n // 2), dtype=torch.bfloat16, device="cuda")
+        fused = torch.empty_like(two)
+        B.fp_op_silu_mul(1, buf[1:].data_ptr(), two.data_ptr(), m, n // 2)
+        B.fp_op_gemm_tail(a.data_ptr(), w.data_ptr(), 0, m, n, k, False, ws.data_ptr(), ws_bytes, B.FP_TAIL_SWIGLU, 0, fused.data_ptr())
+        torch.cuda.synchronize()
+        assert torch.equal(fused, two)
