@@ -11,16 +11,18 @@
 
 namespace fp {
 
-// Router: 64 tokens per workgroup, 16 waves of four tokens: probabilities, top_k selection, renormalised
-// weights.  n_experts <= 256 (lane l holds experts l, l+64, l+128, l+192), top_k <= 8.  A selection step is
+// Router: four tokens per wave: probabilities, top_k selection, renormalised weights.  n_experts <= 256 (lane l holds experts l, l+64, l+128, l+192), top_k <= 8.  A selection step is
 // a chain -- the wave's maximum by DPP, then the first lane that holds it by ballot (ties: lower index) -- so a
 // wave runs the chains of its four tokens side by side (29 us with one after the other on LDS-shuffle reductions).
 // Every chosen (token, expert) pair also takes a rank among the workgroup's pairs of
 // that expert (an LDS counter), and the workgroup leaves its per-expert counts in
 // block_counts[block][expert]: the row plan below needs no global atomics (65536 of them on 128
 // addresses cost more than the rest of the operator).
-constexpr int kRouteTokensPerBlock = 64;
+// The selections are bound by instruction issue, so a short request takes workgroups of 16 tokens (590 tokens: 16 us on
+// ten workgroups of 64, 7 on 37); from 2048 tokens on 64 tokens each fill the chip and keep the plan's walk over
+// the workgroups short.
 constexpr int kRouteTokensPerWave = 4;
+__host__ __device__ inline int route_tokens_per_block(int64_t n_tokens) { return n_tokens < 2048 ? 16 : 64; }
 
 template <int CTRL, int ROWS> __device__ __forceinline__ float max_dpp(float v) {   // lanes without a source keep v
   const int u = __builtin_bit_cast(int, v);
@@ -45,9 +47,9 @@ __global__ __launch_bounds__(1024) void moe_route_kernel(const float* __restrict
   constexpr int Q = kRouteTokensPerWave;
   __shared__ int hist[256];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+  if (threadIdx.x < 256) hist[threadIdx.x] = 0;     // (256 threads or more)
   __syncthreads();
-  const int t0 = blockIdx.x * kRouteTokensPerBlock + wave * Q;   // (a token past the end repeats the last one and is not written)
+  const int t0 = (blockIdx.x * (blockDim.x >> 6) + wave) * Q;   // (a token past the end repeats the last one and is not written)
   float p[Q][4];
 #pragma unroll
   for (int q = 0; q < Q; ++q)
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(256) void moe_plan_kernel(int32_t* __restrict__ pla
                                                        int32_t* __restrict__ block_counts,
                                                        int32_t* __restrict__ groups, int n_experts,
                                                        int n_blocks, int tile_rows) {
-  __shared__ int s_cnt[256], s_off[257], s_tile[257];
+  __shared__ int s_rows[4], s_tiles[4];
   const int e = threadIdx.x;
   int total = 0;
   if (e < n_experts)
@@ -130,27 +132,27 @@ __global__ __launch_bounds__(256) void moe_plan_kernel(int32_t* __restrict__ pla
         total += c[i];
       }
     }
-  s_cnt[e] = total;
-  __syncthreads();
-  if (e == 0) {                                   // 256 LDS steps: cheaper than a parallel scan is worth
-    int off = 0, tiles = 0;
-    for (int i = 0; i < n_experts; ++i) {
-      s_off[i] = off;
-      s_tile[i] = tiles;
-      off += s_cnt[i];
-      tiles += (s_cnt[i] + tile_rows - 1) / tile_rows;
-    }
-    groups[0] = tiles;
+  // Exclusive prefix sums of rows and of tiles over the experts: within a wave by shuffles, across the four waves
+  // through LDS (one thread walking all experts took 5 us).
+  const int tiles = (total + tile_rows - 1) / tile_rows;
+  int off = total, first = tiles;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(off, d), f = __shfl_up(first, d);
+    if ((e & 63) >= d) { off += o; first += f; }
   }
+  if ((e & 63) == 63) { s_rows[e >> 6] = off; s_tiles[e >> 6] = first; }
   __syncthreads();
+  off -= total;
+  first -= tiles;
+  for (int w = 0; w < (e >> 6); ++w) { off += s_rows[w]; first += s_tiles[w]; }
+  if (e == 0) groups[0] = s_tiles[0] + s_tiles[1] + s_tiles[2] + s_tiles[3];
   if (e < n_experts) {
-    plan[e] = s_off[e];
-    const int c = s_cnt[e];
-    int n = s_tile[e];
-    for (int m = 0; m < c; m += tile_rows, ++n) {
-      groups[1 + 3 * n] = e;
-      groups[2 + 3 * n] = s_off[e] + m;
-      groups[3 + 3 * n] = min(tile_rows, c - m);
+    plan[e] = off;
+    for (int m = 0; m < total; m += tile_rows, ++first) {
+      groups[1 + 3 * first] = e;
+      groups[2 + 3 * first] = off + m;
+      groups[3 + 3 * first] = min(tile_rows, total - m);
     }
   }
 }
@@ -163,12 +165,12 @@ __global__ __launch_bounds__(256) void moe_index_kernel(const int32_t* __restric
                                                         const int32_t* __restrict__ block_counts,
                                                         int32_t* __restrict__ slot_of,
                                                         int32_t* __restrict__ row_token, int n_pairs,
-                                                        int top_k, int n_experts) {
+                                                        int top_k, int n_experts, int tokens_per_block) {
   const int pair = blockIdx.x * 256 + threadIdx.x;
   if (pair >= n_pairs) return;
   const int token = pair / top_k;
   const int e = ids[pair];
-  const int slot = plan[e] + block_counts[(int64_t)(token / kRouteTokensPerBlock) * n_experts + e] + slot_of[pair];
+  const int slot = plan[e] + block_counts[(int64_t)(token / tokens_per_block) * n_experts + e] + slot_of[pair];
   slot_of[pair] = slot;
   row_token[slot] = token;
 }
@@ -193,13 +195,16 @@ __global__ __launch_bounds__(256) void moe_combine_kernel(float* __restrict__ x,
   Vec8<float>::store(x + t * d + c * 8, acc);
 }
 
-int moe_route_blocks(int64_t n_tokens) { return (int)((n_tokens + kRouteTokensPerBlock - 1) / kRouteTokensPerBlock); }
+int moe_route_blocks(int64_t n_tokens) {
+  const int per = route_tokens_per_block(n_tokens);
+  return (int)((n_tokens + per - 1) / per);
+}
 
 void launch_moe_route(const float* logits, int32_t* ids, float* wts, int32_t* slot_of, int32_t* plan,
                       int32_t* block_counts, int32_t* groups, int64_t n_tokens, int n_experts, int top_k,
                       int tile_rows, hipStream_t s) {
   const int n_blocks = moe_route_blocks(n_tokens);
-  moe_route_kernel<<<dim3((unsigned)n_blocks), 1024, 0, s>>>(logits, ids, wts, slot_of, block_counts, (int)n_tokens,
+  moe_route_kernel<<<dim3((unsigned)n_blocks), route_tokens_per_block(n_tokens) / kRouteTokensPerWave * 64, 0, s>>>(logits, ids, wts, slot_of, block_counts, (int)n_tokens,
                                                            n_experts, top_k);
   moe_plan_kernel<<<1, 256, 0, s>>>(plan, block_counts, groups, n_experts, n_blocks, tile_rows);
 }
@@ -209,7 +214,8 @@ void launch_moe_index(const int32_t* ids, const int32_t* plan, const int32_t* bl
                       hipStream_t s) {
   const int64_t pairs = n_tokens * top_k;
   moe_index_kernel<<<dim3((unsigned)((pairs + 255) / 256)), 256, 0, s>>>(ids, plan, block_counts, slot_of, row_token,
-                                                                        (int)pairs, top_k, n_experts);
+                                                                        (int)pairs, top_k, n_experts,
+                                                                        route_tokens_per_block(n_tokens));
 }
 
 void launch_moe_combine(float* x, const void* y, const int32_t* slot_of, const float* wts,
