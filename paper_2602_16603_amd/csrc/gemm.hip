@@ -36,7 +36,7 @@ __device__ __forceinline__ void tile_of_workgroup(int wg, int tiles_m, int tiles
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16 MFMA GEMM for tiny or odd-K problems (register-staged loads).  WGM x WGN waves; each wave
+// bf16 MFMA GEMM for operands that are not 16-byte aligned (register-staged loads).  WGM x WGN waves; each wave
 // owns a (BM/WGM)x(BN/WGN) block of 32x32 MFMA accumulators.  K is consumed 64 at a time.  LDS rows hold 64 bf16 = eight 16-byte chunks.  The
 // gfx950 LDS has 64 four-byte banks (256 B per clock for reads); a ds_read_b128 is served one
 // half-wave after the other and a half-wave costs max(2, most lanes on one 16-byte bank group)
@@ -304,7 +304,12 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // latency: the narrow tile's stages are three (144 KB, filled two k-tiles ahead) instead of two with
 // L2 warm-up.  Cold weights, 256 tokens of the 8B shape: gate_up 79 -> 66 us, down 49 -> 45; 50 tokens:
 // 74 -> 55, 40 -> 31; 512 tokens: down 76 -> 67.  (The wide tile's three stages would take 192 KB.)
-template <int EPI, bool GROUPED = false, int NJ = 8>
+//
+// KTAIL (256-column tile, not cut): K is not a multiple of 64; its last K % 64 columns (a multiple of 8) follow the
+// main loop as one more k-tile, not pipelined, whose missing 16-byte chunks are fetched from outside the
+// descriptors (K < 64: there is nothing else; the prologue's k-tile 0 is overwritten unread).  K rows then start at odd multiples of 16 bytes, which the DMA does not mind.  8192 x 8192 x 2056:
+// 470 us on register-staged 128x128 tiles, 305 here (912 TFLOP/s; rows that straddle lines cost the rest).
+template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restrict__ A,
                                                            const bf16* __restrict__ W,
                                                            void* __restrict__ Cout, int M, int N,
@@ -521,6 +526,28 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     }
     if (t < kt_count) W4_TILE(t, 0, 1);
 #undef W4_TILE
+    if constexpr (KTAIL) {
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+      w4_barrier();                            // both stages are free
+      const int left = K - kt_count * kBK, kbyte = kt_count * kBK * 2;
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const int k = ((lane & 7) ^ (((s * 8 + (lane >> 3)) >> 1) & 7)) * 8;
+        w4_dma(rsrc_a, dA0 + s * 8 * kBK, k < left ? voff_a[s] : kOffOutOfRange, kbyte);
+        w4_dma(rsrc_w, dB0 + s * 8 * kBK, k < left ? voff[s] : kOffOutOfRange, kbyte);
+      }
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      w4_barrier();
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        f0.b[s] = *reinterpret_cast<const bf16x8*>(rB0 + s * 16 * kBK + pch0);
+        f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      w4_block<4, false, NJ>(acc, f0, f1, rA0, rB0, pch1, rsrc_none, rsrc_none, dA0, dB0, voff_a, voff, 0);
+      w4_block<0, false, NJ>(acc, f1, f0, rA0, rB0, pch0, rsrc_none, rsrc_none, dA0, dB0, voff_a, voff, 0);
+    }
   } else {
     // Three stages, filled two k-tiles ahead: k-tiles 0, 1 and 2 are requested here and k-tile 0 awaited.
 #define W4_FETCH(u, c)                                                                                        \
@@ -1498,9 +1525,24 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   }
   const bf16* pa = (const bf16*)a;
   const bf16* pw = (const bf16*)w;
-  // K a multiple of 64 and enough 256x256 tiles (or enough K to split) to occupy the chip: the
-  // one-wave-per-SIMD DMA kernel, split over K when the caller's workspace allows.  Otherwise (tiny or
-  // odd-K problems): the register-staged kernel on 128x128 tiles.
+  // Enough 256x256 tiles (or, K a multiple of 64, enough K to split) to occupy the chip: the
+  // one-wave-per-SIMD DMA kernel, split over K when the caller's workspace allows.  Otherwise the ring
+  // kernel on small tiles; operands that are not 16-byte aligned: the register-staged kernel on 128x128 tiles.
+  const bool aligned = (reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(c)) % 16 == 0;
+  const int64_t tiles_m = (m + 255) / 256, tiles_n = (n + 255) / 256;
+  if (k % kBK != 0 && aligned && n <= (1 << 21) && k <= (1 << 21) && tiles_m * tiles_n >= 96 &&
+      tiles_m * tiles_n <= INT32_MAX) {
+    // Odd K on the large tile, from the number of tiles on that K % 64 == 0 takes it.  Against 128x128 tiles, us: 96 tiles
+    // (3000 x 2000 x 4008) 118 -> 99, 256 tiles (4096 x 4096 x 4104) 197 -> 125, but 64 tiles (1000 x 4096 x 1000) 17 -> 25.
+    const dim3 grid((unsigned)(tiles_m * tiles_n));
+    if (residual)
+      gemm_bf16_w4_kernel<kEpiResidual, false, 8, true><<<grid, 256, 0, s>>>(pa, pw, c, (int)m, (int)n, (int)k, (int)tiles_m,
+                                                                            (int)tiles_n, (int)(k / kBK), nullptr, nullptr);
+    else
+      gemm_bf16_w4_kernel<kEpiBf16, false, 8, true><<<grid, 256, 0, s>>>(pa, pw, c, (int)m, (int)n, (int)k, (int)tiles_m,
+                                                                        (int)tiles_n, (int)(k / kBK), nullptr, nullptr);
+    return;
+  }
   W4Shape plan = w4_plan(dtype, m, n, k, workspace_bytes);
   const GemmTail none{};
   const GemmTail& tl = tail && gemm_tail_fusable(dtype, m, n, k, workspace_bytes, tail->kind) ? *tail : none;
@@ -1516,10 +1558,7 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   } else if (splits >= 1) {
     if (residual) launch_bf16_w4<true, 4>(pa, pw, c, (int)m, (int)n, (int)k, splits, (float*)workspace, tl, s);
     else launch_bf16_w4<false, 4>(pa, pw, c, (int)m, (int)n, (int)k, splits, (float*)workspace, tl, s);
-  } else if ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(c)) % 16 == 0 &&
-             k <= (1 << 21) && ((m + 127) / 128) * ((n + 127) / 128) <= 512) {
-    // (more tiles than two per CU: odd K only, where the register-staged kernel is ahead -- 8192 x 8192 x 2056
-    // 440 us against 512, while 513 x 776 x 1000 takes 5.8 us here and 18 there)
+  } else if (aligned && k <= (1 << 21) && ((m + 31) / 32) * ((n + 63) / 64) <= INT32_MAX) {
     if (residual) launch_small_problem<kEpiResidual>(pa, pw, c, m, n, k, s);
     else launch_small_problem<kEpiBf16>(pa, pw, c, m, n, k, s);
   } else {

@@ -467,3 +467,30 @@ def test_three_and_four_row_tiles_on_the_narrow_tile(m, n, k, residual):
         B.fp_op_gemm_tail(a.data_ptr(), w.data_ptr(), 0, m, n, k, False, ws.data_ptr(), ws_bytes, B.FP_TAIL_SWIGLU, 0, fused.data_ptr())
         torch.cuda.synchronize()
         assert torch.equal(fused, two)
+
+
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("m,n,k", [(2560, 2560, 8), (2305, 2568, 72), (2304, 2816, 136), (2305, 2568, 200), (2049, 3080, 632), (4100, 1544, 1016), (8200, 520, 2040)])
+def test_gemm_odd_k_on_the_large_tile(m, n, k, residual):
+    """K not a multiple of 64 on the 256x256 tile (0, 1, 2, 3, 9, 15 and 31 whole k-tiles and a tail of 8 or 56
+    columns), a last row tile of one row and a last column tile of eight columns: the columns of W and A
+    behind K belong to the next row and must not enter."""
+    B = _binding()
+    print(f"gemm odd k m={m} n={n} k={k} residual={residual}", flush=True)
+    a = I.normal_tensor((m, k), 1.0, 72, torch.bfloat16, "cuda")
+    w = I.normal_tensor((n, k), 0.05, 73, torch.bfloat16, "cuda")
+    td = torch.float32 if residual else torch.bfloat16
+    buf = torch.full((m + 300, n), 7.0, dtype=td, device="cuda")
+    if residual:
+        buf[:m] = I.normal_tensor((m, n), 1.0, 74, torch.float32, "cuda")
+    x0 = buf[:m].clone()
+    torch.cuda.synchronize()
+    B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), buf.data_ptr(), m, n, k, residual)
+    torch.cuda.synchronize()
+    ref = O.linear(a.cpu(), w.cpu())
+    if residual:
+        ref = ref + x0.cpu().double()
+    assert max_rel_err(buf[:m], ref) <= TOL["bf16"]
+    # One dropped or foreign column would be off by sqrt(1/k) of the result: far above the bf16 rounding of 2^-9.
+    assert ((buf[:m].cpu().double() - ref).norm() / ref.norm()).item() <= 4e-3
+    assert torch.all(buf[m:] == 7.0)
