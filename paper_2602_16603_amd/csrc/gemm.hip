@@ -1119,6 +1119,8 @@ static int launch_few_rows(const bf16* a, const bf16* w, void* c, int m, int n, 
   return launch_ring<8, EPI>(a, w, c, m, n, k, splits, s);
 }
 
+static bool takes_ring(int64_t m, int64_t n, int64_t k, size_t workspace_bytes);
+
 // Problems with too few 256-row tiles to occupy the chip, and odd K.  A CU works off its tiles one after
 // the other: the tile for which the busiest of 256 CUs has the fewest outputs, padding included; on a tie the
 // larger one, which reads its operands less often.  Against the register-staged kernel on 128x128 tiles, us: 200 x 256
@@ -1130,6 +1132,20 @@ static void launch_small_problem(const bf16* a, const bf16* w, void* c, int64_t 
   if (large <= middle && large <= small) launch_ring<8, EPI>(a, w, c, (int)m, (int)n, (int)k, 1, s);
   else if (middle <= small) launch_ring<4, EPI>(a, w, c, (int)m, (int)n, (int)k, 1, s);
   else launch_ring<2, EPI>(a, w, c, (int)m, (int)n, (int)k, 1, s);
+}
+
+// Small problems' fused gate_up: columns of W are gate and up of 64 outputs per tile; the same choice of rows.
+bool gemm_swiglu_small(int dtype, int64_t m, int64_t f, int64_t k, size_t workspace_bytes) {
+  return dtype == 1 && m > 0 && f % 8 == 0 && k % 8 == 0 && (f + 256) * k * 2 < (int64_t)kOffOutOfRange &&
+         takes_ring(m, 2 * f, k, workspace_bytes) && ((m + 31) / 32) * ((f + 63) / 64) <= INT32_MAX;
+}
+
+void launch_gemm_swiglu_small(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f, int64_t k, hipStream_t s) {
+  auto outputs = [&](int64_t bm) { return (((m + bm - 1) / bm) * ((f + 63) / 64) + 255) / 256 * bm; };
+  const bf16 *pa = (const bf16*)a, *pw = (const bf16*)w_gate_up;
+  if (outputs(128) <= outputs(64) && outputs(128) <= outputs(32)) launch_ring<8, kEpiSwiGLU>(pa, pw, out, (int)m, (int)f, (int)k, 1, s);
+  else if (outputs(64) <= outputs(32)) launch_ring<4, kEpiSwiGLU>(pa, pw, out, (int)m, (int)f, (int)k, 1, s);
+  else launch_ring<2, kEpiSwiGLU>(pa, pw, out, (int)m, (int)f, (int)k, 1, s);
 }
 
 // The router has few outputs and as many rows as the task: 32-row tiles, logits stored in fp32 as they come (590
@@ -1484,6 +1500,19 @@ static W4Shape w4_plan(int dtype, int64_t m, int64_t n, int64_t k, size_t worksp
   return p;
 }
 
+// Odd K on the large tile, from the number of tiles on that K % 64 == 0 takes it.  Against 128x128 tiles, us: 96 tiles
+// (3000 x 2000 x 4008) 118 -> 99, 256 tiles (4096 x 4096 x 4104) 197 -> 125, but 64 tiles (1000 x 4096 x 1000) 17 -> 25.
+static bool takes_w4_tail(int64_t m, int64_t n, int64_t k) {
+  const int64_t tiles = ((m + 255) / 256) * ((n + 255) / 256);
+  return k % kBK != 0 && n <= (1 << 21) && k <= (1 << 21) && tiles >= 96 && tiles <= INT32_MAX;
+}
+
+// Problems that 16-byte aligned operands run on the ring kernel.
+static bool takes_ring(int64_t m, int64_t n, int64_t k, size_t workspace_bytes) {
+  return !takes_w4_tail(m, n, k) && w4_plan(1, m, n, k, workspace_bytes).splits == 0 && k <= (1 << 21) &&
+         ((m + 31) / 32) * ((n + 63) / 64) <= INT32_MAX;
+}
+
 // What a problem that w4_plan cuts over K runs as.  Three or four row tiles and a short K: the 128-column
 // tile in fewer ranges (possibly one: nothing is cut then), if that occupies the chip -- fewer partial sums
 // against more operand reads per MFMA, which a long K would pay for too often.  With the reduction, us:
@@ -1529,11 +1558,8 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   // one-wave-per-SIMD DMA kernel, split over K when the caller's workspace allows.  Otherwise the ring
   // kernel on small tiles; operands that are not 16-byte aligned: the register-staged kernel on 128x128 tiles.
   const bool aligned = (reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(c)) % 16 == 0;
-  const int64_t tiles_m = (m + 255) / 256, tiles_n = (n + 255) / 256;
-  if (k % kBK != 0 && aligned && n <= (1 << 21) && k <= (1 << 21) && tiles_m * tiles_n >= 96 &&
-      tiles_m * tiles_n <= INT32_MAX) {
-    // Odd K on the large tile, from the number of tiles on that K % 64 == 0 takes it.  Against 128x128 tiles, us: 96 tiles
-    // (3000 x 2000 x 4008) 118 -> 99, 256 tiles (4096 x 4096 x 4104) 197 -> 125, but 64 tiles (1000 x 4096 x 1000) 17 -> 25.
+  if (aligned && takes_w4_tail(m, n, k)) {
+    const int64_t tiles_m = (m + 255) / 256, tiles_n = (n + 255) / 256;
     const dim3 grid((unsigned)(tiles_m * tiles_n));
     if (residual)
       gemm_bf16_w4_kernel<kEpiResidual, false, 8, true><<<grid, 256, 0, s>>>(pa, pw, c, (int)m, (int)n, (int)k, (int)tiles_m,
@@ -1558,7 +1584,7 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   } else if (splits >= 1) {
     if (residual) launch_bf16_w4<true, 4>(pa, pw, c, (int)m, (int)n, (int)k, splits, (float*)workspace, tl, s);
     else launch_bf16_w4<false, 4>(pa, pw, c, (int)m, (int)n, (int)k, splits, (float*)workspace, tl, s);
-  } else if (aligned && k <= (1 << 21) && ((m + 31) / 32) * ((n + 63) / 64) <= INT32_MAX) {
+  } else if (aligned && takes_ring(m, n, k, workspace_bytes)) {
     if (residual) launch_small_problem<kEpiResidual>(pa, pw, c, m, n, k, s);
     else launch_small_problem<kEpiBf16>(pa, pw, c, m, n, k, s);
   } else {

@@ -95,6 +95,10 @@ void launch_router_gemm(const void* a, const void* w, float* logits, int64_t m, 
 bool gemm_swiglu_fusable(int dtype, int64_t m, int64_t f, int64_t k);
 void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f,
                         int64_t k, hipStream_t s);
+// The same for problems that launch_gemm, given this workspace, runs on small tiles (K % 8 == 0, 16-byte aligned
+// operands); the same bits again.
+bool gemm_swiglu_small(int dtype, int64_t m, int64_t f, int64_t k, size_t workspace_bytes);
+void launch_gemm_swiglu_small(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f, int64_t k, hipStream_t s);
 // Grouped bf16 GEMM for mixture-of-experts layers (K % 64 == 0, n % 8 == 0): `groups` (device) =
 // {row tiles, then {expert, first row, rows <= tile_rows} per row tile}; row tile i multiplies those
 // rows with expert's matrix of w ([experts][n][k], or [experts][2n][k] gate rows then up rows when

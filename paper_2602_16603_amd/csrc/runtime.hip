@@ -105,7 +105,8 @@ struct fp_prefill : fp::OpBackend {
   void *moe_act = nullptr, *moe_y = nullptr;
   int32_t moe_max_row_tiles = 0, moe_tile_rows = 0;
   bool swiglu_fused = false;   // op 6 writes act directly (fused GEMM epilogue, or fused split-K reduction); op 7 then has no work and gu is not allocated
-  bool swiglu_epilogue = false;   // ... by the GEMM epilogue (the problem fills the chip); else by the split-K reduction
+  bool swiglu_epilogue = false;   // ... by the GEMM epilogue (the problem fills the chip); else by the split-K reduction ...
+  bool swiglu_small = false;   // ... or by the epilogue of the small tiles (the problem is far from filling it)
   bool norm_after_o = false;   // short requests: op 4's split-K reduction also normalises the row (op 5 has no work)
   bool norm_after_down = false;   // ... op 8's does (op 0 of the next layer has no work)
   void* splitk = nullptr;              // split-K partial sums (0 bytes when no GEMM of this task splits)
@@ -193,7 +194,9 @@ fp_status launch_op(fp_prefill* t, int32_t index) {
       if (!t->norm_after_o) fp::launch_rmsnorm(dt, t->x, w.mlp_norm, t->h, T, d, sh.rms_eps, s);
       break;
     case 6:
-      if (t->swiglu_epilogue) {
+      if (t->swiglu_small) {
+        fp::launch_gemm_swiglu_small(t->h, w.w_gate_up, t->act, T, F, d, s);
+      } else if (t->swiglu_epilogue) {
         fp::launch_gemm_swiglu(t->h, w.w_gate_up, t->act, T, F, d, s);
       } else {
         fp::GemmTail tail;
@@ -626,7 +629,8 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
       std::max(fp::gemm_workspace_bytes(sh.dtype, T, (int64_t)W, (int64_t)d), fp::gemm_workspace_bytes(sh.dtype, T, (int64_t)d, (int64_t)qd)),
       moe ? (size_t)0 : sk_dense);
   t->swiglu_epilogue = !moe && fp::gemm_swiglu_fusable(sh.dtype, T, (int64_t)F, (int64_t)d);
-  t->swiglu_fused = t->swiglu_epilogue ||
+  t->swiglu_small = !moe && !t->swiglu_epilogue && fp::gemm_swiglu_small(sh.dtype, T, (int64_t)F, (int64_t)d, sk_bytes);
+  t->swiglu_fused = t->swiglu_epilogue || t->swiglu_small ||
                     (!moe && fp::gemm_tail_fusable(sh.dtype, T, 2 * (int64_t)F, (int64_t)d, sk_bytes, fp::kTailSwiGLU));
   t->norm_after_o = fp::gemm_tail_fusable(sh.dtype, T, (int64_t)d, (int64_t)qd, sk_bytes, fp::kTailRmsNorm);
   t->norm_after_down = !moe && fp::gemm_tail_fusable(sh.dtype, T, (int64_t)d, (int64_t)F, sk_bytes, fp::kTailRmsNorm);

@@ -198,11 +198,12 @@ def test_empty_batch_and_invalid_arguments():
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
-@pytest.mark.parametrize("new,cached", [([1], [1023]), ([257, 40], [1008, 3000]), ([700], [2400]), ([2100], [0])])
+@pytest.mark.parametrize("new,cached", [([1], [1023]), ([257, 40], [1008, 3000]), ([700], [2400]), ([2100], [0]),
+                                        ([1], [0]), ([1], [64]), ([65], [0]), ([129], [50]), ([300, 40], [7, 100]), ([640], [63])])
 def test_attention_cut_over_its_keys(head_dim, new, cached):
     """Few query tiles over many keys: the launch is cut over the keys and the parts are merged (the
     last part holds the diagonal; a tile of one row, of a full and a nearly empty tile, of two
-    sequences of unlike length).  Against the oracle's one-shot prefill."""
+    sequences of unlike length), and left whole over few keys.  Against the oracle's one-shot prefill."""
     spec = I.ShapeSpec(1, 256, 4, 2, head_dim, 704, 1e-5, 10000.0)
     full = [n + c for n, c in zip(new, cached)]
     model, weights = build(spec, 27, "bf16", pool_blocks=512, max_position=max(full), random_gains=True)
@@ -228,4 +229,23 @@ def test_attention_cut_over_its_keys(head_dim, new, cached):
     assert torch.equal(again.hidden(), got)               # parts are merged in a fixed order
     task.end()
     again.end()
+    model.close()
+
+
+@pytest.mark.parametrize("hidden,ffn,lengths", [(256, 704, [200]), (256, 704, [1]), (264, 200, [33, 64]), (320, 1032, [700])])
+def test_small_models_fuse_gate_up(hidden, ffn, lengths):
+    """A stack whose gate_up projection is far from filling the chip runs it on small tiles with
+    SiLU(gate)*up in the epilogue (rows and columns that leave partly filled tiles, K with a tail): against the
+    oracle, and operator 7 launches nothing."""
+    from paper_2602_16603_amd import binding as B
+    spec = I.ShapeSpec(2, hidden, 4, 2, 64, ffn, 1e-5, 10000.0)
+    total = sum(lengths)
+    model, weights = build(spec, 28, "bf16", total_tokens=total, max_position=1024, random_gains=True)
+    rows = I.make_hidden(total, hidden, 28, torch.bfloat16, "cpu")
+    task = model.begin(rows.cuda(), lengths)
+    B.fp_prefill_set_timing(task.handle, True)
+    task.run_to_completion()
+    assert B.fp_prefill_op_times(task.handle, 18)[7] == 0.0
+    check_against_oracle(spec, weights, rows, lengths, task, "bf16")
+    task.end()
     model.close()
