@@ -1194,11 +1194,12 @@ size_t gemm_workspace_bytes(int dtype, int64_t m, int64_t n, int64_t k) {
 
 // tail: what follows the split-K reduction in the same kernel (kTailNone: nothing).
 // Row tile of a grouped launch whose experts receive `mean_rows` rows on average: the smallest that holds most
-// experts in one tile, up to 128 rows of the few-rows kernel; from about 100 rows on the matrix pipes bound the
+// experts in one tile, up to 128 rows of the ring kernel; from about 100 rows on the matrix pipes bound the
 // launch and the 256-row tile is ahead.  experts_up / experts_down (with the combine) of the 30B-A3B shape, us, with tiles
 // of 256, 128, 64 and 32 rows: 6 rows per expert 214/110, 186/97, 170/82, 159/80; 37 rows 224/121, 198/99,
-// 187/99, 192/108; 64 rows 235/126, 204/110, 209/117, -; 125 rows 247/140, 254/150, -, -.
-int moe_tile_rows(int64_t mean_rows) { return mean_rows <= 18 ? 32 : mean_rows <= 44 ? 64 : mean_rows <= 100 ? 128 : 256; }
+// 187/99, 192/108; with every tile's own start in K: 50 rows -, 194/104, 178/102, -; 64 rows -, 194/109,
+// 215/118, -; 119 rows 217/140, 244/145, -, -.
+int moe_tile_rows(int64_t mean_rows) { return mean_rows <= 18 ? 32 : mean_rows <= 52 ? 64 : mean_rows <= 100 ? 128 : 256; }
 
 template <int MI, int EPI>
 static void launch_grouped_ring(const bf16* a, const bf16* w, void* c, int n, int k, const int32_t* groups,
