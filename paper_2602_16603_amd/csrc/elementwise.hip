@@ -162,7 +162,21 @@ void launch_silu_mul(int dtype, const void* gu, void* out, int64_t t, int64_t f,
 // Pair (j, j+D/2) is rotated by angle pos * theta^(-2j/D); cos/sin come from a table computed in
 // fp64 on the host.
 // ------------------------------------------------------------------------------------------
-template <typename T>
+// PARTS: a short request's projection was cut over K and its fp32 partial sums are added up here, in index order and
+// rounded to the storage type -- the bits of the stand-alone reduction, one launch and one pass over qkv less.
+template <typename T, bool PARTS>
+__device__ __forceinline__ f32x8 qkv_load8(const T* __restrict__ qkv, const float* __restrict__ part, int64_t at, int64_t slab, int parts) {
+  if (!PARTS) return Vec8<T>::load(qkv + at);
+  f32x8 acc = Vec8<float>::load(part + at);
+  for (int z = 1; z < parts; ++z) {
+    const f32x8 v = Vec8<float>::load(part + z * slab + at);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] += v[e];
+  }
+  return __builtin_convertvector(__builtin_convertvector(acc, vec8<T>), f32x8);
+}
+
+template <typename T, bool PARTS>
 __global__ __launch_bounds__(256) void rope_kvwrite_kernel(
     T* __restrict__ qkv, const float* __restrict__ rope_cos, const float* __restrict__ rope_sin,
     int n_q_heads, int n_kv_heads, int head_dim, int64_t kv_num_blocks, int layer,
@@ -170,11 +184,12 @@ __global__ __launch_bounds__(256) void rope_kvwrite_kernel(
     const int32_t* __restrict__ tok_seq, const int32_t* __restrict__ tok_pos,
     const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ cached_lens,
     const int32_t* __restrict__ block_tables, int max_blocks,
-    const int32_t* __restrict__ kv_items) {
+    const int32_t* __restrict__ kv_items, const float* __restrict__ part, int parts) {
   const int tid = threadIdx.x;
   const int half = head_dim / 2;
   const int64_t width = (int64_t)(n_q_heads + 2 * n_kv_heads) * head_dim;
   const int n_kv_items = (int)gridDim.x - n_tokens;
+  const int64_t slab = n_tokens * width;
   if ((int)blockIdx.x >= n_kv_items) {
     const int t = (int)blockIdx.x - n_kv_items;
     const int s = tok_seq[t];
@@ -189,8 +204,9 @@ __global__ __launch_bounds__(256) void rope_kvwrite_kernel(
       const int h = u / per_head;
       const int j = (u - h * per_head) * 8;
       T* base = row + (int64_t)h * head_dim;
-      f32x8 a = Vec8<T>::load(base + j);
-      f32x8 b = Vec8<T>::load(base + half + j);
+      const int64_t at = t * width + (int64_t)h * head_dim + j;
+      f32x8 a = qkv_load8<T, PARTS>(qkv, part, at, slab, parts);
+      f32x8 b = qkv_load8<T, PARTS>(qkv, part, at + half, slab, parts);
       f32x8 c = Vec8<float>::load(cs + j);
       f32x8 sv = Vec8<float>::load(sn + j);
       f32x8 ra, rb;
@@ -224,6 +240,47 @@ __global__ __launch_bounds__(256) void rope_kvwrite_kernel(
   const int p_hi = min(lb * kKvBlock + kKvBlock, cached + n_new);
   const int units = n_kv_heads * head_dim / 8;
   const int64_t v_off = (int64_t)(n_q_heads + n_kv_heads) * head_dim;
+  if (PARTS) {                                       // half a block of 8 channels per thread: the sums are loads enough
+    for (int u2 = tid; u2 < 2 * units; u2 += 256) {
+      const int h = u2 / units, u = u2 - h * units;
+      const int kh = u / (head_dim / 8);
+      const int d0 = (u - kh * (head_dim / 8)) * 8;
+      T* dst = v_pool + (((int64_t)layer * kv_num_blocks + blk) * n_kv_heads + kh) *
+                            ((int64_t)head_dim * kKvBlock) + (int64_t)d0 * kKvBlock + 8 * h;
+      const int first = lb * kKvBlock + 8 * h;
+      if (first >= p_hi || first + 8 <= p_lo) continue;
+      int64_t at[8];
+      f32x8 acc[8];
+#pragma unroll
+      for (int tk = 0; tk < 8; ++tk) {
+        const int p = min(max(first + tk, p_lo), p_hi - 1);
+        at[tk] = (seq_lo + (p - cached)) * width + v_off + kh * head_dim + d0;
+        acc[tk] = Vec8<float>::load(part + at[tk]);
+      }
+      for (int z = 1; z < parts; ++z)
+#pragma unroll
+        for (int tk = 0; tk < 8; ++tk) {
+          const f32x8 v = Vec8<float>::load(part + z * slab + at[tk]);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[tk][e] += v[e];
+        }
+      const bool all = first >= p_lo && first + 8 <= p_hi;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        vec8<T> piece;
+#pragma unroll
+        for (int tk = 0; tk < 8; ++tk) piece[tk] = static_cast<T>(acc[tk][e]);
+        if (all) {
+          *reinterpret_cast<vec8<T>*>(dst + e * kKvBlock) = piece;
+        } else {
+#pragma unroll
+          for (int tk = 0; tk < 8; ++tk)
+            if (first + tk >= p_lo && first + tk < p_hi) dst[e * kKvBlock + tk] = piece[tk];
+        }
+      }
+    }
+    return;
+  }
   for (int u = tid; u < units; u += 256) {
     const int kh = u / (head_dim / 8);
     const int d0 = (u - kh * (head_dim / 8)) * 8;
@@ -263,19 +320,24 @@ __global__ __launch_bounds__(256) void rope_kvwrite_kernel(
 
 void launch_rope_kvwrite(int dtype, void* qkv, const float* rope_cos, const float* rope_sin,
                          const Geometry& g, const BatchMeta& m, int layer, void* k_pool,
-                         void* v_pool, hipStream_t s) {
+                         void* v_pool, const float* part, int parts, hipStream_t s) {
   if (m.n_tokens == 0) return;
   dim3 grid((unsigned)(m.n_tokens + m.n_kv_items));
-  if (dtype == 1)
-    rope_kvwrite_kernel<bf16><<<grid, 256, 0, s>>>(
+  if (dtype == 1 && parts > 0)
+    rope_kvwrite_kernel<bf16, true><<<grid, 256, 0, s>>>(
         (bf16*)qkv, rope_cos, rope_sin, g.n_q_heads, g.n_kv_heads, g.head_dim, g.kv_num_blocks,
         layer, (bf16*)k_pool, (bf16*)v_pool, m.n_tokens, m.tok_seq, m.tok_pos, m.cu_seqlens,
-        m.cached_lens, m.block_tables, m.max_blocks, m.kv_items);
+        m.cached_lens, m.block_tables, m.max_blocks, m.kv_items, part, parts);
+  else if (dtype == 1)
+    rope_kvwrite_kernel<bf16, false><<<grid, 256, 0, s>>>(
+        (bf16*)qkv, rope_cos, rope_sin, g.n_q_heads, g.n_kv_heads, g.head_dim, g.kv_num_blocks,
+        layer, (bf16*)k_pool, (bf16*)v_pool, m.n_tokens, m.tok_seq, m.tok_pos, m.cu_seqlens,
+        m.cached_lens, m.block_tables, m.max_blocks, m.kv_items, nullptr, 0);
   else
-    rope_kvwrite_kernel<float><<<grid, 256, 0, s>>>(
+    rope_kvwrite_kernel<float, false><<<grid, 256, 0, s>>>(
         (float*)qkv, rope_cos, rope_sin, g.n_q_heads, g.n_kv_heads, g.head_dim, g.kv_num_blocks,
         layer, (float*)k_pool, (float*)v_pool, m.n_tokens, m.tok_seq, m.tok_pos, m.cu_seqlens,
-        m.cached_lens, m.block_tables, m.max_blocks, m.kv_items);
+        m.cached_lens, m.block_tables, m.max_blocks, m.kv_items, nullptr, 0);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -1100,16 +1100,27 @@ template <int MI, bool SWIGLU> struct RingTile {
   static constexpr bool kWide = SWIGLU || MI > 4;
   static constexpr int NJ = kWide ? 2 : 1, KT = kWide ? 64 : 128, S = 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
 };
+struct KRanges {
+  int per, used;      // k-tiles of 64 per range, ranges (every range has at least one k-tile)
+};
+static KRanges k_ranges(int k, int splits) {
+  const int kt = (k + kBK - 1) / kBK, per = (kt + splits - 1) / splits;
+  return {per, (kt + per - 1) / per};
+}
+// A CU holds one workgroup of the ring kernel: no more K ranges than it takes to occupy the 256 once.
+template <int MI, int EPI>
+static KRanges ring_ranges(int n, int k, int splits) {
+  using T = RingTile<MI, EPI == kEpiSwiGLU>;
+  return k_ranges(k, splits > 1 ? std::max(2, std::min(splits, 256 / ((n + T::BN - 1) / T::BN))) : 1);
+}
 template <int MI, int EPI>
 static int launch_ring(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
   using T = RingTile<MI, EPI == kEpiSwiGLU>;
-  const int tiles_m = (m + 16 * MI - 1) / (16 * MI), tiles_n = (n + T::BN - 1) / T::BN, kt = (k + kBK - 1) / kBK;
-  // A CU holds one of these workgroups: no more K ranges than it takes to occupy the 256 once.
-  if (splits > 1) splits = std::max(2, std::min(splits, 256 / tiles_n));
-  const int per = (kt + splits - 1) / splits, used = (kt + per - 1) / per;   // every range has at least one k-tile
-  gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, EPI, false><<<dim3((unsigned)(tiles_m * tiles_n * used)), 256, 0, s>>>(
-      a, w, c, m, n, k, tiles_m, tiles_n, per, nullptr, nullptr);
-  return used;
+  const int tiles_m = (m + 16 * MI - 1) / (16 * MI), tiles_n = (n + T::BN - 1) / T::BN;
+  const KRanges r = ring_ranges<MI, EPI>(n, k, splits);
+  gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, EPI, false><<<dim3((unsigned)(tiles_m * tiles_n * r.used)), 256, 0, s>>>(
+      a, w, c, m, n, k, tiles_m, tiles_n, r.per, nullptr, nullptr);
+  return r.used;
 }
 // Returns the number of K ranges launched (at most `splits`).
 template <int EPI>
@@ -1256,13 +1267,14 @@ static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, 
         <<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(a, w, c, m, n, k, tiles_m, tiles_n, kt, nullptr, nullptr);
     return;
   }
-  const int per = (kt + splits - 1) / splits;
-  int used = (kt + per - 1) / per;                   // every launched split has at least one k-tile
+  const KRanges r = k_ranges(k, splits);
+  int used = r.used;
   if (m <= kFewRows)
     used = launch_few_rows<kEpiPartial>(a, w, workspace, m, n, k, splits, s);
   else
     gemm_bf16_w4_kernel<kEpiPartial, false, NJ><<<dim3((unsigned)(tiles_m * tiles_n * used)), 256, 0, s>>>(
-        a, w, workspace, m, n, k, tiles_m, tiles_n, per, nullptr, nullptr);
+        a, w, workspace, m, n, k, tiles_m, tiles_n, r.per, nullptr, nullptr);
+  if (tail.kind == kTailLeave) return;               // (gemm_left_ranges tells the caller how many ranges)
   const int64_t mn = (int64_t)m * n;
   if (RESID && tail.kind == kTailRmsNorm)
     splitk_reduce_norm_kernel<<<dim3((unsigned)m), 256, 0, s>>>(workspace, (float*)c, (const bf16*)tail.gain,
@@ -1530,7 +1542,17 @@ bool gemm_tail_fusable(int dtype, int64_t m, int64_t n, int64_t k, size_t worksp
   if (w4_plan(dtype, m, n, k, workspace_bytes).splits <= 1) return false;   // tails ride on the split-K reduction
   if (tail_kind == kTailRmsNorm) return n <= kTailNormCols;
   if (tail_kind == kTailSwiGLU) return n % 16 == 0;
-  return false;
+  return tail_kind == kTailLeave;
+}
+
+int gemm_left_ranges(int dtype, int64_t m, int64_t n, int64_t k, size_t workspace_bytes) {
+  W4Shape plan = w4_plan(dtype, m, n, k, workspace_bytes);
+  if (plan.splits > 1) plan = w4_cut(m, n, k, false, plan);
+  if (plan.splits <= 1) return 0;
+  if (m > kFewRows) return k_ranges((int)k, plan.splits).used;
+  if (m <= 32) return ring_ranges<2, kEpiPartial>((int)n, (int)k, plan.splits).used;
+  if (m <= 64) return ring_ranges<4, kEpiPartial>((int)n, (int)k, plan.splits).used;
+  return ring_ranges<8, kEpiPartial>((int)n, (int)k, plan.splits).used;
 }
 
 void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, int64_t n,

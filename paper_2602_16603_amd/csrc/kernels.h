@@ -57,10 +57,11 @@ void launch_task_start(int dtype, const void* in, float* x, const void* gain, vo
 void launch_rmsnorm(int dtype, const float* x, const void* gain, void* out, int64_t t, int64_t d,
                     float eps, hipStream_t s);
 void launch_silu_mul(int dtype, const void* gu, void* out, int64_t t, int64_t f, hipStream_t s);
-// qkv [T, qkv_width] in place for the query columns; rotated keys and raw values go to the pools.
+// qkv [T, qkv_width] in place for the query columns; rotated keys and raw values go to the pools.  parts > 0 (bf16): the
+// projection left its sums as that many slabs at `part` (kTailLeave), and qkv is only written.
 void launch_rope_kvwrite(int dtype, void* qkv, const float* rope_cos, const float* rope_sin,
                          const Geometry& g, const BatchMeta& m, int layer, void* k_pool,
-                         void* v_pool, hipStream_t s);
+                         void* v_pool, const float* part, int parts, hipStream_t s);
 void launch_attention(int dtype, const void* qkv, const void* k_pool, const void* v_pool,
                       void* o, const Geometry& g, const BatchMeta& m, int layer, hipStream_t s);
 // C[M,N] = A[M,K] W[N,K]^T  (residual == 0, C in the storage dtype), or C_f32 += ... (residual).
@@ -73,8 +74,10 @@ void launch_attention(int dtype, const void* qkv, const void* k_pool, const void
 //   kTailRmsNorm  residual projections: tail.out [M,N] (storage dtype) = rmsnorm(updated C row) * tail.gain
 //   kTailSwiGLU   gate_up projection (N = 2F, gate columns first): tail.out [M,F] = silu(gate) * up and C
 //                 is NOT written
+//   kTailLeave    C is not written: the partial sums stay in the workspace, gemm_left_ranges() slabs of fp32 [M][N], to be
+//                 added in index order and rounded by the operator that follows (qkv projection: launch_rope_kvwrite)
 // with the bits the stand-alone operators give.
-enum { kTailNone = 0, kTailRmsNorm = 1, kTailSwiGLU = 2 };
+enum { kTailNone = 0, kTailRmsNorm = 1, kTailSwiGLU = 2, kTailLeave = 3 };
 struct GemmTail {
   int kind = kTailNone;
   const void* gain = nullptr;
@@ -82,6 +85,8 @@ struct GemmTail {
   float eps = 0.f;
 };
 bool gemm_tail_fusable(int dtype, int64_t m, int64_t n, int64_t k, size_t workspace_bytes, int tail_kind);
+// K ranges a projection without residual is cut into with this workspace; 0: it is not cut.
+int gemm_left_ranges(int dtype, int64_t m, int64_t n, int64_t k, size_t workspace_bytes);
 void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, int64_t n,
                  int64_t k, int residual, void* workspace, size_t workspace_bytes, hipStream_t s,
                  const GemmTail* tail = nullptr);

@@ -109,6 +109,7 @@ struct fp_prefill : fp::OpBackend {
   bool swiglu_small = false;   // ... or by the epilogue of the small tiles (the problem is far from filling it)
   bool norm_after_o = false;   // short requests: op 4's split-K reduction also normalises the row (op 5 has no work)
   bool norm_after_down = false;   // ... op 8's does (op 0 of the next layer has no work)
+  int qkv_parts = 0;                   // short requests: op 1 leaves this many slabs of partial sums, op 2 adds them up
   void* splitk = nullptr;              // split-K partial sums (0 bytes when no GEMM of this task splits)
   size_t splitk_bytes = 0;
   fp::BatchMeta meta{};
@@ -176,10 +177,15 @@ fp_status launch_op(fp_prefill* t, int32_t index) {
       // (the first layer's norm is done when the task starts, a later one's may ride on the layer before)
       if (layer > 0 && !t->norm_after_down) fp::launch_rmsnorm(dt, t->x, w.attn_norm, t->h, T, d, sh.rms_eps, s);
       break;
-    case 1: fp::launch_gemm(dt, t->h, w.w_qkv, t->qkv, T, m->geo.qkv_width(), d, 0, t->splitk, t->splitk_bytes, s); break;
+    case 1: {
+      fp::GemmTail tail;
+      if (t->qkv_parts > 0) tail.kind = fp::kTailLeave;
+      fp::launch_gemm(dt, t->h, w.w_qkv, t->qkv, T, m->geo.qkv_width(), d, 0, t->splitk, t->splitk_bytes, s, &tail);
+      break;
+    }
     case 2:
       fp::launch_rope_kvwrite(dt, t->qkv, m->rope_cos, m->rope_sin, m->geo, t->meta, layer,
-                              m->k_pool, m->v_pool, s);
+                              m->k_pool, m->v_pool, static_cast<const float*>(t->splitk), t->qkv_parts, s);
       break;
     case 3:
       fp::launch_attention(dt, t->qkv, m->k_pool, m->v_pool, t->o, m->geo, t->meta, layer, s);
@@ -632,6 +638,10 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
   t->swiglu_small = !moe && !t->swiglu_epilogue && fp::gemm_swiglu_small(sh.dtype, T, (int64_t)F, (int64_t)d, sk_bytes);
   t->swiglu_fused = t->swiglu_epilogue || t->swiglu_small ||
                     (!moe && fp::gemm_tail_fusable(sh.dtype, T, 2 * (int64_t)F, (int64_t)d, sk_bytes, fp::kTailSwiGLU));
+  // Two slabs are added up in passing (50 tokens of the 8B shape: reduction 4.0 + RoPE 4.6 -> 6.4 us); more of them hold
+  // up the few workgroups that write the value blocks (256 tokens, five slabs: 6.0 + 4.9 -> 14.4).
+  t->qkv_parts = fp::gemm_left_ranges(sh.dtype, T, (int64_t)W, (int64_t)d, sk_bytes);
+  if (t->qkv_parts > 2) t->qkv_parts = 0;
   t->norm_after_o = fp::gemm_tail_fusable(sh.dtype, T, (int64_t)d, (int64_t)qd, sk_bytes, fp::kTailRmsNorm);
   t->norm_after_down = !moe && fp::gemm_tail_fusable(sh.dtype, T, (int64_t)d, (int64_t)F, sk_bytes, fp::kTailRmsNorm);
   const size_t o_x = carve(Tn * d * 4), o_h = carve(Tn * d * e), o_qkv = carve(Tn * W * e),

@@ -249,3 +249,35 @@ def test_small_models_fuse_gate_up(hidden, ffn, lengths):
     check_against_oracle(spec, weights, rows, lengths, task, "bf16")
     task.end()
     model.close()
+
+
+@pytest.mark.parametrize("new,cached", [([1], [0]), ([37], [5]), ([100, 28], [3, 16]), ([300, 7, 64], [9, 30, 0])])
+def test_rope_adds_up_the_projection_of_a_short_request(new, cached):
+    """A short request's qkv projection is cut over K and RoPE + KV write adds the partial sums: few rows, one
+    and two row tiles, first and last cache blocks that are partly old and partly filled.  The slots of
+    tokens that are not new keep their bits."""
+    spec = I.ShapeSpec(1, 1024, 32, 8, 128, 256, 1e-5, 10000.0)
+    from paper_2602_16603_amd import binding as B
+    assert B.fp_op_gemm_workspace_bytes(1, sum(new), spec.qkv_width, spec.hidden) > 0
+    full = [n + c for n, c in zip(new, cached)]
+    model, weights = build(spec, 29, "bf16", pool_blocks=64, max_position=max(full), random_gains=True)
+    rows = [I.make_hidden(n, spec.hidden, 29 + i, torch.bfloat16, "cpu") for i, n in enumerate(full)]
+    table, _ = I.permuted_block_tables(full, None, 16, 64, seed=7)
+    before = None
+    if any(cached):
+        first = model.begin(torch.cat([r[:c] for r, c in zip(rows, cached)]).cuda(), cached, [0] * len(full), table)
+        first.run_to_completion()
+        before = [first.kv(0, s) for s in range(len(full))]
+        first.end()
+    task = model.begin(torch.cat([r[c:] for r, c in zip(rows, cached)]).cuda(), new, cached, table)
+    task.run_to_completion()
+    x_ref, cache_ref = O.prefill(oracle_shape(spec), oracle_layers(weights), torch.cat(rows), I.cu_seqlens_of(full))
+    x_ref = torch.cat([x[c:] for x, c in zip(x_ref.split(full), cached)])
+    assert max_rel_err(task.hidden(), x_ref) <= TOL["bf16"]
+    for s in range(len(full)):
+        k, v = task.kv(0, s)
+        assert max_rel_err(k, cache_ref.k[0][s]) <= TOL["bf16"] and max_rel_err(v, cache_ref.v[0][s]) <= TOL["bf16"]
+        if before is not None and cached[s]:
+            assert torch.equal(k[:cached[s]], before[s][0]) and torch.equal(v[:cached[s]], before[s][1])
+    task.end()
+    model.close()
