@@ -1090,7 +1090,7 @@ static W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
 }
 
 // Few rows: up to kFewRows of them.  Columns per tile, k-tile and stages by row count and epilogue, as measured on
-// cold weights of the 8B shape (us, start -> now): up to 64 rows 64-column tiles of 128 k (256 bytes of a
+// cold weights of the 8B shape (us, against the two-stage 256-row tile): up to 64 rows 64-column tiles of 128 k (256 bytes of a
 // weight row at a time: HBM gives 4.9 TB/s to such pieces where 128-byte pieces get 4.2) -- 50 rows: qkv
 // 22 -> 17, o 17.5 -> 12.7, down 40 -> 27; from 65 rows on the A tile weighs more and 128-column tiles of 64 k
 // read it half as often -- 128 rows: qkv 23, down 34 (26, 41 on the former).  SwiGLU: 128 W rows of 64 k, 74 ->
