@@ -553,27 +553,30 @@ size_t attn_part_floats(const Geometry& g) { return (size_t)g.n_q_heads * 256 * 
 
 // A workgroup walks its keys one tile after the other and a CU holds one workgroup, so a launch of few
 // query tiles over many keys -- a chunk of a long prompt -- keeps most CUs idle for the whole walk.  Cut
-// over the keys it ends when its longest part does, plus the merge.  Times in key tiles (about 1.4 us): a
-// part pays kPartCost on top of its keys (prologue, first loads, storing its output), the merge kMergeCost.
+// over the keys it ends when its longest part does, plus the merge.  Times in key tiles (about 1.4 us): a query
+// tile pays kWholeCost on top of its keys (prologue, first loads), a part kPartCost (and storing its output: 133 KB
+// per head), the merge kMergeCost and the reading of all parts (50 (part, head) pairs in the time of a tile).
 // All heads of a query tile take equally long, so the 256 CUs count as 256 / heads places that each
 // take one (query tile, every head) at a time, longest first.  More than four such rounds balance
 // themselves.  No part is shorter than kMinPart tiles (its first key must be visible to all 256 queries
 // of the tile, which five tiles ensure).  512 tokens behind 15872 cached ones, 32 heads of 128: 365 us
-// whole (64 workgroups of 256 tiles), 130 + 8 us in four parts per query tile.
+// whole (64 workgroups of 256 tiles), 130 + 8 us in four parts per query tile; 128 behind 24576 461 -> 81 us, 1100
+// behind 20000 434 -> 323, 2048 behind 2048 stays whole (101; in parts 106).
 int attention_part_tiles(const std::vector<int32_t>& tiles, int n_q_heads) {
-  constexpr int kPlaces = 256, kMaxPlaces = 64, kRounds = 4, kMinPart = 8, kPartCost = 3, kMergeCost = 6, kMaxParts = 16;
+  constexpr int kPlaces = 256, kMaxPlaces = 64, kRounds = 4, kMinPart = 8, kWholeCost = 3, kPartCost = 5, kMergeCost = 4, kMaxParts = 16;
   const int places = std::min(kMaxPlaces, std::max(1, kPlaces / n_q_heads));
   if (tiles.empty() || (int)tiles.size() > kRounds * places || tiles[0] < 2 * kMinPart) return 0;
   auto end_of = [&](int limit) {                    // when the last part of at most `limit` tiles is done
-    int at[kMaxPlaces] = {};
+    int at[kMaxPlaces] = {}, stored = 0;
     for (int32_t n : tiles) {
       const int parts = limit ? (n + limit - 1) / limit : 1;
+      if (parts > 1) stored += parts;
       for (int p = 0; p < parts; ++p) {
         int* soonest = std::min_element(at, at + places);
-        *soonest += (n + parts - 1) / parts + kPartCost;
+        *soonest += (n + parts - 1) / parts + (parts > 1 ? kPartCost : kWholeCost);
       }
     }
-    return *std::max_element(at, at + places) + (limit ? kMergeCost : 0);
+    return *std::max_element(at, at + places) + (stored ? kMergeCost + stored * n_q_heads / 50 : 0);
   };
   int best = 0, best_end = end_of(0);
   best_end -= best_end / 16;                        // worth it from about a sixteenth on
