@@ -11,9 +11,9 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 PKG = os.path.dirname(HERE)
 LIB = os.path.join(PKG, "libflowprefill.so")
-SOURCES = ["runtime.hip", "gemm.hip", "attention.hip", "elementwise.hip", "scheduler.hip", "moe.hip", "noalloc.hip"]
-# attention.hip never produces a NaN (masked scores are -inf and only ever meet finite values),
-# so the max reductions need no NaN-quieting canonicalisation.
+SOURCES = ["runtime.hip", "gemm.hip", "attention.hip", "attention_f32.hip", "elementwise.hip", "scheduler.hip", "moe.hip", "noalloc.hip"]
+# attention.hip (bf16) makes no NaN of finite operands (masked scores are -inf and only ever meet finite
+# values), so the max reductions need no NaN-quieting canonicalisation.
 EXTRA = {"attention.hip": ["-fno-honor-nans"]}
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -64,6 +64,8 @@ void launch_rope_kvwrite(int dtype, void* qkv, const float* rope_cos, const floa
                          void* v_pool, const float* part, int parts, hipStream_t s);
 void launch_attention(int dtype, const void* qkv, const void* k_pool, const void* v_pool,
                       void* o, const Geometry& g, const BatchMeta& m, int layer, hipStream_t s);
+void launch_attention_f32(const float* qkv, const float* k_pool, const float* v_pool, float* o, const Geometry& g,
+                          const BatchMeta& m, int layer, hipStream_t s);   // launch_attention's fp32 half
 // C[M,N] = A[M,K] W[N,K]^T  (residual == 0, C in the storage dtype), or C_f32 += ... (residual).
 // `workspace` (device, may be null) holds split-K partial sums for problems too small to fill the
 // chip with output tiles alone; gemm_workspace_bytes says how much such a problem wants (0 if

@@ -441,7 +441,7 @@ fp_status fp_model_create(const fp_shape* shape, const fp_layer_weights* layers,
                 hipGetErrorString(e));
   }
   // The pools start at zero so that never-written slots of a partially filled block hold finite
-  // values (the attention kernel multiplies them by an exact zero weight).
+  // values (the bf16 attention kernel multiplies them by an exact zero weight).
   if ((e = hipMemcpy(m->rope_cos, hc.data(), tbytes, hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemcpy(m->rope_sin, hs.data(), tbytes, hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemset(m->k_pool, 0, pool_bytes)) != hipSuccess ||

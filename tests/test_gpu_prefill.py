@@ -281,3 +281,56 @@ def test_rope_adds_up_the_projection_of_a_short_request(new, cached):
             assert torch.equal(k[:cached[s]], before[s][0]) and torch.equal(v[:cached[s]], before[s][1])
     task.end()
     model.close()
+
+
+@pytest.mark.parametrize("lengths", [[5], [16, 3], [37], [300, 21]])
+def test_fp32_slots_of_an_earlier_request_do_not_matter(lengths):
+    """The slots behind a sequence's last token still hold what an earlier request left in the block, here
+    NaN in every slot of the pool: a later request's results have the bits they have in a pool that was never used."""
+    model, _ = build(I.TINY, 61, "fp32", pool_blocks=32, max_position=512)
+    hidden = I.make_hidden(sum(lengths), I.TINY.hidden, 61, torch.float32, "cuda")
+    print(f"fp32 reused blocks {lengths}", flush=True)
+
+    def outputs():
+        task = model.begin(hidden, lengths)
+        task.run_to_completion()
+        out = [task.hidden()] + [t for layer in range(2) for s in range(len(lengths)) for t in task.kv(layer, s)]
+        task.end()
+        return out
+
+    want = outputs()
+    poison = model.begin(torch.full((512, I.TINY.hidden), float("nan"), device="cuda"), [512])   # every block of the pool
+    poison.run_to_completion()
+    assert not torch.isfinite(poison.kv(1, 0)[1]).any()
+    poison.end()
+    got = outputs()
+    assert all(torch.isfinite(t).all() for t in want)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("head_dim", [16, 128])
+@pytest.mark.parametrize("new,cached,at", [(40, 0, 33), (40, 0, 20), (21, 0, 20), (30, 5, 17), (90, 27, 70)])
+def test_fp32_tokens_see_no_later_token_that_is_not_finite(head_dim, new, cached, at):
+    """Causality holds for NaN too: tokens in front of a NaN one, its own cache block's among them, have the bits
+    they have when that token is an ordinary one; from that token on every row is NaN."""
+    spec = I.ShapeSpec(1, 64, 6, 3, head_dim, 64, 1e-5, 10000.0)
+    model, _ = build(spec, 62, "fp32", pool_blocks=32, max_position=256)
+    hidden = I.make_hidden(cached + new, spec.hidden, 62, torch.float32, "cuda")
+    table, _ = I.permuted_block_tables([new], [cached], 16, 32, seed=62)
+    if cached:
+        first = model.begin(hidden[:cached].contiguous(), [cached], [0], table)
+        first.run_to_completion()
+        first.end()
+    print(f"fp32 causality head_dim={head_dim} new={new} cached={cached} at={at}", flush=True)
+    out = []
+    for value in (None, float("nan")):
+        rows = hidden[cached:].clone()
+        if value is not None:
+            rows[at] = value
+        task = model.begin(rows, [new], [cached], table)
+        task.run_to_completion()
+        out.append(task.hidden())
+        task.end()
+    assert torch.isfinite(out[0]).all()
+    assert torch.equal(out[1][:at], out[0][:at])
+    assert torch.isnan(out[1][at:]).all()
