@@ -58,6 +58,7 @@ __global__ __launch_bounds__(1024) void moe_route_kernel(const float* __restrict
       const int e = lane + 64 * i;
       p[q][i] = e < n_experts ? logits[(int64_t)min(t0 + q, n_tokens - 1) * n_experts + e] : -INFINITY;
     }
+  float total[Q];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const float mx = wave_max_dpp(fmaxf(fmaxf(p[q][0], p[q][1]), fmaxf(p[q][2], p[q][3])));
@@ -71,12 +72,13 @@ __global__ __launch_bounds__(1024) void moe_route_kernel(const float* __restrict
     const float inv = 1.0f / sum;
 #pragma unroll
     for (int i = 0; i < 4; ++i) p[q][i] = p[q][i] >= 0.f ? p[q][i] * inv : -1.0f;
+    total[q] = mx == INFINITY ? NAN : 0.f;          // a logit of +inf: the softmax, and with it every weight, is NaN
   }
   // Lane j (< 8) of the wave keeps choice j of every token.
-  float my_p[Q], total[Q];
+  float my_p[Q];
   int my_e[Q];
 #pragma unroll
-  for (int q = 0; q < Q; ++q) { my_p[q] = 0.f; my_e[q] = 0; total[q] = 0.f; }
+  for (int q = 0; q < Q; ++q) { my_p[q] = 0.f; my_e[q] = 0; }
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     if (j >= top_k) break;

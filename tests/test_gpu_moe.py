@@ -166,3 +166,32 @@ def test_expert_row_tiles_of_every_size(tokens):
     model, task, _, _ = run_and_check(I.TINY_MOE, [tokens], 56, pool_blocks=64)
     task.end()
     model.close()
+
+
+def test_a_router_logit_beyond_the_fp32_range_is_not_hidden():
+    """A logit of +inf makes the softmax NaN: that token's weights and output row are NaN, every other row is the
+    one of a run without it."""
+    B, R = _mods()
+    spec = I.TINY_MOE.with_layers(1)
+    tokens, row, expert, channel = 70, 33, 3, 5
+    weights = I.make_weights(spec, 57, torch.bfloat16, "cpu")
+    weights[0]["w_o"].zero_()                          # the router sees the norm of the input itself
+    hidden = I.make_hidden(tokens, spec.hidden, 57, torch.bfloat16, "cpu")
+    hidden[:, channel] = 0
+    hidden[row, channel] = 4.0
+    outs = []
+    for big in (False, True):
+        weights[0]["w_router"][expert] = 0
+        weights[0]["w_router"][expert, channel] = 3e38 if big else 0.0
+        model = R.PrefillModel(spec, weights, B.FP_DTYPE_BF16, 16, 128)
+        task = model.begin(hidden.cuda(), [tokens])
+        task.run_to_completion()
+        outs.append((task.hidden().cpu(), *(t.cpu() for t in task.moe_routing(0))))
+        task.end()
+        model.close()
+    others = torch.arange(tokens) != row
+    (x0, ids0, wts0), (x1, ids1, wts1) = outs
+    assert int(ids1.min()) >= 0 and int(ids1.max()) < spec.n_experts
+    assert torch.isnan(wts1[row]).all() and torch.isnan(x1[row]).all()
+    assert torch.isfinite(x0).all() and torch.equal(ids1[others], ids0[others])
+    assert torch.equal(wts1[others], wts0[others]) and torch.equal(x1[others], x0[others])
