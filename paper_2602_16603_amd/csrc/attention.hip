@@ -269,12 +269,15 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(
         mx1 = max3(mx1, sacc[1][r], sacc[1][r + 1]);
       }
       const float mx = xhalf_max(fmaxf(mx0, mx1));
-      // The item's first key is visible to every query of the tile, so mx is finite from the first tile on.
+      // The item's first key is visible to every query of the tile, so mx is finite from the first tile on -- as long
+      // as the scores are.  A part may open with keys that all score below the fp32 range; it has no reference then
+      // until a tile with a finite score comes (a part without one leaves -inf, which the merge weighs with zero).
       if (__any(m_use == -INFINITY || mx > lazy_gap)) {
-        const float shift = m_use == -INFINITY ? mx : fmaxf(mx, 0.f);   // new reference - old reference
+        const bool none = PARTS && m_use == -INFINITY && mx == -INFINITY;
+        const float shift = none ? 0.f : m_use == -INFINITY ? mx : fmaxf(mx, 0.f);   // new reference - old reference
         const float base = m_use == -INFINITY ? 0.f : m_use;
         const float alpha = m_use == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(-shift);
-        m_use = base + shift;
+        m_use = none ? -INFINITY : base + shift;
         l_run *= alpha;
         l_run2 *= alpha;
 #pragma unroll
@@ -286,7 +289,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(
 #pragma unroll
           for (int r = 0; r < 16; ++r) sacc[rb][r] -= shift;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) neg_m[r] = -m_use;
+        for (int r = 0; r < 16; ++r) neg_m[r] = none ? 0.f : -m_use;
       }
       // The row sum is taken over the bf16-rounded probabilities, the values P V multiplies by:
       // one two-element dot product with (1, 1) per packed pair instead of one add per score.

@@ -334,3 +334,41 @@ def test_fp32_tokens_see_no_later_token_that_is_not_finite(head_dim, new, cached
     assert torch.isfinite(out[0]).all()
     assert torch.equal(out[1][:at], out[0][:at])
     assert torch.isnan(out[1][at:]).all()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_attention_parts_whose_first_keys_score_minus_infinity(head_dim):
+    """Scores below the fp32 range are -inf and weigh nothing.  Keys 128 to 1327 are such for all 32 queries, so the
+    second part of the cut launch opens with tiles that hold nothing but -inf (and the launch as a whole does not)."""
+    hidden, first, far, last = 64, 128, 1200, 32
+    spec = I.ShapeSpec(1, hidden, 4, 2, head_dim, 64, 1e-5, 1e30)
+    weights = I.make_weights(spec, 63, torch.bfloat16, "cpu")
+    w = weights[0]["w_qkv"]
+    q_rows, k_rows = 4 * head_dim, 6 * head_dim
+    w[:k_rows] = 0
+    # Two kinds of token, told apart by their one non-zero channel (8 after the norm): kind 1 asks, and scores
+    # -1e40 on kind 0's keys.  Only channels that the rotation leaves alone over 1360 positions are used.
+    turning = (torch.arange(k_rows) % (head_dim // 2)) < head_dim // 4
+    q, k = w[:q_rows], w[q_rows:k_rows]
+    q[:, 1] = 1e19
+    k[:, 0] = -1e19
+    k[:, 1] = 1e-21
+    w[:k_rows][turning] = 0
+    R = _runner()
+    model = R.PrefillModel(spec, weights, 1, 128, 2048)
+    kind = torch.tensor([1] * first + [0] * far + [1] * last)
+    rows = torch.nn.functional.one_hot(kind, hidden).to(torch.bfloat16)
+    cached = first + far
+    table, _ = I.permuted_block_tables([last], [cached], 16, 128, seed=63)
+    print(f"attention parts over -inf, head_dim={head_dim}", flush=True)
+    task = model.begin(rows[:cached].cuda(), [cached], [0], table)
+    task.run_to_completion()
+    task.end()
+    task = model.begin(rows[cached:].cuda(), [last], [cached], table)
+    task.run_to_completion()
+    got = task.hidden()
+    x_ref, _ = O.prefill(oracle_shape(spec), oracle_layers(weights), rows, [0, cached + last])
+    assert torch.isfinite(got).all()
+    assert max_rel_err(got, x_ref[cached:]) <= TOL["bf16"]
+    task.end()
+    model.close()
