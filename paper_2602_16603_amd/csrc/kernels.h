@@ -4,8 +4,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <vector>
-
 namespace fp {
 
 // Static geometry of the model that the kernels need.
@@ -44,9 +42,6 @@ constexpr int kAttnKeyTile = 64;
 // Rows of queries one attention workgroup owns on the bf16 path (the runtime sizes attn_items
 // with it).
 int attention_q_tile_rows(int head_dim);
-// Number of key tiles a part of a query tile should hold so that the launch ends soonest: `tiles` =
-// key tiles of every query tile, most first.  0: leave the query tiles whole.
-int attention_part_tiles(const std::vector<int32_t>& tiles, int n_q_heads);
 // Floats one part takes (all query heads).
 size_t attn_part_floats(const Geometry& g);
 

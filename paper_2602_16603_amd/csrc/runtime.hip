@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "../../include/flowprefill.h"
+#include "attention_plan.h"
 #include "common.h"
 #include "kernels.h"
 #include "task_core.h"
@@ -252,7 +253,11 @@ fp_status acquire_workspace(fp_model* m, size_t bytes, size_t staging_bytes, Wor
     (void)hipHostFree(w.staging);
   }
   if (!got.base) {
-    FP_HIP(hipMalloc(&got.base, bytes));
+    const hipError_t e = hipMalloc(&got.base, bytes);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();    // not left for the check behind the next launch
+      return fail(e == hipErrorOutOfMemory ? FP_ERR_OOM : FP_ERR_DEVICE, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
+    }
     got.bytes = bytes;
   }
   if (got.staging_bytes < staging_bytes) {
@@ -262,6 +267,7 @@ fp_status acquire_workspace(fp_model* m, size_t bytes, size_t staging_bytes, Wor
     const size_t want = std::max<size_t>(staging_bytes, 64 << 10);
     hipError_t e = hipHostMalloc(&got.staging, want, hipHostMallocDefault);
     if (e != hipSuccess) {
+      (void)hipGetLastError();
       (void)hipFree(got.base);
       return fail(FP_ERR_OOM, "pinned staging buffer: %s", hipGetErrorString(e));
     }
@@ -608,16 +614,21 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
   std::vector<int32_t> tiles;
   if (sh.dtype == FP_DTYPE_BF16)
     for (const Item& it : items) tiles.push_back(it.work);
-  const int part_tiles = fp::attention_part_tiles(tiles, sh.n_q_heads);
   int32_t n_parts = 0;
-  for (const Item& it : items) {
-    const int parts = part_tiles ? (it.work + part_tiles - 1) / part_tiles : 1;
-    if (parts > 1) attn_merges.insert(attn_merges.end(), {it.seq, it.qt, n_parts, parts});
-    for (int p = 0; p < parts; ++p)
-      attn_items.insert(attn_items.end(), {it.seq, it.qt, (int32_t)((int64_t)it.work * p / parts),
-                                           (int32_t)((int64_t)it.work * (p + 1) / parts), parts > 1 ? n_parts + p : -1});
-    if (parts > 1) n_parts += parts;
-  }
+  auto list_attention = [&](int64_t max_parts) {
+    const int part_tiles = fp::attention_part_tiles(tiles, sh.n_q_heads, max_parts);
+    attn_items.clear();
+    attn_merges.clear();
+    n_parts = 0;
+    for (const Item& it : items) {
+      const int parts = part_tiles ? (it.work + part_tiles - 1) / part_tiles : 1;
+      if (parts > 1) attn_merges.insert(attn_merges.end(), {it.seq, it.qt, n_parts, parts});
+      for (int p = 0; p < parts; ++p)
+        attn_items.insert(attn_items.end(), {it.seq, it.qt, (int32_t)((int64_t)it.work * p / parts),
+                                             (int32_t)((int64_t)it.work * (p + 1) / parts), parts > 1 ? n_parts + p : -1});
+      if (parts > 1) n_parts += parts;
+    }
+  };
 
   // ---- workspace layout ----
   const size_t e = m->elem;
@@ -655,12 +666,22 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
                o_mp = carve(moe ? E * 4 : 0), o_mb = carve(moe ? (size_t)fp::moe_route_blocks(T) * E * 4 : 0), o_mg = carve(moe ? (1 + 3 * (size_t)t->moe_max_row_tiles) * 4 : 0),
                o_mh = carve(moe ? pairs * 4 : 0), o_ma = carve(moe ? pairs * F * e : 0),
                o_my = carve(moe ? pairs * d * e : 0);
-  const size_t o_sk = carve(sk_bytes);
-  const size_t o_ap = carve((size_t)n_parts * fp::attn_part_floats(m->geo) * 4);
-  const size_t n_int = tok_seq.size() + tok_pos.size() + t->cu.size() + t->cached.size() +
-                       t->tables.size() + kv_items.size() + attn_items.size() + attn_merges.size();
-  const size_t o_int = carve((n_int + 16) * 4);
-  fp_status st = acquire_workspace(m, off, (n_int + 16) * 4, &t->ws);
+  // The attention's parts share the split-K region: partial sums of a projection are read before it, or made after it.
+  // Without the memory for them the query tiles stay whole.
+  const size_t fixed = off, part_bytes = fp::attn_part_floats(m->geo) * 4;
+  int64_t max_parts = fp::kAttnPartBytes / (int64_t)part_bytes;
+  size_t o_sk, o_int, n_int;
+  fp_status st;
+  for (;; max_parts = 0) {
+    list_attention(max_parts);
+    off = fixed;
+    o_sk = carve(std::max(sk_bytes, n_parts * part_bytes));
+    n_int = tok_seq.size() + tok_pos.size() + t->cu.size() + t->cached.size() + t->tables.size() + kv_items.size() +
+            attn_items.size() + attn_merges.size();
+    o_int = carve((n_int + 16) * 4);
+    st = acquire_workspace(m, off, (n_int + 16) * 4, &t->ws);
+    if (st != FP_ERR_OOM || n_parts == 0) break;
+  }
   if (st != FP_OK) {
     if (!t->owned_blocks.empty()) fp_kv_free(m, (int32_t)t->owned_blocks.size(), t->owned_blocks.data());
     delete t;
@@ -712,7 +733,7 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
   t->meta.n_attn_items = (int32_t)(attn_items.size() / fp::kAttnItemInts);
   t->meta.attn_merges = dints + a_merge;
   t->meta.n_attn_merges = (int32_t)(attn_merges.size() / fp::kAttnMergeInts);
-  t->meta.attn_part = n_parts ? reinterpret_cast<float*>(base + o_ap) : nullptr;
+  t->meta.attn_part = n_parts ? reinterpret_cast<float*>(base + o_sk) : nullptr;
 
   fp::launch_task_start(sh.dtype, hidden_in, t->x, m->layers[0].attn_norm, t->h, T, sh.hidden, sh.rms_eps, ints, dints,
                         (int64_t)n_put, m->stream);
