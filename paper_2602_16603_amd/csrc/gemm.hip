@@ -7,6 +7,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_plan.h"
 #include "kernels.h"
 
 namespace fp {
@@ -209,7 +210,6 @@ constexpr int kWaitVm24 = 0x4F78;  // s_waitcnt vmcnt(24)
 constexpr int kWaitVm17 = 0x4F71;  // s_waitcnt vmcnt(17)
 constexpr int kWaitLgkm0 = 0xC07F; // s_waitcnt lgkmcnt(0)         (vmcnt/expcnt untouched)
 constexpr int kWarmAhead = 3;      // k-tiles between the L2 warm-up load and the DMA of the same lines
-constexpr uint32_t kOffOutOfRange = 0x80000000u;   // a byte offset no descriptor here covers
 
 typedef float f32x4_acc __attribute__((ext_vector_type(4)));
 template <int NJ>
@@ -1203,15 +1203,6 @@ size_t gemm_workspace_bytes(int dtype, int64_t m, int64_t n, int64_t k) {
   return s > 1 ? (size_t)s * m * n * sizeof(float) : 0;
 }
 
-// tail: what follows the split-K reduction in the same kernel (kTailNone: nothing).
-// Row tile of a grouped launch whose experts receive `mean_rows` rows on average: the smallest that holds most
-// experts in one tile, up to 128 rows of the ring kernel; from about 100 rows on the matrix pipes bound the
-// launch and the 256-row tile is ahead.  experts_up / experts_down (with the combine) of the 30B-A3B shape, us, with tiles
-// of 256, 128, 64 and 32 rows: 6 rows per expert 214/110, 186/97, 170/82, 159/80; 37 rows 224/121, 198/99,
-// 187/99, 192/108; with every tile's own start in K: 50 rows -, 194/104, 178/102, -; 64 rows -, 194/109,
-// 215/118, -; 119 rows 217/140, 244/145, -, -.
-int moe_tile_rows(int64_t mean_rows) { return mean_rows <= 18 ? 32 : mean_rows <= 52 ? 64 : mean_rows <= 100 ? 128 : 256; }
-
 template <int MI, int EPI>
 static void launch_grouped_ring(const bf16* a, const bf16* w, void* c, int n, int k, const int32_t* groups,
                                     int max_row_tiles, const int32_t* a_rows, int m_arg, hipStream_t s) {
@@ -1252,6 +1243,7 @@ void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64
                                                             (int)k, max_row_tiles, tiles_n, (int)(k / kBK), groups, a_rows);
 }
 
+// tail: what follows the split-K reduction in the same kernel (kTailNone: nothing).
 template <bool RESID, int NJ>
 static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits,
                            float* workspace, const GemmTail& tail, hipStream_t s) {

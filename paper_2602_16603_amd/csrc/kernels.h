@@ -106,12 +106,11 @@ void launch_gemm_swiglu_small(const void* a, const void* w_gate_up, void* out, i
 // rows with expert's matrix of w ([experts][n][k], or [experts][2n][k] gate rows then up rows when
 // swiglu) into the same rows of c [*, n] (bf16; swiglu: silu(gate)*up).  The rows are rows of a
 // [*, k] itself (a_rows == null) or, gathered, rows a_rows[first row + r] of a [a_total_rows, k]
-// (a_total_rows * k < 2^30).  The grid covers max_row_tiles row tiles; the surplus exits.
+// (a_total_rows * k < 2^30).  tile_rows 32, 64, 128 or 256 as moe_tile_rows (gemm_plan.h) says.  The grid covers
+// max_row_tiles row tiles; the surplus exits.
 void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64_t k, int swiglu,
                          const int32_t* groups, int max_row_tiles, int tile_rows,
                          const int32_t* a_rows, int64_t a_total_rows, hipStream_t s);
-// Rows per tile (32, 64, 128 or 256) for experts that receive mean_rows rows on average.
-int moe_tile_rows(int64_t mean_rows);
 
 // Gathers positions 0..len-1 of one sequence (block table row `table_dev`, device) of one layer
 // into contiguous k_out/v_out [len, Hkv, D].

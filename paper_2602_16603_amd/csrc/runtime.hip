@@ -24,6 +24,7 @@
 #include "../../include/flowprefill.h"
 #include "attention_plan.h"
 #include "common.h"
+#include "gemm_plan.h"
 #include "kernels.h"
 #include "task_core.h"
 
@@ -659,7 +660,7 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
                o_o = carve(Tn * qd * e), o_gu = carve(t->swiglu_fused || moe ? 0 : Tn * 2 * F * e),
                o_act = carve(moe ? 0 : Tn * F * e);
   // Mixture-of-experts scratch: every (token, choice) pair owns one row of the gathered buffers.
-  t->moe_tile_rows = moe ? fp::moe_tile_rows((int64_t)(pairs / E)) : 0;
+  t->moe_tile_rows = moe ? fp::moe_tile_rows((int64_t)(pairs / E), (int64_t)F, (int64_t)d) : 0;
   t->moe_max_row_tiles = moe ? (int32_t)(pairs / t->moe_tile_rows + E) : 0;
   const size_t o_ml = carve(moe ? Tn * E * 4 : 0), o_mw = carve(moe ? pairs * 4 * sh.n_layers : 0),
                o_mi = carve(moe ? pairs * 4 * sh.n_layers : 0), o_ms = carve(moe ? pairs * 4 : 0),
