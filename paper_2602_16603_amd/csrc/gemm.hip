@@ -37,8 +37,9 @@ __device__ __forceinline__ void tile_of_workgroup(int wg, int tiles_m, int tiles
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16 MFMA GEMM for operands that are not 16-byte aligned (register-staged loads).  WGM x WGN waves; each wave
-// owns a (BM/WGM)x(BN/WGN) block of 32x32 MFMA accumulators.  K is consumed 64 at a time.  LDS rows hold 64 bf16 = eight 16-byte chunks.  The
+// bf16 MFMA GEMM for operands at any address (register-staged loads).  WGM x WGN waves; each wave
+// owns a (BM/WGM)x(BN/WGN) block of 32x32 MFMA accumulators.  SWIGLU: the 64 W rows of a wave's two column blocks are
+// 32 gate rows and the up rows of the same 32 outputs.  K is consumed 64 at a time.  LDS rows hold 64 bf16 = eight 16-byte chunks.  The
 // gfx950 LDS has 64 four-byte banks (256 B per clock for reads); a ds_read_b128 is served one
 // half-wave after the other and a half-wave costs max(2, most lanes on one 16-byte bank group)
 // clocks.  Two consecutive 128-byte rows fill one bank period, so chunk c of row r is stored at
@@ -47,18 +48,22 @@ __device__ __forceinline__ void tile_of_workgroup(int wg, int tiles_m, int tiles
 // ------------------------------------------------------------------------------------------
 constexpr int kBK = 64;
 
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // 16 bytes at any bf16's address
+
+// up > 0 (SwiGLU): rows 64 u + (0..31) of the tile are rows row0 + 32 u + (0..31) of src, the next 32 lie `up` rows on.
 template <int ROWS, int NT>
 __device__ __forceinline__ void load_tile_global(const bf16* __restrict__ src, int64_t ld,
                                                  int row0, int row_max, int k0, int K, int tid,
-                                                 u32x4 (&regs)[ROWS * 8 / NT]) {
+                                                 u32x4 (&regs)[ROWS * 8 / NT], int up = 0) {
 #pragma unroll
   for (int i = 0; i < ROWS * 8 / NT; ++i) {
     const int c = tid + i * NT;
     const int row = c >> 3, ch = c & 7;
-    const int grow = min(row0 + row, row_max);
+    const int64_t grow = up ? min(row0 + (row >> 6) * 32 + (row & 31), row_max) + (int64_t)((row >> 5) & 1) * up
+                            : min(row0 + row, row_max);
     const int k = k0 + ch * 8;
     if (k < K)
-      regs[i] = *reinterpret_cast<const u32x4*>(src + (int64_t)grow * ld + k);
+      regs[i] = *reinterpret_cast<const u32x4_any*>(src + grow * ld + k);
     else
       regs[i] = u32x4{0, 0, 0, 0};
   }
@@ -74,7 +79,7 @@ __device__ __forceinline__ void store_tile_lds(bf16* dst, int tid, const u32x4 (
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, bool RESID>
+template <int BM, int BN, int WGM, int WGN, bool RESID, bool SWIGLU = false>
 __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* __restrict__ A,
                                                            const bf16* __restrict__ W,
                                                            void* __restrict__ Cout, int M, int N,
@@ -90,7 +95,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
   const int wm = wave / WGN, wn = wave % WGN;
   int tile_m, tile_n;
   tile_of_workgroup(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int m0 = tile_m * BM, n0 = tile_n * (SWIGLU ? BN / 2 : BN);   // (SWIGLU: N is the number of outputs)
+  const int up = SWIGLU ? N : 0;
+  static_assert(!SWIGLU || (WTN == 64 && !RESID));
 
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -103,7 +110,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
   u32x4 ra[BM * 8 / NT], rb[BN * 8 / NT];
   const int kt_count = (K + kBK - 1) / kBK;
   load_tile_global<BM, NT>(A, K, m0, M - 1, 0, K, tid, ra);
-  load_tile_global<BN, NT>(W, K, n0, N - 1, 0, K, tid, rb);
+  load_tile_global<BN, NT>(W, K, n0, N - 1, 0, K, tid, rb, up);
   store_tile_lds<BM, NT>(sA, tid, ra);
   store_tile_lds<BN, NT>(sB, tid, rb);
   __syncthreads();
@@ -113,7 +120,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
     const int cur = kt & 1;
     if (kt + 1 < kt_count) {
       load_tile_global<BM, NT>(A, K, m0, M - 1, (kt + 1) * kBK, K, tid, ra);
-      load_tile_global<BN, NT>(W, K, n0, N - 1, (kt + 1) * kBK, K, tid, rb);
+      load_tile_global<BN, NT>(W, K, n0, N - 1, (kt + 1) * kBK, K, tid, rb, up);
     }
     const bf16* cA = sA + cur * BM * kBK;
     const bf16* cB = sB + cur * BN * kBK;
@@ -146,6 +153,20 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
 
   // Epilogue.  Accumulator register r of lane l is C[8*(r/4) + 4*(l/32) + r%4][l%32] of its
   // 32x32 block: the 32 lanes of a half-wave write 32 consecutive columns of one row.
+  if constexpr (SWIGLU) {
+    const int n = n0 + wn * 32 + frag_row;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + wm * WTM + i * 32 + 8 * (r >> 2) + 4 * frag_half + (r & 3);
+        if (m < M && n < N)
+          reinterpret_cast<bf16*>(Cout)[(int64_t)m * N + n] =
+              static_cast<bf16>(silu_mul_f32(static_cast<float>(static_cast<bf16>(acc[i][0][r])),
+                                             static_cast<float>(static_cast<bf16>(acc[i][1][r]))));
+      }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -1069,6 +1090,28 @@ __global__ __launch_bounds__(256) void splitk_reduce_norm_kernel(const float* __
   }
 }
 
+// The large-tile kernels move their operands by buffer instructions, which want dwords, the ring kernel also by 8 and 16
+// byte loads and stores; operands off either grid run on gemm_bf16_kernel.
+static bool aligned_to(uintptr_t bytes, const void* a, const void* w, const void* c) {
+  return (reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(c)) % bytes == 0;
+}
+
+// SWIGLU: n outputs, w holds 2 n rows.
+template <bool RESID, bool SWIGLU = false>
+static void launch_bf16_any(const bf16* a, const bf16* w, void* c, int m, int n, int k, hipStream_t s) {
+  constexpr int BM = 128, BN = 128, WGM = 2, WGN = 2, OUT = SWIGLU ? BN / 2 : BN;
+  const int tiles_m = (m + BM - 1) / BM, tiles_n = (n + OUT - 1) / OUT;
+  const size_t smem = (size_t)2 * (BM + BN) * kBK * sizeof(bf16);
+  // Once per instantiation; a function-local static is initialised exactly once even when several
+  // threads launch at the same time.
+  static const hipError_t attr_set =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WGM, WGN, RESID, SWIGLU>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  (void)attr_set;
+  gemm_bf16_kernel<BM, BN, WGM, WGN, RESID, SWIGLU><<<dim3((unsigned)(tiles_m * tiles_n)), WGM * WGN * 64, smem, s>>>(
+      a, w, c, m, n, k, tiles_m, tiles_n);
+}
+
 // Tile width and number of K ranges for a problem.  Enough 256-column tiles to occupy the chip, or
 // more than two row tiles (then the MFMAs bound the launch and the wide tile's operand reuse
 // counts: measured at 768 tokens and up): the 256-column tile.  Otherwise the 128-column tile.
@@ -1181,7 +1224,11 @@ bool gemm_swiglu_fusable(int dtype, int64_t m, int64_t f, int64_t k) {
 
 void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f,
                         int64_t k, hipStream_t s) {
-  if (m <= kFewRows) {
+  if (!aligned_to(4, a, w_gate_up, out)) {
+    launch_bf16_any<false, true>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, s);
+    return;
+  }
+  if (m <= kFewRows && aligned_to(16, a, w_gate_up, out)) {
     launch_few_rows<kEpiSwiGLU>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, 1, s);
     return;
   }
@@ -1247,10 +1294,11 @@ void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64
 template <bool RESID, int NJ>
 static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits,
                            float* workspace, const GemmTail& tail, hipStream_t s) {
+  const bool few = m <= kFewRows && aligned_to(16, a, w, c);
   constexpr int BN = 32 * NJ;
   const int tiles_m = (m + 255) / 256, tiles_n = (n + BN - 1) / BN;
   const int kt = k / kBK;
-  if (splits <= 1 && m <= kFewRows) {
+  if (splits <= 1 && few) {
     launch_few_rows<RESID ? kEpiResidual : kEpiBf16>(a, w, c, m, n, k, 1, s);
     return;
   }
@@ -1261,7 +1309,7 @@ static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, 
   }
   const KRanges r = k_ranges(k, splits);
   int used = r.used;
-  if (m <= kFewRows)
+  if (few)
     used = launch_few_rows<kEpiPartial>(a, w, workspace, m, n, k, splits, s);
   else
     gemm_bf16_w4_kernel<kEpiPartial, false, NJ><<<dim3((unsigned)(tiles_m * tiles_n * used)), 256, 0, s>>>(
@@ -1277,21 +1325,6 @@ static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, 
   else
     splitk_reduce_kernel<RESID><<<dim3((unsigned)((mn / 8 + 255) / 256)), 256, 0, s>>>(workspace, c, mn / 8,
                                                                                      mn, used);
-}
-
-template <int BM, int BN, int WGM, int WGN, bool RESID>
-static void launch_bf16_cfg(const bf16* a, const bf16* w, void* c, int m, int n, int k,
-                            hipStream_t s) {
-  const int tiles_m = (m + BM - 1) / BM, tiles_n = (n + BN - 1) / BN;
-  const size_t smem = (size_t)2 * (BM + BN) * kBK * sizeof(bf16);
-  // Once per instantiation; a function-local static is initialised exactly once even when several
-  // threads launch at the same time.
-  static const hipError_t attr_set =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WGM, WGN, RESID>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  (void)attr_set;
-  gemm_bf16_kernel<BM, BN, WGM, WGN, RESID><<<dim3((unsigned)(tiles_m * tiles_n)), WGM * WGN * 64, smem, s>>>(
-      a, w, c, m, n, k, tiles_m, tiles_n);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1571,8 +1604,20 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   const bf16* pw = (const bf16*)w;
   // Enough 256x256 tiles (or, K a multiple of 64, enough K to split) to occupy the chip: the
   // one-wave-per-SIMD DMA kernel, split over K when the caller's workspace allows.  Otherwise the ring
-  // kernel on small tiles; operands that are not 16-byte aligned: the register-staged kernel on 128x128 tiles.
-  const bool aligned = (reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(c)) % 16 == 0;
+  // kernel on small tiles.  Operands they do not take: the register-staged kernel on 128x128 tiles.
+  W4Shape plan = w4_plan(dtype, m, n, k, workspace_bytes);
+  const GemmTail none{};
+  const GemmTail& tl = tail && gemm_tail_fusable(dtype, m, n, k, workspace_bytes, tail->kind) ? *tail : none;
+  if (!aligned_to(4, a, w, c)) {
+    // The tail (kTailLeave apart, which goes with operands of the runtime's own) as the operator it stands for.  A cut
+    // problem's workspace has room for at least two fp32 [m][n]: the unfused gate_up projection goes there.
+    if (residual) launch_bf16_any<true>(pa, pw, c, (int)m, (int)n, (int)k, s);
+    else launch_bf16_any<false>(pa, pw, tl.kind == kTailSwiGLU ? workspace : c, (int)m, (int)n, (int)k, s);
+    if (tl.kind == kTailRmsNorm) launch_rmsnorm(dtype, (const float*)c, tl.gain, tl.out, m, n, tl.eps, s);
+    if (tl.kind == kTailSwiGLU) launch_silu_mul(dtype, workspace, tl.out, m, n / 2, s);
+    return;
+  }
+  const bool aligned = aligned_to(16, a, w, c);
   if (aligned && takes_w4_tail(m, n, k)) {
     const int64_t tiles_m = (m + 255) / 256, tiles_n = (n + 255) / 256;
     const dim3 grid((unsigned)(tiles_m * tiles_n));
@@ -1584,9 +1629,6 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
                                                                         (int)tiles_n, (int)(k / kBK), nullptr, nullptr);
     return;
   }
-  W4Shape plan = w4_plan(dtype, m, n, k, workspace_bytes);
-  const GemmTail none{};
-  const GemmTail& tl = tail && gemm_tail_fusable(dtype, m, n, k, workspace_bytes, tail->kind) ? *tail : none;
   if (plan.splits > 1) plan = w4_cut(m, n, k, residual, plan);
   const int splits = plan.splits;
   if (splits == 1 && tl.kind == kTailSwiGLU) {       // not cut after all: the fused epilogue gives the same bits
@@ -1603,8 +1645,8 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
     if (residual) launch_small_problem<kEpiResidual>(pa, pw, c, m, n, k, s);
     else launch_small_problem<kEpiBf16>(pa, pw, c, m, n, k, s);
   } else {
-    if (residual) launch_bf16_cfg<128, 128, 2, 2, true>(pa, pw, c, (int)m, (int)n, (int)k, s);
-    else launch_bf16_cfg<128, 128, 2, 2, false>(pa, pw, c, (int)m, (int)n, (int)k, s);
+    if (residual) launch_bf16_any<true>(pa, pw, c, (int)m, (int)n, (int)k, s);
+    else launch_bf16_any<false>(pa, pw, c, (int)m, (int)n, (int)k, s);
   }
 }
 

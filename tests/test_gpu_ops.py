@@ -494,3 +494,87 @@ def test_gemm_odd_k_on_the_large_tile(m, n, k, residual):
     # One dropped or foreign column would be off by sqrt(1/k) of the result: far above the bf16 rounding of 2^-9.
     assert ((buf[:m].cpu().double() - ref).norm() / ref.norm()).item() <= 4e-3
     assert torch.all(buf[m:] == 7.0)
+
+
+def _at(tensor, offset):
+    """A copy of the tensor whose first element lies `offset` elements behind a 256-byte boundary, and its buffer."""
+    buf = torch.full((offset + tensor.numel() + 64,), 7.0, dtype=tensor.dtype, device="cuda")
+    view = buf[offset:offset + tensor.numel()].view(tensor.shape)
+    view.copy_(tensor)
+    return view, buf
+
+
+@pytest.mark.parametrize("offset", [1, 2, 4])
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("m,n,k", [(50, 4104, 1088), (100, 12296, 64), (300, 2056, 4096), (600, 5136, 1024), (2560, 2568, 128), (2305, 2568, 72), (33, 72, 40)])
+def test_bf16_gemm_operands_off_the_16_byte_grid(m, n, k, residual, offset):
+    """Operands 2, 4 and 8 bytes off (views of a larger buffer): few rows, cut over K on either tile, uncut large, odd K,
+    small.  Against the definition; what lies before and behind the output stays untouched."""
+    B = _binding()
+    a, _ = _at(I.normal_tensor((m, k), 1.0, 81, torch.bfloat16, "cuda"), offset)
+    w, _ = _at(I.normal_tensor((n, k), 0.05, 82, torch.bfloat16, "cuda"), offset)
+    x0 = I.normal_tensor((m, n), 1.0, 83, torch.float32 if residual else torch.bfloat16, "cuda")
+    c, buf = _at(x0, offset)
+    ws_bytes = B.fp_op_gemm_workspace_bytes(1, m, n, k)
+    ws = torch.full((ws_bytes + 256,), 0x5A, dtype=torch.uint8, device="cuda")
+    print(f"unaligned gemm m={m} n={n} k={k} residual={residual} offset={offset}", flush=True)
+    torch.cuda.synchronize()
+    B.fp_op_gemm_ws(1, a.data_ptr(), w.data_ptr(), c.data_ptr(), m, n, k, residual, ws.data_ptr(), ws_bytes)
+    torch.cuda.synchronize()
+    ref = O.linear(a.cpu(), w.cpu())
+    if residual:
+        ref = ref + x0.cpu().double()
+    assert max_rel_err(c, ref) <= TOL["bf16"]
+    # bf16 rounding of the result is 2^-9 at most; a chunk fetched from a neighbouring address would be off by its share of K.
+    assert ((c.cpu().double() - ref).norm() / ref.norm()).item() <= 4e-3
+    assert torch.all(buf[:offset] == 7.0) and torch.all(buf[offset + c.numel():] == 7.0) and torch.all(ws[ws_bytes:] == 0x5A)
+
+
+@pytest.mark.parametrize("offset", [1, 2, 4])
+@pytest.mark.parametrize("m", [50, 200, 300])
+def test_bf16_fused_operators_off_the_16_byte_grid(m, offset):
+    """The fused gate_up projection and both tails of a cut projection on operands 2, 4 and 8 bytes off: the bits of the
+    separate operators on the same operands."""
+    B = _binding()
+    f, k = 7176, 704
+    a, _ = _at(I.normal_tensor((m, k), 1.0, 84, torch.bfloat16, "cuda"), offset)
+    w, _ = _at(I.normal_tensor((2 * f, k), 0.02, 85, torch.bfloat16, "cuda"), offset)
+    gu, _ = _at(torch.zeros((m, 2 * f), dtype=torch.bfloat16, device="cuda"), offset)
+    two = torch.empty((m, f), dtype=torch.bfloat16, device="cuda")
+    fused, buf = _at(torch.zeros((m, f), dtype=torch.bfloat16, device="cuda"), offset)
+    print(f"unaligned fused m={m} offset={offset}", flush=True)
+    torch.cuda.synchronize()
+    B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), gu.data_ptr(), m, 2 * f, k, False)
+    gu_copy = gu.clone()
+    torch.cuda.synchronize()
+    B.fp_op_silu_mul(1, gu_copy.data_ptr(), two.data_ptr(), m, f)
+    B.fp_op_gemm_swiglu(a.data_ptr(), w.data_ptr(), fused.data_ptr(), m, f, k)
+    torch.cuda.synchronize()
+    assert torch.equal(fused, two)
+    assert torch.all(buf[:offset] == 7.0) and torch.all(buf[offset + fused.numel():] == 7.0)
+
+    n, k = 4096, 4096                                  # cut over K: the tails of the reduction
+    ws_bytes = B.fp_op_gemm_workspace_bytes(1, m, n, k)
+    assert ws_bytes > 0
+    ws = torch.full((ws_bytes + 256,), 0x5A, dtype=torch.uint8, device="cuda")
+    a, _ = _at(I.normal_tensor((m, k), 1.0, 86, torch.bfloat16, "cuda"), offset)
+    w, _ = _at(I.normal_tensor((n, k), 0.05, 87, torch.bfloat16, "cuda"), offset)
+    gain = I.normal_tensor((n,), 1.0, 88, torch.bfloat16, "cuda")
+    x = I.normal_tensor((m, n), 1.0, 89, torch.float32, "cuda")
+    plain, tailed = x.clone(), x.clone()
+    h, h_tail = (torch.empty((m, n), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    gu, _ = _at(torch.zeros((m, n), dtype=torch.bfloat16, device="cuda"), offset)
+    act, act_tail = (torch.empty((m, n // 2), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    torch.cuda.synchronize()
+    B.fp_op_gemm_ws(1, a.data_ptr(), w.data_ptr(), plain.data_ptr(), m, n, k, True, ws.data_ptr(), ws_bytes)
+    B.fp_op_rmsnorm(1, plain.data_ptr(), gain.data_ptr(), h.data_ptr(), m, n, 1e-5)
+    B.fp_op_gemm_tail(a.data_ptr(), w.data_ptr(), tailed.data_ptr(), m, n, k, True, ws.data_ptr(), ws_bytes, B.FP_TAIL_RMSNORM, gain.data_ptr(), h_tail.data_ptr(), 1e-5)
+    B.fp_op_gemm_ws(1, a.data_ptr(), w.data_ptr(), gu.data_ptr(), m, n, k, False, ws.data_ptr(), ws_bytes)
+    gu_copy = gu.clone()
+    torch.cuda.synchronize()
+    B.fp_op_silu_mul(1, gu_copy.data_ptr(), act.data_ptr(), m, n // 2)
+    B.fp_op_gemm_tail(a.data_ptr(), w.data_ptr(), 0, m, n, k, False, ws.data_ptr(), ws_bytes, B.FP_TAIL_SWIGLU, 0, act_tail.data_ptr())
+    torch.cuda.synchronize()
+    assert torch.equal(tailed, plain) and torch.equal(h_tail, h) and torch.equal(act_tail, act)
+    ref = O.linear(a.cpu(), w.cpu()) + x.cpu().double()
+    assert max_rel_err(tailed, ref) <= TOL["bf16"] and torch.all(ws[ws_bytes:] == 0x5A)
