@@ -46,8 +46,6 @@ __device__ __forceinline__ void tile_of_workgroup(int wg, int tiles_m, int tiles
 // chunk position c ^ ((r >> 1) & 7): the 32 rows a half-wave reads then put exactly two lanes on
 // every bank group (measured: full rate, against half rate with key r & 7).
 // ------------------------------------------------------------------------------------------
-constexpr int kBK = 64;
-
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // 16 bytes at any bf16's address
 
 // up > 0 (SwiGLU): rows 64 u + (0..31) of the tile are rows row0 + 32 u + (0..31) of src, the next 32 lie `up` rows on.
@@ -1173,33 +1171,22 @@ static int launch_few_rows(const bf16* a, const bf16* w, void* c, int m, int n, 
   return launch_ring<8, EPI>(a, w, c, m, n, k, splits, s);
 }
 
-static bool takes_ring(int64_t m, int64_t n, int64_t k, size_t workspace_bytes);
+static bool takes_small_tiles(int64_t m, int64_t n, int64_t k, size_t workspace_bytes);
 
-// Problems with too few 256-row tiles to occupy the chip, and odd K.  A CU works off its tiles one after
-// the other: the tile for which the busiest of 256 CUs has the fewest outputs, padding included; on a tie the
-// larger one, which reads its operands less often.  Against the register-staged kernel on 128x128 tiles, us: 200 x 256
-// x 704 19 -> 6, 256 x 512 x 8192 105 -> 20, 50 x 4096 x 4104 69 -> 18, 2048 x 1024 x 1024 18.7 -> 14.7.
-template <int EPI>
-static void launch_small_problem(const bf16* a, const bf16* w, void* c, int64_t m, int64_t n, int64_t k, hipStream_t s) {
-  auto outputs = [&](int64_t bm, int64_t bn) { return (((m + bm - 1) / bm) * ((n + bn - 1) / bn) + 255) / 256 * bm * bn; };
-  const int64_t large = outputs(128, 128), middle = outputs(64, 64), small = outputs(32, 64);
-  if (large <= middle && large <= small) launch_ring<8, EPI>(a, w, c, (int)m, (int)n, (int)k, 1, s);
-  else if (middle <= small) launch_ring<4, EPI>(a, w, c, (int)m, (int)n, (int)k, 1, s);
-  else launch_ring<2, EPI>(a, w, c, (int)m, (int)n, (int)k, 1, s);
-}
-
-// Small problems' fused gate_up: columns of W are gate and up of 64 outputs per tile; the same choice of rows.
+// Small problems' fused gate_up: columns of W are gate and up of 64 outputs per tile.
 bool gemm_swiglu_small(int dtype, int64_t m, int64_t f, int64_t k, size_t workspace_bytes) {
   return dtype == 1 && m > 0 && f % 8 == 0 && k % 8 == 0 && (f + 256) * k * 2 < (int64_t)kOffOutOfRange &&
-         takes_ring(m, 2 * f, k, workspace_bytes) && ((m + 31) / 32) * ((f + 63) / 64) <= INT32_MAX;
+         takes_small_tiles(m, 2 * f, k, workspace_bytes) && k <= (1 << 21) &&
+         ((m + 31) / 32) * ((f + 63) / 64) <= INT32_MAX && swiglu_tile_rows(m, f, k) > 0;
 }
 
 void launch_gemm_swiglu_small(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f, int64_t k, hipStream_t s) {
-  auto outputs = [&](int64_t bm) { return (((m + bm - 1) / bm) * ((f + 63) / 64) + 255) / 256 * bm; };
   const bf16 *pa = (const bf16*)a, *pw = (const bf16*)w_gate_up;
-  if (outputs(128) <= outputs(64) && outputs(128) <= outputs(32)) launch_ring<8, kEpiSwiGLU>(pa, pw, out, (int)m, (int)f, (int)k, 1, s);
-  else if (outputs(64) <= outputs(32)) launch_ring<4, kEpiSwiGLU>(pa, pw, out, (int)m, (int)f, (int)k, 1, s);
-  else launch_ring<2, kEpiSwiGLU>(pa, pw, out, (int)m, (int)f, (int)k, 1, s);
+  switch (swiglu_tile_rows(m, f, k)) {
+    case 128: launch_ring<8, kEpiSwiGLU>(pa, pw, out, (int)m, (int)f, (int)k, 1, s); break;
+    case 64: launch_ring<4, kEpiSwiGLU>(pa, pw, out, (int)m, (int)f, (int)k, 1, s); break;
+    default: launch_ring<2, kEpiSwiGLU>(pa, pw, out, (int)m, (int)f, (int)k, 1, s); break;
+  }
 }
 
 // The router has few outputs and as many rows as the task: 32-row tiles, logits stored in fp32 as they come (590
@@ -1538,17 +1525,9 @@ static W4Shape w4_plan(int dtype, int64_t m, int64_t n, int64_t k, size_t worksp
   return p;
 }
 
-// Odd K on the large tile, from the number of tiles on that K % 64 == 0 takes it.  Against 128x128 tiles, us: 96 tiles
-// (3000 x 2000 x 4008) 118 -> 99, 256 tiles (4096 x 4096 x 4104) 197 -> 125, but 64 tiles (1000 x 4096 x 1000) 17 -> 25.
-static bool takes_w4_tail(int64_t m, int64_t n, int64_t k) {
-  const int64_t tiles = ((m + 255) / 256) * ((n + 255) / 256);
-  return k % kBK != 0 && n <= (1 << 21) && k <= (1 << 21) && tiles >= 96 && tiles <= INT32_MAX;
-}
-
-// Problems that 16-byte aligned operands run on the ring kernel.
-static bool takes_ring(int64_t m, int64_t n, int64_t k, size_t workspace_bytes) {
-  return !takes_w4_tail(m, n, k) && w4_plan(1, m, n, k, workspace_bytes).splits == 0 && k <= (1 << 21) &&
-         ((m + 31) / 32) * ((n + 63) / 64) <= INT32_MAX;
+// Problems whose tile small_problem_tile chooses.
+static bool takes_small_tiles(int64_t m, int64_t n, int64_t k, size_t workspace_bytes) {
+  return w4_plan(1, m, n, k, workspace_bytes).splits == 0;
 }
 
 // What a problem that w4_plan cuts over K runs as.  Three or four row tiles and a short K: the 128-column
@@ -1580,6 +1559,23 @@ int gemm_left_ranges(int dtype, int64_t m, int64_t n, int64_t k, size_t workspac
   return ring_ranges<8, kEpiPartial>((int)n, (int)k, plan.splits).used;
 }
 
+template <bool RESID>
+static void launch_small_problem(const bf16* a, const bf16* w, void* c, int m, int n, int k, hipStream_t s) {
+  constexpr int EPI = RESID ? kEpiResidual : kEpiBf16;
+  switch (aligned_to(16, a, w, c) ? small_problem_tile(m, n, k, RESID) : GemmTile::kAny128) {
+    case GemmTile::kRing32: launch_ring<2, EPI>(a, w, c, m, n, k, 1, s); break;
+    case GemmTile::kRing64: launch_ring<4, EPI>(a, w, c, m, n, k, 1, s); break;
+    case GemmTile::kRing128: launch_ring<8, EPI>(a, w, c, m, n, k, 1, s); break;
+    case GemmTile::kAny128: launch_bf16_any<RESID>(a, w, c, m, n, k, s); break;
+    case GemmTile::kLarge: {
+      const int tiles_m = (m + 255) / 256, tiles_n = (n + 255) / 256;
+      gemm_bf16_w4_kernel<EPI, false, 8, true><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(
+          a, w, c, m, n, k, tiles_m, tiles_n, k / kBK, nullptr, nullptr);
+      break;
+    }
+  }
+}
+
 void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, int64_t n,
                  int64_t k, int residual, void* workspace, size_t workspace_bytes, hipStream_t s,
                  const GemmTail* tail) {
@@ -1602,9 +1598,9 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   }
   const bf16* pa = (const bf16*)a;
   const bf16* pw = (const bf16*)w;
-  // Enough 256x256 tiles (or, K a multiple of 64, enough K to split) to occupy the chip: the
-  // one-wave-per-SIMD DMA kernel, split over K when the caller's workspace allows.  Otherwise the ring
-  // kernel on small tiles.  Operands they do not take: the register-staged kernel on 128x128 tiles.
+  // K a multiple of 64 and enough 256x256 tiles (or enough K to split) to occupy the chip: the one-wave-per-SIMD DMA
+  // kernel, split over K when the caller's workspace allows.  Otherwise the tile small_problem_tile chooses.  Operands
+  // those do not take: the register-staged kernel on 128x128 tiles.
   W4Shape plan = w4_plan(dtype, m, n, k, workspace_bytes);
   const GemmTail none{};
   const GemmTail& tl = tail && gemm_tail_fusable(dtype, m, n, k, workspace_bytes, tail->kind) ? *tail : none;
@@ -1615,18 +1611,6 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
     else launch_bf16_any<false>(pa, pw, tl.kind == kTailSwiGLU ? workspace : c, (int)m, (int)n, (int)k, s);
     if (tl.kind == kTailRmsNorm) launch_rmsnorm(dtype, (const float*)c, tl.gain, tl.out, m, n, tl.eps, s);
     if (tl.kind == kTailSwiGLU) launch_silu_mul(dtype, workspace, tl.out, m, n / 2, s);
-    return;
-  }
-  const bool aligned = aligned_to(16, a, w, c);
-  if (aligned && takes_w4_tail(m, n, k)) {
-    const int64_t tiles_m = (m + 255) / 256, tiles_n = (n + 255) / 256;
-    const dim3 grid((unsigned)(tiles_m * tiles_n));
-    if (residual)
-      gemm_bf16_w4_kernel<kEpiResidual, false, 8, true><<<grid, 256, 0, s>>>(pa, pw, c, (int)m, (int)n, (int)k, (int)tiles_m,
-                                                                            (int)tiles_n, (int)(k / kBK), nullptr, nullptr);
-    else
-      gemm_bf16_w4_kernel<kEpiBf16, false, 8, true><<<grid, 256, 0, s>>>(pa, pw, c, (int)m, (int)n, (int)k, (int)tiles_m,
-                                                                        (int)tiles_n, (int)(k / kBK), nullptr, nullptr);
     return;
   }
   if (plan.splits > 1) plan = w4_cut(m, n, k, residual, plan);
@@ -1641,12 +1625,10 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   } else if (splits >= 1) {
     if (residual) launch_bf16_w4<true, 4>(pa, pw, c, (int)m, (int)n, (int)k, splits, (float*)workspace, tl, s);
     else launch_bf16_w4<false, 4>(pa, pw, c, (int)m, (int)n, (int)k, splits, (float*)workspace, tl, s);
-  } else if (aligned && takes_ring(m, n, k, workspace_bytes)) {
-    if (residual) launch_small_problem<kEpiResidual>(pa, pw, c, m, n, k, s);
-    else launch_small_problem<kEpiBf16>(pa, pw, c, m, n, k, s);
+  } else if (residual) {
+    launch_small_problem<true>(pa, pw, c, (int)m, (int)n, (int)k, s);
   } else {
-    if (residual) launch_bf16_any<true>(pa, pw, c, (int)m, (int)n, (int)k, s);
-    else launch_bf16_any<false>(pa, pw, c, (int)m, (int)n, (int)k, s);
+    launch_small_problem<false>(pa, pw, c, (int)m, (int)n, (int)k, s);
   }
 }
 

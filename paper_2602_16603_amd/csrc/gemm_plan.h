@@ -4,6 +4,8 @@
 
 namespace fp {
 
+constexpr int kBK = 64;                            // k-tile of the large tiles, and the unit of K ranges
+
 constexpr uint32_t kOffOutOfRange = 0x80000000u;   // a byte offset no buffer descriptor here covers
 
 // Row tile of a grouped launch whose experts receive `mean_rows` rows on average: the smallest that holds most
@@ -17,6 +19,67 @@ constexpr uint32_t kOffOutOfRange = 0x80000000u;   // a byte offset no buffer de
 inline int moe_tile_rows(int64_t mean_rows, int64_t ffn, int64_t hidden) {
   if ((ffn + 256) * hidden * 2 >= (int64_t)kOffOutOfRange) return 256;
   return mean_rows <= 18 ? 32 : mean_rows <= 52 ? 64 : mean_rows <= 100 ? 128 : 256;
+}
+
+// Problems with too few 256x256 tiles to occupy the chip, and odd K.  A CU works off its tiles one after the other, so a
+// tile size costs rounds = ceil(tiles / 256) times what a tile costs: a fixed part (prologue, epilogue, for a residual
+// also its read) and a part per k.  Small tiles keep more CUs busy, large ones read their operands less often; which wins
+// turns on how the rounds come out, so the rule is the estimate itself, in ns, fitted to 510 problems of 16 to 8192 rows,
+// 256 to 8192 columns and K with cold weights: its choice is 0.7 % slower than the best of the five (all five measured),
+// in 5 of the 510 slower than 128x128 register-staged tiles alone, by up to 13 %.  (The fewest outputs on the busiest CU,
+// the rule before, chose many small tiles for wide problems of short K: 725 x 7104 x 256 31.6 us, now 15.2; 1168 x 2648 x
+// 1312 38 -> 21; and the large tile for odd K from 96 tiles on, where 128x128 ones still fit two to a CU: 2012 x 2840 x
+// 2552 64 -> 51.)
+enum class GemmTile { kRing32, kRing64, kRing128, kAny128, kLarge };   // 32x64, 64x64, 128x128; register-staged 128x128; 256x256
+
+inline int64_t tile_rounds(int64_t m, int64_t n, int64_t bm, int64_t bn) {
+  return (((m + bm - 1) / bm) * ((n + bn - 1) / bn) + 255) / 256;
+}
+
+inline double small_problem_ns(GemmTile tile, int64_t m, int64_t n, int64_t k, bool residual) {
+  const double kd = (double)k;
+  switch (tile) {
+    case GemmTile::kRing32: return 2100 + tile_rounds(m, n, 32, 64) * ((residual ? 2500 : 2200) + 2.3 * kd);
+    case GemmTile::kRing64: return 1000 + tile_rounds(m, n, 64, 64) * ((residual ? 4300 : 3500) + 3.9 * kd);
+    case GemmTile::kRing128: return -1400 + tile_rounds(m, n, 128, 128) * ((residual ? 9900 : 6800) + 9.1 * kd);
+    case GemmTile::kAny128: {                      // two workgroups share a CU: a pair takes 1.35 times as long as one
+      const int64_t r = tile_rounds(m, n, 128, 128);
+      return ((r / 2) * 1.35 + r % 2) * ((residual ? 13800 : 4200) + 13.8 * kd);
+    }
+    default: return 900 + tile_rounds(m, n, 256, 256) * ((residual ? 17100 : 8600) + 21.5 * kd);
+  }
+}
+
+// The tile for 16-byte aligned operands.  The large one takes K that is not a multiple of 64 here (kBK), from the number of
+// tiles on that makes it worth a look; the ring kernel's and the large tile's 32-bit offsets bound their sizes.
+inline GemmTile small_problem_tile(int64_t m, int64_t n, int64_t k, bool residual) {
+  GemmTile best = GemmTile::kAny128;
+  double best_ns = small_problem_ns(best, m, n, k, residual);
+  auto consider = [&](GemmTile tile) {
+    const double ns = small_problem_ns(tile, m, n, k, residual);
+    if (ns < best_ns) { best_ns = ns; best = tile; }
+  };
+  if (k <= (1 << 21) && ((m + 31) / 32) * ((n + 63) / 64) <= INT32_MAX) {
+    consider(GemmTile::kRing32);
+    consider(GemmTile::kRing64);
+    consider(GemmTile::kRing128);
+  }
+  const int64_t large = ((m + 255) / 256) * ((n + 255) / 256);
+  if (k % kBK != 0 && n <= (1 << 21) && k <= (1 << 21) && large >= 96 && large <= INT32_MAX) consider(GemmTile::kLarge);
+  return best;
+}
+
+// The gate_up projection of such a problem with SiLU(gate)*up in the ring kernel's epilogue: rows per tile (64 of the f
+// outputs each), or 0 where the projection on its own tile and a silu_mul launch (4 us) are ahead, as they are for many
+// rows of few k (867 rows, 4704 outputs of 1144: 50 + 5 us against 56).  Fitted to 200 problems; 0.4 % from the best.
+inline int swiglu_tile_rows(int64_t m, int64_t f, int64_t k) {
+  const double kd = (double)k;
+  const double ns[3] = {3800 + tile_rounds(m, f, 32, 64) * (600 + 5.6 * kd), 800 + tile_rounds(m, f, 64, 64) * (3900 + 7.5 * kd),
+                        -400 + tile_rounds(m, f, 128, 64) * (5800 + 11.0 * kd)};
+  const int i = ns[0] <= ns[1] && ns[0] <= ns[2] ? 0 : ns[1] <= ns[2] ? 1 : 2;
+  const GemmTile plain = small_problem_tile(m, 2 * f, k, false);
+  const bool ring = plain != GemmTile::kAny128 && plain != GemmTile::kLarge;   // (the same tiles, and a launch more)
+  return ring || ns[i] <= small_problem_ns(plain, m, 2 * f, k, false) + 4000 ? 32 << i : 0;
 }
 
 }  // namespace fp

@@ -98,7 +98,7 @@ bool gemm_swiglu_fusable(int dtype, int64_t m, int64_t f, int64_t k);
 void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f,
                         int64_t k, hipStream_t s);
 // The same for problems that launch_gemm, given this workspace, runs on small tiles (K % 8 == 0, 16-byte aligned
-// operands); the same bits again.
+// operands), where gemm_plan.h finds it faster; the bits of the two operators on the ring kernel.
 bool gemm_swiglu_small(int dtype, int64_t m, int64_t f, int64_t k, size_t workspace_bytes);
 void launch_gemm_swiglu_small(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f, int64_t k, hipStream_t s);
 // Grouped bf16 GEMM for mixture-of-experts layers (K % 64 == 0, n % 8 == 0): `groups` (device) =

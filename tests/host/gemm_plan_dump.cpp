@@ -1,5 +1,7 @@
 // Prints what the GEMM dispatch rules (csrc/gemm_plan.h) say to the lines read from standard input:
 //   moe mean_rows ffn hidden      -> rows per tile of the experts' grouped launches
+//   tile m n k residual           -> tile of a problem too small for the large tiles: ring32, ring64, ring128, any128, large
+//   swiglu m f k                  -> rows per tile of its fused gate_up projection (0: two operators)
 #include <iostream>
 #include <sstream>
 #include <string>
@@ -15,6 +17,16 @@ int main() {
       long long rows, ffn, hidden;
       in >> rows >> ffn >> hidden;
       std::cout << fp::moe_tile_rows(rows, ffn, hidden) << "\n";
+    } else if (kind == "tile") {
+      static const char* const names[] = {"ring32", "ring64", "ring128", "any128", "large"};
+      long long m, n, k;
+      int residual;
+      in >> m >> n >> k >> residual;
+      std::cout << names[(int)fp::small_problem_tile(m, n, k, residual != 0)] << "\n";
+    } else if (kind == "swiglu") {
+      long long m, f, k;
+      in >> m >> f >> k;
+      std::cout << fp::swiglu_tile_rows(m, f, k) << "\n";
     }
   }
   return 0;

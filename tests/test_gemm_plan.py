@@ -31,3 +31,32 @@ def test_expert_matrices_beyond_32_bit_offsets_stay_on_the_large_tile(rules):
         fits = (f + 64) * d * 2 < 1 << 31
         assert int(tile) in (32, 64, 128, 256) and (fits or int(tile) == 256), (rows, f, d, tile)
     assert rules(["moe 18 768 2048", "moe 40 14336 4096", "moe 500 768 2048"]) == ["32", "64", "256"]
+
+
+def test_the_gpu_tests_reach_every_tile(rules):
+    """Which tile the problems of tests/test_gpu_ops.py and tests/test_gpu_prefill.py run on."""
+    odd_k = [(3329, 3080, 8), (3329, 3080, 72), (3329, 3080, 136), (3329, 3080, 200), (3329, 3080, 632), (4100, 2568, 1016), (8200, 1288, 2040)]
+    assert set(rules([f"tile {m} {n} {k} {r}" for m, n, k in odd_k for r in (0, 1)])) == {"large"}
+    about_100 = [(2560, 2560, 8), (2305, 2568, 72), (2304, 2816, 136), (2305, 2568, 200), (2049, 3080, 632), (4100, 1544, 1016), (8200, 520, 2040)]
+    assert set(rules([f"tile {m} {n} {k} 0" for m, n, k in about_100])) == {"any128"}
+    assert set(rules([f"tile {m} {n} {k} 1" for m, n, k in about_100])) == {"large", "ring128"}
+    small = [(1, 8, 8), (37, 520, 264), (300, 1408, 256), (256, 256, 704), (1000, 256, 704), (513, 776, 1000)]
+    assert rules([f"tile {m} {n} {k} 0" for m, n, k in small]) == ["any128", "ring32", "ring32", "ring32", "ring32", "ring32"]
+    assert rules([f"swiglu {m} {f} {k}" for m, f, k in [(200, 704, 256), (1, 704, 256), (97, 200, 264), (700, 1032, 320)]]) == ["32", "32", "32", "64"]
+
+
+def test_wide_problems_of_short_k_do_not_run_on_the_smallest_tiles(rules):
+    """A round of small tiles costs more than its share of the outputs: many rounds of them lose to one or two rounds of
+    128x128 (measured, us, 32x64 tiles against the choice: 31.6/11.1, 38/21, 20.9/14, 28.6/13.4)."""
+    problems = [(725, 7104, 256), (1168, 2648, 1312), (1330, 1848, 704), (953, 3728, 576)]
+    assert set(rules([f"tile {m} {n} {k} 0" for m, n, k in problems])) <= {"ring128", "any128"}
+    # Up to two rounds of 128x128 tiles for odd K: two of their workgroups share a CU, the large tile leaves half the CUs idle.
+    assert set(rules([f"tile {m} {n} {k} 0" for m, n, k in [(2012, 2840, 2552), (3779, 1648, 784), (1596, 4520, 856)]])) == {"any128"}
+    assert rules(["tile 4072 2472 3736 0", "tile 8192 8192 2056 0"]) == ["large", "large"]
+
+
+@pytest.mark.parametrize("k", [8, 64, 1000, 1 << 21, (1 << 21) + 8, 1 << 24])
+def test_sizes_beyond_32_bit_offsets_run_on_the_kernel_without_them(rules, k):
+    tiles = set(rules([f"tile {m} {n} {k} {r}" for m, n in ((8, 8), (4096, 4096), (70000, 70000)) for r in (0, 1)]))
+    assert tiles == {"any128"} if k > 1 << 21 else tiles <= {"ring32", "ring64", "ring128", "any128", "large"}
+    assert "large" not in rules([f"tile 4096 {(1 << 21) + 8} {k} 0"])

@@ -470,11 +470,13 @@ def test_three_and_four_row_tiles_on_the_narrow_tile(m, n, k, residual):
 
 
 @pytest.mark.parametrize("residual", [False, True])
-@pytest.mark.parametrize("m,n,k", [(2560, 2560, 8), (2305, 2568, 72), (2304, 2816, 136), (2305, 2568, 200), (2049, 3080, 632), (4100, 1544, 1016), (8200, 520, 2040)])
+@pytest.mark.parametrize("m,n,k", [(2560, 2560, 8), (2305, 2568, 72), (2304, 2816, 136), (2305, 2568, 200), (2049, 3080, 632), (4100, 1544, 1016), (8200, 520, 2040),
+                                   (3329, 3080, 8), (3329, 3080, 72), (3329, 3080, 136), (3329, 3080, 200), (3329, 3080, 632), (4100, 2568, 1016), (8200, 1288, 2040)])
 def test_gemm_odd_k_on_the_large_tile(m, n, k, residual):
     """K not a multiple of 64 on the 256x256 tile (0, 1, 2, 3, 9, 15 and 31 whole k-tiles and a tail of 8 or 56
     columns), a last row tile of one row and a last column tile of eight columns: the columns of W and A
-    behind K belong to the next row and must not enter."""
+    behind K belong to the next row and must not enter.  The first seven problems, of about 100 such tiles, run on the
+    128x128 tiles that are ahead there, the others on the large one (tests/test_gemm_plan.py)."""
     B = _binding()
     print(f"gemm odd k m={m} n={n} k={k} residual={residual}", flush=True)
     a = I.normal_tensor((m, k), 1.0, 72, torch.bfloat16, "cuda")
