@@ -8,17 +8,23 @@ constexpr int kBK = 64;                            // k-tile of the large tiles,
 
 constexpr uint32_t kOffOutOfRange = 0x80000000u;   // a byte offset no buffer descriptor here covers
 
-// Row tile of a grouped launch whose experts receive `mean_rows` rows on average: the smallest that holds most
-// experts in one tile, up to 128 rows of the ring kernel; from about 100 rows on the matrix pipes bound the
-// launch and the 256-row tile is ahead.  experts_up / experts_down (with the combine) of the 30B-A3B shape, us, with tiles
-// of 256, 128, 64 and 32 rows: 6 rows per expert 214/110, 186/97, 170/82, 159/80; 37 rows 224/121, 198/99,
-// 187/99, 192/108; with every tile's own start in K: 50 rows -, 194/104, 178/102, -; 64 rows -, 194/109,
-// 215/118, -; 119 rows 217/140, 244/145, -, -.
+// Row tile of a grouped launch whose experts receive `mean_rows` rows on average: the smallest that holds nearly every
+// expert in one tile (a second one reads the expert's weights again), up to 128 rows of the ring kernel; from about 100
+// rows on the matrix pipes bound the launch and the 256-row tile is ahead.  The counts spread by about the root of their
+// mean, hence the lines below 64 and 128.  experts_up + experts_down (with the combine), us, on tiles of 32, 64, 128 and 256
+// rows, [hidden, ffn, experts, top_k]:
+//   rows per expert   [2048 768 128 8]      [4096 1536 64 8]      [4096 14336 8 2]        [2048 1408 64 6]
+//   16                230  234  258  325    434  438  465  523    491   487   589   733   211  219  241  291
+//   44                303  254  272  335    669  480  491  543    919   501   596   744   293  230  252  299
+//   52                320  272  285  350    703  496  499  558    1137  790   613   747   311  252  252  297
+//   86                400  376  305  362    1016 725  540  577    1584  966   629   771   434  339  268  317
+//   100               452  395  343  370    1149 769  602  580    1715  974   642   776   482  346  275  319
+//   130               532  478  438  385    1478 896  757  602    2126  1314  1053  799   620  434  393  333
 // The smaller tiles reach an expert's gate and up rows through one 32-bit offset, as the dense fused kernel does
 // ([2 ffn][hidden] below 2 GiB); the 256-row tile has a base for each.
 inline int moe_tile_rows(int64_t mean_rows, int64_t ffn, int64_t hidden) {
   if ((ffn + 256) * hidden * 2 >= (int64_t)kOffOutOfRange) return 256;
-  return mean_rows <= 18 ? 32 : mean_rows <= 52 ? 64 : mean_rows <= 100 ? 128 : 256;
+  return mean_rows <= 18 ? 32 : mean_rows <= 48 ? 64 : mean_rows <= 96 ? 128 : 256;
 }
 
 // Problems with too few 256x256 tiles to occupy the chip, and odd K.  A CU works off its tiles one after the other, so a
