@@ -2,6 +2,7 @@
 // the plan can be built and checked on the CPU.
 #pragma once
 #include <algorithm>
+#include <array>
 #include <cstdint>
 #include <vector>
 
@@ -31,28 +32,46 @@ inline int attention_part_tiles(const std::vector<int32_t>& tiles, int n_q_heads
   constexpr int kPlaces = 256, kMaxPlaces = 64, kRounds = 4, kMinPart = 8, kWholeCost = 3, kPartCost = 5, kMergeCost = 4, kMaxParts = 16;
   const int places = std::min(kMaxPlaces, std::max(1, kPlaces / n_q_heads));
   if (tiles.empty() || (int)tiles.size() > kRounds * places || tiles[0] < 2 * kMinPart) return 0;
-  int stored = 0;                                   // parts of the plan end_of has just gone through
-  auto end_of = [&](int limit) {                    // when the last part of at most `limit` tiles is done
-    int at[kMaxPlaces] = {};
+  auto parts_of = [](int n, int limit) { return limit ? (n + limit - 1) / limit : 1; };
+  // Parts of at most `limit` tiles: how many of them leave their output, and when the last one is done -- not gone
+  // through for a limit whose work alone, spread evenly over the places, takes until `give_up`.
+  int64_t stored = 0;
+  auto end_of = [&](int limit, int64_t give_up) {
+    int64_t work = 0;
     stored = 0;
     for (int32_t n : tiles) {
-      const int parts = limit ? (n + limit - 1) / limit : 1;
+      const int parts = parts_of(n, limit);
       if (parts > 1) stored += parts;
+      work += (int64_t)parts * ((n + parts - 1) / parts + (parts > 1 ? kPartCost : kWholeCost));
+    }
+    const int64_t merge = stored ? kMergeCost + stored * n_q_heads / 50 : 0;
+    if (work / places + merge >= give_up) return give_up;
+    std::array<int64_t, kMaxPlaces> at{};           // a heap: the place that is free soonest in front
+    for (int32_t n : tiles) {
+      const int parts = parts_of(n, limit);
       for (int p = 0; p < parts; ++p) {
-        int* soonest = std::min_element(at, at + places);
-        *soonest += (n + parts - 1) / parts + (parts > 1 ? kPartCost : kWholeCost);
+        const int64_t end = at[0] + (n + parts - 1) / parts + (parts > 1 ? kPartCost : kWholeCost);
+        int i = 0;
+        for (int c = 1; c < places; c = 2 * i + 1) {
+          if (c + 1 < places && at[c + 1] < at[c]) ++c;
+          if (at[c] >= end) break;
+          at[i] = at[c];
+          i = c;
+        }
+        at[i] = end;
       }
     }
-    return *std::max_element(at, at + places) + (stored ? kMergeCost + stored * n_q_heads / 50 : 0);
+    return *std::max_element(at.begin(), at.begin() + places) + merge;
   };
-  int best = 0, best_end = end_of(0);
+  int best = 0;
+  int64_t best_end = end_of(0, INT64_MAX);
   best_end -= best_end / 16;                        // worth it from about a sixteenth on
   int last = 0;
   for (int parts = 2; parts <= kMaxParts; ++parts) {
     const int limit = std::max(2 * kMinPart - 1, (tiles[0] + parts - 1) / parts);   // (then no part is below kMinPart)
     if (limit == last || limit >= tiles[0]) continue;
     last = limit;
-    const int end = end_of(limit);
+    const int64_t end = end_of(limit, best_end);
     if (stored <= max_parts && end < best_end) { best_end = end; best = limit; }
   }
   return best;
