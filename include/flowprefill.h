@@ -122,10 +122,10 @@ fp_status fp_model_kv_pools(const fp_model* model, const void** k_pool /*device*
 /* "submit" (Section 4; Alg. 2 submit_new_execution): creates a task for a request set of n_seqs
  * prompts (or prompt chunks) packed token-major.
  *   hidden_in    device [T, hidden] in the storage dtype, T = cu_seqlens[n_seqs]; widened into
- *                the task's own fp32 residual buffer by a kernel this call enqueues on the
- *                model's stream WITHOUT waiting for it: the caller keeps hidden_in valid and
- *                unchanged until the first fp_prefill_advance on the task has returned (or the
- *                stream has otherwise drained); the library never writes it.
+ *                the task's own fp32 residual buffer, and normalised for the first layer, by a
+ *                kernel this call enqueues on the model's stream WITHOUT waiting for it: the caller
+ *                keeps hidden_in valid and unchanged until the first fp_prefill_advance on the task
+ *                has returned (or the stream has otherwise drained); the library never writes it.
  *   cu_seqlens   host [n_seqs+1], non-decreasing, cu_seqlens[0] = 0.  Empty sequences allowed.
  *   cached_lens  host [n_seqs] tokens of each sequence already in the cache (earlier chunks), or
  *                NULL for all zero.  Token i of sequence s has position cached_lens[s] + i.
@@ -211,7 +211,11 @@ fp_status fp_prefill_kv_gather(const fp_prefill* task, int32_t layer, int32_t se
 
 /* Device time of each operator of the task's most recent advance call, in milliseconds, when
  * per-op timing was switched on with fp_prefill_set_timing(task, 1) before that call.  Writes
- * min(n, ops of that call) entries to ms_out (host) and the count to *n_out.                     */
+ * min(n, ops of that call) entries to ms_out (host) and the count to *n_out.  A kernel's time goes to
+ * the operator that launches it; an operator whose work rides in another's kernel reports 0:
+ * operator 0 of layer 0 always (fp_prefill_begin enqueues that norm, which is in no operator's time),
+ * operators 0, 5 and 7 where a projection carries them out.  The partial sums of a short request's qkv
+ * projection may be added up in operator 2.                                                       */
 fp_status fp_prefill_set_timing(fp_prefill* task, int32_t on);
 fp_status fp_prefill_op_times(fp_prefill* task, float* ms_out /*host*/, int32_t n,
                               int32_t* n_out /*host*/);
