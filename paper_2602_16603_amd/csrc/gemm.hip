@@ -1,8 +1,8 @@
 // Dense projections of the prefill layer: C[M,N] = A[M,K] * W[N,K]^T (both operands K-major),
 // FlowPrefill Eq. (1) and the operators qkv_proj / o_proj / gate_up_proj / down_proj of
-// Section 5.1.  bf16 path: MFMA tiles with fp32 accumulation, LDS-staged and double-buffered (the
-// fast kernel on 16x16x32, the small-problem kernel on 32x32x16).  fp32 path (debug): MFMA tiles in
-// fp32 throughout.
+// Section 5.1.  bf16 path: MFMA tiles with fp32 accumulation, operands staged through LDS by DMA (the
+// large-tile and the ring kernel, on 16x16x32) or through registers (the kernel for any operand
+// address, on 32x32x16).  fp32 path (debug): MFMA tiles in fp32 throughout.
 #include <algorithm>
 #include <type_traits>
 
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16 MFMA GEMM, one wave per SIMD (the fast path; K % 64 == 0).
+// bf16 MFMA GEMM, one wave per SIMD (the fast path; K % 64 == 0, or KTAIL below).
 //
 // 256x256 output tile, K consumed 64 at a time, 256 threads = 4 waves, one per SIMD, each with the
 // whole 512-register budget: a wave owns a 128x128 block of the tile, 8x8 accumulators of 16x16 =
@@ -766,8 +766,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA GEMM on small tiles (16 MI = 32, 64 or 128 rows, 64 NJ columns; any K % 8 == 0).  Its main use is a
 // launch of few rows, which reads every weight once from HBM for a handful of MFMAs, so the weights'
-// stream is all there is to it; it also takes what has too few 256-row tiles to occupy the chip, and
-// odd K.
+// stream is all there is to it; it also takes most of what has too few 256-row tiles to occupy the chip,
+// and of odd K (gemm_plan.h).
 // 256 threads = 4 waves side by side along N; every wave multiplies all rows by its 16 NJ columns with
 // v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits).  K is consumed KT at a
 // time through a ring of S LDS stages, separate arrays filled by DMA S - 1 k-tiles ahead; the loop body has no
@@ -799,13 +799,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
   constexpr int RPI = 64 / CPR;                      // rows per DMA instruction
   constexpr int IA = BM / RPI / 4, IW = WR / RPI / 4;   // DMA instructions per wave and stage
   constexpr int STAGE = (BM + WR) * KT;
-  static_assert(BM % (4 * RPI) == 0 && S >= 2 && S <= 6 && (!SWIGLU || NJ % 2 == 0));
+  static_assert(BM % (4 * RPI) == 0 && S >= 2 && S <= 4 && (!SWIGLU || NJ % 2 == 0));
   __shared__ __attribute__((aligned(1024))) bf16 s0[STAGE];
   __shared__ __attribute__((aligned(1024))) bf16 s1[STAGE];
   __shared__ __attribute__((aligned(1024))) bf16 s2[S > 2 ? STAGE : 8];
   __shared__ __attribute__((aligned(1024))) bf16 s3[S > 3 ? STAGE : 8];
-  __shared__ __attribute__((aligned(1024))) bf16 s4[S > 4 ? STAGE : 8];
-  __shared__ __attribute__((aligned(1024))) bf16 s5[S > 5 ? STAGE : 8];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -828,7 +826,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
     // Experts' matrices lie at multiples of the HBM channels' period, and workgroups in step would ask a few
     // channels for the same columns of all of them: every (expert, column tile) starts at another k-tile
     // (experts_up of the 30B-A3B shape, 590 tokens 183 -> 164 us, 16 tokens 100 -> 89).  The start depends on
-    // nothing else, so neither do a row's bits.  (Dense projections, whose columns are one matrix and whose uncut
+    // nothing else, so neither do a row's bits among these tiles; the 256-row tile starts every expert at 0, so a batch of
+    // more than 96 rows per expert rounds differently.  (Dense projections, whose columns are one matrix and whose uncut
     // form has the bits of the large kernels, do not gain: 48 -> 64 us for gate_up.)
     rot = (expert * tiles_n + tile_n) % ((K + KT - 1) / KT);
   } else {
@@ -915,17 +914,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
   fetch(0, s0);
   if (S > 2) fetch(1, s1);
   if (S > 3) fetch(2, s2);
-  if (S > 4) fetch(3, s3);
-  if (S > 5) fetch(4, s4);
   __builtin_amdgcn_s_waitcnt(wait_vm<(S - 2) * (IA + IW)>());
   w4_barrier();
   for (int t = 0; t * KT < k_count; t += S) {
-    step(t, s0, S == 2 ? s1 : S == 3 ? s2 : S == 4 ? s3 : S == 5 ? s4 : s5);
+    step(t, s0, S == 2 ? s1 : S == 3 ? s2 : s3);
     step(t + 1, s1, s0);
     if (S > 2) step(t + 2, s2, s1);
     if (S > 3) step(t + 3, s3, s2);
-    if (S > 4) step(t + 4, s4, s3);
-    if (S > 5) step(t + 5, s5, s4);
   }
   __builtin_amdgcn_s_waitcnt(kWaitVm0);              // the last (empty) fetches
 
