@@ -372,3 +372,43 @@ def test_attention_parts_whose_first_keys_score_minus_infinity(head_dim):
     assert max_rel_err(got, x_ref[cached:]) <= TOL["bf16"]
     task.end()
     model.close()
+
+
+@pytest.mark.parametrize("name", ["fp32", "bf16"])
+def test_model_on_a_stream_of_its_own(name):
+    """begin() and kv() of a model whose kernels run on another stream than torch's: inputs that torch is still
+    producing are waited for, and memory that torch is still using is not written early."""
+    R = _runner()
+    code, td = DT[name]
+    spec, lengths = I.TINY, [37, 200]
+    weights = I.make_weights(spec, 64, td, "cpu")
+    hidden = I.make_hidden(sum(lengths), spec.hidden, 64, td, "cuda")
+
+    def outputs(model):
+        busy = torch.randn(4096, 4096, device="cuda")
+        for _ in range(20):
+            busy = busy @ busy.T * 1e-4                # torch's stream is some way behind the host
+        rows = hidden + (busy[:1, :1] * 0).nan_to_num().to(td)
+        task = model.begin(rows, lengths)
+        task.run_to_completion()
+        out = [task.hidden()]
+        for layer in range(spec.n_layers):
+            for s in range(len(lengths)):
+                garbage = torch.full((lengths[s], spec.n_kv_heads, spec.head_dim), 7.0, dtype=td, device="cuda")
+                del garbage                            # its memory goes to the next kv(), its fill may still be queued
+                out += task.kv(layer, s)
+        task.end()
+        return out
+
+    same = R.PrefillModel(spec, weights, code, 64, 256)
+    own = R.PrefillModel(spec, weights, code, 64, 256, stream=torch.cuda.Stream())
+    want = outputs(same)
+    for _ in range(3):
+        assert all(torch.equal(a, b) for a, b in zip(outputs(own), want))
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):                      # torch on a stream of its own, the model on the default one
+        side.wait_stream(torch.cuda.default_stream())
+        assert all(torch.equal(a, b) for a, b in zip(outputs(same), want))
+    torch.cuda.synchronize()
+    same.close()
+    own.close()
