@@ -22,7 +22,7 @@ constexpr int64_t kAttnPartBytes = 256ll << 20;
 // take one (query tile, every head) at a time, longest first.  More than four such rounds balance
 // themselves.  No part is shorter than kMinPart tiles (its first key must be visible to all 256 queries
 // of the tile, which five tiles ensure).  512 tokens behind 15872 cached ones, 32 heads of 128: 365 us
-// whole (64 workgroups of 256 tiles), 130 + 8 us in four parts per query tile; 128 behind 24576 461 -> 81 us, 1100
+// whole (64 workgroups of 256 tiles), 125 + 8 us in four parts per query tile; 128 behind 24576 461 -> 81 us, 1100
 // behind 20000 434 -> 323, 2048 behind 2048 stays whole (101; in parts 106).  With 5 to 64 heads of 64 and 128, prompts
 // of 1024 to 4100 tokens and chunks behind 600 to 40000: none slower than whole, 1.39 times as fast on average.
 //

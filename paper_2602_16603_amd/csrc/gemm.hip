@@ -321,13 +321,13 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // bound the launch and the wide tile's operand reuse wins).  Such a launch streams its weights from
 // HBM, every line for one or two workgroups only, and what a CU gets is its bytes in flight per
 // latency: the narrow tile's stages are three (144 KB, filled two k-tiles ahead) instead of two with
-// L2 warm-up.  Cold weights, 256 tokens of the 8B shape: gate_up 79 -> 66 us, down 49 -> 45; 50 tokens:
-// 74 -> 55, 40 -> 31; 512 tokens: down 76 -> 67.  (The wide tile's three stages would take 192 KB.)
+// L2 warm-up.  Cold weights, 256 tokens of the 8B shape: gate_up 81 -> 71 us, down 48 -> 44;
+// 512 tokens: down 74 -> 66.  (The wide tile's three stages would take 192 KB.)
 //
 // KTAIL (256-column tile, not cut): K is not a multiple of 64; its last K % 64 columns (a multiple of 8) follow the
 // main loop as one more k-tile, not pipelined, whose missing 16-byte chunks are fetched from outside the
 // descriptors (K < 64: there is nothing else; the prologue's k-tile 0 is overwritten unread).  K rows then start at odd multiples of 16 bytes, which the DMA does not mind.  8192 x 8192 x 2056:
-// 470 us on register-staged 128x128 tiles, 305 here (912 TFLOP/s; rows that straddle lines cost the rest).
+// 408 us on register-staged 128x128 tiles, 265 here (1.04 PFLOP/s; rows that straddle lines cost the rest).
 template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restrict__ A,
                                                            const bf16* __restrict__ W,
@@ -1128,9 +1128,9 @@ static W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
 // Few rows: up to kFewRows of them.  Columns per tile, k-tile and stages by row count and epilogue, as measured on
 // cold weights of the 8B shape (us, against the two-stage 256-row tile): up to 64 rows 64-column tiles of 128 k (256 bytes of a
 // weight row at a time: HBM gives 4.9 TB/s to such pieces where 128-byte pieces get 4.2) -- 50 rows: qkv
-// 22 -> 17, o 17.5 -> 12.7, down 40 -> 27; from 65 rows on the A tile weighs more and 128-column tiles of 64 k
-// read it half as often -- 128 rows: qkv 23, down 34 (26, 41 on the former).  SwiGLU: 128 W rows of 64 k, 74 ->
-// 48 at 50 rows, 56 at 128.
+// 22 -> 17, o 17 -> 12.6, down 40 -> 28; from 65 rows on the A tile weighs more and 128-column tiles of 64 k
+// read it half as often -- 128 rows: qkv 24 -> 23.5, down 42 -> 34 (26, 41 on the former).  SwiGLU: 128 W rows of 64 k,
+// 75 -> 52 at 50 rows, 80 -> 64 at 128.
 constexpr int kFewRows = 128;
 template <int MI, bool SWIGLU> struct RingTile {
   static constexpr bool kWide = SWIGLU || MI > 4;
@@ -1528,8 +1528,9 @@ static bool takes_small_tiles(int64_t m, int64_t n, int64_t k, size_t workspace_
 // What a problem that w4_plan cuts over K runs as.  Three or four row tiles and a short K: the 128-column
 // tile in fewer ranges (possibly one: nothing is cut then), if that occupies the chip -- fewer partial sums
 // against more operand reads per MFMA, which a long K would pay for too often.  With the reduction, us:
-// 777 x 6144 x 4096 59 -> 51, 777 x 4096 x 4096 48 -> 45, 590 x 5120 x 2048 31 -> 25, but x 14336 110 -> 115; 600 x 6144 x
-// 4096 has 144 tiles and stays (47.7, 49).  Residual projections stay cut (their tail rides on the reduction).
+// 777 x 6144 x 4096 54 -> 45, 777 x 4096 x 4096 44 -> 40, 590 x 5120 x 2048 30 -> 24, but x 14336 110 -> 115; 600 x 6144 x
+// 4096 has 144 tiles and stays (47.7, 49).  Of 80 drawn problems of 513 to 1024 rows and K up to 6144 none was more than 3 %
+// slower than without this rule.  Residual projections stay cut (their tail rides on the reduction).
 static W4Shape w4_cut(int64_t m, int64_t n, int64_t k, bool residual, W4Shape p) {
   const int64_t tiles_m = (m + 255) / 256, tiles = tiles_m * ((n + 127) / 128);
   if (p.nj != 8 || tiles_m > 4 || k > 6144 || tiles > 256) return p;

@@ -650,7 +650,7 @@ fp_status fp_prefill_begin(fp_model* m, const void* hidden_in, const int32_t* cu
   t->swiglu_small = !moe && !t->swiglu_epilogue && fp::gemm_swiglu_small(sh.dtype, T, (int64_t)F, (int64_t)d, sk_bytes);
   t->swiglu_fused = t->swiglu_epilogue || t->swiglu_small ||
                     (!moe && fp::gemm_tail_fusable(sh.dtype, T, 2 * (int64_t)F, (int64_t)d, sk_bytes, fp::kTailSwiGLU));
-  // Two slabs are added up in passing (50 tokens of the 8B shape: reduction 4.0 + RoPE 4.6 -> 6.4 us); more of them hold
+  // Two slabs are added up in passing (50 tokens of the 8B shape: reduction 4.0 + RoPE 4.6 -> 6.3 us); more of them hold
   // up the few workgroups that write the value blocks (256 tokens, five slabs: 6.0 + 4.9 -> 14.4).
   t->qkv_parts = fp::gemm_left_ranges(sh.dtype, T, (int64_t)W, (int64_t)d, sk_bytes);
   if (t->qkv_parts > 2) t->qkv_parts = 0;
