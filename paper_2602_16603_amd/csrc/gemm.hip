@@ -244,8 +244,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t panel_rsrc(const void* base, u
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 
+// NT: non-temporal, for lines that one workgroup reads and nobody after it.
+template <bool NT = false>
 __device__ __forceinline__ void w4_dma(__amdgpu_buffer_rsrc_t r, bf16* lds_rows, uint32_t voff, int kbyte) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_rows, 16, voff, kbyte, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_rows, 16, voff, kbyte, 0, NT ? 2 : 0);
 }
 
 // One k-step: 8 NJ MFMAs from `cur` (A block s against the NJ W blocks, s = 0..7; NJ = 8: the
@@ -261,7 +263,7 @@ __device__ __forceinline__ void w4_dma(__amdgpu_buffer_rsrc_t r, bf16* lds_rows,
 // overflows the completely used accumulation registers (the 8-pass 32x32x16 is tied by itself).
 // No accumulator is touched twice within 64 MFMAs, and LDS results reach the operands through
 // the s_waitcnt the compiler places for the asm inputs, so no software-managed hazard arises.
-template <int READS, bool DMA, int NJ>
+template <int READS, bool DMA, int NJ, bool NT = false>
 __device__ __forceinline__ void w4_block(f32x4_acc (&acc)[8][NJ], const W4Frags<NJ>& cur, W4Frags<NJ>& nxt,
                                          const bf16* rA, const bf16* rB, int pch,
                                          __amdgpu_buffer_rsrc_t rs_a, __amdgpu_buffer_rsrc_t rs_w, bf16* dA,
@@ -281,7 +283,7 @@ __device__ __forceinline__ void w4_block(f32x4_acc (&acc)[8][NJ], const W4Frags<
       if (DMA && (j == NJ / 2 || j == NJ / 2 + NJ / 4)) {
         const int d = 2 * s + (j != NJ / 2);
         if (d < 8) w4_dma(rs_a, dA + d * 8 * kBK, voff_a[d], kbyte);
-        else if (d - 8 < NJ) w4_dma(rs_w, dB + (d - 8) * 8 * kBK, voff[d - 8], kbyte);
+        else if (d - 8 < NJ) w4_dma<NT>(rs_w, dB + (d - 8) * 8 * kBK, voff[d - 8], kbyte);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -328,7 +330,13 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // main loop as one more k-tile, not pipelined, whose missing 16-byte chunks are fetched from outside the
 // descriptors (K < 64: there is nothing else; the prologue's k-tile 0 is overwritten unread).  K rows then start at odd multiples of 16 bytes, which the DMA does not mind.  8192 x 8192 x 2056:
 // 408 us on register-staged 128x128 tiles, 265 here (1.04 PFLOP/s; rows that straddle lines cost the rest).
-template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false>
+//
+// STREAM (narrow tile, one row tile, not cut): every line of W is read by one workgroup, once.  In step, the workgroups
+// would ask for the same 128 bytes of every row, which fall on a few of the HBM's channels where a row is a multiple of their
+// period; so each column tile starts at another k-tile (and adds up in that order), and the lines are fetched
+// non-temporally, so that they leave A in the L2.  Either alone gives little.  The 8B shape's gate_up, cold, 256 rows
+// 68.5 -> 60.3 us (63.3 without the hint).  The sums then have another order than the other tiles'.
+template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false, bool STREAM = false>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restrict__ A,
                                                            const bf16* __restrict__ W,
                                                            void* __restrict__ Cout, int M, int N,
@@ -569,11 +577,15 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     }
   } else {
     // Three stages, filled two k-tiles ahead: k-tiles 0, 1 and 2 are requested here and k-tile 0 awaited.
+    const int rot = STREAM ? tile_n % kt_count : 0;
+    auto kbyte = [&](int u) __attribute__((always_inline)) {
+      return kbyte0 + (STREAM && u + rot >= kt_count ? u + rot - kt_count : u + rot) * kBK * 2;
+    };
 #define W4_FETCH(u, c)                                                                                        \
   {                                                                                                           \
     const __amdgpu_buffer_rsrc_t ra_ = (u) < kt_count ? rsrc_a : rsrc_none, rw_ = (u) < kt_count ? rsrc_w : rsrc_none; \
-    _Pragma("unroll") for (int s = 0; s < 8; ++s) w4_dma(ra_, dA##c + s * 8 * kBK, voff_a[s], kbyte0 + (u) * kBK * 2); \
-    _Pragma("unroll") for (int s = 0; s < NJ; ++s) w4_dma(rw_, dB##c + s * 8 * kBK, voff[s], kbyte0 + (u) * kBK * 2); \
+    _Pragma("unroll") for (int s = 0; s < 8; ++s) w4_dma(ra_, dA##c + s * 8 * kBK, voff_a[s], kbyte(u)); \
+    _Pragma("unroll") for (int s = 0; s < NJ; ++s) w4_dma<STREAM>(rw_, dB##c + s * 8 * kBK, voff[s], kbyte(u)); \
   }
     W4_FETCH(0, 0);
     W4_FETCH(1, 1);
@@ -607,8 +619,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                                                                   \
     __builtin_amdgcn_s_waitcnt(kWaitVm12);                                                                    \
     w4_barrier();                                                                                             \
-    w4_block<2, true, NJ>(acc, f1, f0, rA##o, rB##o, pch0, t3_ < kt_count ? rsrc_a : rsrc_none,                   \
-                      t3_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte0 + t3_ * kBK * 2); \
+    w4_block<2, true, NJ, STREAM>(acc, f1, f0, rA##o, rB##o, pch0, t3_ < kt_count ? rsrc_a : rsrc_none,           \
+                      t3_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t3_));             \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
   }
     int t = 0;
@@ -775,6 +787,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // zeros to multiply), since with a branch between stages the compiler waits for all DMA before a read.
 // LDS rows hold KT bf16, 16-byte chunk c of row r at c ^ ((r >> 1) & 7) (KT = 64) or c ^ (r & 15)
 // (KT = 128): a half-wave's 16 rows x 2 chunks put two lanes on every bank group.
+// STREAM (grouped, or one row tile and not cut): workgroups start at different k and read W non-temporally, as above.  Cold, us:
+// gate_up of the 8B shape, 50 rows 52 -> 39 (6.0 TB/s; 44.7 without the hint, 52 with the hint alone), 128 rows 58 -> 56; the
+// hint in the experts' projections of the 30B-A3B shape, 16 tokens 87 -> 80 and 55 -> 49, 590 tokens 164 -> 147 and 97 -> 92 (with
+// the combine).  K ranges start at different k as it is, and gain nothing.
 // ------------------------------------------------------------------------------------------
 template <int N> constexpr int wait_vm() { return 0x0F70 | (N & 15) | ((N >> 4) << 14); }
 
@@ -782,11 +798,12 @@ template <int KT> __device__ __forceinline__ int ring_chunk(int chunk, int row) 
   return KT == 128 ? chunk ^ (row & 15) : chunk ^ ((row >> 1) & 7);
 }
 
+template <bool NT = false>
 __device__ __forceinline__ void ring_dma(const bf16* base, uint32_t bytes, bf16* lds, uint32_t voff, int kbyte) {
-  w4_dma(panel_rsrc(base, bytes), lds, voff, kbyte);
+  w4_dma<NT>(panel_rsrc(base, bytes), lds, voff, kbyte);
 }
 
-template <int MI, int NJ, int KT, int S, int EPI, bool GROUPED>
+template <int MI, int NJ, int KT, int S, int EPI, bool GROUPED, bool STREAM = GROUPED>
 __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
                                                                  void* __restrict__ Cout, int M, int N, int K,
                                                                  int tiles_m, int tiles_n, int kt_per_split,
@@ -827,8 +844,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
     // channels for the same columns of all of them: every (expert, column tile) starts at another k-tile
     // (experts_up of the 30B-A3B shape, 590 tokens 183 -> 164 us, 16 tokens 100 -> 89).  The start depends on
     // nothing else, so neither do a row's bits among these tiles; the 256-row tile starts every expert at 0, so a batch of
-    // more than 96 rows per expert rounds differently.  (Dense projections, whose columns are one matrix and whose uncut
-    // form has the bits of the large kernels, do not gain: 48 -> 64 us for gate_up.)
+    // more than 96 rows per expert rounds differently.
     rot = (expert * tiles_n + tile_n) % ((K + KT - 1) / KT);
   } else {
     tile_n = blockIdx.x - split * (tiles_m * tiles_n);
@@ -837,6 +853,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
     A += (int64_t)m0 * K;
     Cout = reinterpret_cast<char*>(Cout) + ((int64_t)m0 * N + slab) * (EPI == kEpiBf16 || SWIGLU ? 2 : 4);
     M = min(BM, M - m0);
+    if (STREAM) rot = tile_n % ((K + KT - 1) / KT);
   }
   const int n0 = tile_n * BN;
   const int k_first = split * kt_per_split * kBK;    // (K ranges are counted in k-tiles of 64)
@@ -871,7 +888,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
   const int kt_count = (k_count + KT - 1) / KT;
   auto fetch = [&](int t, bf16* s) __attribute__((always_inline)) {
     int left = k_count - t * KT;                     // behind the last k-tile every chunk is out of range
-    if (GROUPED && left > 0) {
+    if (STREAM && left > 0) {
       t = t + rot >= kt_count ? t + rot - kt_count : t + rot;
       left = k_count - t * KT;
     }
@@ -880,7 +897,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
       ring_dma(panel_a, bytes_a, s + RPI * (IA * wave + i) * KT, k_a[i] < left ? off_a[i] : kOffOutOfRange, t * KT * 2);
 #pragma unroll
     for (int i = 0; i < IW; ++i)
-      ring_dma(panel_w, bytes_w, s + (BM + RPI * (IW * wave + i)) * KT, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * KT * 2);
+      ring_dma<STREAM>(panel_w, bytes_w, s + (BM + RPI * (IW * wave + i)) * KT, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * KT * 2);
   };
 
   f32x4 acc[MI][NJ];
@@ -1158,6 +1175,14 @@ static int launch_ring(const bf16* a, const bf16* w, void* c, int m, int n, int 
       a, w, c, m, n, k, tiles_m, tiles_n, r.per, nullptr, nullptr);
   return r.used;
 }
+// The uncut SwiGLU projection with STREAM.
+template <int MI>
+static void launch_ring_stream(const bf16* a, const bf16* w, void* c, int m, int f, int k, hipStream_t s) {
+  using T = RingTile<MI, true>;
+  const int tiles_n = (f + T::BN - 1) / T::BN;
+  gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, kEpiSwiGLU, false, true><<<dim3((unsigned)tiles_n), 256, 0, s>>>(
+      a, w, c, m, f, k, 1, tiles_n, k_ranges(k, 1).per, nullptr, nullptr);
+}
 // Returns the number of K ranges launched (at most `splits`).
 template <int EPI>
 static int launch_few_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
@@ -1205,9 +1230,16 @@ bool gemm_swiglu_fusable(int dtype, int64_t m, int64_t f, int64_t k) {
 }
 
 void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f,
-                        int64_t k, hipStream_t s) {
+                        int64_t k, bool any_order, hipStream_t s) {
   if (!aligned_to(4, a, w_gate_up, out)) {
     launch_bf16_any<false, true>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, s);
+    return;
+  }
+  if (m <= kFewRows && any_order && aligned_to(16, a, w_gate_up, out)) {
+    const bf16 *pa = (const bf16*)a, *pw = (const bf16*)w_gate_up;
+    if (m <= 32) launch_ring_stream<2>(pa, pw, out, (int)m, (int)f, (int)k, s);
+    else if (m <= 64) launch_ring_stream<4>(pa, pw, out, (int)m, (int)f, (int)k, s);
+    else launch_ring_stream<8>(pa, pw, out, (int)m, (int)f, (int)k, s);
     return;
   }
   if (m <= kFewRows && aligned_to(16, a, w_gate_up, out)) {
@@ -1220,6 +1252,9 @@ void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t
   if (nj == 8)
     gemm_bf16_w4_kernel<kEpiSwiGLU><<<grid, 256, 0, s>>>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f,
                                                          (int)k, tiles_m, tiles_n, (int)(k / kBK), nullptr, nullptr);
+  else if (any_order && tiles_m == 1)
+    gemm_bf16_w4_kernel<kEpiSwiGLU, false, 4, false, true><<<grid, 256, 0, s>>>(
+        (const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, tiles_m, tiles_n, (int)(k / kBK), nullptr, nullptr);
   else
     gemm_bf16_w4_kernel<kEpiSwiGLU, false, 4><<<grid, 256, 0, s>>>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m,
                                                                    (int)f, (int)k, tiles_m, tiles_n, (int)(k / kBK),
@@ -1612,7 +1647,7 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   if (plan.splits > 1) plan = w4_cut(m, n, k, residual, plan);
   const int splits = plan.splits;
   if (splits == 1 && tl.kind == kTailSwiGLU) {       // not cut after all: the fused epilogue gives the same bits
-    launch_gemm_swiglu(a, w, tl.out, m, n / 2, k, s);
+    launch_gemm_swiglu(a, w, tl.out, m, n / 2, k, false, s);
     return;
   }
   if (splits >= 1 && plan.nj == 8) {
