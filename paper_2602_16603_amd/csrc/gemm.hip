@@ -224,16 +224,14 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
 // ------------------------------------------------------------------------------------------
 constexpr int kWaitVm0 = 0x0F70;   // s_waitcnt vmcnt(0)           (expcnt/lgkmcnt untouched)
 constexpr int kWaitVm1 = 0x0F71;   // s_waitcnt vmcnt(1)
-constexpr int kWaitVm12 = 0x0F7C;  // s_waitcnt vmcnt(12)
-constexpr int kWaitVm24 = 0x4F78;  // s_waitcnt vmcnt(24)
-constexpr int kWaitVm17 = 0x4F71;  // s_waitcnt vmcnt(17)
+template <int N> constexpr int wait_vm() { return 0x0F70 | (N & 15) | ((N >> 4) << 14); }   // s_waitcnt vmcnt(N)
 constexpr int kWaitLgkm0 = 0xC07F; // s_waitcnt lgkmcnt(0)         (vmcnt/expcnt untouched)
 constexpr int kWarmAhead = 3;      // k-tiles between the L2 warm-up load and the DMA of the same lines
 
 typedef float f32x4_acc __attribute__((ext_vector_type(4)));
-template <int NJ>
-struct W4Frags {     // MFMA operands of one k-step (32 of K): eight 16-row blocks of A and NJ of W
-  bf16x8 a[8];
+template <int MI, int NJ>
+struct W4Frags {     // MFMA operands of one k-step (32 of K): MI 16-row blocks of A and NJ of W
+  bf16x8 a[MI];
   bf16x8 b[NJ];
 };
 
@@ -250,40 +248,45 @@ __device__ __forceinline__ void w4_dma(__amdgpu_buffer_rsrc_t r, bf16* lds_rows,
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_rows, 16, voff, kbyte, 0, NT ? 2 : 0);
 }
 
-// One k-step: 8 NJ MFMAs from `cur` (A block s against the NJ W blocks, s = 0..7; NJ = 8: the
-// 256-column tile described here, NJ = 4: the 128-column tile of short requests, with half the W
-// fragments and DMA instructions in the same slots).  Every other
-// instruction sits alone behind an MFMA: READS fragment reads of the next k-step per A block (2:
-// spread over the k-step; 4: all in its first half, for the k-step that ends at the barrier, so
-// that the wait in front of the barrier finds them done), in the order of their first use (all of
-// W, then A blocks 0..7); if DMA, two of the wave's 16 DMA instructions per A block (0..7: its A
-// rows, 8..15: its W rows, 8 rows of 128 bytes each).
+// One k-step: MI NJ MFMAs from `cur` (A block s against the NJ W blocks, s = 0 .. MI - 1; MI = 8: the 256-row
+// tile described here, less: the row tiles of few rows of the grouped launches; NJ = 8: 256 columns, NJ = 4: the 128-column
+// tile of short requests, with half the W fragments and DMA instructions in the same slots).  Every other
+// instruction sits alone behind an MFMA: the fragment reads of the next k-step (EARLY: all in its first half,
+// for the k-step that ends at the barrier, so that the wait in front of the barrier finds them done; else
+// spread over the k-step), in the order of their first use (all of W, then the A blocks); if DMA, the wave's
+// MI + NJ DMA instructions (its A rows, then its W rows, 8 rows of 128 bytes each) in the second half of the A blocks' MFMAs.
 // The MFMA is written as inline assembly to accumulate in place: the compiler leaves the
 // destination of this 4-pass instruction free to differ from its accumulator input, which
 // overflows the completely used accumulation registers (the 8-pass 32x32x16 is tied by itself).
-// No accumulator is touched twice within 64 MFMAs, and LDS results reach the operands through
+// No accumulator is touched twice within MI NJ MFMAs, and LDS results reach the operands through
 // the s_waitcnt the compiler places for the asm inputs, so no software-managed hazard arises.
-template <int READS, bool DMA, int NJ, bool NT = false>
-__device__ __forceinline__ void w4_block(f32x4_acc (&acc)[8][NJ], const W4Frags<NJ>& cur, W4Frags<NJ>& nxt,
+enum { kReadsNone, kReadsSpread, kReadsEarly };
+template <int READS, bool DMA, int MI, int NJ, bool NT = false>
+__device__ __forceinline__ void w4_block(f32x4_acc (&acc)[MI][NJ], const W4Frags<MI, NJ>& cur, W4Frags<MI, NJ>& nxt,
                                          const bf16* rA, const bf16* rB, int pch,
                                          __amdgpu_buffer_rsrc_t rs_a, __amdgpu_buffer_rsrc_t rs_w, bf16* dA,
-                                         bf16* dB, const uint32_t (&voff_a)[8], const uint32_t (&voff)[8], int kbyte) {
+                                         bf16* dB, const uint32_t (&voff_a)[MI], const uint32_t (&voff)[8], int kbyte) {
+  constexpr int kSpread = (MI + NJ + MI - 1) / MI;    // per A block, so that MI blocks place all of them
+  constexpr int kReads = READS == kReadsNone ? 0 : READS == kReadsSpread ? kSpread : kSpread < NJ / 2 ? 2 * kSpread : NJ;
+  static_assert(kSpread <= NJ);
 #pragma unroll
-  for (int s = 0; s < 8; ++s) {
+  for (int s = 0; s < MI; ++s) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[s][j]) : "v"(cur.b[j]), "v"(cur.a[s]));
-      if (j < READS) {
-        const int r = s * READS + j;
-        if (r < NJ + 8) {
-          if (r < NJ) nxt.b[r] = *reinterpret_cast<const bf16x8*>(rB + r * 16 * kBK + pch);
-          else nxt.a[r - NJ] = *reinterpret_cast<const bf16x8*>(rA + (r - NJ) * 16 * kBK + pch);
-        }
+      if (j < kReads) {
+        const int r = s * kReads + j;
+        if (r < NJ) nxt.b[r] = *reinterpret_cast<const bf16x8*>(rB + r * 16 * kBK + pch);
+        else if (r < NJ + MI) nxt.a[r - NJ] = *reinterpret_cast<const bf16x8*>(rA + (r - NJ) * 16 * kBK + pch);
       }
-      if (DMA && (j == NJ / 2 || j == NJ / 2 + NJ / 4)) {
-        const int d = 2 * s + (j != NJ / 2);
-        if (d < 8) w4_dma(rs_a, dA + d * 8 * kBK, voff_a[d], kbyte);
-        else if (d - 8 < NJ) w4_dma<NT>(rs_w, dB + (d - 8) * 8 * kBK, voff[d - 8], kbyte);
+      if (DMA) {
+#pragma unroll
+        for (int i = 0; i < kSpread; ++i) {
+          const int d = kSpread * s + i;
+          if (j != NJ / 2 + i * (NJ / 2) / kSpread || d >= MI + NJ) continue;
+          if (d < MI) w4_dma(rs_a, dA + d * 8 * kBK, voff_a[d], kbyte);
+          else w4_dma<NT>(rs_w, dB + (d - MI) * 8 * kBK, voff[d - MI], kbyte);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -315,6 +318,14 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // of A (the tokens routed to an expert, fetched by the DMA from where they lie -- no gathered copy
 // of the activations is ever written); the kernel's M argument then holds the number of rows of A.
 //
+// An expert of a few dozen to a few hundred rows does not fill 256-row tiles: the kernel holds the tile on 64, 96, .. 256
+// rows and takes the one that a row tile's rows fit (the plan spreads an expert's rows evenly over its tiles: moe_plan_kernel).
+// What bounds these launches is the latency of their lines rather than MFMAs (15 % fewer of those gave 4 % at 8192
+// tokens): W panels come from HBM for one to three row tiles, so every (expert, column tile) starts at another k-tile, as
+// in the kernel for few rows below, and the L2 warm-up asks for more of them.  30B-A3B shape, us, experts_up / experts_down
+// (with the combine): 2000 tokens 244 / 141 -> 193 / 132 (even tiles 232 / 133), 5000 tokens 340 / 252 -> 303 / 231 (314 / 240),
+// 8192 tokens 429 / 343 -> 395 / 328 (425 / 341), 16000 tokens 720 / 605 -> 675 / 582.
+//
 // NJ = 4: the tile is half as wide (128 W rows per stage, wave tile 128 x 64).  A request of a few
 // hundred tokens has one or two row tiles: the narrow tile doubles the number of output tiles, so
 // the chip is occupied with half as many K ranges -- half the fp32 partial sums through memory,
@@ -336,7 +347,7 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // period; so each column tile starts at another k-tile (and adds up in that order), and the lines are fetched
 // non-temporally, so that they leave A in the L2.  Either alone gives little.  The 8B shape's gate_up, cold, 256 rows
 // 68.5 -> 60.3 us (63.3 without the hint).  The sums then have another order than the other tiles'.
-template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false, bool STREAM = false>
+template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false, bool STREAM = false, int ROWS = 256>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restrict__ A,
                                                            const bf16* __restrict__ W,
                                                            void* __restrict__ Cout, int M, int N,
@@ -348,11 +359,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   constexpr bool SWIGLU = EPI == kEpiSwiGLU;
   constexpr int WR = 32 * NJ;                        // W rows per stage (256 or 128)
   constexpr int Q = WR / 4;                          // of which each wave fetches this many
-  constexpr int BM = 256, BN = SWIGLU ? WR / 2 : WR; // output columns per tile
+  constexpr int BM = ROWS, BN = SWIGLU ? WR / 2 : WR;   // output rows and columns per tile
+  static_assert(BM % 32 == 0 && BM <= 256 && (!GROUPED || BM == 256));
   __shared__ __attribute__((aligned(1024))) bf16 sA0[BM * kBK];
   __shared__ __attribute__((aligned(1024))) bf16 sA1[BM * kBK];
-  __shared__ __attribute__((aligned(1024))) bf16 sB0[256 * kBK];   // (32 KB also when WR = 128: the epilogue
-  __shared__ __attribute__((aligned(1024))) bf16 sB1[(NJ == 8 ? 256 : WR) * kBK];   //  stages 32 KB per wave through the first four)
+  __shared__ __attribute__((aligned(1024))) bf16 sB0[(WR > BM ? WR : BM) * kBK];   // (as large as an A stage: the epilogue
+  __shared__ __attribute__((aligned(1024))) bf16 sB1[(NJ == 8 ? 256 : WR) * kBK];   //  stages its wave's outputs through the first four)
   __shared__ __attribute__((aligned(1024))) bf16 sA2[NJ == 8 ? 8 : BM * kBK];      // third stage of the narrow tile
   __shared__ __attribute__((aligned(1024))) bf16 sB2[NJ == 8 ? 8 : WR * kBK];
   __shared__ __attribute__((aligned(256))) uint32_t sWarm[NJ == 8 ? 4 * 64 : 4];   // landing pad of the L2 warm-up loads
@@ -361,7 +373,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wn = wave >> 1;           // 2 x 2 waves, wave tile 128 x WR/2 (SwiGLU: 128 x WR/4 outputs)
-  int tile_m, tile_n, share_m;
+  int tile_m, tile_n, share_m, rot = 0;
+  bool shared = true;                                // somebody else reads these rows of W
   int a_total_rows = 0;
   const int n_tiles = tiles_m * tiles_n;
   const int split = GROUPED ? 0 : blockIdx.x / n_tiles;   // which K range (0 unless split-K)
@@ -387,17 +400,26 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     tile_m = 0;
     tile_n = in_xcd % tiles_n;
     share_m = ti;
+    rot = (expert * tiles_n + tile_n) % (K / kBK);
+    shared = (ti > 0 && groups[1 + 3 * (ti - 1)] == expert) || (ti + 1 < n_row_tiles && groups[1 + 3 * (ti + 1)] == expert);
   } else {
     tile_of_workgroup(blockIdx.x - split * n_tiles, tiles_m, tiles_n, tile_m, tile_n);
     share_m = tile_m;
   }
   const int m0 = tile_m * BM, n0 = tile_n * BN;
+  // The tile itself, on 32 MI rows.
+  auto tile = [&](auto mi) __attribute__((always_inline)) {
+  constexpr int MI = decltype(mi)::value;
   const int kt_first = split * kt_per_split;
   const int kt_count = min(kt_per_split, K / kBK - kt_first);
   const int kbyte0 = kt_first * kBK * 2;
+  if (STREAM) rot = tile_n % kt_count;
+  auto kbyte = [&](int u) __attribute__((always_inline)) {   // of k-tile u of this workgroup
+    return kbyte0 + (!(STREAM || GROUPED) ? u : u + rot >= kt_count ? u + rot - kt_count : u + rot) * kBK * 2;
+  };
 
-  // DMA sources.  Wave w fetches LDS rows [64w, 64w+64) of each operand, 8 rows per instruction;
-  // voff[j] is lane's byte offset inside the wave's 64-row panel for instruction j (the same for A
+  // DMA sources.  Wave w fetches LDS rows [8 MI w, 8 MI w + 8 MI) of A and [Q w, Q w + Q) of W, 8 rows per instruction;
+  // voff[j] is lane's byte offset inside the wave's panel for instruction j (the same for A
   // and W: both have K as row stride): row 8j + lane/8, 16-byte chunk (lane%8) ^ swizzle key.
   uint32_t voff[8];
 #pragma unroll
@@ -408,14 +430,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   }
   // A rows of the same lanes: the same offsets, unless the rows are gathered (then absolute
   // offsets into all of A, rows past the tile's end pointing outside the descriptor).
-  uint32_t voff_a[8];
+  uint32_t voff_a[MI];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) voff_a[j] = voff[j];
+  for (int j = 0; j < MI; ++j) {                     // (8 MI w is not a multiple of 16 where MI and w are odd)
+    const int row = j * 8 + (lane >> 3);
+    const int ch = (lane & 7) ^ (((8 * MI * wave + row) >> 1) & 7);
+    voff_a[j] = MI % 2 ? (uint32_t)((row * K + ch * 8) * 2) : voff[j];
+  }
   const bool gathered = GROUPED && a_rows != nullptr;
   if (gathered) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int row = 64 * wave + j * 8 + (lane >> 3);          // tile_m = 0 in grouped launches
+    for (int j = 0; j < MI; ++j) {
+      const int row = 8 * MI * wave + j * 8 + (lane >> 3);          // tile_m = 0 in grouped launches
       const int ch = (lane & 7) ^ ((row >> 1) & 7);
       const int src = row < M ? a_rows[row] : -1;
       voff_a[j] = src >= 0 ? (uint32_t)((src * K + ch * 8) * 2) : kOffOutOfRange;
@@ -425,16 +451,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   // rows 2Q wn + Q + (0..Q-1) the up rows N + the same -- waves 2*wn and 2*wn+1 fetch them.
   const int w_col0 = SWIGLU ? n0 + Q * (wave >> 1) : n0 + Q * wave;
   const int64_t w_row0 = SWIGLU ? (int64_t)(wave & 1) * N + w_col0 : w_col0;
-  const int a_panel_rows = __builtin_amdgcn_readfirstlane(min(64, max(0, M - m0 - 64 * wave)));
+  const int a_panel_rows = __builtin_amdgcn_readfirstlane(min(8 * MI, max(0, M - m0 - 8 * MI * wave)));
   const int w_rows = __builtin_amdgcn_readfirstlane(min(Q, max(0, N - w_col0)));
   const __amdgpu_buffer_rsrc_t rsrc_a =
       gathered ? panel_rsrc(A, (uint32_t)(a_total_rows * K * 2))
-               : panel_rsrc(A + (int64_t)(m0 + 64 * wave) * K, (uint32_t)(a_panel_rows * K * 2));
+               : panel_rsrc(A + (int64_t)(m0 + 8 * MI * wave) * K, (uint32_t)(a_panel_rows * K * 2));
   const __amdgpu_buffer_rsrc_t rsrc_w = panel_rsrc(W + w_row0 * K, (uint32_t)(w_rows * K * 2));
   const __amdgpu_buffer_rsrc_t rsrc_none = panel_rsrc(A, 0u);
-  bf16* const dA0 = sA0 + 64 * wave * kBK;
-  bf16* const dA1 = sA1 + 64 * wave * kBK;
-  bf16* const dA2 = sA2 + 64 * wave * kBK;
+  bf16* const dA0 = sA0 + 8 * MI * wave * kBK;
+  bf16* const dA1 = sA1 + 8 * MI * wave * kBK;
+  bf16* const dA2 = sA2 + 8 * MI * wave * kBK;
   bf16* const dB0 = sB0 + Q * wave * kBK;
   bf16* const dB1 = sB1 + Q * wave * kBK;
   bf16* const dB2 = sB2 + Q * wave * kBK;
@@ -447,19 +473,25 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const int warm_rows_w = __builtin_amdgcn_readfirstlane(SWIGLU ? N + min(BN, N - n0) : min(BN, N - n0));
   const __amdgpu_buffer_rsrc_t rsrc_warm_a = panel_rsrc(A + (int64_t)m0 * K, (uint32_t)(warm_rows_a * K * 2));
   const __amdgpu_buffer_rsrc_t rsrc_warm_w = panel_rsrc(W + (int64_t)n0 * K, (uint32_t)(warm_rows_w * K * 2));
-  // (gathered rows are not contiguous: their lines are not warmed)
-  const __amdgpu_buffer_rsrc_t rsrc_warm = wave == 0 ? (gathered ? rsrc_none : rsrc_warm_a) : wave == 1 ? rsrc_warm_w : rsrc_none;
-  // Grouped launches: a W panel is shared by the two or three row tiles of its expert only, so
-  // there every workgroup takes a quarter of the W lines (all 64 lanes, every 4th row) instead of
-  // an eighth.
-  constexpr int kWShares = GROUPED ? 4 : 8;
+  // Grouped launches: a W panel is shared by the two or three row tiles of its expert only, so there waves 1 and 2 ask
+  // for every other row of it, and for none where the expert has one tile; gathered rows of A have an address each, and
+  // their shares do not rotate (8192 tokens of the 30B-A3B shape: experts_up 409 -> 396 us, experts_down 335 -> 329).
+  constexpr int kWShares = GROUPED ? 2 : 8;
+  const __amdgpu_buffer_rsrc_t rsrc_warm = GROUPED && !shared ? rsrc_none
+                                           : wave == 0 ? (gathered ? rsrc_a : rsrc_warm_a)
+                                           : wave == 1 || (GROUPED && wave == 2) ? rsrc_warm_w : rsrc_none;
   const int warm_mask = wave == 0 ? 3 : kWShares - 1;
   const int warm_id = wave == 0 ? (tile_n & 3) : (share_m & (kWShares - 1));
+  const int warm_step = gathered && wave == 0 ? 0 : K * 2;
   uint32_t voff_warm;
   {
-    const int r0 = lane * kWShares;                  // wave 1: W-stage row of this lane's share 0
+    const int r0 = (lane + (wave == 2 ? 64 : 0)) * kWShares;   // waves 1 and 2: W-stage row of this lane's share 0
     const int64_t wrow = SWIGLU ? (int64_t)((r0 / Q) & 1) * N + Q * (r0 / (2 * Q)) + (r0 % Q) : r0;
     voff_warm = wave == 0 ? (uint32_t)(lane * 4 * K * 2) : r0 < WR ? (uint32_t)(wrow * K * 2) : kOffOutOfRange;
+    if (gathered && wave == 0) {
+      const int row = 4 * lane + warm_id;
+      voff_warm = row < M ? (uint32_t)(a_rows[row] * K * 2) : kOffOutOfRange;
+    }
   }
 
   // MFMA fragment addresses: lane reads row (lane%16) of each 16-row block, k-chunk 4*ks + lane/16
@@ -467,9 +499,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const int frag_row = lane & 15, quad = lane >> 4;
   const int key = (lane >> 1) & 7;
   const int pch0 = ((0 + quad) ^ key) << 3, pch1 = ((4 + quad) ^ key) << 3;
-  const bf16* const rA0 = sA0 + (wm * 128 + frag_row) * kBK;
-  const bf16* const rA1 = sA1 + (wm * 128 + frag_row) * kBK;
-  const bf16* const rA2 = sA2 + (wm * 128 + frag_row) * kBK;
+  const bf16* const rA0 = sA0 + (wm * 16 * MI + frag_row) * kBK;
+  const bf16* const rA1 = sA1 + (wm * 16 * MI + frag_row) * kBK;
+  const bf16* const rA2 = sA2 + (wm * 16 * MI + frag_row) * kBK;
   const bf16* const rB2 = sB2 + (wn * (WR / 2) + frag_row) * kBK;
   const bf16* const rB0 = sB0 + (wn * (WR / 2) + frag_row) * kBK;
   const bf16* const rB1 = sB1 + (wn * (WR / 2) + frag_row) * kBK;
@@ -477,43 +509,43 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 #define W4_WARM(u)                                                                                            \
   __builtin_amdgcn_raw_ptr_buffer_load_lds((u) < kt_count ? rsrc_warm : rsrc_none,                            \
                                            (__attribute__((address_space(3))) void*)warm, 4, voff_warm,       \
-                                           kbyte0 + (u) * kBK * 2 + ((warm_id - (u)) & warm_mask) * K * 2, 0, 0)
-  f32x4_acc acc[8][NJ];
-  W4Frags<NJ> f0, f1;
+                                           kbyte(u) + ((warm_id - (u)) & warm_mask) * warm_step, 0, 0)
+  f32x4_acc acc[MI][NJ];
+  W4Frags<MI, NJ> f0, f1;
   if constexpr (NJ == 8) {
     // Prologue: k-tile 0 into stage 0 (awaited), k-tile 1 into stage 1 (in flight), then one warm-up
     // load, so that "all but one" is the right wait from the first barrier on.
 #pragma unroll
-    for (int s = 0; s < 8; ++s) w4_dma(rsrc_a, dA0 + s * 8 * kBK, voff_a[s], kbyte0);
+    for (int s = 0; s < MI; ++s) w4_dma(rsrc_a, dA0 + s * 8 * kBK, voff_a[s], kbyte(0));
 #pragma unroll
-    for (int s = 0; s < NJ; ++s) w4_dma(rsrc_w, dB0 + s * 8 * kBK, voff[s], kbyte0);
+    for (int s = 0; s < NJ; ++s) w4_dma(rsrc_w, dB0 + s * 8 * kBK, voff[s], kbyte(0));
     {
       const __amdgpu_buffer_rsrc_t ra1 = kt_count > 1 ? rsrc_a : rsrc_none, rw1 = kt_count > 1 ? rsrc_w : rsrc_none;
 #pragma unroll
-      for (int s = 0; s < 8; ++s) w4_dma(ra1, dA1 + s * 8 * kBK, voff_a[s], kbyte0 + kBK * 2);
+      for (int s = 0; s < MI; ++s) w4_dma(ra1, dA1 + s * 8 * kBK, voff_a[s], kbyte(1));
 #pragma unroll
-      for (int s = 0; s < NJ; ++s) w4_dma(rw1, dB1 + s * 8 * kBK, voff[s], kbyte0 + kBK * 2);
+      for (int s = 0; s < NJ; ++s) w4_dma(rw1, dB1 + s * 8 * kBK, voff[s], kbyte(1));
     }
     W4_WARM(kWarmAhead - 1);
     __builtin_amdgcn_sched_barrier(0);
     // Cleared while the first k-tile is on its way.
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));   // materialise the zeros here, not at first use
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(kWaitVm17);   // all but k-tile 1 (8 + NJ) and the warm-up load
+    __builtin_amdgcn_s_waitcnt(wait_vm<MI + NJ + 1>());   // all but k-tile 1 and the warm-up load
     w4_barrier();
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       if (s < NJ) f0.b[s] = *reinterpret_cast<const bf16x8*>(rB0 + s * 16 * kBK + pch0);
-      f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
+      if (s < MI) f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -525,12 +557,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 #define W4_TILE(t, c, o)                                                                                      \
   {                                                                                                           \
     const int t2_ = (t) + 2;                                                                                  \
-    w4_block<4, false, NJ>(acc, f0, f1, rA##c, rB##c, pch1, rsrc_none, rsrc_none, dA##c, dB##c, voff_a, voff, 0); \
+    w4_block<kReadsEarly, false, MI, NJ>(acc, f0, f1, rA##c, rB##c, pch1, rsrc_none, rsrc_none, dA##c, dB##c, voff_a, voff, 0); \
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                                                                   \
     __builtin_amdgcn_s_waitcnt(kWaitVm1);                                                                     \
     w4_barrier();                                                                                             \
-    w4_block<2, true, NJ>(acc, f1, f0, rA##o, rB##o, pch0, t2_ < kt_count ? rsrc_a : rsrc_none,                   \
-                      t2_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte0 + t2_ * kBK * 2); \
+    w4_block<kReadsSpread, true, MI, NJ>(acc, f1, f0, rA##o, rB##o, pch0, t2_ < kt_count ? rsrc_a : rsrc_none,                   \
+                      t2_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t2_)); \
     W4_WARM((t) + kWarmAhead);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
     }
@@ -557,12 +589,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
       __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
       w4_barrier();                            // both stages are free
-      const int left = K - kt_count * kBK, kbyte = kt_count * kBK * 2;
+      const int left = K - kt_count * kBK, kb = kt_count * kBK * 2;
 #pragma unroll
       for (int s = 0; s < 8; ++s) {
         const int k = ((lane & 7) ^ (((s * 8 + (lane >> 3)) >> 1) & 7)) * 8;
-        w4_dma(rsrc_a, dA0 + s * 8 * kBK, k < left ? voff_a[s] : kOffOutOfRange, kbyte);
-        w4_dma(rsrc_w, dB0 + s * 8 * kBK, k < left ? voff[s] : kOffOutOfRange, kbyte);
+        w4_dma(rsrc_a, dA0 + s * 8 * kBK, k < left ? voff_a[s] : kOffOutOfRange, kb);
+        w4_dma(rsrc_w, dB0 + s * 8 * kBK, k < left ? voff[s] : kOffOutOfRange, kb);
       }
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
       w4_barrier();
@@ -572,19 +604,15 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
         f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
       }
       __builtin_amdgcn_sched_barrier(0);
-      w4_block<4, false, NJ>(acc, f0, f1, rA0, rB0, pch1, rsrc_none, rsrc_none, dA0, dB0, voff_a, voff, 0);
-      w4_block<0, false, NJ>(acc, f1, f0, rA0, rB0, pch0, rsrc_none, rsrc_none, dA0, dB0, voff_a, voff, 0);
+      w4_block<kReadsEarly, false, MI, NJ>(acc, f0, f1, rA0, rB0, pch1, rsrc_none, rsrc_none, dA0, dB0, voff_a, voff, 0);
+      w4_block<kReadsNone, false, MI, NJ>(acc, f1, f0, rA0, rB0, pch0, rsrc_none, rsrc_none, dA0, dB0, voff_a, voff, 0);
     }
   } else {
     // Three stages, filled two k-tiles ahead: k-tiles 0, 1 and 2 are requested here and k-tile 0 awaited.
-    const int rot = STREAM ? tile_n % kt_count : 0;
-    auto kbyte = [&](int u) __attribute__((always_inline)) {
-      return kbyte0 + (STREAM && u + rot >= kt_count ? u + rot - kt_count : u + rot) * kBK * 2;
-    };
 #define W4_FETCH(u, c)                                                                                        \
   {                                                                                                           \
     const __amdgpu_buffer_rsrc_t ra_ = (u) < kt_count ? rsrc_a : rsrc_none, rw_ = (u) < kt_count ? rsrc_w : rsrc_none; \
-    _Pragma("unroll") for (int s = 0; s < 8; ++s) w4_dma(ra_, dA##c + s * 8 * kBK, voff_a[s], kbyte(u)); \
+    _Pragma("unroll") for (int s = 0; s < MI; ++s) w4_dma(ra_, dA##c + s * 8 * kBK, voff_a[s], kbyte(u)); \
     _Pragma("unroll") for (int s = 0; s < NJ; ++s) w4_dma<STREAM>(rw_, dB##c + s * 8 * kBK, voff[s], kbyte(u)); \
   }
     W4_FETCH(0, 0);
@@ -593,33 +621,33 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 #undef W4_FETCH
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(kWaitVm24);       // all but k-tiles 1 and 2
+    __builtin_amdgcn_s_waitcnt(wait_vm<2 * (MI + NJ)>());   // all but k-tiles 1 and 2
     w4_barrier();
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       if (s < NJ) f0.b[s] = *reinterpret_cast<const bf16x8*>(rB0 + s * 16 * kBK + pch0);
-      f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
+      if (s < MI) f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
     }
     __builtin_amdgcn_sched_barrier(0);
     // As above, but at the barrier k-tile t + 2 may still be in flight, and k-step 1 asks for t + 3.
 #define W4_TILE(t, c, o)                                                                                      \
   {                                                                                                           \
     const int t3_ = (t) + 3;                                                                                  \
-    w4_block<4, false, NJ>(acc, f0, f1, rA##c, rB##c, pch1, rsrc_none, rsrc_none, dA##c, dB##c, voff_a, voff, 0); \
+    w4_block<kReadsEarly, false, MI, NJ>(acc, f0, f1, rA##c, rB##c, pch1, rsrc_none, rsrc_none, dA##c, dB##c, voff_a, voff, 0); \
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                                                                   \
-    __builtin_amdgcn_s_waitcnt(kWaitVm12);                                                                    \
+    __builtin_amdgcn_s_waitcnt(wait_vm<MI + NJ>());                                                           \
     w4_barrier();                                                                                             \
-    w4_block<2, true, NJ, STREAM>(acc, f1, f0, rA##o, rB##o, pch0, t3_ < kt_count ? rsrc_a : rsrc_none,           \
+    w4_block<kReadsSpread, true, MI, NJ, STREAM>(acc, f1, f0, rA##o, rB##o, pch0, t3_ < kt_count ? rsrc_a : rsrc_none,           \
                       t3_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t3_));             \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
   }
@@ -659,13 +687,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   // the residual reads, 16 row segments at a time -- are in flight together instead of one after
   // the other.
   bf16* region = wave == 0 ? sA0 : wave == 1 ? sA1 : wave == 2 ? sB0 : NJ == 8 ? sB1 : sA2;
-  const int rows_valid = __builtin_amdgcn_readfirstlane(min(128, max(0, M - m0 - wm * 128)));
+  const int rows_valid = __builtin_amdgcn_readfirstlane(min(16 * MI, max(0, M - m0 - wm * 16 * MI)));
   if (SWIGLU) {
     // Accumulators [i][0..NJ/2-1] are gate, [i][NJ/2..NJ-1] up of outputs n0 + (WR/4)*wn + (0..WR/4-1):
     // staged as [128 rows][CH = NJ chunks of 8 bf16], chunk c of row r at position c ^ ((r>>1) & (CH-1)).
     constexpr int CH = NJ;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < MI; ++i) {
       const int row = i * 16 + frag_row;
       const int rkey = (row >> 1) & (CH - 1);
 #pragma unroll
@@ -681,12 +709,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
       }
     }
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);     // own wave's LDS writes have landed; no other wave touches the region
-    bf16* cb = reinterpret_cast<bf16*>(Cout) + (int64_t)(m0 + wm * 128) * N;
+    bf16* cb = reinterpret_cast<bf16*>(Cout) + (int64_t)(m0 + wm * 16 * MI) * N;
     const __amdgpu_buffer_rsrc_t rc = panel_rsrc(cb, (uint32_t)(rows_valid * N * 2));
     const int col = n0 + wn * (CH * 8) + (lane % CH) * 8;
     const uint32_t cbyte = col < N ? (uint32_t)(((lane / CH) * N + col) * 2) : kOffOutOfRange;
 #pragma unroll
-    for (int it = 0; it < 2 * CH; ++it) {
+    for (int it = 0; it < MI * CH / 4; ++it) {
       const int idx = lane + it * 64;
       const int row = idx / CH, ch = idx % CH;
       const u32x4 v = *reinterpret_cast<const u32x4*>(region + row * (CH * 8) + ((ch ^ ((row >> 1) & (CH - 1))) << 3));
@@ -696,7 +724,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     // [128 rows][CH = 2 NJ chunks of 8 bf16], chunk c of row r at position c ^ (r & (CH-1)).
     constexpr int CH = 2 * NJ;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < MI; ++i) {
       const int row = i * 16 + frag_row;
       const int rkey = row & (CH - 1);
 #pragma unroll
@@ -708,12 +736,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
       }
     }
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    bf16* cb = reinterpret_cast<bf16*>(Cout) + (int64_t)(m0 + wm * 128) * N;
+    bf16* cb = reinterpret_cast<bf16*>(Cout) + (int64_t)(m0 + wm * 16 * MI) * N;
     const __amdgpu_buffer_rsrc_t rc = panel_rsrc(cb, (uint32_t)(rows_valid * N * 2));
     const int col = n0 + wn * (CH * 8) + (lane % CH) * 8;
     const uint32_t cbyte = col < N ? (uint32_t)(((lane / CH) * N + col) * 2) : kOffOutOfRange;
 #pragma unroll
-    for (int it = 0; it < 2 * CH; ++it) {
+    for (int it = 0; it < MI * CH / 4; ++it) {
       const int idx = lane + it * 64;
       const int row = idx / CH, ch = idx % CH;
       const u32x4 v = *reinterpret_cast<const u32x4*>(region + row * (CH * 8) + ((ch ^ (row & (CH - 1))) << 3));
@@ -725,7 +753,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     // at position c ^ (r & 15).
     float* stage = reinterpret_cast<float*>(region);
     float* cf = reinterpret_cast<float*>(Cout) + (EPI == kEpiPartial ? (int64_t)split * M * N : 0) +
-                (int64_t)(m0 + wm * 128) * N;
+                (int64_t)(m0 + wm * 16 * MI) * N;
     const __amdgpu_buffer_rsrc_t rc = panel_rsrc(cf, (uint32_t)(rows_valid * N * 4));
     const int col0 = n0 + wn * (WR / 2) + (lane & 15) * 4;
 #pragma unroll
@@ -735,11 +763,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
       f32x4 x[16];
       if (RESID) {
 #pragma unroll
-        for (int it = 0; it < 16; ++it)
+        for (int it = 0; it < (MI < 4 ? 4 * MI : 16); ++it)
           x[it] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rc, cbyte, it * 4 * N * 4, 0));
       }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < MI; ++i) {
         const int row = i * 16 + frag_row;
         const int rkey = row & 15;
 #pragma unroll
@@ -752,14 +780,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
       }
       __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < (MI + 3) / 4; ++h) {
         if (RESID && h == 1) {
 #pragma unroll
-          for (int it = 0; it < 16; ++it)
+          for (int it = 0; it < 4 * MI - 16; ++it)
             x[it] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rc, cbyte, (16 + it) * 4 * N * 4, 0));
         }
 #pragma unroll
-        for (int it = 0; it < 16; ++it) {
+        for (int it = 0; it < (4 * MI - 16 * h < 16 ? 4 * MI - 16 * h : 16); ++it) {
           const int idx = lane + (h * 16 + it) * 64;
           const int row = idx >> 4, ch = idx & 15;
           f32x4 v = *reinterpret_cast<const f32x4*>(stage + row * 64 + ((ch ^ (row & 15)) << 2));
@@ -772,6 +800,20 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
       }
       __builtin_amdgcn_s_waitcnt(kWaitLgkm0);   // the stage is rewritten by the next pass
     }
+  }
+  };
+  if constexpr (GROUPED) {
+    switch ((M + 31) / 32) {
+      case 1: case 2: tile(std::integral_constant<int, 2>{}); break;
+      case 3: tile(std::integral_constant<int, 3>{}); break;
+      case 4: tile(std::integral_constant<int, 4>{}); break;
+      case 5: tile(std::integral_constant<int, 5>{}); break;
+      case 6: tile(std::integral_constant<int, 6>{}); break;
+      case 7: tile(std::integral_constant<int, 7>{}); break;
+      default: tile(std::integral_constant<int, 8>{}); break;
+    }
+  } else {
+    tile(std::integral_constant<int, BM / 32>{});
   }
 }
 
@@ -792,8 +834,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // hint in the experts' projections of the 30B-A3B shape, 16 tokens 87 -> 80 and 55 -> 49, 590 tokens 164 -> 147 and 97 -> 92 (with
 // the combine).  K ranges start at different k as it is, and gain nothing.
 // ------------------------------------------------------------------------------------------
-template <int N> constexpr int wait_vm() { return 0x0F70 | (N & 15) | ((N >> 4) << 14); }
-
 template <int KT> __device__ __forceinline__ int ring_chunk(int chunk, int row) {
   return KT == 128 ? chunk ^ (row & 15) : chunk ^ ((row >> 1) & 7);
 }
@@ -843,7 +883,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
     // Experts' matrices lie at multiples of the HBM channels' period, and workgroups in step would ask a few
     // channels for the same columns of all of them: every (expert, column tile) starts at another k-tile
     // (experts_up of the 30B-A3B shape, 590 tokens 183 -> 164 us, 16 tokens 100 -> 89).  The start depends on
-    // nothing else, so neither do a row's bits among these tiles; the 256-row tile starts every expert at 0, so a batch of
+    // nothing else, so neither do a row's bits among these tiles; the 256-row tile's columns are others, so a batch of
     // more than 96 rows per expert rounds differently.
     rot = (expert * tiles_n + tile_n) % ((K + KT - 1) / KT);
   } else {

@@ -134,9 +134,17 @@ __global__ __launch_bounds__(256) void moe_plan_kernel(int32_t* __restrict__ pla
         total += c[i];
       }
     }
+  // The 256-row tile multiplies only the multiple of 32 rows that a tile has: an expert's rows are spread evenly over as
+  // few tiles as hold them (520 rows: three tiles of 192, where 256 + 256 + 8 are three full ones and the last is bound by
+  // the latency of its k-tiles however few rows it has).
+  int rows = tile_rows;
+  if (tile_rows == 256 && total > 0) {
+    const int n = (total + 255) / 256;
+    rows = ((total + n - 1) / n + 31) / 32 * 32;
+  }
   // Exclusive prefix sums of rows and of tiles over the experts: within a wave by shuffles, across the four waves
   // through LDS (one thread walking all experts took 5 us).
-  const int tiles = (total + tile_rows - 1) / tile_rows;
+  const int tiles = (total + rows - 1) / rows;
   int off = total, first = tiles;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -151,10 +159,10 @@ __global__ __launch_bounds__(256) void moe_plan_kernel(int32_t* __restrict__ pla
   if (e == 0) groups[0] = s_tiles[0] + s_tiles[1] + s_tiles[2] + s_tiles[3];
   if (e < n_experts) {
     plan[e] = off;
-    for (int m = 0; m < total; m += tile_rows, ++first) {
+    for (int m = 0; m < total; m += rows, ++first) {
       groups[1 + 3 * first] = e;
       groups[2 + 3 * first] = off + m;
-      groups[3 + 3 * first] = min(tile_rows, total - m);
+      groups[3 + 3 * first] = min(rows, total - m);
     }
   }
 }

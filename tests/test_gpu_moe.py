@@ -195,3 +195,30 @@ def test_a_router_logit_beyond_the_fp32_range_is_not_hidden():
     assert torch.isnan(wts1[row]).all() and torch.isnan(x1[row]).all()
     assert torch.isfinite(x0).all() and torch.equal(ids1[others], ids0[others])
     assert torch.equal(wts1[others], wts0[others]) and torch.equal(x1[others], x0[others])
+
+
+@pytest.mark.parametrize("ffn,seed", [(192, 61), (128, 62)])
+def test_experts_of_unlike_sizes_run_on_large_tiles_of_every_height(ffn, seed):
+    """A router that favours some of its 32 experts: from a few rows to several hundred each, so the large tile of the
+    experts' GEMMs multiplies 64 to 256 rows in steps of 32, alone and as one of an expert's evenly filled tiles (odd
+    multiples of 32 among them; five k-tiles, and three or two; a last column tile that is half outside)."""
+    B, R = _mods()
+    spec = I.ShapeSpec(1, 320, 4, 2, 64, ffn, 1e-5, 10000.0, n_experts=32, top_k=4)
+    n = 1100
+    weights = I.make_weights(spec, seed, torch.bfloat16, "cpu")
+    weights[0]["w_router"] *= torch.linspace(0.3, 1.6, 32)[:, None].to(torch.bfloat16)
+    hidden = I.make_hidden(n, spec.hidden, seed, torch.bfloat16, "cpu")
+    model = R.PrefillModel(spec, weights, B.FP_DTYPE_BF16, 128, n)
+    print(f"experts of unlike sizes ffn={ffn}", flush=True)
+    task = model.begin(hidden.cuda(), [n])
+    task.run_to_completion()
+    got, ids = task.hidden(), task.moe_routing(0)[0].cpu()
+    rows = torch.bincount(ids.flatten().long(), minlength=32).tolist()
+    heights = {max(2, -(-(-(-r // -(-r // 256))) // 32)) for r in rows if r}
+    assert heights == set(range(2, 9)), rows
+    assert max(rows) > 256                                # ... and an expert of more than one tile
+    x_ref, _ = O.prefill(oracle_shape(spec), oracle_layers(weights), hidden, [0, n], forced_ids=[ids])
+    # Eight intermediates rounded to bf16 (2^-9 each): 1.2e-2 at most, and 1e-2 for their mean square.
+    assert fro_rel_err(got, x_ref) <= 1e-2 and max_rel_err(got, x_ref) <= TOL["bf16"]
+    task.end()
+    model.close()
