@@ -337,6 +337,10 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // L2 warm-up.  Cold weights, 256 tokens of the 8B shape: gate_up 81 -> 71 us, down 48 -> 44;
 // 512 tokens: down 74 -> 66.  (The wide tile's three stages would take 192 KB.)
 //
+// ROWS (256-column tile, not cut): the tile on 128, 160, .. 256 rows, the same sums in the same order.  What a launch of few
+// rounds of tiles loses is its last, partly filled round and the padding of its last row tile; another height often
+// comes out better (large_tile_rows).
+//
 // KTAIL (256-column tile, not cut): K is not a multiple of 64; its last K % 64 columns (a multiple of 8) follow the
 // main loop as one more k-tile, not pipelined, whose missing 16-byte chunks are fetched from outside the
 // descriptors (K < 64: there is nothing else; the prologue's k-tile 0 is overwritten unread).  K rows then start at odd multiples of 16 bytes, which the DMA does not mind.  8192 x 8192 x 2056:
@@ -686,6 +690,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   // fall outside it, columns past N get an out-of-range offset): no branches, so the stores -- and
   // the residual reads, 16 row segments at a time -- are in flight together instead of one after
   // the other.
+  // (The lane's number is made anew here: computed from the first one, the epilogue's addresses would be hoisted above the
+  // main loop and spilled.)
+  int lane_out = lane;
+  asm volatile("" : "+v"(lane_out));
+  const int row_out = lane_out & 15, quad_out = lane_out >> 4;
   bf16* region = wave == 0 ? sA0 : wave == 1 ? sA1 : wave == 2 ? sB0 : NJ == 8 ? sB1 : sA2;
   const int rows_valid = __builtin_amdgcn_readfirstlane(min(16 * MI, max(0, M - m0 - wm * 16 * MI)));
   if (SWIGLU) {
@@ -694,7 +703,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     constexpr int CH = NJ;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      const int row = i * 16 + frag_row;
+      const int row = i * 16 + row_out;
       const int rkey = (row >> 1) & (CH - 1);
 #pragma unroll
       for (int j = 0; j < NJ / 2; ++j) {
@@ -705,17 +714,17 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
           const float u = static_cast<float>(static_cast<bf16>(acc[i][NJ / 2 + j][b]));
           v[b] = static_cast<bf16>(silu_mul_f32(g, u));
         }
-        *reinterpret_cast<bf16x4*>(region + row * (CH * 8) + (((2 * j + (quad >> 1)) ^ rkey) << 3) + 4 * (quad & 1)) = v;
+        *reinterpret_cast<bf16x4*>(region + row * (CH * 8) + (((2 * j + (quad_out >> 1)) ^ rkey) << 3) + 4 * (quad_out & 1)) = v;
       }
     }
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);     // own wave's LDS writes have landed; no other wave touches the region
     bf16* cb = reinterpret_cast<bf16*>(Cout) + (int64_t)(m0 + wm * 16 * MI) * N;
     const __amdgpu_buffer_rsrc_t rc = panel_rsrc(cb, (uint32_t)(rows_valid * N * 2));
-    const int col = n0 + wn * (CH * 8) + (lane % CH) * 8;
-    const uint32_t cbyte = col < N ? (uint32_t)(((lane / CH) * N + col) * 2) : kOffOutOfRange;
+    const int col = n0 + wn * (CH * 8) + (lane_out % CH) * 8;
+    const uint32_t cbyte = col < N ? (uint32_t)(((lane_out / CH) * N + col) * 2) : kOffOutOfRange;
 #pragma unroll
     for (int it = 0; it < MI * CH / 4; ++it) {
-      const int idx = lane + it * 64;
+      const int idx = lane_out + it * 64;
       const int row = idx / CH, ch = idx % CH;
       const u32x4 v = *reinterpret_cast<const u32x4*>(region + row * (CH * 8) + ((ch ^ ((row >> 1) & (CH - 1))) << 3));
       __builtin_amdgcn_raw_buffer_store_b128(v, rc, cbyte, it * (64 / CH) * N * 2, 0);
@@ -725,24 +734,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     constexpr int CH = 2 * NJ;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      const int row = i * 16 + frag_row;
+      const int row = i * 16 + row_out;
       const int rkey = row & (CH - 1);
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         bf16x4 v;
 #pragma unroll
         for (int b = 0; b < 4; ++b) v[b] = static_cast<bf16>(acc[i][j][b]);
-        *reinterpret_cast<bf16x4*>(region + row * (CH * 8) + (((2 * j + (quad >> 1)) ^ rkey) << 3) + 4 * (quad & 1)) = v;
+        *reinterpret_cast<bf16x4*>(region + row * (CH * 8) + (((2 * j + (quad_out >> 1)) ^ rkey) << 3) + 4 * (quad_out & 1)) = v;
       }
     }
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
     bf16* cb = reinterpret_cast<bf16*>(Cout) + (int64_t)(m0 + wm * 16 * MI) * N;
     const __amdgpu_buffer_rsrc_t rc = panel_rsrc(cb, (uint32_t)(rows_valid * N * 2));
-    const int col = n0 + wn * (CH * 8) + (lane % CH) * 8;
-    const uint32_t cbyte = col < N ? (uint32_t)(((lane / CH) * N + col) * 2) : kOffOutOfRange;
+    const int col = n0 + wn * (CH * 8) + (lane_out % CH) * 8;
+    const uint32_t cbyte = col < N ? (uint32_t)(((lane_out / CH) * N + col) * 2) : kOffOutOfRange;
 #pragma unroll
     for (int it = 0; it < MI * CH / 4; ++it) {
-      const int idx = lane + it * 64;
+      const int idx = lane_out + it * 64;
       const int row = idx / CH, ch = idx % CH;
       const u32x4 v = *reinterpret_cast<const u32x4*>(region + row * (CH * 8) + ((ch ^ (row & (CH - 1))) << 3));
       __builtin_amdgcn_raw_buffer_store_b128(v, rc, cbyte, it * (64 / CH) * N * 2, 0);
@@ -755,11 +764,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     float* cf = reinterpret_cast<float*>(Cout) + (EPI == kEpiPartial ? (int64_t)split * M * N : 0) +
                 (int64_t)(m0 + wm * 16 * MI) * N;
     const __amdgpu_buffer_rsrc_t rc = panel_rsrc(cf, (uint32_t)(rows_valid * N * 4));
-    const int col0 = n0 + wn * (WR / 2) + (lane & 15) * 4;
+    const int col0 = n0 + wn * (WR / 2) + (lane_out & 15) * 4;
 #pragma unroll
     for (int jp = 0; jp < NJ / 4; ++jp) {
       const int col = col0 + jp * 64;
-      const uint32_t cbyte = col < N ? (uint32_t)(((lane >> 4) * N + col) * 4) : kOffOutOfRange;   // N % 8 == 0: quads all-in or all-out
+      const uint32_t cbyte = col < N ? (uint32_t)(((lane_out >> 4) * N + col) * 4) : kOffOutOfRange;   // N % 8 == 0: quads all-in or all-out
       f32x4 x[16];
       if (RESID) {
 #pragma unroll
@@ -768,14 +777,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
       }
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
-        const int row = i * 16 + frag_row;
+        const int row = i * 16 + row_out;
         const int rkey = row & 15;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
           f32x4 v;
 #pragma unroll
           for (int b = 0; b < 4; ++b) v[b] = acc[i][jp * 4 + jj][b];
-          *reinterpret_cast<f32x4*>(stage + row * 64 + (((jj * 4 + quad) ^ rkey) << 2)) = v;
+          *reinterpret_cast<f32x4*>(stage + row * 64 + (((jj * 4 + quad_out) ^ rkey) << 2)) = v;
         }
       }
       __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
@@ -788,7 +797,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
         }
 #pragma unroll
         for (int it = 0; it < (4 * MI - 16 * h < 16 ? 4 * MI - 16 * h : 16); ++it) {
-          const int idx = lane + (h * 16 + it) * 64;
+          const int idx = lane_out + (h * 16 + it) * 64;
           const int row = idx >> 4, ch = idx & 15;
           f32x4 v = *reinterpret_cast<const f32x4*>(stage + row * 64 + ((ch ^ (row & 15)) << 2));
           if (RESID) {
@@ -1255,6 +1264,26 @@ void launch_router_gemm(const void* a, const void* w, float* logits, int64_t m, 
   launch_ring<2, kEpiPartial>((const bf16*)a, (const bf16*)w, logits, (int)m, (int)n, (int)k, 1, s);
 }
 
+// An uncut problem on the large tile, 256 columns (SwiGLU: 128 outputs) by as many rows as large_tile_rows says.
+template <int EPI, int ROWS>
+static void launch_large_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int tiles_n, hipStream_t s) {
+  const int tiles_m = (m + ROWS - 1) / ROWS;
+  gemm_bf16_w4_kernel<EPI, false, 8, false, false, ROWS><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(
+      a, w, c, m, n, k, tiles_m, tiles_n, k / kBK, nullptr, nullptr);
+}
+template <int EPI>
+static void launch_large(const bf16* a, const bf16* w, void* c, int m, int n, int k, hipStream_t s) {
+  const int tiles_n = EPI == kEpiSwiGLU ? (n + 127) / 128 : (n + 255) / 256;
+  switch (large_tile_rows(m, tiles_n, k, EPI == kEpiResidual ? LargeEpilogue::kResidual
+                                         : EPI == kEpiSwiGLU ? LargeEpilogue::kSwiGLU : LargeEpilogue::kBf16)) {
+    case 128: launch_large_rows<EPI, 128>(a, w, c, m, n, k, tiles_n, s); break;
+    case 160: launch_large_rows<EPI, 160>(a, w, c, m, n, k, tiles_n, s); break;
+    case 192: launch_large_rows<EPI, 192>(a, w, c, m, n, k, tiles_n, s); break;
+    case 224: launch_large_rows<EPI, 224>(a, w, c, m, n, k, tiles_n, s); break;
+    default: launch_large_rows<EPI, 256>(a, w, c, m, n, k, tiles_n, s); break;
+  }
+}
+
 // Tile of the fused gate_up projection: 128 FFN columns when that occupies the chip or the
 // request has more than two row tiles, else 64.
 static int swiglu_nj(int64_t m, int64_t f) {
@@ -1290,8 +1319,7 @@ void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t
   const int tiles_m = (int)((m + 255) / 256), tiles_n = (int)((f + nj * 16 - 1) / (nj * 16));
   const dim3 grid((unsigned)(tiles_m * tiles_n));
   if (nj == 8)
-    gemm_bf16_w4_kernel<kEpiSwiGLU><<<grid, 256, 0, s>>>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f,
-                                                         (int)k, tiles_m, tiles_n, (int)(k / kBK), nullptr, nullptr);
+    launch_large<kEpiSwiGLU>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, s);
   else if (any_order && tiles_m == 1)
     gemm_bf16_w4_kernel<kEpiSwiGLU, false, 4, false, true><<<grid, 256, 0, s>>>(
         (const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, tiles_m, tiles_n, (int)(k / kBK), nullptr, nullptr);
@@ -1354,14 +1382,17 @@ static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, 
   const bool few = m <= kFewRows && aligned_to(16, a, w, c);
   constexpr int BN = 32 * NJ;
   const int tiles_m = (m + 255) / 256, tiles_n = (n + BN - 1) / BN;
-  const int kt = k / kBK;
   if (splits <= 1 && few) {
     launch_few_rows<RESID ? kEpiResidual : kEpiBf16>(a, w, c, m, n, k, 1, s);
     return;
   }
   if (splits <= 1) {
-    gemm_bf16_w4_kernel<RESID ? kEpiResidual : kEpiBf16, false, NJ>
-        <<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(a, w, c, m, n, k, tiles_m, tiles_n, kt, nullptr, nullptr);
+    constexpr int EPI = RESID ? kEpiResidual : kEpiBf16;
+    if constexpr (NJ == 8)
+      launch_large<EPI>(a, w, c, m, n, k, s);
+    else
+      gemm_bf16_w4_kernel<EPI, false, NJ><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(a, w, c, m, n, k, tiles_m,
+                                                                                            tiles_n, k / kBK, nullptr, nullptr);
     return;
   }
   const KRanges r = k_ranges(k, splits);

@@ -1,6 +1,7 @@
 // Prints what the GEMM dispatch rules (csrc/gemm_plan.h) say to the lines read from standard input:
 //   moe mean_rows ffn hidden      -> rows per tile of the experts' grouped launches
 //   tile m n k residual           -> tile of a problem too small for the large tiles: ring32, ring64, ring128, any128, large
+//   rows m n k bf16|swiglu|residual -> rows of the large tile for an uncut problem (swiglu: n outputs)
 //   swiglu m f k                  -> rows per tile of its fused gate_up projection (0: two operators)
 #include <iostream>
 #include <sstream>
@@ -23,6 +24,14 @@ int main() {
       int residual;
       in >> m >> n >> k >> residual;
       std::cout << names[(int)fp::small_problem_tile(m, n, k, residual != 0)] << "\n";
+    } else if (kind == "rows") {
+      long long m, n, k;
+      std::string epilogue;
+      in >> m >> n >> k >> epilogue;
+      const bool swiglu = epilogue == "swiglu";
+      std::cout << fp::large_tile_rows(m, (n + (swiglu ? 127 : 255)) / (swiglu ? 128 : 256), k,
+                                       swiglu ? fp::LargeEpilogue::kSwiGLU : epilogue == "residual" ? fp::LargeEpilogue::kResidual
+                                                                                                    : fp::LargeEpilogue::kBf16) << "\n";
     } else if (kind == "swiglu") {
       long long m, f, k;
       in >> m >> f >> k;

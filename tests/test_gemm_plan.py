@@ -69,3 +69,11 @@ def test_expert_tiles_leave_room_for_uneven_counts(rules):
     means = list(range(1, 400))
     for mean, tile in zip(means, map(int, rules([f"moe {m} 14336 4096" for m in means]))):
         assert tile == 256 or mean + 2 * mean ** 0.5 <= tile, (mean, tile)
+
+
+def test_the_gpu_tests_reach_every_height_of_the_large_tile(rules):
+    from tests.test_gpu_ops import LARGE_TILE_SIZES
+    got = rules([f"rows {m} {n} {k} {epilogue}" for _, epilogue, m, n, k in LARGE_TILE_SIZES])
+    assert [int(r) for r in got] == [rows for rows, *_ in LARGE_TILE_SIZES]
+    for _, epilogue, m, n, _ in LARGE_TILE_SIZES:             # none of them is cut over K or left to the small tiles
+        assert (m + 255) // 256 * ((n + (127 if epilogue == "swiglu" else 255)) // (128 if epilogue == "swiglu" else 256)) >= 160

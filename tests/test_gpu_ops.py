@@ -580,3 +580,45 @@ def test_bf16_fused_operators_off_the_16_byte_grid(m, offset):
     assert torch.equal(tailed, plain) and torch.equal(h_tail, h) and torch.equal(act_tail, act)
     ref = O.linear(a.cpu(), w.cpu()) + x.cpu().double()
     assert max_rel_err(tailed, ref) <= TOL["bf16"] and torch.all(ws[ws_bytes:] == 0x5A)
+
+
+LARGE_TILE_SIZES = [          # rows of the tile, epilogue, m (one to three rows past the last whole tile, or as many short of one), n, k
+    (128, "bf16", 2051, 7184, 64), (160, "bf16", 1283, 6672, 64), (192, "bf16", 5762, 1544, 64), (224, "bf16", 5379, 2064, 64),
+    (256, "bf16", 5634, 2320, 64), (128, "bf16", 2430, 6408, 576), (160, "bf16", 5759, 1544, 576),
+    (192, "bf16", 4029, 2320, 576), (224, "bf16", 1566, 7176, 576), (256, "bf16", 5631, 2320, 576),
+    (128, "residual", 2049, 7184, 64), (160, "residual", 1282, 6920, 64), (192, "residual", 5761, 1560, 64),
+    (224, "residual", 4931, 2312, 64), (256, "residual", 5633, 2312, 64), (128, "residual", 4990, 3088, 576),
+    (160, "residual", 1117, 7960, 576), (192, "residual", 1342, 7176, 576), (224, "residual", 4927, 2312, 576),
+    (256, "residual", 2047, 6424, 576), (128, "swiglu", 1537, 4616, 64), (160, "swiglu", 801, 5112, 64),
+    (192, "swiglu", 3073, 1552, 64), (224, "swiglu", 1346, 4112, 64), (256, "swiglu", 1795, 3600, 64),
+    (128, "swiglu", 1406, 5400, 576), (160, "swiglu", 799, 5112, 576), (192, "swiglu", 4607, 1040, 576),
+    (224, "swiglu", 4478, 1288, 576), (256, "swiglu", 1022, 6664, 576)]
+
+
+@pytest.mark.parametrize("rows,epilogue,m,n,k", LARGE_TILE_SIZES)
+def test_large_tile_of_every_height(rows, epilogue, m, n, k):
+    """An uncut projection on the large tile of 128 to 256 rows (tests/test_gemm_plan.py checks which): one k-tile and nine, a
+    nearly empty and a nearly full last row tile, a last column tile of one or two column blocks; rows behind M stay."""
+    B = _binding()
+    print(f"large tile rows={rows} {epilogue} m={m} n={n} k={k}", flush=True)
+    a = I.normal_tensor((m, k), 1.0, 91, torch.bfloat16, "cuda")
+    w = I.normal_tensor((2 * n if epilogue == "swiglu" else n, k), 0.1, 92, torch.bfloat16, "cuda")
+    c = torch.full((m + 256, n), 7.0, dtype=torch.float32 if epilogue == "residual" else torch.bfloat16, device="cuda")
+    ref = a.double() @ w.double().T
+    if epilogue == "residual":
+        c[:m] = I.normal_tensor((m, n), 1.0, 93, torch.float32, "cuda")
+        ref += c[:m].double()
+    elif epilogue == "swiglu":
+        ref = torch.nn.functional.silu(ref[:, :n]) * ref[:, n:]
+    torch.cuda.synchronize()
+    if epilogue == "swiglu":
+        B.fp_op_gemm_swiglu(a.data_ptr(), w.data_ptr(), c.data_ptr(), m, n, k)
+    else:
+        B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), c.data_ptr(), m, n, k, epilogue == "residual")
+    torch.cuda.synchronize()
+    # bf16 results: 2^-9 relative each; SiLU(gate) * up of gate and up rounded to bf16: three such roundings, the gate's
+    # amplified by at most 1 + |g|/4 or so.  fp32 results: sums of 576 products in fp32, 1e-6 at most.
+    bound = {"bf16": 4e-3, "swiglu": 1e-2, "residual": 1e-5}[epilogue]
+    err = (c[:m].double() - ref).norm(dim=1) / ref.norm(dim=1)
+    assert err.max().item() <= bound, (err.argmax().item(), err.max().item())
+    assert torch.all(c[m:] == 7.0)
