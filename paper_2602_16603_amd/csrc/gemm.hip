@@ -21,19 +21,20 @@ namespace fp {
 constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
 
-__device__ __forceinline__ void tile_of_workgroup(int wg, int tiles_m, int tiles_n, int& tm,
-                                                  int& tn) {
+__device__ __forceinline__ int tile_of_workgroup(int wg, int tiles_m, int tiles_n, int& tm, int& tn) {
   const int total = tiles_m * tiles_n;
   const int xcd = wg % kXcds;
   const int local = wg / kXcds;
   const int base = total / kXcds, rem = total % kXcds;
   const int logical = xcd * base + min(xcd, rem) + local;
-  const int per_group = kGroupM * tiles_n;
+  const int groups = (tiles_m + kGroupM - 1) / kGroupM, rows = (tiles_m + groups - 1) / groups;
+  const int per_group = rows * tiles_n;
   const int group = logical / per_group;
   const int in_group = logical - group * per_group;
-  const int gm = min(kGroupM, tiles_m - group * kGroupM);
-  tm = group * kGroupM + in_group % gm;
+  const int gm = min(rows, tiles_m - group * rows);
+  tm = group * rows + in_group % gm;
   tn = in_group / gm;
+  return gm;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
 // queues behind that miss (measured: 480 cycles average L2 read latency in gate_up_proj, 3300
 // cycles per k-tile in down_proj).  Instead each workgroup asks for its share of the lines three
 // k-tiles ahead of the DMA -- every 4th row of its A panel (wave 0) and every 8th row of its W
-// panel (wave 1), the shares rotating with the k-tile -- with a one-dword-per-lane load into a
+// panel (wave 1; every 4th or 2nd where fewer row tiles share it), the shares rotating with the k-tile -- with a one-dword-per-lane load into a
 // dummy LDS pad, so the DMA requests of all sharers find the line resident (2180-2240 cycles per
 // k-tile for both projections).  The pad load is the last VMEM instruction before the wave's
 // wait, which therefore asks for "all but one" and never blocks on it.
@@ -377,7 +378,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wn = wave >> 1;           // 2 x 2 waves, wave tile 128 x WR/2 (SwiGLU: 128 x WR/4 outputs)
-  int tile_m, tile_n, share_m, rot = 0;
+  int tile_m, tile_n, share_m, rot = 0, w_sharers = 2;
   bool shared = true;                                // somebody else reads these rows of W
   int a_total_rows = 0;
   const int n_tiles = tiles_m * tiles_n;
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     rot = (expert * tiles_n + tile_n) % (K / kBK);
     shared = (ti > 0 && groups[1 + 3 * (ti - 1)] == expert) || (ti + 1 < n_row_tiles && groups[1 + 3 * (ti + 1)] == expert);
   } else {
-    tile_of_workgroup(blockIdx.x - split * n_tiles, tiles_m, tiles_n, tile_m, tile_n);
+    w_sharers = tile_of_workgroup(blockIdx.x - split * n_tiles, tiles_m, tiles_n, tile_m, tile_n);
     share_m = tile_m;
   }
   const int m0 = tile_m * BM, n0 = tile_n * BN;
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   bf16* const dB1 = sB1 + Q * wave * kBK;
   bf16* const dB2 = sB2 + Q * wave * kBK;
 
-  // L2 warm-up sources: wave 0 lane l -> A row 4l + share, wave 1 lane l < 32 -> W-stage row 8l +
+  // L2 warm-up sources: wave 0 lane l -> A row 4l + share, wave 1 lane l (below 256 / shares) -> W-stage row shares l +
   // share (SwiGLU: stage row r is gate row n0 + Q*(r/2Q) + r%Q, or the up row N + that, for
   // r%2Q >= Q).  The share is added through the scalar offset.
   uint32_t* const warm = sWarm + 64 * wave;
@@ -477,19 +478,22 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const int warm_rows_w = __builtin_amdgcn_readfirstlane(SWIGLU ? N + min(BN, N - n0) : min(BN, N - n0));
   const __amdgpu_buffer_rsrc_t rsrc_warm_a = panel_rsrc(A + (int64_t)m0 * K, (uint32_t)(warm_rows_a * K * 2));
   const __amdgpu_buffer_rsrc_t rsrc_warm_w = panel_rsrc(W + (int64_t)n0 * K, (uint32_t)(warm_rows_w * K * 2));
+  // There are as many shares of W as workgroups to ask for them: eight row tiles walk a column panel together where there are
+  // as many, and with eight shares among two to seven the rest of the lines was never asked for (all five heights of the tile,
+  // 2-7 row tiles: 4 to 15 % faster with four or two shares; more row tiles: 0 to 5 %).
   // Grouped launches: a W panel is shared by the two or three row tiles of its expert only, so there waves 1 and 2 ask
-  // for every other row of it, and for none where the expert has one tile; gathered rows of A have an address each, and
+  // for every other row of it, and nobody where the expert has one tile; gathered rows of A have an address each, and
   // their shares do not rotate (8192 tokens of the 30B-A3B shape: experts_up 409 -> 396 us, experts_down 335 -> 329).
-  constexpr int kWShares = GROUPED ? 2 : 8;
+  const int w_shares = w_sharers >= 8 ? 8 : w_sharers >= 4 ? 4 : 2;
   const __amdgpu_buffer_rsrc_t rsrc_warm = GROUPED && !shared ? rsrc_none
                                            : wave == 0 ? (gathered ? rsrc_a : rsrc_warm_a)
-                                           : wave == 1 || (GROUPED && wave == 2) ? rsrc_warm_w : rsrc_none;
-  const int warm_mask = wave == 0 ? 3 : kWShares - 1;
-  const int warm_id = wave == 0 ? (tile_n & 3) : (share_m & (kWShares - 1));
+                                           : wave == 1 || (w_shares == 2 && wave == 2) ? rsrc_warm_w : rsrc_none;
+  const int warm_mask = wave == 0 ? 3 : w_shares - 1;
+  const int warm_id = wave == 0 ? (tile_n & 3) : (share_m & (w_shares - 1));
   const int warm_step = gathered && wave == 0 ? 0 : K * 2;
   uint32_t voff_warm;
   {
-    const int r0 = (lane + (wave == 2 ? 64 : 0)) * kWShares;   // waves 1 and 2: W-stage row of this lane's share 0
+    const int r0 = (lane + (wave == 2 ? 64 : 0)) * w_shares;   // waves 1 and 2: W-stage row of this lane's share 0
     const int64_t wrow = SWIGLU ? (int64_t)((r0 / Q) & 1) * N + Q * (r0 / (2 * Q)) + (r0 % Q) : r0;
     voff_warm = wave == 0 ? (uint32_t)(lane * 4 * K * 2) : r0 < WR ? (uint32_t)(wrow * K * 2) : kOffOutOfRange;
     if (gathered && wave == 0) {
