@@ -622,3 +622,31 @@ def test_large_tile_of_every_height(rows, epilogue, m, n, k):
     err = (c[:m].double() - ref).norm(dim=1) / ref.norm(dim=1)
     assert err.max().item() <= bound, (err.argmax().item(), err.max().item())
     assert torch.all(c[m:] == 7.0)
+
+
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("m,n,k", [(m, 2056, 1088) for m in (129, 160, 161, 192, 193, 224, 225, 257, 321, 385, 450, 511)] +
+                                  [(m, 2056, 6208) for m in (513, 576, 577, 672, 673, 771, 1023)] +
+                                  [(m, 21000, 192) for m in (159, 191, 223, 255)])
+def test_few_row_tiles_of_every_height(m, n, k, residual):
+    """Problems of one to four row tiles, cut over K on both widths of the large tile and (21000 columns) uncut on the narrow
+    one: row tiles of 160 to 256 rows, as few as hold m; rows behind M and the workspace's guard stay."""
+    B = _binding()
+    print(f"few row tiles m={m} n={n} k={k} residual={residual}", flush=True)
+    a = I.normal_tensor((m, k), 1.0, 94, torch.bfloat16, "cuda")
+    w = I.normal_tensor((n, k), 0.05, 95, torch.bfloat16, "cuda")
+    c = torch.full((m + 256, n), 7.0, dtype=torch.float32 if residual else torch.bfloat16, device="cuda")
+    ref = a.double() @ w.double().T
+    if residual:
+        c[:m] = I.normal_tensor((m, n), 1.0, 96, torch.float32, "cuda")
+        ref += c[:m].double()
+    ws_bytes = B.fp_op_gemm_workspace_bytes(1, m, n, k)
+    assert (ws_bytes > 0) == (k != 192)
+    ws = torch.full((ws_bytes + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    B.fp_op_gemm_ws(1, a.data_ptr(), w.data_ptr(), c.data_ptr(), m, n, k, residual, ws.data_ptr(), ws_bytes)
+    torch.cuda.synchronize()
+    err = (c[:m].double() - ref).norm(dim=1) / ref.norm(dim=1)
+    # bf16 results: 2^-9 relative each; fp32: sums of 6208 products in fp32, 64 at a time in the matrix unit: 1e-5 at most.
+    assert err.max().item() <= (1e-5 if residual else 4e-3), (err.argmax().item(), err.max().item())
+    assert torch.all(c[m:] == 7.0) and torch.all(ws[ws_bytes:] == 0x5A)

@@ -415,7 +415,7 @@ def test_model_on_a_stream_of_its_own(name):
 
 
 @pytest.mark.parametrize("hidden", [64, 192, 1088])
-@pytest.mark.parametrize("n", [1, 32, 33, 64, 65, 128, 129, 256])
+@pytest.mark.parametrize("n", [1, 32, 33, 64, 65, 128, 129, 161, 193, 256])
 def test_gate_up_of_one_row_tile_starts_its_column_tiles_at_different_k(n, hidden):
     """The fused gate_up projection of up to 256 tokens (three row tiles of the few-rows kernel, then the 128-column tile;
     one k-tile, fewer than the ring holds, a number that is no multiple of it; a last column tile of eight outputs)."""
