@@ -62,10 +62,11 @@ class PrefillModel:
 
     def wait_for_torch(self) -> None:
         """What torch has enqueued on its current stream comes before what the library enqueues next: nothing
-        to do where both use the same stream."""
-        current = torch.cuda.current_stream()
-        if current.cuda_stream != (self.stream.cuda_stream if self.stream is not None else 0):
-            current.synchronize()
+        to do where both use the same stream.  (Its handle alone: the object current_stream() makes costs 2.9 us, once per
+        begin and per K/V read-out of a request that takes 150.)"""
+        current = torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        if current != (self.stream.cuda_stream if self.stream is not None else 0):
+            torch.cuda.current_stream().synchronize()
 
     def close(self) -> None:
         if self.handle:
