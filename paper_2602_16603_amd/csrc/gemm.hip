@@ -347,11 +347,13 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // descriptors (K < 64: there is nothing else; the prologue's k-tile 0 is overwritten unread).  K rows then start at odd multiples of 16 bytes, which the DMA does not mind.  8192 x 8192 x 2056:
 // 408 us on register-staged 128x128 tiles, 265 here (1.04 PFLOP/s; rows that straddle lines cost the rest).
 //
-// STREAM (narrow tile, one row tile, not cut): every line of W is read by one workgroup, once.  In step, the workgroups
+// STREAM (one row tile, not cut): every line of W is read by one workgroup, once.  In step, the workgroups
 // would ask for the same 128 bytes of every row, which fall on a few of the HBM's channels where a row is a multiple of their
 // period; so each column tile starts at another k-tile (and adds up in that order), and the lines are fetched
 // non-temporally, so that they leave A in the L2.  Either alone gives little.  The 8B shape's gate_up, cold, 256 rows
-// 68.5 -> 60.3 us (63.3 without the hint).  The sums then have another order than the other tiles'.
+// 68.5 -> 60.3 us (63.3 without the hint); the 32B shape's, whose columns fill the chip with wide tiles, 160 rows 160 -> 140, 256 rows
+// 174 -> 156 (without the L2 warm-up: nobody shares these lines).  The sums then have another order than the other
+// tiles'.  (Two row tiles and more: the rotation alone is within 3 % either way, the hint 3 to 20 % slower.)
 template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false, bool STREAM = false, int ROWS = 256>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restrict__ A,
                                                            const bf16* __restrict__ W,
@@ -485,7 +487,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   // for every other row of it, and nobody where the expert has one tile; gathered rows of A have an address each, and
   // their shares do not rotate (8192 tokens of the 30B-A3B shape: experts_up 409 -> 396 us, experts_down 335 -> 329).
   const int w_shares = w_sharers >= 8 ? 8 : w_sharers >= 4 ? 4 : 2;
-  const __amdgpu_buffer_rsrc_t rsrc_warm = GROUPED && !shared ? rsrc_none
+  const __amdgpu_buffer_rsrc_t rsrc_warm = STREAM || (GROUPED && !shared) ? rsrc_none
                                            : wave == 0 ? (gathered ? rsrc_a : rsrc_warm_a)
                                            : wave == 1 || (w_shares == 2 && wave == 2) ? rsrc_warm_w : rsrc_none;
   const int warm_mask = wave == 0 ? 3 : w_shares - 1;
@@ -526,13 +528,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 #pragma unroll
     for (int s = 0; s < MI; ++s) w4_dma(rsrc_a, dA0 + s * 8 * kBK, voff_a[s], kbyte(0));
 #pragma unroll
-    for (int s = 0; s < NJ; ++s) w4_dma(rsrc_w, dB0 + s * 8 * kBK, voff[s], kbyte(0));
+    for (int s = 0; s < NJ; ++s) w4_dma<STREAM>(rsrc_w, dB0 + s * 8 * kBK, voff[s], kbyte(0));
     {
       const __amdgpu_buffer_rsrc_t ra1 = kt_count > 1 ? rsrc_a : rsrc_none, rw1 = kt_count > 1 ? rsrc_w : rsrc_none;
 #pragma unroll
       for (int s = 0; s < MI; ++s) w4_dma(ra1, dA1 + s * 8 * kBK, voff_a[s], kbyte(1));
 #pragma unroll
-      for (int s = 0; s < NJ; ++s) w4_dma(rw1, dB1 + s * 8 * kBK, voff[s], kbyte(1));
+      for (int s = 0; s < NJ; ++s) w4_dma<STREAM>(rw1, dB1 + s * 8 * kBK, voff[s], kbyte(1));
     }
     W4_WARM(kWarmAhead - 1);
     __builtin_amdgcn_sched_barrier(0);
@@ -569,7 +571,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                                                                   \
     __builtin_amdgcn_s_waitcnt(kWaitVm1);                                                                     \
     w4_barrier();                                                                                             \
-    w4_block<kReadsSpread, true, MI, NJ>(acc, f1, f0, rA##o, rB##o, pch0, t2_ < kt_count ? rsrc_a : rsrc_none,                   \
+    w4_block<kReadsSpread, true, MI, NJ, STREAM>(acc, f1, f0, rA##o, rB##o, pch0, t2_ < kt_count ? rsrc_a : rsrc_none,                   \
                       t2_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t2_)); \
     W4_WARM((t) + kWarmAhead);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
@@ -1302,7 +1304,8 @@ static void launch_even_rows(const bf16* a, const bf16* w, void* c, int m, int n
         a, w, c, m, n, k, tiles_m, tiles_n, kt_per_split, nullptr, nullptr);
   };
   const int rows = (m + tiles_m - 1) / tiles_m;
-  if (NJ == 4 && rows <= 160) launch(std::integral_constant<int, NJ == 4 ? 160 : 256>{});   // (NJ = 8: three row tiles or more)
+  constexpr bool kAnyNumber = NJ == 4 || STREAM;     // (else three row tiles or more)
+  if (kAnyNumber && rows <= 160) launch(std::integral_constant<int, kAnyNumber ? 160 : 256>{});
   else if (rows <= 192) launch(std::integral_constant<int, 192>{});
   else if (rows <= 224) launch(std::integral_constant<int, 224>{});
   else launch(std::integral_constant<int, 256>{});
@@ -1340,10 +1343,13 @@ void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t
     return;
   }
   const int nj = swiglu_nj(m, f);
-  if (nj == 8)
+  if (any_order && m <= 256) {
+    if (nj == 8)
+      launch_even_rows<kEpiSwiGLU, 8, true>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, (int)(k / kBK), 1, s);
+    else
+      launch_even_rows<kEpiSwiGLU, 4, true>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, (int)(k / kBK), 1, s);
+  } else if (nj == 8)
     launch_large<kEpiSwiGLU>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, s);
-  else if (any_order && m <= 256)
-    launch_even_rows<kEpiSwiGLU, 4, true>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, (int)(k / kBK), 1, s);
   else
     launch_even_rows<kEpiSwiGLU, 4>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, (int)(k / kBK), 1, s);
 }

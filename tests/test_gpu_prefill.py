@@ -414,15 +414,17 @@ def test_model_on_a_stream_of_its_own(name):
     own.close()
 
 
-@pytest.mark.parametrize("hidden", [64, 192, 1088])
-@pytest.mark.parametrize("n", [1, 32, 33, 64, 65, 128, 129, 161, 193, 256])
-def test_gate_up_of_one_row_tile_starts_its_column_tiles_at_different_k(n, hidden):
-    """The fused gate_up projection of up to 256 tokens (three row tiles of the few-rows kernel, then the 128-column tile;
-    one k-tile, fewer than the ring holds, a number that is no multiple of it; a last column tile of eight outputs)."""
-    spec = I.ShapeSpec(1, hidden, 2, 1, 64, 6152, 1e-5, 10000.0)
+@pytest.mark.parametrize("ffn,hidden,n", [(6152, hidden, n) for hidden in (64, 192, 1088)
+                                          for n in (1, 32, 33, 64, 65, 128, 129, 161, 193, 256)] +
+                                         [(20488, hidden, n) for hidden in (64, 576) for n in (129, 161, 193, 256)])
+def test_gate_up_of_one_row_tile_starts_its_column_tiles_at_different_k(ffn, hidden, n):
+    """The fused gate_up projection of up to 256 tokens (three row tiles of the few-rows kernel, then the 128-column tile and,
+    where its columns fill the chip, the 256-column one on every height; one k-tile, fewer than the stages hold, a number
+    that is no multiple of them; a last column tile of eight outputs)."""
+    spec = I.ShapeSpec(1, hidden, 2, 1, 64, ffn, 1e-5, 10000.0)
     model, weights = build(spec, 31, "bf16", total_tokens=n, random_gains=True)
     x = I.make_hidden(n, hidden, 31, torch.bfloat16, "cpu")
-    print(f"gate_up streamed n={n} hidden={hidden}", flush=True)
+    print(f"gate_up streamed n={n} hidden={hidden} ffn={ffn}", flush=True)
     task = model.begin(x.cuda(), [n])
     task.run_to_completion()
     x_ref, _ = O.prefill(oracle_shape(spec), oracle_layers(weights), x, [0, n])
