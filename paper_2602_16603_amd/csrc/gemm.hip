@@ -1197,13 +1197,16 @@ static W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
   return {narrow ? 4 : 8, s};
 }
 
-// Few rows: up to kFewRows of them.  Columns per tile, k-tile and stages by row count and epilogue, as measured on
-// cold weights of the 8B shape (us, against the two-stage 256-row tile): up to 64 rows 64-column tiles of 128 k (256 bytes of a
-// weight row at a time: HBM gives 4.9 TB/s to such pieces where 128-byte pieces get 4.2) -- 50 rows: qkv
-// 22 -> 17, o 17 -> 12.6, down 40 -> 28; from 65 rows on the A tile weighs more and 128-column tiles of 64 k
-// read it half as often -- 128 rows: qkv 24 -> 23.5, down 42 -> 34 (26, 41 on the former).  SwiGLU: 128 W rows of 64 k,
-// 75 -> 52 at 50 rows, 80 -> 64 at 128.
-constexpr int kFewRows = 128;
+// Few rows: up to kFewRows of them, and up to twice as many where the large kernel's 128-column tile on 96 or 128 rows is not
+// ahead: projections of a long K (32B shape's down, 128 rows 77 us, 80 there) and the fused gate_up projection whose columns
+// fill the chip with wide tiles (32B shape 135 us, 140).  The others are faster there: 8B shape, 70 / 128 rows, cold, us, gate_up
+// 58 / 57 -> 47 / 52, qkv 24 / 27.5 -> 20.5 / 24.5, o 21.5 / 24 -> 20.5 / 23, down 35 / 41 -> 34 / 40.  Columns per tile, k-tiles and stages by
+// row count and epilogue, as measured on cold weights of the 8B shape (us, against the two-stage 256-row tile): up to
+// 64 rows 64-column tiles of 128 k (256 bytes of a weight row at a time: HBM gives 4.9 TB/s to such pieces where 128-byte
+// pieces get 4.2) -- 50 rows: qkv 22 -> 17, o 17 -> 12.6, down 40 -> 28; from 65 rows on the A tile weighs more and 128-column
+// tiles of 64 k read it half as often.  SwiGLU: 128 W rows of 64 k, 75 -> 52 at 50 rows.
+constexpr int kFewRows = 64;
+static bool few_rows(int64_t m, int64_t k) { return m <= kFewRows || (m <= 2 * kFewRows && k > 16384); }
 template <int MI, bool SWIGLU> struct RingTile {
   static constexpr bool kWide = SWIGLU || MI > 4;
   static constexpr int NJ = kWide ? 2 : 1, KT = kWide ? 64 : 128, S = 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
@@ -1305,7 +1308,9 @@ static void launch_even_rows(const bf16* a, const bf16* w, void* c, int m, int n
   };
   const int rows = (m + tiles_m - 1) / tiles_m;
   constexpr bool kAnyNumber = NJ == 4 || STREAM;     // (else three row tiles or more)
-  if (kAnyNumber && rows <= 160) launch(std::integral_constant<int, kAnyNumber ? 160 : 256>{});
+  if (kAnyNumber && rows <= 96) launch(std::integral_constant<int, kAnyNumber ? 96 : 256>{});
+  else if (kAnyNumber && rows <= 128) launch(std::integral_constant<int, kAnyNumber ? 128 : 256>{});
+  else if (kAnyNumber && rows <= 160) launch(std::integral_constant<int, kAnyNumber ? 160 : 256>{});
   else if (rows <= 192) launch(std::integral_constant<int, 192>{});
   else if (rows <= 224) launch(std::integral_constant<int, 224>{});
   else launch(std::integral_constant<int, 256>{});
@@ -1331,18 +1336,19 @@ void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t
     launch_bf16_any<false, true>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, s);
     return;
   }
-  if (m <= kFewRows && any_order && aligned_to(16, a, w_gate_up, out)) {
+  const int nj = swiglu_nj(m, f);
+  const bool few = m <= kFewRows || (m <= 2 * kFewRows && nj == 8);
+  if (few && any_order && aligned_to(16, a, w_gate_up, out)) {
     const bf16 *pa = (const bf16*)a, *pw = (const bf16*)w_gate_up;
     if (m <= 32) launch_ring_stream<2>(pa, pw, out, (int)m, (int)f, (int)k, s);
     else if (m <= 64) launch_ring_stream<4>(pa, pw, out, (int)m, (int)f, (int)k, s);
     else launch_ring_stream<8>(pa, pw, out, (int)m, (int)f, (int)k, s);
     return;
   }
-  if (m <= kFewRows && aligned_to(16, a, w_gate_up, out)) {
+  if (few && aligned_to(16, a, w_gate_up, out)) {
     launch_few_rows<kEpiSwiGLU>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, 1, s);
     return;
   }
-  const int nj = swiglu_nj(m, f);
   if (any_order && m <= 256) {
     if (nj == 8)
       launch_even_rows<kEpiSwiGLU, 8, true>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, (int)(k / kBK), 1, s);
@@ -1404,7 +1410,7 @@ void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64
 template <bool RESID, int NJ>
 static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits,
                            float* workspace, const GemmTail& tail, hipStream_t s) {
-  const bool few = m <= kFewRows && aligned_to(16, a, w, c);
+  const bool few = few_rows(m, k) && aligned_to(16, a, w, c);
   if (splits <= 1 && few) {
     launch_few_rows<RESID ? kEpiResidual : kEpiBf16>(a, w, c, m, n, k, 1, s);
     return;
@@ -1676,7 +1682,7 @@ int gemm_left_ranges(int dtype, int64_t m, int64_t n, int64_t k, size_t workspac
   W4Shape plan = w4_plan(dtype, m, n, k, workspace_bytes);
   if (plan.splits > 1) plan = w4_cut(m, n, k, false, plan);
   if (plan.splits <= 1) return 0;
-  if (m > kFewRows) return k_ranges((int)k, plan.splits).used;
+  if (!few_rows(m, k)) return k_ranges((int)k, plan.splits).used;
   if (m <= 32) return ring_ranges<2, kEpiPartial>((int)n, (int)k, plan.splits).used;
   if (m <= 64) return ring_ranges<4, kEpiPartial>((int)n, (int)k, plan.splits).used;
   return ring_ranges<8, kEpiPartial>((int)n, (int)k, plan.splits).used;

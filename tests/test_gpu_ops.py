@@ -625,12 +625,12 @@ def test_large_tile_of_every_height(rows, epilogue, m, n, k):
 
 
 @pytest.mark.parametrize("residual", [False, True])
-@pytest.mark.parametrize("m,n,k", [(m, 2056, 1088) for m in (129, 160, 161, 192, 193, 224, 225, 257, 321, 385, 450, 511)] +
+@pytest.mark.parametrize("m,n,k", [(m, 2056, 1088) for m in (65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 225, 257, 321, 385, 450, 511)] +
                                   [(m, 2056, 6208) for m in (513, 576, 577, 672, 673, 771, 1023)] +
-                                  [(m, 21000, 192) for m in (159, 191, 223, 255)])
+                                  [(m, 21000, 192) for m in (65, 95, 127, 159, 191, 223, 255)] + [(128, 1032, 17408)])
 def test_few_row_tiles_of_every_height(m, n, k, residual):
     """Problems of one to four row tiles, cut over K on both widths of the large tile and (21000 columns) uncut on the narrow
-    one: row tiles of 160 to 256 rows, as few as hold m; rows behind M and the workspace's guard stay."""
+    one: row tiles of 96 to 256 rows, as few as hold m (and 128 rows of a long K on the few-rows kernel); rows behind M and the workspace's guard stay."""
     B = _binding()
     print(f"few row tiles m={m} n={n} k={k} residual={residual}", flush=True)
     a = I.normal_tensor((m, k), 1.0, 94, torch.bfloat16, "cuda")
@@ -647,6 +647,6 @@ def test_few_row_tiles_of_every_height(m, n, k, residual):
     B.fp_op_gemm_ws(1, a.data_ptr(), w.data_ptr(), c.data_ptr(), m, n, k, residual, ws.data_ptr(), ws_bytes)
     torch.cuda.synchronize()
     err = (c[:m].double() - ref).norm(dim=1) / ref.norm(dim=1)
-    # bf16 results: 2^-9 relative each; fp32: sums of 6208 products in fp32, 64 at a time in the matrix unit: 1e-5 at most.
+    # bf16 results: 2^-9 relative each; fp32: sums of up to 17408 products in fp32, 32 at a time in the matrix unit: 1e-5 at most.
     assert err.max().item() <= (1e-5 if residual else 4e-3), (err.argmax().item(), err.max().item())
     assert torch.all(c[m:] == 7.0) and torch.all(ws[ws_bytes:] == 0x5A)
