@@ -1444,14 +1444,15 @@ static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, 
 
 // ------------------------------------------------------------------------------------------
 // fp32 GEMM (debug path) on v_mfma_f32_16x16x4_f32: products and sums in fp32, 256 FLOP per clock and
-// CU.  256 threads = 2 x 2 waves, wave tile (16 TM) x (16 TN), K consumed 32 at a time through a ring
+// CU.  256 threads = WM x 4 / WM waves, wave tile (16 TM) x (16 TN), K consumed 32 at a time through a ring
 // of three LDS stages filled by DMA two k-tiles ahead (128-byte rows, chunk c of row r at position
 // c ^ ((r >> 1) & 7): conflict-free for the 16-row fragment reads, as in the bf16 kernel).  The
 // instruction takes one k per lane quarter; a lane reads four consecutive k of its row with one
 // ds_read_b128 and step j of four multiplies the j-th of each quarter -- A and W are permuted over k
 // alike.  Chunks past K are fetched from outside the descriptor, so they read as zero (K % 4 == 0).
 // The matrix pipes bound it (157 TFLOP/s): 300 rows of the 8B shape's gate_up projection 2040 -> 630 us
-// (119 TFLOP/s, row padding included), down 2476 -> 381 us, against the plain FMA kernel below.
+// (119 TFLOP/s, row padding included), down 2476 -> 381 us, against the plain FMA kernel below; f32_tile_rows chooses the tile
+// (down 338 us on 80 rows).  Waves side by side along N (WM = 1) for heights that are no multiple of 32.
 // ------------------------------------------------------------------------------------------
 constexpr int kFK = 32;
 
@@ -1460,20 +1461,22 @@ __device__ __forceinline__ void f32_dma(const float* panel, uint32_t bytes, floa
                                            voff, kbyte, 0, 0);
 }
 
-template <int TM, int TN, bool RESID>
+template <int TM, int TN, int WM, bool RESID>
 __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restrict__ A,
                                                             const float* __restrict__ W,
                                                             float* __restrict__ C, int M, int N, int K,
                                                             int tiles_m, int tiles_n) {
-  constexpr int BM = 32 * TM, BN = 32 * TN;
-  constexpr int IA = BM / 32, IW = BN / 32;          // DMA instructions (8 rows of 128 bytes) per wave and k-tile
+  constexpr int WN = 4 / WM, BM = 16 * TM * WM, BN = 16 * TN * WN;
+  constexpr int IA = (BM + 31) / 32, IW = BN / 32;   // DMA instructions (8 rows of 128 bytes) per wave and k-tile
+  constexpr int RA = 32 * IA;                        // rows of A per stage: BM, or 16 more, which are zeros
   constexpr int kWaitNewest = 0x0F70 | (IA + IW);    // vmcnt: all but the newest k-tile's
-  __shared__ __attribute__((aligned(1024))) float s0[(BM + BN) * kFK];
-  __shared__ __attribute__((aligned(1024))) float s1[(BM + BN) * kFK];
-  __shared__ __attribute__((aligned(1024))) float s2[(BM + BN) * kFK];
+  static_assert(BN % 32 == 0 && IA + IW < 16);
+  __shared__ __attribute__((aligned(1024))) float s0[(RA + BN) * kFK];
+  __shared__ __attribute__((aligned(1024))) float s1[(RA + BN) * kFK];
+  __shared__ __attribute__((aligned(1024))) float s2[(RA + BN) * kFK];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave & 1, wn = wave >> 1;
+  const int wm = wave % WM, wn = wave / WM;
   int tile_m, tile_n;
   tile_of_workgroup(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
@@ -1488,7 +1491,7 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restr
   for (int i = 0; i < IA; ++i) {
     const int row = 8 * (wave * IA + i) + (lane >> 3);
     k_a[i] = 4 * ((lane & 7) ^ ((row >> 1) & 7));
-    off_a[i] = (uint32_t)((row * K + k_a[i]) * 4);
+    off_a[i] = row < BM ? (uint32_t)((row * K + k_a[i]) * 4) : kOffOutOfRange;
   }
 #pragma unroll
   for (int i = 0; i < IW; ++i) {
@@ -1504,7 +1507,7 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restr
       f32_dma(panel_a, bytes_a, s + 8 * (wave * IA + i) * kFK, k_a[i] < left ? off_a[i] : kOffOutOfRange, t * kFK * 4);
 #pragma unroll
     for (int i = 0; i < IW; ++i)
-      f32_dma(panel_w, bytes_w, s + (BM + 8 * (wave * IW + i)) * kFK, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * kFK * 4);
+      f32_dma(panel_w, bytes_w, s + (RA + 8 * (wave * IW + i)) * kFK, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * kFK * 4);
   };
 
   f32x4 acc[TM][TN];
@@ -1526,7 +1529,7 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restr
         fa[i] = *reinterpret_cast<const f32x4*>(s + (wm * 16 * TM + i * 16 + frag_row) * kFK + at);
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        fw[j] = *reinterpret_cast<const f32x4*>(s + (BM + wn * 16 * TN + j * 16 + frag_row) * kFK + at);
+        fw[j] = *reinterpret_cast<const f32x4*>(s + (RA + wn * 16 * TN + j * 16 + frag_row) * kFK + at);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -1574,21 +1577,23 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restr
   }
 }
 
-template <int TM, int TN, bool RESID>
+template <int TM, int TN, int WM, bool RESID>
 static void launch_f32_mfma(const float* a, const float* w, float* c, int m, int n, int k, hipStream_t s) {
-  const int tiles_m = (m + 32 * TM - 1) / (32 * TM), tiles_n = (n + 32 * TN - 1) / (32 * TN);
-  gemm_f32_mfma_kernel<TM, TN, RESID><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(a, w, c, m, n, k, tiles_m, tiles_n);
+  constexpr int BM = 16 * TM * WM, BN = 16 * TN * (4 / WM);
+  const int tiles_m = (m + BM - 1) / BM, tiles_n = (n + BN - 1) / BN;
+  gemm_f32_mfma_kernel<TM, TN, WM, RESID><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(a, w, c, m, n, k, tiles_m, tiles_n);
 }
 
 template <bool RESID>
 static void launch_f32(const float* a, const float* w, float* c, int64_t m, int64_t n, int64_t k, hipStream_t s) {
-  // A CU's tiles share its matrix pipes, so what counts is how many outputs the busiest of 256 CUs
-  // has, padding included; on a tie the larger tile, which reads its operands less often.
-  auto outputs = [&](int64_t bm, int64_t bn) { return (((m + bm - 1) / bm) * ((n + bn - 1) / bn) + 255) / 256 * bm * bn; };
-  const int64_t large = outputs(128, 128), middle = outputs(64, 64), small = outputs(32, 64);
-  if (large <= middle && large <= small) launch_f32_mfma<4, 4, RESID>(a, w, c, (int)m, (int)n, (int)k, s);
-  else if (middle <= small) launch_f32_mfma<2, 2, RESID>(a, w, c, (int)m, (int)n, (int)k, s);
-  else launch_f32_mfma<1, 2, RESID>(a, w, c, (int)m, (int)n, (int)k, s);
+  switch (f32_tile_rows(m, n, k, RESID)) {
+    case 16: launch_f32_mfma<1, 1, 1, RESID>(a, w, c, (int)m, (int)n, (int)k, s); break;
+    case 32: launch_f32_mfma<1, 2, 2, RESID>(a, w, c, (int)m, (int)n, (int)k, s); break;
+    case 48: launch_f32_mfma<3, 1, 1, RESID>(a, w, c, (int)m, (int)n, (int)k, s); break;
+    case 64: launch_f32_mfma<2, 2, 2, RESID>(a, w, c, (int)m, (int)n, (int)k, s); break;
+    case 80: launch_f32_mfma<5, 1, 1, RESID>(a, w, c, (int)m, (int)n, (int)k, s); break;
+    default: launch_f32_mfma<4, 4, 2, RESID>(a, w, c, (int)m, (int)n, (int)k, s); break;
+  }
 }
 
 // ------------------------------------------------------------------------------------------

@@ -114,4 +114,35 @@ inline int swiglu_tile_rows(int64_t m, int64_t f, int64_t k) {
   return ring || ns[i] <= small_problem_ns(plain, m, 2 * f, k, false) + 4000 ? 32 << i : 0;
 }
 
+// Rows of the fp32 tile (64 columns; 128 rows: 128 columns).  128 rows where the busiest of 256 CUs then has no more outputs
+// than with 64 or 32, padding included; else an estimate in ns.  The tiles of a CU share its matrix pipes, and small ones hide
+// each other's latencies, so it has a part per tile of the busiest CU and one per tile on average; fitted to 250 problems of
+// 1 to 1024 rows (the 8B shape's projections, the tiny shape's, drawn ones).  us, against the tile of 32, 64 or 128 rows whose busiest CU
+// has the fewest outputs: 300 x 4096 x 4096 110 -> 100 and 300 x 4096 x 14336 373 -> 338 (80 rows), 67 x 6144 x 4096 77 -> 53, 56 x
+// 4096 x 4096 50 -> 43 and 15 x 1832 x 2600 30 -> 21 (16 rows); 150 other problems 9 to 10 % on average.
+inline double f32_tile_ns(int rows, int64_t m, int64_t n, int64_t k, bool residual) {
+  struct Cost { int rows; double launch, tile, residual, busiest_k, average_k; };
+  constexpr Cost costs[] = {{16, 4200, 0, 242, 5.06, 0.21}, {32, 3210, 265, 289, 6.38, 2.94}, {48, 2877, 554, 450, 8.63, 4.90},
+                            {64, 2286, 1107, 573, 12.74, 4.58}, {80, 1553, 2063, 412, 14.98, 7.22}};
+  const int64_t tiles = (m + rows - 1) / rows * ((n + 63) / 64);
+  const double busiest = (double)((tiles + 255) / 256), average = tiles > 256 ? tiles / 256.0 : 1.0;
+  for (const Cost& c : costs)
+    if (c.rows == rows)
+      return c.launch + busiest * (c.tile + (residual ? c.residual : 0)) + (double)k * (c.busiest_k * busiest + c.average_k * average);
+  return 0;
+}
+
+inline int f32_tile_rows(int64_t m, int64_t n, int64_t k, bool residual) {
+  auto outputs = [&](int64_t bm, int64_t bn) { return (((m + bm - 1) / bm) * ((n + bn - 1) / bn) + 255) / 256 * bm * bn; };
+  const int64_t large = outputs(128, 128);
+  if (large <= outputs(64, 64) && large <= outputs(32, 64)) return 128;
+  int best = 80;
+  double best_ns = f32_tile_ns(80, m, n, k, residual);
+  for (int rows : {64, 48, 32, 16}) {
+    const double ns = f32_tile_ns(rows, m, n, k, residual);
+    if (ns < best_ns && (m + rows - 1) / rows * ((n + 63) / 64) <= INT32_MAX) { best_ns = ns; best = rows; }
+  }
+  return best;
+}
+
 }  // namespace fp

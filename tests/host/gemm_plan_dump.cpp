@@ -2,6 +2,7 @@
 //   moe mean_rows ffn hidden      -> rows per tile of the experts' grouped launches
 //   tile m n k residual           -> tile of a problem too small for the large tiles: ring32, ring64, ring128, any128, large
 //   rows m n k bf16|swiglu|residual -> rows of the large tile for an uncut problem (swiglu: n outputs)
+//   f32 m n k residual            -> rows of the fp32 tile
 //   swiglu m f k                  -> rows per tile of its fused gate_up projection (0: two operators)
 #include <iostream>
 #include <sstream>
@@ -24,6 +25,11 @@ int main() {
       int residual;
       in >> m >> n >> k >> residual;
       std::cout << names[(int)fp::small_problem_tile(m, n, k, residual != 0)] << "\n";
+    } else if (kind == "f32") {
+      long long m, n, k;
+      int residual;
+      in >> m >> n >> k >> residual;
+      std::cout << fp::f32_tile_rows(m, n, k, residual != 0) << "\n";
     } else if (kind == "rows") {
       long long m, n, k;
       std::string epilogue;

@@ -77,3 +77,10 @@ def test_the_gpu_tests_reach_every_height_of_the_large_tile(rules):
     assert [int(r) for r in got] == [rows for rows, *_ in LARGE_TILE_SIZES]
     for _, epilogue, m, n, _ in LARGE_TILE_SIZES:             # none of them is cut over K or left to the small tiles
         assert (m + 255) // 256 * ((n + (127 if epilogue == "swiglu" else 255)) // (128 if epilogue == "swiglu" else 256)) >= 160
+
+
+def test_the_gpu_tests_reach_every_fp32_tile(rules):
+    from tests.test_gpu_ops import F32_TILE_SIZES
+    got = rules([f"f32 {m} {n} {k} {residual}" for _, m, n, k, residual in F32_TILE_SIZES])
+    assert [int(r) for r in got] == [rows for rows, *_ in F32_TILE_SIZES]
+    assert {int(r) for r in got} == {16, 32, 48, 64, 80, 128}

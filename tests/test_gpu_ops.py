@@ -650,3 +650,32 @@ def test_few_row_tiles_of_every_height(m, n, k, residual):
     # bf16 results: 2^-9 relative each; fp32: sums of up to 17408 products in fp32, 32 at a time in the matrix unit: 1e-5 at most.
     assert err.max().item() <= (1e-5 if residual else 4e-3), (err.argmax().item(), err.max().item())
     assert torch.all(c[m:] == 7.0) and torch.all(ws[ws_bytes:] == 0x5A)
+
+
+F32_TILE_SIZES = [            # rows of the tile, m (one row past the last whole tile, or one short of one), n, k, residual
+    (16, 431, 24, 520, 0), (16, 417, 8, 520, 0), (16, 31, 72, 520, 1), (16, 1, 104, 304, 1), (32, 63, 416, 40, 0), (32, 1, 2784, 40, 0),
+    (32, 31, 576, 8, 1), (48, 95, 5496, 40, 0), (48, 385, 1384, 40, 0), (48, 335, 1528, 8, 1), (48, 97, 4616, 8, 1),
+    (64, 255, 16, 8, 0), (64, 255, 2720, 8, 1), (64, 193, 3768, 8, 1), (80, 159, 5840, 8, 0), (80, 321, 2808, 8, 0),
+    (80, 300, 4096, 4096, 1), (80, 321, 2824, 8, 1), (128, 1151, 3360, 136, 0), (128, 639, 5712, 8, 1), (128, 897, 3912, 8, 1)]
+
+
+@pytest.mark.parametrize("rows,m,n,k,residual", F32_TILE_SIZES)
+def test_fp32_gemm_on_tiles_of_every_height(rows, m, n, k, residual):
+    """The fp32 MFMA kernel on 16 to 128 rows (tests/test_gemm_plan.py checks which), among them heights that are no
+    multiple of the 32 rows a round of DMA fills; rows before and behind the output stay."""
+    B = _binding()
+    print(f"fp32 tile rows={rows} m={m} n={n} k={k} residual={residual}", flush=True)
+    a = I.normal_tensor((m, k), 1.0, 97, torch.float32, "cuda")
+    w = I.normal_tensor((n, k), 0.05, 98, torch.float32, "cuda")
+    c = torch.full((m + 256, n), 7.0, device="cuda")
+    ref = a.double() @ w.double().T
+    if residual:
+        c[128:m + 128] = I.normal_tensor((m, n), 1.0, 99, torch.float32, "cuda")
+        ref += c[128:m + 128].double()
+    torch.cuda.synchronize()
+    B.fp_op_gemm(0, a.data_ptr(), w.data_ptr(), c[128:].data_ptr(), m, n, k, bool(residual))
+    torch.cuda.synchronize()
+    err = (c[128:m + 128].double() - ref).norm(dim=1) / ref.norm(dim=1)
+    # Sums of k products, four at a time: a random walk of k / 4 roundings of 2^-24, 2e-6 at k = 4096 (a row of few columns: twice that).
+    assert err.max().item() <= 4e-6, (err.argmax().item(), err.max().item())
+    assert torch.all(c[:128] == 7.0) and torch.all(c[m + 128:] == 7.0)
