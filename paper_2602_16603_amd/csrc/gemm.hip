@@ -21,13 +21,17 @@ namespace fp {
 constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
 
+// EVEN: panels of equally many tile rows, at most kGroupM (the large kernel, whose L2 warm-up wants sharers in every panel; to
+// the others it makes no difference or costs: 4261 x 992 x 4888 on 128-row tiles 85 -> 92 us, 4859 x 1992 x 5832 with its K
+// tail 142 -> 150).  Returns the panel's rows.
+template <bool EVEN = false>
 __device__ __forceinline__ int tile_of_workgroup(int wg, int tiles_m, int tiles_n, int& tm, int& tn) {
   const int total = tiles_m * tiles_n;
   const int xcd = wg % kXcds;
   const int local = wg / kXcds;
   const int base = total / kXcds, rem = total % kXcds;
   const int logical = xcd * base + min(xcd, rem) + local;
-  const int groups = (tiles_m + kGroupM - 1) / kGroupM, rows = (tiles_m + groups - 1) / groups;
+  const int groups = (tiles_m + kGroupM - 1) / kGroupM, rows = EVEN ? (tiles_m + groups - 1) / groups : kGroupM;
   const int per_group = rows * tiles_n;
   const int group = logical / per_group;
   const int in_group = logical - group * per_group;
@@ -410,7 +414,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     rot = (expert * tiles_n + tile_n) % (K / kBK);
     shared = (ti > 0 && groups[1 + 3 * (ti - 1)] == expert) || (ti + 1 < n_row_tiles && groups[1 + 3 * (ti + 1)] == expert);
   } else {
-    w_sharers = tile_of_workgroup(blockIdx.x - split * n_tiles, tiles_m, tiles_n, tile_m, tile_n);
+    w_sharers = tile_of_workgroup<!KTAIL>(blockIdx.x - split * n_tiles, tiles_m, tiles_n, tile_m, tile_n);
     share_m = tile_m;
   }
   const int m0 = tile_m * BM, n0 = tile_n * BN;
