@@ -266,7 +266,7 @@ __device__ __forceinline__ void w4_dma(__amdgpu_buffer_rsrc_t r, bf16* lds_rows,
 // No accumulator is touched twice within MI NJ MFMAs, and LDS results reach the operands through
 // the s_waitcnt the compiler places for the asm inputs, so no software-managed hazard arises.
 enum { kReadsNone, kReadsSpread, kReadsEarly };
-template <int READS, bool DMA, int MI, int NJ, bool NT = false>
+template <int READS, bool DMA, int MI, int NJ>
 __device__ __forceinline__ void w4_block(f32x4_acc (&acc)[MI][NJ], const W4Frags<MI, NJ>& cur, W4Frags<MI, NJ>& nxt,
                                          const bf16* rA, const bf16* rB, int pch,
                                          __amdgpu_buffer_rsrc_t rs_a, __amdgpu_buffer_rsrc_t rs_w, bf16* dA,
@@ -290,7 +290,7 @@ __device__ __forceinline__ void w4_block(f32x4_acc (&acc)[MI][NJ], const W4Frags
           const int d = kSpread * s + i;
           if (j != NJ / 2 + i * (NJ / 2) / kSpread || d >= MI + NJ) continue;
           if (d < MI) w4_dma(rs_a, dA + d * 8 * kBK, voff_a[d], kbyte);
-          else w4_dma<NT>(rs_w, dB + (d - MI) * 8 * kBK, voff[d - MI], kbyte);
+          else w4_dma(rs_w, dB + (d - MI) * 8 * kBK, voff[d - MI], kbyte);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -350,15 +350,7 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // main loop as one more k-tile, not pipelined, whose missing 16-byte chunks are fetched from outside the
 // descriptors (K < 64: there is nothing else; the prologue's k-tile 0 is overwritten unread).  K rows then start at odd multiples of 16 bytes, which the DMA does not mind.  8192 x 8192 x 2056:
 // 408 us on register-staged 128x128 tiles, 265 here (1.04 PFLOP/s; rows that straddle lines cost the rest).
-//
-// STREAM (one row tile, not cut): every line of W is read by one workgroup, once.  In step, the workgroups
-// would ask for the same 128 bytes of every row, which fall on a few of the HBM's channels where a row is a multiple of their
-// period; so each column tile starts at another k-tile (and adds up in that order), and the lines are fetched
-// non-temporally, so that they leave A in the L2.  Either alone gives little.  The 8B shape's gate_up, cold, 256 rows
-// 68.5 -> 60.3 us (63.3 without the hint); the 32B shape's, whose columns fill the chip with wide tiles, 160 rows 160 -> 140, 256 rows
-// 174 -> 156 (without the L2 warm-up: nobody shares these lines).  The sums then have another order than the other
-// tiles'.  (Two row tiles and more: the rotation alone is within 3 % either way, the hint 3 to 20 % slower.)
-template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false, bool STREAM = false, int ROWS = 256>
+template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false, int ROWS = 256>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restrict__ A,
                                                            const bf16* __restrict__ W,
                                                            void* __restrict__ Cout, int M, int N,
@@ -383,7 +375,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave & 1, wn = wave >> 1;           // 2 x 2 waves, wave tile 128 x WR/2 (SwiGLU: 128 x WR/4 outputs)
+  const int wm = wave & 1, wn = wave >> 1;           // 2 x 2 waves, wave tile 16 MI x WR/2 (SwiGLU: 16 MI x WR/4 outputs)
   int tile_m, tile_n, share_m, rot = 0, w_sharers = 2;
   bool shared = true;                                // somebody else reads these rows of W
   int a_total_rows = 0;
@@ -424,9 +416,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const int kt_first = split * kt_per_split;
   const int kt_count = min(kt_per_split, K / kBK - kt_first);
   const int kbyte0 = kt_first * kBK * 2;
-  if (STREAM) rot = tile_n % kt_count;
   auto kbyte = [&](int u) __attribute__((always_inline)) {   // of k-tile u of this workgroup
-    return kbyte0 + (!(STREAM || GROUPED) ? u : u + rot >= kt_count ? u + rot - kt_count : u + rot) * kBK * 2;
+    return kbyte0 + (!GROUPED ? u : u + rot >= kt_count ? u + rot - kt_count : u + rot) * kBK * 2;
   };
 
   // DMA sources.  Wave w fetches LDS rows [8 MI w, 8 MI w + 8 MI) of A and [Q w, Q w + Q) of W, 8 rows per instruction;
@@ -491,7 +482,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   // for every other row of it, and nobody where the expert has one tile; gathered rows of A have an address each, and
   // their shares do not rotate (8192 tokens of the 30B-A3B shape: experts_up 409 -> 396 us, experts_down 335 -> 329).
   const int w_shares = w_sharers >= 8 ? 8 : w_sharers >= 4 ? 4 : 2;
-  const __amdgpu_buffer_rsrc_t rsrc_warm = STREAM || (GROUPED && !shared) ? rsrc_none
+  const __amdgpu_buffer_rsrc_t rsrc_warm = GROUPED && !shared ? rsrc_none
                                            : wave == 0 ? (gathered ? rsrc_a : rsrc_warm_a)
                                            : wave == 1 || (w_shares == 2 && wave == 2) ? rsrc_warm_w : rsrc_none;
   const int warm_mask = wave == 0 ? 3 : w_shares - 1;
@@ -532,13 +523,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 #pragma unroll
     for (int s = 0; s < MI; ++s) w4_dma(rsrc_a, dA0 + s * 8 * kBK, voff_a[s], kbyte(0));
 #pragma unroll
-    for (int s = 0; s < NJ; ++s) w4_dma<STREAM>(rsrc_w, dB0 + s * 8 * kBK, voff[s], kbyte(0));
+    for (int s = 0; s < NJ; ++s) w4_dma(rsrc_w, dB0 + s * 8 * kBK, voff[s], kbyte(0));
     {
       const __amdgpu_buffer_rsrc_t ra1 = kt_count > 1 ? rsrc_a : rsrc_none, rw1 = kt_count > 1 ? rsrc_w : rsrc_none;
 #pragma unroll
       for (int s = 0; s < MI; ++s) w4_dma(ra1, dA1 + s * 8 * kBK, voff_a[s], kbyte(1));
 #pragma unroll
-      for (int s = 0; s < NJ; ++s) w4_dma<STREAM>(rw1, dB1 + s * 8 * kBK, voff[s], kbyte(1));
+      for (int s = 0; s < NJ; ++s) w4_dma(rw1, dB1 + s * 8 * kBK, voff[s], kbyte(1));
     }
     W4_WARM(kWarmAhead - 1);
     __builtin_amdgcn_sched_barrier(0);
@@ -575,7 +566,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                                                                   \
     __builtin_amdgcn_s_waitcnt(kWaitVm1);                                                                     \
     w4_barrier();                                                                                             \
-    w4_block<kReadsSpread, true, MI, NJ, STREAM>(acc, f1, f0, rA##o, rB##o, pch0, t2_ < kt_count ? rsrc_a : rsrc_none,                   \
+    w4_block<kReadsSpread, true, MI, NJ>(acc, f1, f0, rA##o, rB##o, pch0, t2_ < kt_count ? rsrc_a : rsrc_none,                   \
                       t2_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t2_)); \
     W4_WARM((t) + kWarmAhead);                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
@@ -627,7 +618,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   {                                                                                                           \
     const __amdgpu_buffer_rsrc_t ra_ = (u) < kt_count ? rsrc_a : rsrc_none, rw_ = (u) < kt_count ? rsrc_w : rsrc_none; \
     _Pragma("unroll") for (int s = 0; s < MI; ++s) w4_dma(ra_, dA##c + s * 8 * kBK, voff_a[s], kbyte(u)); \
-    _Pragma("unroll") for (int s = 0; s < NJ; ++s) w4_dma<STREAM>(rw_, dB##c + s * 8 * kBK, voff[s], kbyte(u)); \
+    _Pragma("unroll") for (int s = 0; s < NJ; ++s) w4_dma(rw_, dB##c + s * 8 * kBK, voff[s], kbyte(u)); \
   }
     W4_FETCH(0, 0);
     W4_FETCH(1, 1);
@@ -661,7 +652,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                                                                   \
     __builtin_amdgcn_s_waitcnt(wait_vm<MI + NJ>());                                                           \
     w4_barrier();                                                                                             \
-    w4_block<kReadsSpread, true, MI, NJ, STREAM>(acc, f1, f0, rA##o, rB##o, pch0, t3_ < kt_count ? rsrc_a : rsrc_none,           \
+    w4_block<kReadsSpread, true, MI, NJ>(acc, f1, f0, rA##o, rB##o, pch0, t3_ < kt_count ? rsrc_a : rsrc_none,           \
                       t3_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t3_));             \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
   }
@@ -842,16 +833,17 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // stream is all there is to it; it also takes most of what has too few 256-row tiles to occupy the chip,
 // and of odd K (gemm_plan.h).
 // 256 threads = 4 waves side by side along N; every wave multiplies all rows by its 16 NJ columns with
-// v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits).  K is consumed KT at a
+// v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits, unless grouped).  K is consumed KT at a
 // time through a ring of S LDS stages, separate arrays filled by DMA S - 1 k-tiles ahead; the loop body has no
 // branch and always runs a multiple of S k-tiles (behind the last one there is nothing to fetch and
 // zeros to multiply), since with a branch between stages the compiler waits for all DMA before a read.
 // LDS rows hold KT bf16, 16-byte chunk c of row r at c ^ ((r >> 1) & 7) (KT = 64) or c ^ (r & 15)
 // (KT = 128): a half-wave's 16 rows x 2 chunks put two lanes on every bank group.
-// STREAM (grouped, or one row tile and not cut): workgroups start at different k and read W non-temporally, as above.  Cold, us:
-// gate_up of the 8B shape, 50 rows 52 -> 39 (6.0 TB/s; 44.7 without the hint, 52 with the hint alone), 128 rows 58 -> 56; the
-// hint in the experts' projections of the 30B-A3B shape, 16 tokens 87 -> 80 and 55 -> 49, 590 tokens 164 -> 147 and 97 -> 92 (with
-// the combine).  K ranges start at different k as it is, and gain nothing.
+// Grouped: workgroups start at different k and read W non-temporally, so that the stream leaves the activations in the L2: the
+// experts' projections of the 30B-A3B shape, cold, us: 16 tokens 87 -> 80 and 55 -> 49, 590 tokens 164 -> 147 and 97 -> 92 (with the
+// combine).  K ranges start at different k as it is, and gain nothing.  The dense gate_up projection would gain from both (50
+// rows 52 -> 39 us), but starting at another k rounds its sums differently, and its bits are promised to be fp_op_gemm's; the hint
+// alone gives nothing.
 // ------------------------------------------------------------------------------------------
 template <int KT> __device__ __forceinline__ int ring_chunk(int chunk, int row) {
   return KT == 128 ? chunk ^ (row & 15) : chunk ^ ((row >> 1) & 7);
@@ -862,7 +854,7 @@ __device__ __forceinline__ void ring_dma(const bf16* base, uint32_t bytes, bf16*
   w4_dma<NT>(panel_rsrc(base, bytes), lds, voff, kbyte);
 }
 
-template <int MI, int NJ, int KT, int S, int EPI, bool GROUPED, bool STREAM = GROUPED>
+template <int MI, int NJ, int KT, int S, int EPI, bool GROUPED>
 __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
                                                                  void* __restrict__ Cout, int M, int N, int K,
                                                                  int tiles_m, int tiles_n, int kt_per_split,
@@ -912,7 +904,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
     A += (int64_t)m0 * K;
     Cout = reinterpret_cast<char*>(Cout) + ((int64_t)m0 * N + slab) * (EPI == kEpiBf16 || SWIGLU ? 2 : 4);
     M = min(BM, M - m0);
-    if (STREAM) rot = tile_n % ((K + KT - 1) / KT);
   }
   const int n0 = tile_n * BN;
   const int k_first = split * kt_per_split * kBK;    // (K ranges are counted in k-tiles of 64)
@@ -947,7 +938,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
   const int kt_count = (k_count + KT - 1) / KT;
   auto fetch = [&](int t, bf16* s) __attribute__((always_inline)) {
     int left = k_count - t * KT;                     // behind the last k-tile every chunk is out of range
-    if (STREAM && left > 0) {
+    if (GROUPED && left > 0) {
       t = t + rot >= kt_count ? t + rot - kt_count : t + rot;
       left = k_count - t * KT;
     }
@@ -956,7 +947,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
       ring_dma(panel_a, bytes_a, s + RPI * (IA * wave + i) * KT, k_a[i] < left ? off_a[i] : kOffOutOfRange, t * KT * 2);
 #pragma unroll
     for (int i = 0; i < IW; ++i)
-      ring_dma<STREAM>(panel_w, bytes_w, s + (BM + RPI * (IW * wave + i)) * KT, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * KT * 2);
+      ring_dma<GROUPED>(panel_w, bytes_w, s + (BM + RPI * (IW * wave + i)) * KT, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * KT * 2);
   };
 
   f32x4 acc[MI][NJ];
@@ -1202,9 +1193,9 @@ static W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
 }
 
 // Few rows: up to kFewRows of them, and up to twice as many where the large kernel's 128-column tile on 96 or 128 rows is not
-// ahead: projections of a long K (32B shape's down, 128 rows 77 us, 80 there) and the fused gate_up projection whose columns
-// fill the chip with wide tiles (32B shape 135 us, 140).  The others are faster there: 8B shape, 70 / 128 rows, cold, us, gate_up
-// 58 / 57 -> 47 / 52, qkv 24 / 27.5 -> 20.5 / 24.5, o 21.5 / 24 -> 20.5 / 23, down 35 / 41 -> 34 / 40.  Columns per tile, k-tiles and stages by
+// ahead: projections of a long K and the fused gate_up projection whose columns fill the chip with wide tiles (32B shape, 70 /
+// 128 rows 120 / 129 us, 140 / 149 there).  The others are faster there: 8B shape, 70 / 128 rows, cold, us, gate_up 54 / 55.5 ->
+// 51 / 54, qkv 19 / 22.5 -> 16 / 19.5, o 15.5 / 18.5 -> 14.5 / 17.5, down 29 / 34 -> 28.5 / 33.5.  Columns per tile, k-tiles and stages by
 // row count and epilogue, as measured on cold weights of the 8B shape (us, against the two-stage 256-row tile): up to
 // 64 rows 64-column tiles of 128 k (256 bytes of a weight row at a time: HBM gives 4.9 TB/s to such pieces where 128-byte
 // pieces get 4.2) -- 50 rows: qkv 22 -> 17, o 17 -> 12.6, down 40 -> 28; from 65 rows on the A tile weighs more and 128-column
@@ -1236,14 +1227,6 @@ static int launch_ring(const bf16* a, const bf16* w, void* c, int m, int n, int 
   gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, EPI, false><<<dim3((unsigned)(tiles_m * tiles_n * r.used)), 256, 0, s>>>(
       a, w, c, m, n, k, tiles_m, tiles_n, r.per, nullptr, nullptr);
   return r.used;
-}
-// The uncut SwiGLU projection with STREAM.
-template <int MI>
-static void launch_ring_stream(const bf16* a, const bf16* w, void* c, int m, int f, int k, hipStream_t s) {
-  using T = RingTile<MI, true>;
-  const int tiles_n = (f + T::BN - 1) / T::BN;
-  gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, kEpiSwiGLU, false, true><<<dim3((unsigned)tiles_n), 256, 0, s>>>(
-      a, w, c, m, f, k, 1, tiles_n, k_ranges(k, 1).per, nullptr, nullptr);
 }
 // Returns the number of K ranges launched (at most `splits`).
 template <int EPI>
@@ -1281,7 +1264,7 @@ void launch_router_gemm(const void* a, const void* w, float* logits, int64_t m, 
 template <int EPI, int ROWS>
 static void launch_large_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int tiles_n, hipStream_t s) {
   const int tiles_m = (m + ROWS - 1) / ROWS;
-  gemm_bf16_w4_kernel<EPI, false, 8, false, false, ROWS><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(
+  gemm_bf16_w4_kernel<EPI, false, 8, false, ROWS><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(
       a, w, c, m, n, k, tiles_m, tiles_n, k / kBK, nullptr, nullptr);
 }
 template <int EPI>
@@ -1301,17 +1284,17 @@ static void launch_large(const bf16* a, const bf16* w, void* c, int m, int n, in
 // The launch is bound by its lines (W from HBM, A from the L2 for every column tile), so a row tile that is not padded to 256
 // fetches less: 8B shape, cold, us: 140 tokens gate_up 57 -> 53.5, 270 tokens qkv 30 -> 27.3, down 56 -> 52, 560 tokens qkv 46 -> 41.5,
 // down 84 -> 77; 300 tokens of the 32B shape down 142 -> 115.
-template <int EPI, int NJ, bool STREAM = false>
+template <int EPI, int NJ>
 static void launch_even_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int kt_per_split, int splits, hipStream_t s) {
   constexpr int BN = EPI == kEpiSwiGLU ? 16 * NJ : 32 * NJ;
   const int tiles_m = (m + 255) / 256, tiles_n = (n + BN - 1) / BN;
   auto launch = [&](auto rows) {
     constexpr int ROWS = decltype(rows)::value;
-    gemm_bf16_w4_kernel<EPI, false, NJ, false, STREAM, ROWS><<<dim3((unsigned)(tiles_m * tiles_n * splits)), 256, 0, s>>>(
+    gemm_bf16_w4_kernel<EPI, false, NJ, false, ROWS><<<dim3((unsigned)(tiles_m * tiles_n * splits)), 256, 0, s>>>(
         a, w, c, m, n, k, tiles_m, tiles_n, kt_per_split, nullptr, nullptr);
   };
   const int rows = (m + tiles_m - 1) / tiles_m;
-  constexpr bool kAnyNumber = NJ == 4 || STREAM;     // (else three row tiles or more)
+  constexpr bool kAnyNumber = NJ == 4;     // (else three row tiles or more)
   if (kAnyNumber && rows <= 96) launch(std::integral_constant<int, kAnyNumber ? 96 : 256>{});
   else if (kAnyNumber && rows <= 128) launch(std::integral_constant<int, kAnyNumber ? 128 : 256>{});
   else if (kAnyNumber && rows <= 160) launch(std::integral_constant<int, kAnyNumber ? 160 : 256>{});
@@ -1335,30 +1318,18 @@ bool gemm_swiglu_fusable(int dtype, int64_t m, int64_t f, int64_t k) {
 }
 
 void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f,
-                        int64_t k, bool any_order, hipStream_t s) {
+                        int64_t k, hipStream_t s) {
   if (!aligned_to(4, a, w_gate_up, out)) {
     launch_bf16_any<false, true>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, s);
     return;
   }
   const int nj = swiglu_nj(m, f);
   const bool few = m <= kFewRows || (m <= 2 * kFewRows && nj == 8);
-  if (few && any_order && aligned_to(16, a, w_gate_up, out)) {
-    const bf16 *pa = (const bf16*)a, *pw = (const bf16*)w_gate_up;
-    if (m <= 32) launch_ring_stream<2>(pa, pw, out, (int)m, (int)f, (int)k, s);
-    else if (m <= 64) launch_ring_stream<4>(pa, pw, out, (int)m, (int)f, (int)k, s);
-    else launch_ring_stream<8>(pa, pw, out, (int)m, (int)f, (int)k, s);
-    return;
-  }
   if (few && aligned_to(16, a, w_gate_up, out)) {
     launch_few_rows<kEpiSwiGLU>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, 1, s);
     return;
   }
-  if (any_order && m <= 256) {
-    if (nj == 8)
-      launch_even_rows<kEpiSwiGLU, 8, true>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, (int)(k / kBK), 1, s);
-    else
-      launch_even_rows<kEpiSwiGLU, 4, true>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, (int)(k / kBK), 1, s);
-  } else if (nj == 8)
+  if (nj == 8)
     launch_large<kEpiSwiGLU>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, s);
   else
     launch_even_rows<kEpiSwiGLU, 4>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, (int)(k / kBK), 1, s);
@@ -1754,7 +1725,7 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
   if (plan.splits > 1) plan = w4_cut(m, n, k, residual, plan);
   const int splits = plan.splits;
   if (splits == 1 && tl.kind == kTailSwiGLU) {       // not cut after all: the fused epilogue gives the same bits
-    launch_gemm_swiglu(a, w, tl.out, m, n / 2, k, false, s);
+    launch_gemm_swiglu(a, w, tl.out, m, n / 2, k, s);
     return;
   }
   if (splits >= 1 && plan.nj == 8) {

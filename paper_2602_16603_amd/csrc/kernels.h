@@ -93,11 +93,10 @@ void launch_router_gemm(const void* a, const void* w, float* logits, int64_t m, 
 // Fused gate_up projection + SiLU(gate)*up (bf16): out[m][f] from a[m][k] and w_gate_up[2f][k]
 // (gate rows first), bit-identical to launch_gemm into [m][2f] followed by launch_silu_mul.
 // Only for problems gemm_swiglu_fusable accepts (K % 64 == 0, f % 8 == 0, enough tiles to fill the
-// chip without splitting K).  any_order: the sums over k of a short request may start at any k-tile (another rounding than
-// launch_gemm's, for the caller that does not compare the two).
+// chip without splitting K).
 bool gemm_swiglu_fusable(int dtype, int64_t m, int64_t f, int64_t k);
 void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f,
-                        int64_t k, bool any_order, hipStream_t s);
+                        int64_t k, hipStream_t s);
 // The same for problems that launch_gemm, given this workspace, runs on small tiles (K % 8 == 0, 16-byte aligned
 // operands), where gemm_plan.h finds it faster; the bits of the two operators on the ring kernel.
 bool gemm_swiglu_small(int dtype, int64_t m, int64_t f, int64_t k, size_t workspace_bytes);

@@ -205,7 +205,7 @@ fp_status launch_op(fp_prefill* t, int32_t index) {
       if (t->swiglu_small) {
         fp::launch_gemm_swiglu_small(t->h, w.w_gate_up, t->act, T, F, d, s);
       } else if (t->swiglu_epilogue) {
-        fp::launch_gemm_swiglu(t->h, w.w_gate_up, t->act, T, F, d, true, s);
+        fp::launch_gemm_swiglu(t->h, w.w_gate_up, t->act, T, F, d, s);
       } else {
         fp::GemmTail tail;
         if (t->swiglu_fused) tail = fp::GemmTail{fp::kTailSwiGLU, nullptr, t->act, 0.f};
@@ -987,7 +987,7 @@ fp_status fp_op_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int
   if (!fp::gemm_swiglu_fusable(FP_DTYPE_BF16, m, f, k))
     return fail(FP_ERR_INVALID, "fp_op_gemm_swiglu: shape not handled by the fused kernel "
                                 "(needs K %% 64 == 0, F %% 8 == 0 and at least 96 output tiles)");
-  fp::launch_gemm_swiglu(a, w_gate_up, out, m, f, k, false, reinterpret_cast<hipStream_t>(hip_stream));
+  fp::launch_gemm_swiglu(a, w_gate_up, out, m, f, k, reinterpret_cast<hipStream_t>(hip_stream));
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? FP_OK : fail(FP_ERR_DEVICE, "gemm_swiglu launch: %s", hipGetErrorString(e));
 }

@@ -414,21 +414,63 @@ def test_model_on_a_stream_of_its_own(name):
     own.close()
 
 
-@pytest.mark.parametrize("ffn,hidden,n", [(6152, hidden, n) for hidden in (64, 192, 1088)
-                                          for n in (1, 32, 33, 64, 65, 128, 129, 161, 193, 256)] +
-                                         [(20488, hidden, n) for hidden in (64, 576) for n in (65, 129, 161, 193, 256)])
-def test_gate_up_of_one_row_tile_starts_its_column_tiles_at_different_k(ffn, hidden, n):
-    """The fused gate_up projection of up to 256 tokens (three row tiles of the few-rows kernel, then the 128-column tile and,
-    where its columns fill the chip, the 256-column one on every height; one k-tile, fewer than the stages hold, a number
+GATE_UP_OF_ONE_ROW_TILE = ([(6152, hidden, n) for hidden in (64, 192, 1088) for n in (1, 32, 33, 64, 65, 128, 129, 161, 193, 256)] +
+                           [(20488, hidden, n) for hidden in (64, 576) for n in (65, 129, 161, 193, 256)])
+
+
+@pytest.mark.parametrize("ffn,hidden,n", GATE_UP_OF_ONE_ROW_TILE)
+def test_gate_up_of_one_row_tile(ffn, hidden, n):
+    """The fused gate_up projection of up to 256 tokens (row tiles of the few-rows kernel, then the 128-column tile and,
+    where its columns fill the chip, the 256-column one; one k-tile, fewer than the stages hold, a number
     that is no multiple of them; a last column tile of eight outputs)."""
     spec = I.ShapeSpec(1, hidden, 2, 1, 64, ffn, 1e-5, 10000.0)
     model, weights = build(spec, 31, "bf16", total_tokens=n, random_gains=True)
     x = I.make_hidden(n, hidden, 31, torch.bfloat16, "cpu")
-    print(f"gate_up streamed n={n} hidden={hidden} ffn={ffn}", flush=True)
+    print(f"gate_up of one row tile n={n} hidden={hidden} ffn={ffn}", flush=True)
     task = model.begin(x.cuda(), [n])
     task.run_to_completion()
     x_ref, _ = O.prefill(oracle_shape(spec), oracle_layers(weights), x, [0, n])
-    # Six intermediates rounded to bf16 (2^-9 each): 1e-2 at most; a k-tile left out or taken twice is off by its share of K.
+    # Six intermediates rounded to bf16 (2^-9 each): 1e-2 at most.  (Of the residual: the projection alone is checked below.)
     assert fro_rel_err(task.hidden(), x_ref) <= 1e-2
+    task.end()
+    model.close()
+
+
+@pytest.mark.parametrize("ffn,hidden,n", GATE_UP_OF_ONE_ROW_TILE)
+def test_gate_up_of_a_short_request_has_the_operators_bits(ffn, hidden, n):
+    """The prefill path launches the kernels of the single-operator entry points: with nothing coming from attention, the
+    residual is that of rmsnorm, gemm_swiglu and gemm called one by one, bit for bit; gemm_swiglu has the bits of gemm and
+    silu_mul, and every value of it is as near its definition as its three bf16 roundings are."""
+    from paper_2602_16603_amd import binding as B
+    spec = I.ShapeSpec(1, hidden, 2, 1, 64, ffn, 1e-5, 10000.0)
+    weights = I.make_weights(spec, 32, torch.bfloat16, "cuda")
+    I.randomize_gains(weights, 32)
+    w = weights[0]
+    w["w_o"].zero_()
+    rows = I.make_hidden(n, hidden, 32, torch.bfloat16, "cuda")
+    model = _runner().PrefillModel(spec, weights, 1, 64, 256)
+    print(f"gate_up against its operators n={n} hidden={hidden} ffn={ffn}", flush=True)
+    task = model.begin(rows, [n])
+    task.run_to_completion()
+    got = task.hidden()
+    x = rows.float()
+    h, gu, two, act = (torch.empty(n, width, dtype=torch.bfloat16, device="cuda") for width in (hidden, 2 * ffn, ffn, ffn))
+    ws_bytes = B.fp_op_gemm_workspace_bytes(1, n, hidden, ffn)
+    ws = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    B.fp_op_rmsnorm(1, x.data_ptr(), w["mlp_norm"].data_ptr(), h.data_ptr(), n, hidden, spec.rms_eps)
+    B.fp_op_gemm(1, h.data_ptr(), w["w_gate_up"].data_ptr(), gu.data_ptr(), n, 2 * ffn, hidden, False)
+    B.fp_op_silu_mul(1, gu.data_ptr(), two.data_ptr(), n, ffn)
+    B.fp_op_gemm_swiglu(h.data_ptr(), w["w_gate_up"].data_ptr(), act.data_ptr(), n, ffn, hidden)
+    B.fp_op_gemm_ws(1, act.data_ptr(), w["w_down"].data_ptr(), x.data_ptr(), n, hidden, ffn, True, ws.data_ptr(), ws_bytes)
+    torch.cuda.synchronize()
+    assert torch.equal(act, two)
+    gate, up = (h.double() @ w["w_gate_up"].double().T).split(ffn, dim=1)
+    ref = torch.nn.functional.silu(gate) * up
+    # gate, up and their product each rounded to bf16, whose eight significant bits are off by up to 2^-8 of the value
+    # (silu's slope is at most 1.1; 2 % for the terms of second order); sums of up to 1088 products of about 0.02 in fp32: 1e-5 at most.
+    bound = 2.0 ** -8 * 1.02 * (1.1 * (gate * up).abs() + 2 * ref.abs()) + 1e-5 * (1 + gate.abs() + up.abs())
+    assert torch.all((act.double() - ref).abs() <= bound), ((act.double() - ref).abs() / bound).max().item()
+    assert torch.equal(got, x)
     task.end()
     model.close()
