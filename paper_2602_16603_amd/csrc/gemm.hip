@@ -475,18 +475,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const int warm_rows_w = __builtin_amdgcn_readfirstlane(SWIGLU ? N + min(BN, N - n0) : min(BN, N - n0));
   const __amdgpu_buffer_rsrc_t rsrc_warm_a = panel_rsrc(A + (int64_t)m0 * K, (uint32_t)(warm_rows_a * K * 2));
   const __amdgpu_buffer_rsrc_t rsrc_warm_w = panel_rsrc(W + (int64_t)n0 * K, (uint32_t)(warm_rows_w * K * 2));
-  // There are as many shares of W as workgroups to ask for them: eight row tiles walk a column panel together where there are
-  // as many, and with eight shares among two to seven the rest of the lines was never asked for (all five heights of the tile,
-  // 2-7 row tiles: 4 to 15 % faster with four or two shares; more row tiles: 0 to 5 %).
+  // As many shares of W as workgroups to ask for them (warm_shares).
   // Grouped launches: a W panel is shared by the two or three row tiles of its expert only, so there waves 1 and 2 ask
   // for every other row of it, and nobody where the expert has one tile; gathered rows of A have an address each, and
   // their shares do not rotate (8192 tokens of the 30B-A3B shape: experts_up 409 -> 396 us, experts_down 335 -> 329).
-  const int w_shares = w_sharers >= 8 ? 8 : w_sharers >= 4 ? 4 : 2;
+  const int w_shares = warm_shares(w_sharers);
   const __amdgpu_buffer_rsrc_t rsrc_warm = GROUPED && !shared ? rsrc_none
                                            : wave == 0 ? (gathered ? rsrc_a : rsrc_warm_a)
-                                           : wave == 1 || (w_shares == 2 && wave == 2) ? rsrc_warm_w : rsrc_none;
-  const int warm_mask = wave == 0 ? 3 : w_shares - 1;
-  const int warm_id = wave == 0 ? (tile_n & 3) : (share_m & (w_shares - 1));
+                                           : w_shares > 0 && (wave == 1 || (w_shares == 2 && wave == 2)) ? rsrc_warm_w : rsrc_none;
+  const int warm_mask = wave == 0 ? 3 : max(w_shares, 1) - 1;
+  const int warm_id = wave == 0 ? (tile_n & 3) : (share_m & warm_mask);
   const int warm_step = gathered && wave == 0 ? 0 : K * 2;
   uint32_t voff_warm;
   {

@@ -27,6 +27,13 @@ inline int moe_tile_rows(int64_t mean_rows, int64_t ffn, int64_t hidden) {
   return mean_rows <= 18 ? 32 : mean_rows <= 48 ? 64 : mean_rows <= 96 ? 128 : 256;
 }
 
+// Shares of a W panel in the large tile's L2 warm-up, for as many row tiles as walk the panel together (at most eight): with
+// eight shares among two to seven the rest of the lines was never asked for (all five heights of the tile, 2-7 row tiles: 4 to 15 %
+// faster with four or two shares; more row tiles: 0 to 5 %).  One row tile shares its lines with nobody, and asking for them
+// ahead only crowds out the others: 256 x 27648 x 5120 SwiGLU 168 us with two shares, 158 with eight, 153 with none; 129 to 256 rows of
+// 160 column tiles and more 0 to 10 % faster than with eight, 1 % slower at most.
+constexpr int warm_shares(int row_tiles) { return row_tiles >= 8 ? 8 : row_tiles >= 4 ? 4 : row_tiles >= 2 ? 2 : 0; }
+
 // Rows of the large tile (256 columns; SwiGLU 128 outputs; K % 64 == 0, not cut).  A CU works off its tiles one after the other;
 // a launch of a few rounds loses what its last round leaves empty and the padding of its last row tile, a smaller tile
 // reads W more often.  The rule is an estimate in ns fitted to 698 problems on all five heights (257-9000 rows, the dense

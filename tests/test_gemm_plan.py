@@ -84,3 +84,9 @@ def test_the_gpu_tests_reach_every_fp32_tile(rules):
     got = rules([f"f32 {m} {n} {k} {residual}" for _, m, n, k, residual in F32_TILE_SIZES])
     assert [int(r) for r in got] == [rows for rows, *_ in F32_TILE_SIZES]
     assert {int(r) for r in got} == {16, 32, 48, 64, 80, 128}
+
+
+def test_the_l2_warm_up_asks_for_shared_lines_only(rules):
+    """Every line of a W panel is asked for by one of the row tiles that share it, and by nobody where one row tile is alone."""
+    shares = [int(n) for n in rules([f"warm {n}" for n in range(1, 9)])]
+    assert shares[0] == 0 and all(n / 2 < s <= n for n, s in enumerate(shares[1:], 2)), shares
