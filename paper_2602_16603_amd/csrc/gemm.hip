@@ -1182,7 +1182,7 @@ struct W4Shape {
 static W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
   const int64_t tiles_m = (m + 255) / 256;
   const int64_t wide = tiles_m * ((n + 255) / 256);
-  if (wide >= 160) return {8, 1};
+  if (wide >= kWideTiles) return {8, 1};
   const bool narrow = tiles_m <= 2;
   const int64_t tiles = std::max<int64_t>(1, narrow ? tiles_m * ((n + 127) / 128) : wide);
   int s = (int)std::max<int64_t>(1, std::min<int64_t>(16, 256 / tiles));
@@ -1190,16 +1190,11 @@ static W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
   return {narrow ? 4 : 8, s};
 }
 
-// Few rows: up to kFewRows of them, and up to twice as many where the large kernel's 128-column tile on 96 or 128 rows is not
-// ahead: projections of a long K and the fused gate_up projection whose columns fill the chip with wide tiles (32B shape, 70 /
-// 128 rows 120 / 129 us, 140 / 149 there).  The others are faster there: 8B shape, 70 / 128 rows, cold, us, gate_up 54 / 55.5 ->
-// 51 / 54, qkv 19 / 22.5 -> 16 / 19.5, o 15.5 / 18.5 -> 14.5 / 17.5, down 29 / 34 -> 28.5 / 33.5.  Columns per tile, k-tiles and stages by
+// Few rows (gemm_plan.h's few_rows): columns per tile, k-tiles and stages by
 // row count and epilogue, as measured on cold weights of the 8B shape (us, against the two-stage 256-row tile): up to
 // 64 rows 64-column tiles of 128 k (256 bytes of a weight row at a time: HBM gives 4.9 TB/s to such pieces where 128-byte
 // pieces get 4.2) -- 50 rows: qkv 22 -> 17, o 17 -> 12.6, down 40 -> 28; from 65 rows on the A tile weighs more and 128-column
 // tiles of 64 k read it half as often.  SwiGLU: 128 W rows of 64 k, 75 -> 52 at 50 rows.
-constexpr int kFewRows = 64;
-static bool few_rows(int64_t m, int64_t k) { return m <= kFewRows || (m <= 2 * kFewRows && k > 16384); }
 template <int MI, bool SWIGLU> struct RingTile {
   static constexpr bool kWide = SWIGLU || MI > 4;
   static constexpr int NJ = kWide ? 2 : 1, KT = kWide ? 64 : 128, S = 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
@@ -1383,7 +1378,7 @@ void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64
 template <bool RESID, int NJ>
 static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits,
                            float* workspace, const GemmTail& tail, hipStream_t s) {
-  const bool few = few_rows(m, k) && aligned_to(16, a, w, c);
+  const bool few = few_rows(m, n, k) && aligned_to(16, a, w, c);
   if (splits <= 1 && few) {
     launch_few_rows<RESID ? kEpiResidual : kEpiBf16>(a, w, c, m, n, k, 1, s);
     return;
@@ -1660,7 +1655,7 @@ int gemm_left_ranges(int dtype, int64_t m, int64_t n, int64_t k, size_t workspac
   W4Shape plan = w4_plan(dtype, m, n, k, workspace_bytes);
   if (plan.splits > 1) plan = w4_cut(m, n, k, false, plan);
   if (plan.splits <= 1) return 0;
-  if (!few_rows(m, k)) return k_ranges((int)k, plan.splits).used;
+  if (!few_rows(m, n, k)) return k_ranges((int)k, plan.splits).used;
   if (m <= 32) return ring_ranges<2, kEpiPartial>((int)n, (int)k, plan.splits).used;
   if (m <= 64) return ring_ranges<4, kEpiPartial>((int)n, (int)k, plan.splits).used;
   return ring_ranges<8, kEpiPartial>((int)n, (int)k, plan.splits).used;

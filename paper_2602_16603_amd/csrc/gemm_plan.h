@@ -34,6 +34,27 @@ inline int moe_tile_rows(int64_t mean_rows, int64_t ffn, int64_t hidden) {
 // 160 column tiles and more 0 to 10 % faster than with eight, 1 % slower at most.
 constexpr int warm_shares(int row_tiles) { return row_tiles >= 8 ? 8 : row_tiles >= 4 ? 4 : row_tiles >= 2 ? 2 : 0; }
 
+// Column tiles of 256 from which on a launch of one row tile is not cut over K and does not take the 128-column tile.
+constexpr int64_t kWideTiles = 160;
+
+// Whether a problem runs on the few-rows (ring) kernel: up to kFewRows rows, and up to twice as many where the large kernel's
+// tile on 96 or 128 rows is not ahead.  That is where the latter is slower, us, few-rows kernel / large kernel, cold weights:
+//  - kWideTiles column tiles and more, where it is 256 columns wide: 65 x 49152 x 5120 110 / 137, 65 x 128256 x 5120 244 / 288,
+//    128 x 57344 x 5120 6 % ahead.  Not so for a short K in one round of its tiles, whose prologues and stores it has fewer of
+//    (K of 256 to 1088: the large kernel 1 % behind to 75 % ahead).  558 problems of 65 to 128 rows on 41000 to 180000 columns: none
+//    slower than on the few-rows kernel alone, 1.03 times its speed; what is left on the table is K of 8192 (up to 22 %), of
+//    1536 to 2112 in one round (up to 22 %) and two whole rounds of short K (up to 40 %), beside losses close by.
+//  - fused gate_up projections of that width, which are asked about apart (32B shape, 70 / 128 rows: 120 / 129, 140 / 149).
+//  - a long K: 128 x 5120 x 24576 66 / 71; 16448 to 17664 are up to 9 % faster on the large kernel, 20480 is even.
+// The others are faster there: 8B shape, 70 / 128 rows, cold, us, gate_up 54 / 55.5 -> 51 / 54, qkv 19 / 22.5 -> 16 / 19.5, o
+// 15.5 / 18.5 -> 14.5 / 17.5, down 29 / 34 -> 28.5 / 33.5; 300 drawn projections of 65 to 128 rows 8 % on average.
+constexpr int kFewRows = 64;
+inline bool few_rows(int64_t m, int64_t n, int64_t k) {
+  if (m <= kFewRows || m > 2 * kFewRows) return m <= kFewRows;
+  const int64_t tiles = (n + 255) / 256;
+  return tiles >= kWideTiles ? tiles > 256 || k > 1152 : k > 16384;
+}
+
 // Rows of the large tile (256 columns; SwiGLU 128 outputs; K % 64 == 0, not cut).  A CU works off its tiles one after the other;
 // a launch of a few rounds loses what its last round leaves empty and the padding of its last row tile, a smaller tile
 // reads W more often.  The rule is an estimate in ns fitted to 698 problems on all five heights (257-9000 rows, the dense

@@ -3,6 +3,7 @@
 //   tile m n k residual           -> tile of a problem too small for the large tiles: ring32, ring64, ring128, any128, large
 //   rows m n k bf16|swiglu|residual -> rows of the large tile for an uncut problem (swiglu: n outputs)
 //   f32 m n k residual            -> rows of the fp32 tile
+//   few m n k                     -> 1 if the problem runs on the few-rows kernel
 //   warm row_tiles                -> shares of a W panel in the large tile's L2 warm-up
 //   swiglu m f k                  -> rows per tile of its fused gate_up projection (0: two operators)
 #include <iostream>
@@ -31,6 +32,10 @@ int main() {
       int residual;
       in >> m >> n >> k >> residual;
       std::cout << fp::f32_tile_rows(m, n, k, residual != 0) << "\n";
+    } else if (kind == "few") {
+      long long m, n, k;
+      in >> m >> n >> k;
+      std::cout << fp::few_rows(m, n, k) << "\n";
     } else if (kind == "warm") {
       int row_tiles;
       in >> row_tiles;

@@ -90,3 +90,11 @@ def test_the_l2_warm_up_asks_for_shared_lines_only(rules):
     """Every line of a W panel is asked for by one of the row tiles that share it, and by nobody where one row tile is alone."""
     shares = [int(n) for n in rules([f"warm {n}" for n in range(1, 9)])]
     assert shares[0] == 0 and all(n / 2 < s <= n for n, s in enumerate(shares[1:], 2)), shares
+
+
+def test_wide_projections_of_65_to_128_rows_stay_on_the_few_rows_kernel(rules):
+    """Measured, us, few-rows kernel / large kernel: 110 / 137, 244 / 288, 107 / 131, 124 / 130, 128 / 135 -- and, a short K
+    in one round of large tiles, the other way round."""
+    wide = [(65, 49152, 5120), (65, 128256, 5120), (65, 41000, 5120), (65, 65536, 4096), (65, 128256, 2048)]
+    assert rules([f"few {m} {n} {k}" for m, n, k in wide]) == ["1"] * 5
+    assert rules(["few 128 41000 512", "few 128 65536 1024", "few 65 40704 5120", "few 129 49152 5120", "few 64 8 8"]) == ["0", "0", "0", "0", "1"]

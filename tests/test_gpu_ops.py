@@ -652,6 +652,34 @@ def test_few_row_tiles_of_every_height(m, n, k, residual):
     assert torch.all(c[m:] == 7.0) and torch.all(ws[ws_bytes:] == 0x5A)
 
 
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("m,n,k", [(65, 40968, 1152), (128, 40968, 1216), (65, 65800, 64), (97, 65800, 192), (128, 65536, 128)])
+def test_wide_projections_of_65_to_128_rows(m, n, k, residual):
+    """Columns that fill the chip with wide tiles: the large kernel (one round of tiles, K up to 1152), else the few-rows kernel; the
+    bits of 200 rows, which run on the former, and every row behind M stays."""
+    B = _binding()
+    print(f"wide projection m={m} n={n} k={k} residual={residual}", flush=True)
+    a = I.normal_tensor((200, k), 1.0, 101, torch.bfloat16, "cuda")
+    w = I.normal_tensor((n, k), 0.05, 102, torch.bfloat16, "cuda")
+    td = torch.float32 if residual else torch.bfloat16
+    c = torch.full((200, n), 7.0, dtype=td, device="cuda")
+    if residual:
+        c[:m] = I.normal_tensor((m, n), 1.0, 103, td, "cuda")
+    all_rows = c.clone()
+    ref = a[:m].double() @ w.double().T
+    if residual:
+        ref += c[:m].double()
+    assert B.fp_op_gemm_workspace_bytes(1, m, n, k) == 0
+    torch.cuda.synchronize()
+    B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), c.data_ptr(), m, n, k, residual)
+    B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), all_rows.data_ptr(), 200, n, k, residual)
+    torch.cuda.synchronize()
+    err = (c[:m].double() - ref).norm(dim=1) / ref.norm(dim=1)
+    # bf16 results: 2^-9 relative each; fp32: sums of up to 1216 products in fp32, 32 at a time in the matrix unit: 1e-5 at most.
+    assert err.max().item() <= (1e-5 if residual else 4e-3), (err.argmax().item(), err.max().item())
+    assert torch.equal(c[:m], all_rows[:m]) and torch.all(c[m:] == 7.0)
+
+
 F32_TILE_SIZES = [            # rows of the tile, m (one row past the last whole tile, or one short of one), n, k, residual
     (16, 431, 24, 520, 0), (16, 417, 8, 520, 0), (16, 31, 72, 520, 1), (16, 1, 104, 304, 1), (32, 63, 416, 40, 0), (32, 1, 2784, 40, 0),
     (32, 31, 576, 8, 1), (48, 95, 5496, 40, 0), (48, 385, 1384, 40, 0), (48, 335, 1528, 8, 1), (48, 97, 4616, 8, 1),
