@@ -222,3 +222,43 @@ def test_experts_of_unlike_sizes_run_on_large_tiles_of_every_height(ffn, seed):
     assert fro_rel_err(got, x_ref) <= 1e-2 and max_rel_err(got, x_ref) <= TOL["bf16"]
     task.end()
     model.close()
+
+
+@pytest.mark.parametrize("ffn,seed", [(192, 61), (128, 62)])
+@pytest.mark.parametrize("n", [100, 300, 600, 1100])
+def test_what_experts_add_to_each_token(n, ffn, seed):
+    """The experts' contribution by itself, token by token and 32 columns at a time, against its definition in 64 bits: 32 to 256-row
+    tiles (n / 8 rows per expert on average, from a few to several hundred at n = 1100), every (expert, column tile) starting at
+    another of its five, three or two k-tiles.  Attention adds nothing here, so what the layer adds is the experts' sum."""
+    B, R = _mods()
+    spec = I.ShapeSpec(1, 320, 4, 2, 64, ffn, 1e-5, 10000.0, n_experts=32, top_k=4)
+    weights = I.make_weights(spec, seed, torch.bfloat16, "cuda")
+    w = weights[0]
+    w["w_o"].zero_()
+    w["w_router"] *= torch.linspace(0.3, 1.6, 32, device="cuda")[:, None].to(torch.bfloat16)
+    x = I.make_hidden(n, spec.hidden, seed, torch.bfloat16, "cuda")
+    model = R.PrefillModel(spec, weights, B.FP_DTYPE_BF16, 128, n)
+    print(f"experts' contribution n={n} ffn={ffn}", flush=True)
+    task = model.begin(x, [n])
+    task.run_to_completion()
+    ids, wts = task.moe_routing(0)
+    h = torch.empty_like(x)
+    x32 = x.float()
+    torch.cuda.synchronize()
+    B.fp_op_rmsnorm(1, x32.data_ptr(), w["mlp_norm"].data_ptr(), h.data_ptr(), n, spec.hidden, spec.rms_eps)
+    torch.cuda.synchronize()
+    ref = torch.zeros(n, spec.hidden, dtype=torch.float64, device="cuda")
+    for e in range(spec.n_experts):
+        token, slot = (ids == e).nonzero(as_tuple=True)
+        g, u = (h[token].double() @ w["w_gate_up"][e].double().T).split(ffn, dim=1)
+        y = (torch.nn.functional.silu(g) * u) @ w["w_down"][e].double().T
+        ref.index_add_(0, token, wts[token, slot, None].double() * y)
+    off = task.hidden().double() - x.double() - ref
+    # Four roundings to bf16 (gate, up, their product, the expert's output), 2^-8 / sqrt(3) in the mean square each, the gate's
+    # up to doubled: 6e-3 of a token's contribution, 8e-3 of 32 of its columns at most (computed on the CPU); twice that.  One
+    # k-tile left out of one expert's last eight columns is 0.2 and 0.25, a lost row or column tile more.
+    assert (off.norm(dim=1) / ref.norm(dim=1)).max().item() <= 1.2e-2
+    blocks = (n, spec.hidden // 32, 32)
+    assert (off.view(blocks).norm(dim=2) / ref.view(blocks).norm(dim=2)).max().item() <= 1.6e-2
+    task.end()
+    model.close()
