@@ -412,10 +412,13 @@ def test_gemm_of_few_rows(m, n, k, residual):
         assert torch.equal(buf[:m], large[:m])
 
 
-@pytest.mark.parametrize("m", [1, 32, 64, 127])
-@pytest.mark.parametrize("f,k", [(6152, 128), (7176, 704)])
+@pytest.mark.parametrize("m,f,k", [(m, f, k) for f, k in [(6152, 128), (7176, 704)] for m in (1, 32, 64, 127)] +
+                                  [(m, 20488, k) for m in (65, 127, 128) for k in (64, 320, 1216)] +
+                                  [(m, 6152, 448) for m in (70, 180, 370)])
 def test_fused_gate_up_swiglu_of_few_rows(m, f, k):
-    """SiLU(gate)*up in the epilogue of the few-rows kernel: the bits of the two operators."""
+    """SiLU(gate)*up in the epilogue of the few-rows kernel (up to 64 rows; 65 to 128 where 20488 outputs fill the chip with wide tiles,
+    the plain projection then on the large kernel up to K = 1152) and of the 128-column tile on 96, 128 and 192 rows: the bits of
+    the two operators."""
     B = _binding()
     a = I.normal_tensor((m, k), 1.0, 64, torch.bfloat16, "cuda")
     w = I.normal_tensor((2 * f, k), 0.02, 65, torch.bfloat16, "cuda")
