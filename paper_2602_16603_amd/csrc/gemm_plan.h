@@ -10,16 +10,18 @@ constexpr uint32_t kOffOutOfRange = 0x80000000u;   // a byte offset no buffer de
 
 // Row tile of a grouped launch whose experts receive `mean_rows` rows on average: the smallest that holds nearly every
 // expert in one tile (a second one reads the expert's weights again), up to 128 rows of the ring kernel; from about 100
-// rows on the matrix pipes bound the launch and the 256-row tile is ahead.  The counts spread by about the root of their
-// mean, hence the lines below 64 and 128.  experts_up + experts_down (with the combine), us, on tiles of 32, 64, 128 and 256
-// rows, [hidden, ffn, experts, top_k]:
+// rows on the matrix pipes bound the launch and the 256-row tile, which multiplies only the rows it has in steps of 32, is ahead.  The
+// counts spread by about the root of their mean, hence the lines below 64 and 128.  experts_up + experts_down (with the combine), us,
+// on tiles of 32, 64, 128 and 256 rows, [hidden, ffn, experts, top_k]:
 //   rows per expert   [2048 768 128 8]      [4096 1536 64 8]      [4096 14336 8 2]        [2048 1408 64 6]
-//   16                230  234  258  325    434  438  465  523    491   487   589   733   211  219  241  291
-//   44                303  254  272  335    669  480  491  543    919   501   596   744   293  230  252  299
-//   52                320  272  285  350    703  496  499  558    1137  790   613   747   311  252  252  297
-//   86                400  376  305  362    1016 725  540  577    1584  966   629   771   434  339  268  317
-//   100               452  395  343  370    1149 769  602  580    1715  974   642   776   482  346  275  319
-//   130               532  478  438  385    1478 896  757  602    2126  1314  1053  799   620  434  393  333
+//   16                207  215  262  245    398  404  457  469    445   447   600   666   193  205  237  231
+//   44                365  240  268  260    747  433  476  479    884   469   608   676   348  224  249  238
+//   52                381  262  273  266    802  478  482  487    887   483   613   680   372  252  254  242
+//   86                574  433  298  289    1227 845  522  518    1518  926   641   719   573  403  273  260
+//   100               684  449  315  301    1384 854  547  528    1596  939   651   730   640  410  279  268
+//   130               844  583  461  323    1770 1118 864  554    2014  1299  1041  735   812  551  419  284
+// (Between 52 and 96 rows the 256-row tile is up to 5 % ahead of the 128-row one on the narrow experts and 10 to 12 % behind on the
+// wide ones.)
 // The smaller tiles reach an expert's gate and up rows through one 32-bit offset, as the dense fused kernel does
 // ([2 ffn][hidden] below 2 GiB); the 256-row tile has a base for each.
 inline int moe_tile_rows(int64_t mean_rows, int64_t ffn, int64_t hidden) {
