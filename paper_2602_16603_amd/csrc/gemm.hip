@@ -329,7 +329,8 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // tokens): W panels come from HBM for one to three row tiles, so every (expert, column tile) starts at another k-tile, as
 // in the kernel for few rows below, and the L2 warm-up asks for more of them.  30B-A3B shape, us, experts_up / experts_down
 // (with the combine): 2000 tokens 244 / 141 -> 193 / 132 (even tiles 232 / 133), 5000 tokens 340 / 252 -> 303 / 231 (314 / 240),
-// 8192 tokens 429 / 343 -> 395 / 328 (425 / 341), 16000 tokens 720 / 605 -> 675 / 582.
+// 8192 tokens 429 / 343 -> 395 / 328 (425 / 341), 16000 tokens 720 / 605 -> 675 / 582.  (The switch over seven bodies spills 15 to 20
+// scalar registers, none of them inside a loop over k.)
 //
 // NJ = 4: the tile is half as wide (128 W rows per stage, wave tile 128 x 64).  A request of a few
 // hundred tokens has one or two row tiles: the narrow tile doubles the number of output tiles, so
@@ -342,7 +343,7 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // L2 warm-up.  Cold weights, 256 tokens of the 8B shape: gate_up 81 -> 71 us, down 48 -> 44;
 // 512 tokens: down 74 -> 66.  (The wide tile's three stages would take 192 KB.)
 //
-// ROWS (256-column tile, not cut): the tile on 128, 160, .. 256 rows, the same sums in the same order.  What a launch of few
+// ROWS: the tile on 96, 128, .. 256 rows, the same sums in the same order.  What an uncut launch of few
 // rounds of tiles loses is its last, partly filled round and the padding of its last row tile; another height often
 // comes out better (large_tile_rows).
 //
@@ -1275,8 +1276,8 @@ static void launch_large(const bf16* a, const bf16* w, void* c, int m, int n, in
 
 // A problem of few row tiles, whose number the columns and K ranges were chosen by: as many, on as few rows as hold m.
 // The launch is bound by its lines (W from HBM, A from the L2 for every column tile), so a row tile that is not padded to 256
-// fetches less: 8B shape, cold, us: 140 tokens gate_up 57 -> 53.5, 270 tokens qkv 30 -> 27.3, down 56 -> 52, 560 tokens qkv 46 -> 41.5,
-// down 84 -> 77; 300 tokens of the 32B shape down 142 -> 115.
+// fetches less: 8B shape, cold, us: 140 tokens gate_up 58 -> 55.5, 270 tokens qkv 33 -> 28.5, down 55 -> 49, 560 tokens qkv 43.5 -> 41,
+// down 84 -> 75; 300 tokens of the 32B shape down 145 -> 112.
 template <int EPI, int NJ>
 static void launch_even_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int kt_per_split, int splits, hipStream_t s) {
   constexpr int BN = EPI == kEpiSwiGLU ? 16 * NJ : 32 * NJ;
