@@ -840,7 +840,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // (KT = 128): a half-wave's 16 rows x 2 chunks put two lanes on every bank group.
 // Grouped: workgroups start at different k and read W non-temporally, so that the stream leaves the activations in the L2: the
 // experts' projections of the 30B-A3B shape, cold, us: 16 tokens 87 -> 80 and 55 -> 49, 590 tokens 164 -> 147 and 97 -> 92 (with the
-// combine).  K ranges start at different k as it is, and gain nothing.  The dense gate_up projection would gain from both (50
+// combine).  Not the experts' gate_up on 128 rows, which loses by the hint from 70 rows per expert on (96 rows of 8 experts [4096 14336]
+// 390 us, 377 without; of 64 [4096 1536] 345 and 331) and gains less below (50 rows: 367 and 371, 314 and 320).
+// K ranges start at different k as it is, and gain nothing.  The dense gate_up projection would gain from both (50
 // rows 52 -> 39 us), but starting at another k rounds its sums differently, and its bits are promised to be fp_op_gemm's; the hint
 // alone gives nothing.
 // ------------------------------------------------------------------------------------------
@@ -866,6 +868,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
   constexpr int RPI = 64 / CPR;                      // rows per DMA instruction
   constexpr int IA = BM / RPI / 4, IW = WR / RPI / 4;   // DMA instructions per wave and stage
   constexpr int STAGE = (BM + WR) * KT;
+  constexpr bool kNonTemporal = GROUPED && !(SWIGLU && MI == 8);   // W (above)
   static_assert(BM % (4 * RPI) == 0 && S >= 2 && S <= 4 && (!SWIGLU || NJ % 2 == 0));
   __shared__ __attribute__((aligned(1024))) bf16 s0[STAGE];
   __shared__ __attribute__((aligned(1024))) bf16 s1[STAGE];
@@ -946,7 +949,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
       ring_dma(panel_a, bytes_a, s + RPI * (IA * wave + i) * KT, k_a[i] < left ? off_a[i] : kOffOutOfRange, t * KT * 2);
 #pragma unroll
     for (int i = 0; i < IW; ++i)
-      ring_dma<GROUPED>(panel_w, bytes_w, s + (BM + RPI * (IW * wave + i)) * KT, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * KT * 2);
+      ring_dma<kNonTemporal>(panel_w, bytes_w, s + (BM + RPI * (IW * wave + i)) * KT, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * KT * 2);
   };
 
   f32x4 acc[MI][NJ];

@@ -14,13 +14,13 @@ constexpr uint32_t kOffOutOfRange = 0x80000000u;   // a byte offset no buffer de
 // counts spread by about the root of their mean, hence the lines below 64 and 128.  experts_up + experts_down (with the combine), us,
 // on tiles of 32, 64, 128 and 256 rows, [hidden, ffn, experts, top_k]:
 //   rows per expert   [2048 768 128 8]      [4096 1536 64 8]      [4096 14336 8 2]        [2048 1408 64 6]
-//   16                207  215  262  245    398  404  457  469    445   447   600   666   193  205  237  231
-//   44                365  240  268  260    747  433  476  479    884   469   608   676   348  224  249  238
-//   52                381  262  273  266    802  478  482  487    887   483   613   680   372  252  254  242
-//   86                574  433  298  289    1227 845  522  518    1518  926   641   719   573  403  273  260
-//   100               684  449  315  301    1384 854  547  528    1596  939   651   730   640  410  279  268
-//   130               844  583  461  323    1770 1118 864  554    2014  1299  1041  735   812  551  419  284
-// (Between 52 and 96 rows the 256-row tile is up to 5 % ahead of the 128-row one on the narrow experts and 10 to 12 % behind on the
+//   16                207  215  259  245    398  404  450  469    445   447   604   666   193  205  238  231
+//   44                365  240  270  260    747  433  480  479    884   469   610   676   348  224  250  238
+//   52                381  262  275  266    802  478  488  487    887   483   613   680   372  252  254  242
+//   86                574  433  297  289    1227 845  516  518    1518  926   629   719   573  403  271  260
+//   100               684  449  309  301    1384 854  528  528    1596  939   637   730   640  410  278  268
+//   130               844  583  444  323    1770 1118 834  554    2014  1299  1074  735   812  551  403  284
+// (Between 52 and 96 rows the 256-row tile is up to 5 % ahead of the 128-row one on the narrow experts and 10 to 14 % behind on the
 // wide ones.)
 // The smaller tiles reach an expert's gate and up rows through one 32-bit offset, as the dense fused kernel does
 // ([2 ffn][hidden] below 2 GiB); the 256-row tile has a base for each.
