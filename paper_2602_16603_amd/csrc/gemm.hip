@@ -227,6 +227,11 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
 // k-tile for both projections).  The pad load is the last VMEM instruction before the wave's
 // wait, which therefore asks for "all but one" and never blocks on it.
 // ------------------------------------------------------------------------------------------
+// Where a workgroup whose columns begin at `col` starts in K (start_groups of gemm_plan.h: 0 = at its beginning).
+__device__ __forceinline__ int k_start(int col, int K, int groups) {
+  return groups ? (col / 128 % groups) * (K / 128) / groups * 128 : 0;
+}
+
 constexpr int kWaitVm0 = 0x0F70;   // s_waitcnt vmcnt(0)           (expcnt/lgkmcnt untouched)
 constexpr int kWaitVm1 = 0x0F71;   // s_waitcnt vmcnt(1)
 template <int N> constexpr int wait_vm() { return 0x0F70 | (N & 15) | ((N >> 4) << 14); }   // s_waitcnt vmcnt(N)
@@ -266,7 +271,7 @@ __device__ __forceinline__ void w4_dma(__amdgpu_buffer_rsrc_t r, bf16* lds_rows,
 // No accumulator is touched twice within MI NJ MFMAs, and LDS results reach the operands through
 // the s_waitcnt the compiler places for the asm inputs, so no software-managed hazard arises.
 enum { kReadsNone, kReadsSpread, kReadsEarly };
-template <int READS, bool DMA, int MI, int NJ>
+template <int READS, bool DMA, int MI, int NJ, bool NT = false>
 __device__ __forceinline__ void w4_block(f32x4_acc (&acc)[MI][NJ], const W4Frags<MI, NJ>& cur, W4Frags<MI, NJ>& nxt,
                                          const bf16* rA, const bf16* rB, int pch,
                                          __amdgpu_buffer_rsrc_t rs_a, __amdgpu_buffer_rsrc_t rs_w, bf16* dA,
@@ -290,7 +295,7 @@ __device__ __forceinline__ void w4_block(f32x4_acc (&acc)[MI][NJ], const W4Frags
           const int d = kSpread * s + i;
           if (j != NJ / 2 + i * (NJ / 2) / kSpread || d >= MI + NJ) continue;
           if (d < MI) w4_dma(rs_a, dA + d * 8 * kBK, voff_a[d], kbyte);
-          else w4_dma(rs_w, dB + (d - MI) * 8 * kBK, voff[d - MI], kbyte);
+          else w4_dma<NT>(rs_w, dB + (d - MI) * 8 * kBK, voff[d - MI], kbyte);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -343,6 +348,9 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // L2 warm-up.  Cold weights, 256 tokens of the 8B shape: gate_up 81 -> 71 us, down 48 -> 44;
 // 512 tokens: down 74 -> 66.  (The wide tile's three stages would take 192 KB.)
 //
+// STREAM (NJ = 4, one row tile, not cut): W is loaded non-temporally, as in the kernel for few rows below.  Narrow uncut tiles
+// may start at another k-tile (start_groups).
+//
 // ROWS: the tile on 96, 128, .. 256 rows, the same sums in the same order.  What an uncut launch of few
 // rounds of tiles loses is its last, partly filled round and the padding of its last row tile; another height often
 // comes out better (large_tile_rows).
@@ -351,12 +359,12 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // main loop as one more k-tile, not pipelined, whose missing 16-byte chunks are fetched from outside the
 // descriptors (K < 64: there is nothing else; the prologue's k-tile 0 is overwritten unread).  K rows then start at odd multiples of 16 bytes, which the DMA does not mind.  8192 x 8192 x 2056:
 // 408 us on register-staged 128x128 tiles, 265 here (1.04 PFLOP/s; rows that straddle lines cost the rest).
-template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false, int ROWS = 256>
+template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false, int ROWS = 256, bool STREAM = false>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restrict__ A,
                                                            const bf16* __restrict__ W,
                                                            void* __restrict__ Cout, int M, int N,
                                                            int K, int tiles_m, int tiles_n,
-                                                           int kt_per_split,
+                                                           int kt_per_split, int start_groups,
                                                            const int32_t* __restrict__ groups,
                                                            const int32_t* __restrict__ a_rows) {
   constexpr bool RESID = EPI == kEpiResidual;
@@ -364,7 +372,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   constexpr int WR = 32 * NJ;                        // W rows per stage (256 or 128)
   constexpr int Q = WR / 4;                          // of which each wave fetches this many
   constexpr int BM = ROWS, BN = SWIGLU ? WR / 2 : WR;   // output rows and columns per tile
-  static_assert(BM % 32 == 0 && BM <= 256 && (!GROUPED || BM == 256));
+  constexpr bool kStarts = NJ == 4 && (EPI == kEpiBf16 || SWIGLU);   // may start at another k-tile than 0
+  static_assert(BM % 32 == 0 && BM <= 256 && (!GROUPED || BM == 256) && (!STREAM || kStarts));
   __shared__ __attribute__((aligned(1024))) bf16 sA0[BM * kBK];
   __shared__ __attribute__((aligned(1024))) bf16 sA1[BM * kBK];
   __shared__ __attribute__((aligned(1024))) bf16 sB0[(WR > BM ? WR : BM) * kBK];   // (as large as an A stage: the epilogue
@@ -409,6 +418,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   } else {
     w_sharers = tile_of_workgroup<!KTAIL>(blockIdx.x - split * n_tiles, tiles_m, tiles_n, tile_m, tile_n);
     share_m = tile_m;
+    if (kStarts) rot = k_start(tile_n * BN, K, start_groups) / kBK;
   }
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   // The tile itself, on 32 MI rows.
@@ -418,7 +428,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const int kt_count = min(kt_per_split, K / kBK - kt_first);
   const int kbyte0 = kt_first * kBK * 2;
   auto kbyte = [&](int u) __attribute__((always_inline)) {   // of k-tile u of this workgroup
-    return kbyte0 + (!GROUPED ? u : u + rot >= kt_count ? u + rot - kt_count : u + rot) * kBK * 2;
+    return kbyte0 + (!GROUPED && !kStarts ? u : u + rot >= kt_count ? u + rot - kt_count : u + rot) * kBK * 2;
   };
 
   // DMA sources.  Wave w fetches LDS rows [8 MI w, 8 MI w + 8 MI) of A and [Q w, Q w + Q) of W, 8 rows per instruction;
@@ -617,7 +627,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   {                                                                                                           \
     const __amdgpu_buffer_rsrc_t ra_ = (u) < kt_count ? rsrc_a : rsrc_none, rw_ = (u) < kt_count ? rsrc_w : rsrc_none; \
     _Pragma("unroll") for (int s = 0; s < MI; ++s) w4_dma(ra_, dA##c + s * 8 * kBK, voff_a[s], kbyte(u)); \
-    _Pragma("unroll") for (int s = 0; s < NJ; ++s) w4_dma(rw_, dB##c + s * 8 * kBK, voff[s], kbyte(u)); \
+    _Pragma("unroll") for (int s = 0; s < NJ; ++s) w4_dma<STREAM>(rw_, dB##c + s * 8 * kBK, voff[s], kbyte(u)); \
   }
     W4_FETCH(0, 0);
     W4_FETCH(1, 1);
@@ -651,7 +661,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                                                                   \
     __builtin_amdgcn_s_waitcnt(wait_vm<MI + NJ>());                                                           \
     w4_barrier();                                                                                             \
-    w4_block<kReadsSpread, true, MI, NJ>(acc, f1, f0, rA##o, rB##o, pch0, t3_ < kt_count ? rsrc_a : rsrc_none,           \
+    w4_block<kReadsSpread, true, MI, NJ, STREAM>(acc, f1, f0, rA##o, rB##o, pch0, t3_ < kt_count ? rsrc_a : rsrc_none,           \
                       t3_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t3_));             \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
   }
@@ -832,7 +842,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // stream is all there is to it; it also takes most of what has too few 256-row tiles to occupy the chip,
 // and of odd K (gemm_plan.h).
 // 256 threads = 4 waves side by side along N; every wave multiplies all rows by its 16 NJ columns with
-// v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits, unless grouped).  K is consumed KT at a
+// v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits, unless grouped or cut).  K is consumed KT at a
 // time through a ring of S LDS stages, separate arrays filled by DMA S - 1 k-tiles ahead; the loop body has no
 // branch and always runs a multiple of S k-tiles (behind the last one there is nothing to fetch and
 // zeros to multiply), since with a branch between stages the compiler waits for all DMA before a read.
@@ -842,9 +852,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // experts' projections of the 30B-A3B shape, cold, us: 16 tokens 87 -> 80 and 55 -> 49, 590 tokens 164 -> 147 and 97 -> 92 (with the
 // combine).  Not the experts' gate_up on 128 rows, which loses by the hint from 70 rows per expert on (96 rows of 8 experts [4096 14336]
 // 390 us, 377 without; of 64 [4096 1536] 345 and 331) and gains less below (50 rows: 367 and 371, 314 and 320).
-// K ranges start at different k as it is, and gain nothing.  The dense gate_up projection would gain from both (50
-// rows 52 -> 39 us), but starting at another k rounds its sums differently, and its bits are promised to be fp_op_gemm's; the hint
-// alone gives nothing.
+// K ranges start at different k as it is, and gain nothing.
+// STREAM (uncut launches of one row tile, the W of all of them read once): the same two, the start by start_groups, which
+// keeps the fused projection and the plain one on one order of sums.  The hint by itself: 50 rows of [14336 outputs 4096]
+// 52.5 -> 49.3 us, 27648 x 5120 110 -> 103; with the starts 41.2, and 256 rows on the 128-column tile 68.2 -> 60.4.  Not on 128 rows here: 27648 x 5120
+// 125 -> 126.7.
 // ------------------------------------------------------------------------------------------
 template <int KT> __device__ __forceinline__ int ring_chunk(int chunk, int row) {
   return KT == 128 ? chunk ^ (row & 15) : chunk ^ ((row >> 1) & 7);
@@ -855,10 +867,10 @@ __device__ __forceinline__ void ring_dma(const bf16* base, uint32_t bytes, bf16*
   w4_dma<NT>(panel_rsrc(base, bytes), lds, voff, kbyte);
 }
 
-template <int MI, int NJ, int KT, int S, int EPI, bool GROUPED>
+template <int MI, int NJ, int KT, int S, int EPI, bool GROUPED, bool STREAM = false>
 __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
                                                                  void* __restrict__ Cout, int M, int N, int K,
-                                                                 int tiles_m, int tiles_n, int kt_per_split,
+                                                                 int tiles_m, int tiles_n, int kt_per_split, int start_groups,
                                                                  const int32_t* __restrict__ groups,
                                                                  const int32_t* __restrict__ a_rows) {
   constexpr bool SWIGLU = EPI == kEpiSwiGLU;
@@ -868,7 +880,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
   constexpr int RPI = 64 / CPR;                      // rows per DMA instruction
   constexpr int IA = BM / RPI / 4, IW = WR / RPI / 4;   // DMA instructions per wave and stage
   constexpr int STAGE = (BM + WR) * KT;
-  constexpr bool kNonTemporal = GROUPED && !(SWIGLU && MI == 8);   // W (above)
+  constexpr bool kNonTemporal = STREAM || (GROUPED && !(SWIGLU && MI == 8));   // W (above)
   static_assert(BM % (4 * RPI) == 0 && S >= 2 && S <= 4 && (!SWIGLU || NJ % 2 == 0));
   __shared__ __attribute__((aligned(1024))) bf16 s0[STAGE];
   __shared__ __attribute__((aligned(1024))) bf16 s1[STAGE];
@@ -906,6 +918,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
     A += (int64_t)m0 * K;
     Cout = reinterpret_cast<char*>(Cout) + ((int64_t)m0 * N + slab) * (EPI == kEpiBf16 || SWIGLU ? 2 : 4);
     M = min(BM, M - m0);
+    if (STREAM) rot = k_start(tile_n * BN, K, start_groups) / KT;
   }
   const int n0 = tile_n * BN;
   const int k_first = split * kt_per_split * kBK;    // (K ranges are counted in k-tiles of 64)
@@ -940,7 +953,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
   const int kt_count = (k_count + KT - 1) / KT;
   auto fetch = [&](int t, bf16* s) __attribute__((always_inline)) {
     int left = k_count - t * KT;                     // behind the last k-tile every chunk is out of range
-    if (GROUPED && left > 0) {
+    if ((GROUPED || STREAM) && left > 0) {
       t = t + rot >= kt_count ? t + rot - kt_count : t + rot;
       left = k_count - t * KT;
     }
@@ -1198,10 +1211,12 @@ static W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
 // row count and epilogue, as measured on cold weights of the 8B shape (us, against the two-stage 256-row tile): up to
 // 64 rows 64-column tiles of 128 k (256 bytes of a weight row at a time: HBM gives 4.9 TB/s to such pieces where 128-byte
 // pieces get 4.2) -- 50 rows: qkv 22 -> 17, o 17 -> 12.6, down 40 -> 28; from 65 rows on the A tile weighs more and 128-column
-// tiles of 64 k read it half as often.  SwiGLU: 128 W rows of 64 k, 75 -> 52 at 50 rows.
-template <int MI, bool SWIGLU> struct RingTile {
+// tiles of 64 k read it half as often.  SwiGLU: 128 W rows of 64 k, 75 -> 52 at 50 rows; from 3072 k on (LONG_K) 128 k at a time there too, through
+// three stages for 64 rows (50 rows, outputs x k: 8192 x 3072 32.1 -> 29.8, 14336 x 6144 61.9 -> 59.5, 8192 x 8192 73 -> 69; 8192 x 2048
+// 23.5 -> 23.8, 14336 x 1024 15.8 -> 16.7).
+template <int MI, bool SWIGLU, bool LONG_K = false> struct RingTile {
   static constexpr bool kWide = SWIGLU || MI > 4;
-  static constexpr int NJ = kWide ? 2 : 1, KT = kWide ? 64 : 128, S = 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
+  static constexpr int NJ = kWide ? 2 : 1, KT = kWide && !LONG_K ? 64 : 128, S = LONG_K && MI == 4 ? 3 : 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
 };
 struct KRanges {
   int per, used;      // k-tiles of 64 per range, ranges (every range has at least one k-tile)
@@ -1216,20 +1231,26 @@ static KRanges ring_ranges(int n, int k, int splits) {
   using T = RingTile<MI, EPI == kEpiSwiGLU>;
   return k_ranges(k, splits > 1 ? std::max(2, std::min(splits, 256 / ((n + T::BN - 1) / T::BN))) : 1);
 }
-template <int MI, int EPI>
-static int launch_ring(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
-  using T = RingTile<MI, EPI == kEpiSwiGLU>;
+template <int MI, int EPI, bool STREAM = false, bool LONG_K = false>
+static int launch_ring(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s, int start_groups = 0) {
+  using T = RingTile<MI, EPI == kEpiSwiGLU, LONG_K>;
   const int tiles_m = (m + 16 * MI - 1) / (16 * MI), tiles_n = (n + T::BN - 1) / T::BN;
   const KRanges r = ring_ranges<MI, EPI>(n, k, splits);
-  gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, EPI, false><<<dim3((unsigned)(tiles_m * tiles_n * r.used)), 256, 0, s>>>(
-      a, w, c, m, n, k, tiles_m, tiles_n, r.per, nullptr, nullptr);
+  gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, EPI, false, STREAM><<<dim3((unsigned)(tiles_m * tiles_n * r.used)), 256, 0, s>>>(
+      a, w, c, m, n, k, tiles_m, tiles_n, r.per, start_groups, nullptr, nullptr);
   return r.used;
 }
 // Returns the number of K ranges launched (at most `splits`).
 template <int EPI>
 static int launch_few_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
-  if (m <= 32) return launch_ring<2, EPI>(a, w, c, m, n, k, splits, s);
-  if (m <= 64) return launch_ring<4, EPI>(a, w, c, m, n, k, splits, s);
+  constexpr bool SWIGLU = EPI == kEpiSwiGLU, STREAM = SWIGLU || EPI == kEpiBf16;
+  const int starts = STREAM ? start_groups(m, SWIGLU ? 2 * (int64_t)n : n, k) : 0;
+  if (SWIGLU && k >= 3072) {
+    if (m <= 32) return launch_ring<2, EPI, STREAM, SWIGLU>(a, w, c, m, n, k, splits, s, starts);
+    if (m <= 64) return launch_ring<4, EPI, STREAM, SWIGLU>(a, w, c, m, n, k, splits, s, starts);
+  }
+  if (m <= 32) return launch_ring<2, EPI, STREAM>(a, w, c, m, n, k, splits, s, starts);
+  if (m <= 64) return launch_ring<4, EPI, STREAM>(a, w, c, m, n, k, splits, s, starts);
   return launch_ring<8, EPI>(a, w, c, m, n, k, splits, s);
 }
 
@@ -1262,7 +1283,7 @@ template <int EPI, int ROWS>
 static void launch_large_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int tiles_n, hipStream_t s) {
   const int tiles_m = (m + ROWS - 1) / ROWS;
   gemm_bf16_w4_kernel<EPI, false, 8, false, ROWS><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(
-      a, w, c, m, n, k, tiles_m, tiles_n, k / kBK, nullptr, nullptr);
+      a, w, c, m, n, k, tiles_m, tiles_n, k / kBK, 0, nullptr, nullptr);
 }
 template <int EPI>
 static void launch_large(const bf16* a, const bf16* w, void* c, int m, int n, int k, hipStream_t s) {
@@ -1285,10 +1306,16 @@ template <int EPI, int NJ>
 static void launch_even_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int kt_per_split, int splits, hipStream_t s) {
   constexpr int BN = EPI == kEpiSwiGLU ? 16 * NJ : 32 * NJ;
   const int tiles_m = (m + 255) / 256, tiles_n = (n + BN - 1) / BN;
+  constexpr bool kUncut = NJ == 4 && (EPI == kEpiBf16 || EPI == kEpiSwiGLU);
+  const int starts = kUncut ? start_groups(m, EPI == kEpiSwiGLU ? 2 * (int64_t)n : n, k) : 0;
   auto launch = [&](auto rows) {
     constexpr int ROWS = decltype(rows)::value;
-    gemm_bf16_w4_kernel<EPI, false, NJ, false, ROWS><<<dim3((unsigned)(tiles_m * tiles_n * splits)), 256, 0, s>>>(
-        a, w, c, m, n, k, tiles_m, tiles_n, kt_per_split, nullptr, nullptr);
+    if (kUncut && tiles_m == 1)
+      gemm_bf16_w4_kernel<EPI, false, NJ, false, ROWS, kUncut><<<dim3((unsigned)tiles_n), 256, 0, s>>>(
+          a, w, c, m, n, k, 1, tiles_n, kt_per_split, starts, nullptr, nullptr);
+    else
+      gemm_bf16_w4_kernel<EPI, false, NJ, false, ROWS><<<dim3((unsigned)(tiles_m * tiles_n * splits)), 256, 0, s>>>(
+          a, w, c, m, n, k, tiles_m, tiles_n, kt_per_split, starts, nullptr, nullptr);
   };
   const int rows = (m + tiles_m - 1) / tiles_m;
   constexpr bool kAnyNumber = NJ == 4;     // (else three row tiles or more)
@@ -1349,7 +1376,7 @@ static void launch_grouped_ring(const bf16* a, const bf16* w, void* c, int n, in
   const int tiles_n = (n + BN - 1) / BN;
   gemm_bf16_ring_kernel<MI, NJ, KT, S, EPI, true>
       <<<dim3((unsigned)((max_row_tiles + kXcds - 1) / kXcds * kXcds * tiles_n)), 256, 0, s>>>(
-          a, w, c, m_arg, n, k, max_row_tiles, tiles_n, k / kBK, groups, a_rows);
+          a, w, c, m_arg, n, k, max_row_tiles, tiles_n, k / kBK, 0, groups, a_rows);
 }
 
 void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64_t k, int swiglu,
@@ -1372,10 +1399,10 @@ void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64
   const int m_arg = a_rows ? (int)a_total_rows : 0;
   if (swiglu)
     gemm_bf16_w4_kernel<kEpiSwiGLU, true><<<grid, 256, 0, s>>>((const bf16*)a, (const bf16*)w, c, m_arg, (int)n,
-                                                              (int)k, max_row_tiles, tiles_n, (int)(k / kBK), groups, a_rows);
+                                                              (int)k, max_row_tiles, tiles_n, (int)(k / kBK), 0, groups, a_rows);
   else
     gemm_bf16_w4_kernel<kEpiBf16, true><<<grid, 256, 0, s>>>((const bf16*)a, (const bf16*)w, c, m_arg, (int)n,
-                                                            (int)k, max_row_tiles, tiles_n, (int)(k / kBK), groups, a_rows);
+                                                            (int)k, max_row_tiles, tiles_n, (int)(k / kBK), 0, groups, a_rows);
 }
 
 // tail: what follows the split-K reduction in the same kernel (kTailNone: nothing).
@@ -1676,7 +1703,7 @@ static void launch_small_problem(const bf16* a, const bf16* w, void* c, int m, i
     case GemmTile::kLarge: {
       const int tiles_m = (m + 255) / 256, tiles_n = (n + 255) / 256;
       gemm_bf16_w4_kernel<EPI, false, 8, true><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(
-          a, w, c, m, n, k, tiles_m, tiles_n, k / kBK, nullptr, nullptr);
+          a, w, c, m, n, k, tiles_m, tiles_n, k / kBK, 0, nullptr, nullptr);
       break;
     }
   }

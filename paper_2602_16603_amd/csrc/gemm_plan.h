@@ -57,6 +57,20 @@ inline bool few_rows(int64_t m, int64_t n, int64_t k) {
   return tiles >= kWideTiles ? tiles > 256 || k > 1152 : k > 16384;
 }
 
+// A launch of one or two row tiles on the 128-column or the few-rows tile reads every line of W for one or two workgroups only,
+// and workgroups in step ask for the same 128 or 256 bytes of every row.  Where rows lie a power of two or three of them apart those
+// fall on few HBM channels, on fewer or more of them with where the allocation lies; so the columns' starts in K are spread evenly
+// over it, in groups of 128 columns.  Returns the number of such groups, 0: all start at the beginning.  A projection fused with SiLU*up
+// and the plain one of the same matrix have to add up their products in the same order whatever kernel takes them: the start
+// depends on the column modulo half the columns (gate and up of one output start alike) and nothing else, and
+// where either form could be on a tile that does not start elsewhere (kWideTiles, few_rows of a long K) neither does.
+// us, cold, five allocations each, gate_up of [14336 outputs 4096]: 50 rows 52.5 (45..57) -> 43.0 (42.7..43.4), 256 rows 69.3 -> 63.1;
+// [14336 6144] 50 rows 82.3 -> 65.6, 200 rows 102.6 -> 89.1; [8192 2048] 23.7 -> 23.6, 31.8 -> 30.7; [18944 3584] 73.7 -> 73.4, 98.9 -> 98.1.  Other spreads are worse or no better: 8 or 16 starts in turn 44 to 68, a random one 46.6.
+inline int start_groups(int64_t m, int64_t n, int64_t k) {
+  const bool narrow = m <= 512 && (m + 255) / 256 * ((n + 255) / 256) < kWideTiles;
+  return narrow && n % 256 == 0 && k % 128 == 0 && k >= 2048 && k <= 16384 ? (int)(n / 256) : 0;
+}
+
 // Rows of the large tile (256 columns; SwiGLU 128 outputs; K % 64 == 0, not cut).  A CU works off its tiles one after the other;
 // a launch of a few rounds loses what its last round leaves empty and the padding of its last row tile, a smaller tile
 // reads W more often.  The rule is an estimate in ns fitted to 698 problems on all five heights (257-9000 rows, the dense

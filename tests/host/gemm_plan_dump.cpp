@@ -36,6 +36,10 @@ int main() {
       long long m, n, k;
       in >> m >> n >> k;
       std::cout << fp::few_rows(m, n, k) << "\n";
+    } else if (kind == "starts") {
+      long long m, n, k;
+      in >> m >> n >> k;
+      std::cout << fp::start_groups(m, n, k) << "\n";
     } else if (kind == "warm") {
       int row_tiles;
       in >> row_tiles;

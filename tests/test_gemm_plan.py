@@ -98,3 +98,14 @@ def test_wide_projections_of_65_to_128_rows_stay_on_the_few_rows_kernel(rules):
     wide = [(65, 49152, 5120), (65, 128256, 5120), (65, 41000, 5120), (65, 65536, 4096), (65, 128256, 2048)]
     assert rules([f"few {m} {n} {k}" for m, n, k in wide]) == ["1"] * 5
     assert rules(["few 128 41000 512", "few 128 65536 1024", "few 65 40704 5120", "few 129 49152 5120", "few 64 8 8"]) == ["0", "0", "0", "0", "1"]
+
+
+def test_columns_start_elsewhere_only_where_either_form_does(rules):
+    """A projection fused with SiLU*up and the plain one of the same matrix take the same starts, whichever tile they run on: none
+    for problems that could be on a tile without them (the 256-column one, 65 to 128 rows of a long K on the few-rows one)."""
+    asked = [(m, n, k) for m in (1, 64, 65, 128, 129, 256, 257, 512, 513) for n in (12544, 14336, 28672, 40704, 40960, 57344) for k in (1024, 2048, 4096, 16384, 16512)]
+    for (m, n, k), groups, few in zip(asked, rules([f"starts {m} {n} {k}" for m, n, k in asked]), rules([f"few {m} {n} {k}" for m, n, k in asked])):
+        narrow = m <= 512 and (m + 255) // 256 * (n // 256) < 160
+        assert int(groups) == (n // 256 if narrow and 2048 <= k <= 16384 else 0), (m, n, k, groups)
+        assert int(groups) == 0 or m <= 64 or few == "0", (m, n, k)
+    assert rules(["starts 50 28680 4096", "starts 50 28672 4160", "starts 50 128 4096"]) == ["0", "0", "0"]

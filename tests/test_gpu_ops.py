@@ -434,6 +434,33 @@ def test_fused_gate_up_swiglu_of_few_rows(m, f, k):
     assert max_rel_err(fused[:m], O.silu_mul(O.linear(a.cpu(), w.cpu()))) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("m", [1, 32, 33, 64, 65, 256, 257, 512])
+@pytest.mark.parametrize("f,k", [(6272, 2048), (6272, 3200), (7168, 3136), (6400, 16384)])
+def test_gate_up_whose_columns_start_at_different_k(m, f, k):
+    """Up to two row tiles on the few-rows and the 128-column tile, long rows: every group of 128 columns starts at another k (49
+    and 50 groups over 16, 25 and 128 starts; none where K is no multiple of 128, whose last k-tile of 128 is half empty). The
+    fused form has the bits of the two operators, and each value is as near its definition as its roundings are."""
+    B = _binding()
+    print(f"starts m={m} f={f} k={k}", flush=True)
+    a = I.normal_tensor((m, k), 1.0, 104, torch.bfloat16, "cuda")
+    w = I.normal_tensor((2 * f, k), 0.02, 105, torch.bfloat16, "cuda")
+    gu = torch.full((m + 1, 2 * f), 7.0, dtype=torch.bfloat16, device="cuda")
+    two = torch.empty((m, f), dtype=torch.bfloat16, device="cuda")
+    fused = torch.full((m + 1, f), 7.0, dtype=torch.bfloat16, device="cuda")
+    torch.cuda.synchronize()
+    B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), gu.data_ptr(), m, 2 * f, k, False)
+    B.fp_op_silu_mul(1, gu.data_ptr(), two.data_ptr(), m, f)
+    B.fp_op_gemm_swiglu(a.data_ptr(), w.data_ptr(), fused.data_ptr(), m, f, k)
+    torch.cuda.synchronize()
+    assert torch.equal(fused[:m], two) and torch.all(fused[m] == 7.0) and torch.all(gu[m] == 7.0)
+    ref = a.double() @ w.double().T
+    # bf16 rounding 2^-9 of a row's values; sums of up to 16384 products of about 0.02 in fp32, 32 at a time: 1e-6.  A k-tile left out or
+    # taken twice is 1/256 of K or more, 6e-2 of a row.
+    err = (gu[:m].double() - ref).norm(dim=1) / ref.norm(dim=1)
+    assert err.max().item() <= 4e-3, (err.argmax().item(), err.max().item())
+    assert max_rel_err(fused[:m], torch.nn.functional.silu(ref[:, :f]) * ref[:, f:]) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("m,n,k", [(777, 6144, 1088), (513, 7824, 2048), (1024, 4096, 1600), (600, 5136, 1024)])
 @pytest.mark.parametrize("residual", [False, True])
 def test_three_and_four_row_tiles_on_the_narrow_tile(m, n, k, residual):
