@@ -1368,11 +1368,12 @@ size_t gemm_workspace_bytes(int dtype, int64_t m, int64_t n, int64_t k) {
 template <int MI, int EPI>
 static void launch_grouped_ring(const bf16* a, const bf16* w, void* c, int n, int k, const int32_t* groups,
                                     int max_row_tiles, const int32_t* a_rows, int m_arg, hipStream_t s) {
-  // The down projection's K is short: two workgroups per CU, so that one's prologue and stores lie under the
-  // other's k-tiles, are worth more than the stages they cost (37 rows per expert: 102 -> 99 us with three
-  // stages; 64 rows: 117 -> 110 with two).
+  // Stages such that two workgroups share a CU (up to 32 rows: no fewer than four), so that one's prologue and stores lie under the
+  // other's k-tiles: worth more than a stage more.  30B-A3B shape, cold, us, experts_up on four stages: 64-row tiles (350 to 720 tokens) 140 ->
+  // 132, 160 -> 151, 128-row ones (850, 1200 tokens) 185 -> 171.5, 188 -> 175; experts_down (with the combine) on 32-row tiles 49.2 -> 46 with four
+  // stages instead of three (16 tokens), 64-row ones 87 -> 81 with three instead of four.
   constexpr bool SWIGLU = EPI == kEpiSwiGLU;
-  constexpr int NJ = 2, KT = 64, S = SWIGLU ? 4 : MI == 8 ? 2 : 3, BN = SWIGLU ? 32 * NJ : 64 * NJ;
+  constexpr int NJ = 2, KT = 64, S = MI == 8 ? 2 : MI == 4 ? 3 : 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
   const int tiles_n = (n + BN - 1) / BN;
   gemm_bf16_ring_kernel<MI, NJ, KT, S, EPI, true>
       <<<dim3((unsigned)((max_row_tiles + kXcds - 1) / kXcds * kXcds * tiles_n)), 256, 0, s>>>(
