@@ -1445,14 +1445,16 @@ static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, 
 // ------------------------------------------------------------------------------------------
 // fp32 GEMM (debug path) on v_mfma_f32_16x16x4_f32: products and sums in fp32, 256 FLOP per clock and
 // CU.  256 threads = WM x 4 / WM waves, wave tile (16 TM) x (16 TN), K consumed 32 at a time through a ring
-// of three LDS stages filled by DMA two k-tiles ahead (128-byte rows, chunk c of row r at position
+// of three LDS stages filled by DMA two to three k-tiles ahead (128-byte rows, chunk c of row r at position
 // c ^ ((r >> 1) & 7): conflict-free for the 16-row fragment reads, as in the bf16 kernel).  The
 // instruction takes one k per lane quarter; a lane reads four consecutive k of its row with one
 // ds_read_b128 and step j of four multiplies the j-th of each quarter -- A and W are permuted over k
 // alike.  Chunks past K are fetched from outside the descriptor, so they read as zero (K % 4 == 0).
-// The matrix pipes bound it (157 TFLOP/s): 300 rows of the 8B shape's gate_up projection 2040 -> 630 us
-// (119 TFLOP/s, row padding included), down 2476 -> 381 us, against the plain FMA kernel below; f32_tile_rows chooses the tile
-// (down 338 us on 80 rows).  Waves side by side along N (WM = 1) for heights that are no multiple of 32.
+// The matrix pipes bound it (157 TFLOP/s at 2.4 GHz; under this load the clock is 2.1): 300 rows of the 8B shape's gate_up projection
+// 2040 -> 568 us (132 TFLOP/s, row padding included), down 2476 -> 317 us, against the plain FMA kernel below; f32_tile_rows chooses
+// the tile.  Half a k-tile's fragments are read, and the next DMA issued, while the other half is multiplied: with both in front
+// of their MFMAs, us, 16-row tiles 67 x 4096 x 14336 179 -> 161, 80-row ones 300 x 4096 x 14336 330 -> 317, 64-row ones 300 x 28672 x 4096
+// 580 -> 568, 128-row ones 1000 x 4096 x 4096 273 -> 261.  Waves side by side along N (WM = 1) for heights that are no multiple of 32.
 // ------------------------------------------------------------------------------------------
 constexpr int kFK = 32;
 
@@ -1469,8 +1471,8 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restr
   constexpr int WN = 4 / WM, BM = 16 * TM * WM, BN = 16 * TN * WN;
   constexpr int IA = (BM + 31) / 32, IW = BN / 32;   // DMA instructions (8 rows of 128 bytes) per wave and k-tile
   constexpr int RA = 32 * IA;                        // rows of A per stage: BM, or 16 more, which are zeros
-  constexpr int kWaitNewest = 0x0F70 | (IA + IW);    // vmcnt: all but the newest k-tile's
-  static_assert(BN % 32 == 0 && IA + IW < 16);
+  constexpr int kWaitNewest = wait_vm<IA + IW>(), kWaitTwoNewest = wait_vm<2 * (IA + IW)>();   // all but the newest k-tile's, two
+  static_assert(BN % 32 == 0 && 2 * (IA + IW) < 64);
   __shared__ __attribute__((aligned(1024))) float s0[(RA + BN) * kFK];
   __shared__ __attribute__((aligned(1024))) float s1[(RA + BN) * kFK];
   __shared__ __attribute__((aligned(1024))) float s2[(RA + BN) * kFK];
@@ -1500,14 +1502,15 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restr
     off_w[i] = (uint32_t)((row * K + k_w[i]) * 4);
   }
   const int kt_count = (K + kFK - 1) / kFK;
+  // DMA instruction d of k-tile t (past the last k-tile every chunk is outside: nothing to fetch).
+  auto fetch_one = [&](int t, float* s, int d) __attribute__((always_inline)) {
+    const int left = K - t * kFK;
+    if (d < IA) f32_dma(panel_a, bytes_a, s + 8 * (wave * IA + d) * kFK, k_a[d] < left ? off_a[d] : kOffOutOfRange, t * kFK * 4);
+    else f32_dma(panel_w, bytes_w, s + (RA + 8 * (wave * IW + d - IA)) * kFK, k_w[d - IA] < left ? off_w[d - IA] : kOffOutOfRange, t * kFK * 4);
+  };
   auto fetch = [&](int t, float* s) __attribute__((always_inline)) {
-    const int left = K - t * kFK;                    // past the last k-tile every chunk is outside: nothing to fetch
 #pragma unroll
-    for (int i = 0; i < IA; ++i)
-      f32_dma(panel_a, bytes_a, s + 8 * (wave * IA + i) * kFK, k_a[i] < left ? off_a[i] : kOffOutOfRange, t * kFK * 4);
-#pragma unroll
-    for (int i = 0; i < IW; ++i)
-      f32_dma(panel_w, bytes_w, s + (RA + 8 * (wave * IW + i)) * kFK, k_w[i] < left ? off_w[i] : kOffOutOfRange, t * kFK * 4);
+    for (int d = 0; d < IA + IW; ++d) fetch_one(t, s, d);
   };
 
   f32x4 acc[TM][TN];
@@ -1517,41 +1520,59 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restr
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int frag_row = lane & 15, quad = lane >> 4;
   const int key = (frag_row >> 1) & 7;               // (16-row blocks: the block's first row does not change it)
-  auto step = [&](int t, const float* s, float* next) __attribute__((always_inline)) {
-    fetch(t + 2, next);                              // the stage every wave finished before the last barrier
-    __builtin_amdgcn_sched_barrier(0);
+  // Half a k-tile is 16 k, four per lane and fragment (TM of A, then TN of W).
+  struct Half { f32x4 f[TM + TN]; };
+  auto read_one = [&](const float* s, int kk, Half& h, int i) __attribute__((always_inline)) {
+    const int at = ((kk * 4 + quad) ^ key) * 4;
+    const int row = i < TM ? wm * 16 * TM + i * 16 : RA + wn * 16 * TN + (i - TM) * 16;
+    h.f[i] = *reinterpret_cast<const f32x4*>(s + (row + frag_row) * kFK + at);
+  };
+  // The MFMAs of one half, and behind each of them, inside the cycles it takes, one of `n` reads and DMA instructions (in front of the MFMAs
+  // 300 x 4096 x 14336 323 us, so 317).  Up to two accumulators, whose MFMAs wait for each other anyway: in front of them (67 x 6144 x
+  // 4096 52.9 us, between them 57).
+  auto multiply = [&](const Half& h, int n, auto&& other) __attribute__((always_inline)) {
+    constexpr int kMfmas = 4 * TM * TN;
+    constexpr bool kBetween = TM * TN > 2;
+    static_assert(!kBetween || kMfmas >= TM + TN + IA + IW);
+    if (!kBetween) {
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const int at = ((kk * 4 + quad) ^ key) * 4;
-      f32x4 fa[TM], fw[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        fa[i] = *reinterpret_cast<const f32x4*>(s + (wm * 16 * TM + i * 16 + frag_row) * kFK + at);
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        fw[j] = *reinterpret_cast<const f32x4*>(s + (RA + wn * 16 * TN + j * 16 + frag_row) * kFK + at);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[j][e], fa[i][e], acc[i][j], 0, 0, 0);
+      for (int x = 0; x < n; ++x) other(x);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);          // this wave is done with the stage ...
-    __builtin_amdgcn_s_waitcnt(kWaitNewest);         // ... and its share of the next one has landed
+#pragma unroll
+    for (int m = 0; m < kMfmas; ++m) {
+      const int e = m / (TM * TN), i = m / TN % TM, j = m % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(h.f[TM + j][e], h.f[i][e], acc[i][j], 0, 0, 0);
+      if (kBetween && m < n) other(m);
+      if (kBetween || m == kMfmas - 1) __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  Half h0, h1;
+  // K-tile t on stage s, t + 1 on `next`.  On entry the first half's fragments are read (or on their way) and t + 1 and t + 2 in flight; at
+  // the barrier this wave is done with the stage and its share of t + 1 has landed.
+  auto step = [&](int t, float* s, const float* next) __attribute__((always_inline)) {
+    multiply(h0, TM + TN, [&](int x) __attribute__((always_inline)) { read_one(s, 1, h1, x); });
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    __builtin_amdgcn_s_waitcnt(kWaitNewest);
     w4_barrier();
+    multiply(h1, TM + TN + IA + IW, [&](int x) __attribute__((always_inline)) {
+      if (x < TM + TN) read_one(next, 0, h0, x);
+      else fetch_one(t + 3, s, x - TM - TN);
+    });
   };
   fetch(0, s0);
   fetch(1, s1);
-  __builtin_amdgcn_s_waitcnt(kWaitNewest);
+  fetch(2, s2);
+  __builtin_amdgcn_s_waitcnt(kWaitTwoNewest);
   w4_barrier();
+#pragma unroll
+  for (int x = 0; x < TM + TN; ++x) read_one(s0, 0, h0, x);
   for (int t = 0; t < kt_count; t += 3) {
     // Always three: up to two k-tiles of zeros at the end.  (With a branch between them the compiler
     // waits for all DMA before it reads a stage.)
-    step(t, s0, s2);
-    step(t + 1, s1, s0);
-    step(t + 2, s2, s1);
+    step(t, s0, s1);
+    step(t + 1, s1, s2);
+    step(t + 2, s2, s0);
   }
   __builtin_amdgcn_s_waitcnt(kWaitVm0);              // the last (empty) fetches
 
