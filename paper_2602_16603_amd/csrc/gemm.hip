@@ -209,7 +209,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
 // Global -> LDS goes through the DMA path (buffer_load_dwordx4 ... lds: no VGPR staging, no
 // ds_write).  A DMA instruction writes lane i's 16 bytes at base + 16*i, i.e. one wave fills
 // eight consecutive 128-byte LDS rows; the LDS swizzle is obtained by permuting which 16-byte
-// global chunk each lane fetches.  Two LDS stages (A and W, 32 KB each per stage) as four
+// global chunk each lane fetches.  Two LDS stages (A and W, 32 KB each per stage; less high or narrow tiles have three, below) as four
 // separate __shared__ arrays, so that the compiler can tell that DMA in flight to one stage does
 // not alias LDS reads of the other (otherwise it would serialise them with vmcnt(0)).  Wave w
 // fetches rows [64w, 64w+64) of both operands, 16 instructions per k-tile, all in the k-step after
@@ -263,22 +263,24 @@ __device__ __forceinline__ void w4_dma(__amdgpu_buffer_rsrc_t r, bf16* lds_rows,
 // tile of short requests, with half the W fragments and DMA instructions in the same slots).  Every other
 // instruction sits alone behind an MFMA: the fragment reads of the next k-step (EARLY: all in its first half,
 // for the k-step that ends at the barrier, so that the wait in front of the barrier finds them done; else
-// spread over the k-step), in the order of their first use (all of W, then the A blocks); if DMA, the wave's
-// MI + NJ DMA instructions (its A rows, then its W rows, 8 rows of 128 bytes each) in the second half of the A blocks' MFMAs.
+// spread over the k-step), in the order of their first use (all of W, then the A blocks); and D0 .. D1 - 1 of the wave's
+// MI + NJ DMA instructions (its A rows, then its W rows, 8 rows of 128 bytes each), evenly over the k-step: the CU takes one per 16
+// cycles from its four waves together.
 // The MFMA is written as inline assembly to accumulate in place: the compiler leaves the
 // destination of this 4-pass instruction free to differ from its accumulator input, which
 // overflows the completely used accumulation registers (the 8-pass 32x32x16 is tied by itself).
 // No accumulator is touched twice within MI NJ MFMAs, and LDS results reach the operands through
 // the s_waitcnt the compiler places for the asm inputs, so no software-managed hazard arises.
 enum { kReadsNone, kReadsSpread, kReadsEarly };
-template <int READS, bool DMA, int MI, int NJ, bool NT = false>
+template <int READS, int D0, int D1, int MI, int NJ, bool NT = false>
 __device__ __forceinline__ void w4_block(f32x4_acc (&acc)[MI][NJ], const W4Frags<MI, NJ>& cur, W4Frags<MI, NJ>& nxt,
                                          const bf16* rA, const bf16* rB, int pch,
                                          __amdgpu_buffer_rsrc_t rs_a, __amdgpu_buffer_rsrc_t rs_w, bf16* dA,
                                          bf16* dB, const uint32_t (&voff_a)[MI], const uint32_t (&voff)[8], int kbyte) {
   constexpr int kSpread = (MI + NJ + MI - 1) / MI;    // per A block, so that MI blocks place all of them
   constexpr int kReads = READS == kReadsNone ? 0 : READS == kReadsSpread ? kSpread : kSpread < NJ / 2 ? 2 * kSpread : NJ;
-  static_assert(kSpread <= NJ);
+  constexpr int kTwice = D1 > D0 ? 2 * (D1 - D0) : 1;
+  static_assert(kSpread <= NJ && 0 <= D0 && D0 <= D1 && D1 <= MI + NJ);
 #pragma unroll
   for (int s = 0; s < MI; ++s) {
 #pragma unroll
@@ -289,14 +291,13 @@ __device__ __forceinline__ void w4_block(f32x4_acc (&acc)[MI][NJ], const W4Frags
         if (r < NJ) nxt.b[r] = *reinterpret_cast<const bf16x8*>(rB + r * 16 * kBK + pch);
         else if (r < NJ + MI) nxt.a[r - NJ] = *reinterpret_cast<const bf16x8*>(rA + (r - NJ) * 16 * kBK + pch);
       }
-      if (DMA) {
 #pragma unroll
-        for (int i = 0; i < kSpread; ++i) {
-          const int d = kSpread * s + i;
-          if (j != NJ / 2 + i * (NJ / 2) / kSpread || d >= MI + NJ) continue;
-          if (d < MI) w4_dma(rs_a, dA + d * 8 * kBK, voff_a[d], kbyte);
-          else w4_dma<NT>(rs_w, dB + (d - MI) * 8 * kBK, voff[d - MI], kbyte);
-        }
+      for (int d = D0; d < D1; ++d) {
+        // (256 rows by 256 columns: two behind the second half of every A block, 0.3 % faster than one behind every fourth MFMA)
+        const int slot = D1 - D0 == 16 ? 4 + (d / 2) * 8 + d % 2 * 2 : (2 * (d - D0) + 1) * MI * NJ / kTwice;
+        if (slot != s * NJ + j) continue;
+        if (d < MI) w4_dma(rs_a, dA + d * 8 * kBK, voff_a[d], kbyte);
+        else w4_dma<NT>(rs_w, dB + (d - MI) * 8 * kBK, voff[d - MI], kbyte);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -344,12 +345,18 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 // 256-token request through the 8B-shaped stack 7.3 -> 6.5 ms; from three row tiles on the MFMAs
 // bound the launch and the wide tile's operand reuse wins).  Such a launch streams its weights from
 // HBM, every line for one or two workgroups only, and what a CU gets is its bytes in flight per
-// latency: the narrow tile's stages are three (144 KB, filled two k-tiles ahead) instead of two with
+// latency: the narrow tile's stages are three (144 KB, filled two to three k-tiles ahead) instead of two with
 // L2 warm-up.  Cold weights, 256 tokens of the 8B shape: gate_up 81 -> 71 us, down 48 -> 44;
-// 512 tokens: down 74 -> 66.  (The wide tile's three stages would take 192 KB.)
+// 512 tokens: down 74 -> 66.  (Three stages of the 256-row wide tile would take 192 KB.)
 //
 // STREAM (NJ = 4, one row tile, not cut): W is loaded non-temporally, as in the kernel for few rows below.  Narrow uncut tiles
 // may start at another k-tile (start_groups).
+//
+// Three stages (the narrow tile, and the wide one up to 160 rows, where they fit): half of a k-tile's DMA is issued in either k-step.  A CU
+// takes one DMA instruction per 16 cycles from its four waves, so all of a k-tile's in one k-step took longer than that k-step's
+// MFMAs on every tile but 256 x 256 (64 x 16 cycles there, as many as its MFMAs); with two stages the other k-step is what
+// they have to land in, and they are spread evenly (224 rows: 2100 -> 2040 cycles a k-tile).  Cold, us, with the heights chosen anew:
+// 600 x 14336 x 4096 SwiGLU 133 -> 122, 777 149 -> 145, 1300 x 6144 x 4096 66 -> 58, 1500 x 27648 x 5120 SwiGLU 632 -> 583.
 //
 // ROWS: the tile on 96, 128, .. 256 rows, the same sums in the same order.  What an uncut launch of few
 // rounds of tiles loses is its last, partly filled round and the padding of its last row tile; another height often
@@ -378,8 +385,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   __shared__ __attribute__((aligned(1024))) bf16 sA1[BM * kBK];
   __shared__ __attribute__((aligned(1024))) bf16 sB0[(WR > BM ? WR : BM) * kBK];   // (as large as an A stage: the epilogue
   __shared__ __attribute__((aligned(1024))) bf16 sB1[(NJ == 8 ? 256 : WR) * kBK];   //  stages its wave's outputs through the first four)
-  __shared__ __attribute__((aligned(1024))) bf16 sA2[NJ == 8 ? 8 : BM * kBK];      // third stage of the narrow tile
-  __shared__ __attribute__((aligned(1024))) bf16 sB2[NJ == 8 ? 8 : WR * kBK];
+  constexpr bool kThree = NJ == 4 || (ROWS <= 160 && !GROUPED && !KTAIL);         // stages: three where they fit, else two
+  __shared__ __attribute__((aligned(1024))) bf16 sA2[kThree ? BM * kBK : 8];
+  __shared__ __attribute__((aligned(1024))) bf16 sB2[kThree ? WR * kBK : 8];
   __shared__ __attribute__((aligned(256))) uint32_t sWarm[NJ == 8 ? 4 * 64 : 4];   // landing pad of the L2 warm-up loads
 
   const int tid = threadIdx.x;
@@ -491,7 +499,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   // for every other row of it, and nobody where the expert has one tile; gathered rows of A have an address each, and
   // their shares do not rotate (8192 tokens of the 30B-A3B shape: experts_up 409 -> 396 us, experts_down 335 -> 329).
   const int w_shares = warm_shares(w_sharers);
-  const __amdgpu_buffer_rsrc_t rsrc_warm = GROUPED && !shared ? rsrc_none
+  // Three stages hide what sharers wait for each other, and the extra requests then cost 2 to 5 % -- but not where rows lie an odd multiple
+  // of a power of two apart, whose lines crowd a few sets: 1900 x 7168 on 160 rows, without / with, K = 5120 172 / 153 us, 10240 338 / 299, 6144
+  // 186 / 179, 14336 426 / 397; 4096 113 / 116, 8192 216 / 224, 4160 118 / 121.
+  const bool warm_up = GROUPED ? shared : !kThree || (K % 512 == 0 && (K & (K - 1)) != 0);
+  const __amdgpu_buffer_rsrc_t rsrc_warm = !warm_up ? rsrc_none
                                            : wave == 0 ? (gathered ? rsrc_a : rsrc_warm_a)
                                            : w_shares > 0 && (wave == 1 || (w_shares == 2 && wave == 2)) ? rsrc_warm_w : rsrc_none;
   const int warm_mask = wave == 0 ? 3 : max(w_shares, 1) - 1;
@@ -520,13 +532,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   const bf16* const rB0 = sB0 + (wn * (WR / 2) + frag_row) * kBK;
   const bf16* const rB1 = sB1 + (wn * (WR / 2) + frag_row) * kBK;
 
-#define W4_WARM(u)                                                                                            \
-  __builtin_amdgcn_raw_ptr_buffer_load_lds((u) < kt_count ? rsrc_warm : rsrc_none,                            \
+// `last`: the last k-tile of the trip, which exists (the compiler does not always see that those before it do).
+#define W4_WARM(u, last)                                                                                      \
+  __builtin_amdgcn_raw_ptr_buffer_load_lds((u) <= (last) || (u) < kt_count ? rsrc_warm : rsrc_none,           \
                                            (__attribute__((address_space(3))) void*)warm, 4, voff_warm,       \
                                            kbyte(u) + ((warm_id - (u)) & warm_mask) * warm_step, 0, 0)
   f32x4_acc acc[MI][NJ];
   W4Frags<MI, NJ> f0, f1;
-  if constexpr (NJ == 8) {
+  if constexpr (!kThree) {
     // Prologue: k-tile 0 into stage 0 (awaited), k-tile 1 into stage 1 (in flight), then one warm-up
     // load, so that "all but one" is the right wait from the first barrier on.
 #pragma unroll
@@ -540,7 +553,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 #pragma unroll
       for (int s = 0; s < NJ; ++s) w4_dma(rw1, dB1 + s * 8 * kBK, voff[s], kbyte(1));
     }
-    W4_WARM(kWarmAhead - 1);
+    W4_WARM(kWarmAhead - 1, 0);
     __builtin_amdgcn_sched_barrier(0);
     // Cleared while the first k-tile is on its way.
 #pragma unroll
@@ -568,36 +581,37 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     // warm-up load must have landed; the barrier tells all waves that tile t+1 is complete and stage
     // c is free; k-step 1 (fed from registers) refills stage c with tile t+2, asks for the wave's
     // share of tile t+3's lines, and starts reading tile t+1.
-#define W4_TILE(t, c, o)                                                                                      \
+#define W4_TILE(first, x, last, c, o)                                                                         \
   {                                                                                                           \
-    const int t2_ = (t) + 2;                                                                                  \
-    w4_block<kReadsEarly, false, MI, NJ>(acc, f0, f1, rA##c, rB##c, pch1, rsrc_none, rsrc_none, dA##c, dB##c, voff_a, voff, 0); \
+    const int t2_ = (first) + (x) + 2;                                                                        \
+    const bool more_ = (x) + 2 <= (last) || t2_ < kt_count;                                                   \
+    w4_block<kReadsEarly, 0, 0, MI, NJ>(acc, f0, f1, rA##c, rB##c, pch1, rsrc_none, rsrc_none, dA##c, dB##c, voff_a, voff, 0); \
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                                                                   \
     __builtin_amdgcn_s_waitcnt(kWaitVm1);                                                                     \
     w4_barrier();                                                                                             \
-    w4_block<kReadsSpread, true, MI, NJ>(acc, f1, f0, rA##o, rB##o, pch0, t2_ < kt_count ? rsrc_a : rsrc_none,                   \
-                      t2_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t2_)); \
-    W4_WARM((t) + kWarmAhead);                                                                                \
+    w4_block<kReadsSpread, 0, MI + NJ, MI, NJ>(acc, f1, f0, rA##o, rB##o, pch0, more_ ? rsrc_a : rsrc_none, \
+                      more_ ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t2_)); \
+    W4_WARM((first) + (x) + kWarmAhead, (first) + (last));                                                                                \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
     }
     // Eight k-tiles per trip: the taken branch at the end of a trip costs the matrix pipe about 200
     // cycles.
     int t = 0;
     for (; t + 7 < kt_count; t += 8) {
-      W4_TILE(t, 0, 1);
-      W4_TILE(t + 1, 1, 0);
-      W4_TILE(t + 2, 0, 1);
-      W4_TILE(t + 3, 1, 0);
-      W4_TILE(t + 4, 0, 1);
-      W4_TILE(t + 5, 1, 0);
-      W4_TILE(t + 6, 0, 1);
-      W4_TILE(t + 7, 1, 0);
+      W4_TILE(t, 0, 7, 0, 1);
+      W4_TILE(t, 1, 7, 1, 0);
+      W4_TILE(t, 2, 7, 0, 1);
+      W4_TILE(t, 3, 7, 1, 0);
+      W4_TILE(t, 4, 7, 0, 1);
+      W4_TILE(t, 5, 7, 1, 0);
+      W4_TILE(t, 6, 7, 0, 1);
+      W4_TILE(t, 7, 7, 1, 0);
     }
     for (; t + 1 < kt_count; t += 2) {
-      W4_TILE(t, 0, 1);
-      W4_TILE(t + 1, 1, 0);
+      W4_TILE(t, 0, 1, 0, 1);
+      W4_TILE(t, 1, 1, 1, 0);
     }
-    if (t < kt_count) W4_TILE(t, 0, 1);
+    if (t < kt_count) W4_TILE(t, 0, 0, 0, 1);
 #undef W4_TILE
     if constexpr (KTAIL) {
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
@@ -618,21 +632,25 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
         f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
       }
       __builtin_amdgcn_sched_barrier(0);
-      w4_block<kReadsEarly, false, MI, NJ>(acc, f0, f1, rA0, rB0, pch1, rsrc_none, rsrc_none, dA0, dB0, voff_a, voff, 0);
-      w4_block<kReadsNone, false, MI, NJ>(acc, f1, f0, rA0, rB0, pch0, rsrc_none, rsrc_none, dA0, dB0, voff_a, voff, 0);
+      w4_block<kReadsEarly, 0, 0, MI, NJ>(acc, f0, f1, rA0, rB0, pch1, rsrc_none, rsrc_none, dA0, dB0, voff_a, voff, 0);
+      w4_block<kReadsNone, 0, 0, MI, NJ>(acc, f1, f0, rA0, rB0, pch0, rsrc_none, rsrc_none, dA0, dB0, voff_a, voff, 0);
     }
   } else {
-    // Three stages, filled two k-tiles ahead: k-tiles 0, 1 and 2 are requested here and k-tile 0 awaited.
-#define W4_FETCH(u, c)                                                                                        \
+    // Three stages, filled two to three k-tiles ahead, half of a k-tile's DMA in either k-step: k-tiles 0, 1 and the first half of 2
+    // are requested here and k-tile 0 awaited.
+    constexpr int HALF = (MI + NJ) / 2;
+#define W4_FETCH(u, c, n)                                                                                     \
   {                                                                                                           \
     const __amdgpu_buffer_rsrc_t ra_ = (u) < kt_count ? rsrc_a : rsrc_none, rw_ = (u) < kt_count ? rsrc_w : rsrc_none; \
-    _Pragma("unroll") for (int s = 0; s < MI; ++s) w4_dma(ra_, dA##c + s * 8 * kBK, voff_a[s], kbyte(u)); \
-    _Pragma("unroll") for (int s = 0; s < NJ; ++s) w4_dma<STREAM>(rw_, dB##c + s * 8 * kBK, voff[s], kbyte(u)); \
+    _Pragma("unroll") for (int s = 0; s < MI && s < (n); ++s) w4_dma(ra_, dA##c + s * 8 * kBK, voff_a[s], kbyte(u)); \
+    _Pragma("unroll") for (int s = 0; s < NJ && s < (n) - MI; ++s) w4_dma<STREAM>(rw_, dB##c + s * 8 * kBK, voff[s], kbyte(u)); \
   }
-    W4_FETCH(0, 0);
-    W4_FETCH(1, 1);
-    W4_FETCH(2, 2);
+    W4_FETCH(0, 0, MI + NJ);
+    W4_FETCH(1, 1, MI + NJ);
+    W4_FETCH(2, 2, HALF);
 #undef W4_FETCH
+    constexpr int WARM = NJ == 8;                    // (the narrow tile asks for nothing ahead)
+    if (WARM) W4_WARM(3, 0);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -645,7 +663,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 #pragma unroll
       for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(wait_vm<2 * (MI + NJ)>());   // all but k-tiles 1 and 2
+    __builtin_amdgcn_s_waitcnt(wait_vm<MI + NJ + HALF + WARM>());   // all but k-tiles 1 and 2 and the warm-up load
     w4_barrier();
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
@@ -653,34 +671,38 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
       if (s < MI) f0.a[s] = *reinterpret_cast<const bf16x8*>(rA0 + s * 16 * kBK + pch0);
     }
     __builtin_amdgcn_sched_barrier(0);
-    // As above, but at the barrier k-tile t + 2 may still be in flight, and k-step 1 asks for t + 3.
-#define W4_TILE(t, c, o)                                                                                      \
+    // As above (p: the stage before c), but k-step 0 asks for the second half of k-tile t + 2, which may still be in flight at the barrier,
+    // and k-step 1 for the first half of t + 3.
+#define W4_TILE(first, x, last, c, o, p)                                                                      \
   {                                                                                                           \
-    const int t3_ = (t) + 3;                                                                                  \
-    w4_block<kReadsEarly, false, MI, NJ>(acc, f0, f1, rA##c, rB##c, pch1, rsrc_none, rsrc_none, dA##c, dB##c, voff_a, voff, 0); \
+    const int t2_ = (first) + (x) + 2, t3_ = t2_ + 1;                                                         \
+    const bool more2_ = (x) + 2 <= (last) || t2_ < kt_count, more3_ = (x) + 3 <= (last) || t3_ < kt_count;    \
+    w4_block<kReadsEarly, HALF, MI + NJ, MI, NJ, STREAM>(acc, f0, f1, rA##c, rB##c, pch1, more2_ ? rsrc_a : rsrc_none, \
+                      more2_ ? rsrc_w : rsrc_none, dA##p, dB##p, voff_a, voff, kbyte(t2_));           \
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);                                                                   \
-    __builtin_amdgcn_s_waitcnt(wait_vm<MI + NJ>());                                                           \
+    __builtin_amdgcn_s_waitcnt(wait_vm<MI + NJ + WARM>());                                                    \
     w4_barrier();                                                                                             \
-    w4_block<kReadsSpread, true, MI, NJ, STREAM>(acc, f1, f0, rA##o, rB##o, pch0, t3_ < kt_count ? rsrc_a : rsrc_none,           \
-                      t3_ < kt_count ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t3_));             \
+    w4_block<kReadsSpread, 0, HALF, MI, NJ, STREAM>(acc, f1, f0, rA##o, rB##o, pch0, more3_ ? rsrc_a : rsrc_none, \
+                      more3_ ? rsrc_w : rsrc_none, dA##c, dB##c, voff_a, voff, kbyte(t3_));           \
+    if (WARM) W4_WARM((first) + (x) + kWarmAhead + 1, (first) + (last));                                                                       \
     __builtin_amdgcn_sched_barrier(0);                                                                        \
   }
     int t = 0;
     for (; t + 5 < kt_count; t += 6) {
-      W4_TILE(t, 0, 1);
-      W4_TILE(t + 1, 1, 2);
-      W4_TILE(t + 2, 2, 0);
-      W4_TILE(t + 3, 0, 1);
-      W4_TILE(t + 4, 1, 2);
-      W4_TILE(t + 5, 2, 0);
+      W4_TILE(t, 0, 5, 0, 1, 2);
+      W4_TILE(t, 1, 5, 1, 2, 0);
+      W4_TILE(t, 2, 5, 2, 0, 1);
+      W4_TILE(t, 3, 5, 0, 1, 2);
+      W4_TILE(t, 4, 5, 1, 2, 0);
+      W4_TILE(t, 5, 5, 2, 0, 1);
     }
     for (; t + 2 < kt_count; t += 3) {
-      W4_TILE(t, 0, 1);
-      W4_TILE(t + 1, 1, 2);
-      W4_TILE(t + 2, 2, 0);
+      W4_TILE(t, 0, 2, 0, 1, 2);
+      W4_TILE(t, 1, 2, 1, 2, 0);
+      W4_TILE(t, 2, 2, 2, 0, 1);
     }
-    if (t < kt_count) W4_TILE(t, 0, 1);
-    if (t + 1 < kt_count) W4_TILE(t + 1, 1, 2);
+    if (t < kt_count) W4_TILE(t, 0, 0, 0, 1, 2);
+    if (t + 1 < kt_count) W4_TILE(t, 1, 1, 1, 2, 0);
   }
 #undef W4_TILE
 #undef W4_WARM

@@ -73,18 +73,18 @@ inline int start_groups(int64_t m, int64_t n, int64_t k) {
 
 // Rows of the large tile (256 columns; SwiGLU 128 outputs; K % 64 == 0, not cut).  A CU works off its tiles one after the other;
 // a launch of a few rounds loses what its last round leaves empty and the padding of its last row tile, a smaller tile
-// reads W more often.  The rule is an estimate in ns fitted to 698 problems on all five heights (257-9000 rows, the dense
+// reads W more often.  The rule is an estimate in ns fitted to 700 problems on all five heights (257-9000 rows, the dense
 // shapes' projections and drawn ones, cold weights): a round costs a fixed part and a part per k, a partly filled one at
-// least 0.67 of that.  Its choice is 0.4 % slower than the best of the five and 8.2 % faster than 256 rows on average, more than 1 %
-// slower than those on 9 problems, by 2.7 % at most.  us, 256 rows against the choice: 3001 x 7168 x 5120 221 -> 192 (192 rows),
-// 1500 x 6144 x 4096 82 -> 68 (160), 300 x 14336 x 4096 SwiGLU 94 -> 87 (160), 3129 x 5120 x 27648 with residual 1264 -> 926.
+// least 0.66 of that.  Its choice is 0.2 % slower than the best of the five and 9.0 % faster than 256 rows on average, more than 1 %
+// slower than those on 4 problems, by 1.04 at most.  us, 256 rows against the choice: 600 x 14336 x 4096 SwiGLU 139 -> 121 (160 rows),
+// 1300 x 6144 x 4096 73 -> 57 (160), 3001 x 27648 x 5120 SwiGLU 1255 -> 1204 (224), 3000 x 14336 x 4096 SwiGLU 514 -> 492 (192).
 enum class LargeEpilogue { kBf16, kSwiGLU, kResidual };
 
 inline double large_tile_ns(int rows, int64_t m, int64_t tiles_n, int64_t k, LargeEpilogue epilogue) {
-  const double per_k = rows == 128 ? 14.8 : rows == 160 ? 15.4 : rows == 192 ? 16.5 : rows == 224 ? 18.7 : 19.8;
-  const double fixed = epilogue == LargeEpilogue::kResidual ? 17300 : epilogue == LargeEpilogue::kSwiGLU ? 8900 : 8100;
+  const double per_k = rows == 128 ? 12.66 : rows == 160 ? 14.56 : rows == 192 ? 16.51 : rows == 224 ? 18.02 : 20.76;
+  const double fixed = epilogue == LargeEpilogue::kResidual ? 20880 : epilogue == LargeEpilogue::kSwiGLU ? 8370 : 6890;
   const int64_t tiles = (m + rows - 1) / rows * tiles_n, left = tiles % 256;
-  return (tiles / 256 + (left ? 0.67 + 0.33 * left / 256.0 : 0.0)) * (fixed * rows / 256.0 + per_k * (double)k);
+  return (tiles / 256 + (left ? 0.66 + 0.34 * left / 256.0 : 0.0)) * (fixed * rows / 256.0 + per_k * (double)k);
 }
 
 inline int large_tile_rows(int64_t m, int64_t tiles_n, int64_t k, LargeEpilogue epilogue) {
