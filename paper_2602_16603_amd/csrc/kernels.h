@@ -120,12 +120,12 @@ void launch_kv_gather(int dtype, const void* k_pool, const void* v_pool, void* k
 
 // Mixture-of-experts FFN (bf16 path).  plan = device int32 [n_experts] (row offset of every
 // expert); block_counts = device int32 [moe_route_blocks(T)][n_experts]; slot_of = device int32
-// [T*top_k] (rank inside the route workgroup after launch_moe_route, final row after
-// launch_moe_gather); groups = device int32 [1 + 3 * (T*top_k/tile_rows + n_experts)]: the row-tile
+// [T*top_k] and row_token = the token of every row (final after launch_moe_index, which has something left to do only
+// where launch_moe_route's plan does not place the pairs itself); groups = device int32 [1 + 3 * (T*top_k/tile_rows + n_experts)]: the row-tile
 // table launch_gemm_grouped reads.
 int moe_route_blocks(int64_t n_tokens);
 void launch_moe_route(const float* logits, int32_t* ids, float* wts, int32_t* slot_of, int32_t* plan,
-                      int32_t* block_counts, int32_t* groups, int64_t n_tokens, int n_experts, int top_k,
+                      int32_t* block_counts, int32_t* groups, int32_t* row_token, int64_t n_tokens, int n_experts, int top_k,
                       int tile_rows, hipStream_t s);
 void launch_moe_index(const int32_t* ids, const int32_t* plan, const int32_t* block_counts,
                       int32_t* slot_of, int32_t* row_token, int64_t n_tokens, int top_k, int n_experts,

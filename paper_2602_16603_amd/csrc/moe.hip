@@ -112,28 +112,10 @@ __global__ __launch_bounds__(1024) void moe_route_kernel(const float* __restrict
   if (threadIdx.x < n_experts) block_counts[(int64_t)blockIdx.x * n_experts + threadIdx.x] = hist[threadIdx.x];
 }
 
-// One workgroup: per-expert totals and row offsets, the route workgroups' counts turned into
-// their first row inside each expert's range (in place), and the grouped GEMMs' row-tile table.
-//   plan[0 .. E) offsets;   groups[0] = row tiles, then {expert, first row, rows} per tile of tile_rows rows
-__global__ __launch_bounds__(256) void moe_plan_kernel(int32_t* __restrict__ plan,
-                                                       int32_t* __restrict__ block_counts,
-                                                       int32_t* __restrict__ groups, int n_experts,
-                                                       int n_blocks, int tile_rows) {
+// Row offset of expert e among all experts' rows (256 threads, thread e of an expert with `total` rows; all of them call), and, if `table`,
+// the grouped GEMMs' row-tile table: groups[0] = row tiles, then {expert, first row, rows} per tile of tile_rows rows.
+__device__ __forceinline__ int expert_rows(int total, int e, int n_experts, int tile_rows, bool table, int32_t* __restrict__ groups) {
   __shared__ int s_rows[4], s_tiles[4];
-  const int e = threadIdx.x;
-  int total = 0;
-  if (e < n_experts)
-    for (int b0 = 0; b0 < n_blocks; b0 += 16) {    // 16 loads in flight, then their prefix, then 16 stores
-      int c[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        c[i] = b0 + i < n_blocks ? block_counts[(int64_t)(b0 + i) * n_experts + e] : 0;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        if (b0 + i < n_blocks) block_counts[(int64_t)(b0 + i) * n_experts + e] = total;
-        total += c[i];
-      }
-    }
   // The 256-row tile multiplies only the multiple of 32 rows that a tile has: an expert's rows are spread evenly over as
   // few tiles as hold them (520 rows: three tiles of 192, where 256 + 256 + 8 are three full ones and the last is bound by
   // the latency of its k-tiles however few rows it has).
@@ -156,15 +138,40 @@ __global__ __launch_bounds__(256) void moe_plan_kernel(int32_t* __restrict__ pla
   off -= total;
   first -= tiles;
   for (int w = 0; w < (e >> 6); ++w) { off += s_rows[w]; first += s_tiles[w]; }
-  if (e == 0) groups[0] = s_tiles[0] + s_tiles[1] + s_tiles[2] + s_tiles[3];
-  if (e < n_experts) {
-    plan[e] = off;
+  if (table && e == 0) groups[0] = s_tiles[0] + s_tiles[1] + s_tiles[2] + s_tiles[3];
+  if (table && e < n_experts)
     for (int m = 0; m < total; m += rows, ++first) {
       groups[1 + 3 * first] = e;
       groups[2 + 3 * first] = off + m;
       groups[3 + 3 * first] = min(rows, total - m);
     }
-  }
+  return off;
+}
+
+
+// One workgroup: per-expert totals and row offsets, the route workgroups' counts turned into
+// their first row inside each expert's range (in place), and the grouped GEMMs' row-tile table.
+//   plan[0 .. E) offsets;   groups[0] = row tiles, then {expert, first row, rows} per tile of tile_rows rows
+__global__ __launch_bounds__(256) void moe_plan_kernel(int32_t* __restrict__ plan,
+                                                       int32_t* __restrict__ block_counts,
+                                                       int32_t* __restrict__ groups, int n_experts,
+                                                       int n_blocks, int tile_rows) {
+  const int e = threadIdx.x;
+  int total = 0;
+  if (e < n_experts)
+    for (int b0 = 0; b0 < n_blocks; b0 += 16) {    // 16 loads in flight, then their prefix, then 16 stores
+      int c[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        c[i] = b0 + i < n_blocks ? block_counts[(int64_t)(b0 + i) * n_experts + e] : 0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        if (b0 + i < n_blocks) block_counts[(int64_t)(b0 + i) * n_experts + e] = total;
+        total += c[i];
+      }
+    }
+  const int off = expert_rows(total, e, n_experts, tile_rows, true, groups);
+  if (e < n_experts) plan[e] = off;
 }
 
 // One thread per (token, choice): the pair's row = expert's offset + its route workgroup's first
@@ -183,6 +190,49 @@ __global__ __launch_bounds__(256) void moe_index_kernel(const int32_t* __restric
   const int slot = plan[e] + block_counts[(int64_t)(token / tokens_per_block) * n_experts + e] + slot_of[pair];
   slot_of[pair] = slot;
   row_token[slot] = token;
+}
+
+// Both of the above in one launch for up to kFusedPlanBlocks route workgroups: workgroup b adds up the counts itself (four threads per
+// expert, each a quarter of the route workgroups) and places the pairs of route workgroup b; the first one writes the table.  A launch
+// and the gap before it less: gate and experts_up together, us, 16 tokens 101 -> 98, 590 tokens 162 -> 160, 4096 299 -> 296, 16000 741 -> 733.
+// Every workgroup reads all counts, so their number squared bounds it: beyond the line the two kernels.
+constexpr int kFusedPlanBlocks = 256;
+__global__ __launch_bounds__(1024) void moe_plan_index_kernel(const int32_t* __restrict__ ids,
+                                                              const int32_t* __restrict__ block_counts,
+                                                              int32_t* __restrict__ slot_of, int32_t* __restrict__ row_token,
+                                                              int32_t* __restrict__ groups, int n_pairs, int top_k, int n_experts,
+                                                              int n_blocks, int tokens_per_block, int tile_rows) {
+  __shared__ int s_total[4][256], s_before[4][256], s_base[256];
+  const int e = threadIdx.x & 255, part = threadIdx.x >> 8;
+  const int lo = n_blocks * part / 4, hi = n_blocks * (part + 1) / 4;
+  int total = 0, before = 0;
+  if (e < n_experts)
+    for (int b0 = lo; b0 < hi; b0 += 16) {           // 16 loads in flight
+      int c[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) c[i] = b0 + i < hi ? block_counts[(int64_t)(b0 + i) * n_experts + e] : 0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        total += c[i];
+        before += b0 + i < (int)blockIdx.x ? c[i] : 0;
+      }
+    }
+  s_total[part][e] = total;
+  s_before[part][e] = before;
+  __syncthreads();
+  total = s_total[0][e] + s_total[1][e] + s_total[2][e] + s_total[3][e];
+  before = s_before[0][e] + s_before[1][e] + s_before[2][e] + s_before[3][e];
+  // (Four waves' prefix sums; the other twelve repeat them, since everybody calls.)
+  const int off = expert_rows(total, e, n_experts, tile_rows, blockIdx.x == 0 && part == 0, groups);
+  if (part == 0) s_base[e] = off + before;
+  __syncthreads();
+  const int per_block = tokens_per_block * top_k, first = blockIdx.x * per_block;
+  for (int i = threadIdx.x; i < per_block && first + i < n_pairs; i += 1024) {
+    const int pair = first + i;
+    const int slot = s_base[ids[pair]] + slot_of[pair];
+    slot_of[pair] = slot;
+    row_token[slot] = pair / top_k;
+  }
 }
 
 // x[t] += sum_j wts[t][j] * y[slot_of[t][j]], j ascending, fp32.
@@ -210,18 +260,24 @@ int moe_route_blocks(int64_t n_tokens) {
   return (int)((n_tokens + per - 1) / per);
 }
 
+// Selection, row plan and index (up to kFusedPlanBlocks route workgroups; beyond, launch_moe_index has the index left to do).
 void launch_moe_route(const float* logits, int32_t* ids, float* wts, int32_t* slot_of, int32_t* plan,
-                      int32_t* block_counts, int32_t* groups, int64_t n_tokens, int n_experts, int top_k,
+                      int32_t* block_counts, int32_t* groups, int32_t* row_token, int64_t n_tokens, int n_experts, int top_k,
                       int tile_rows, hipStream_t s) {
-  const int n_blocks = moe_route_blocks(n_tokens);
-  moe_route_kernel<<<dim3((unsigned)n_blocks), route_tokens_per_block(n_tokens) / kRouteTokensPerWave * 64, 0, s>>>(logits, ids, wts, slot_of, block_counts, (int)n_tokens,
+  const int n_blocks = moe_route_blocks(n_tokens), per_block = route_tokens_per_block(n_tokens);
+  moe_route_kernel<<<dim3((unsigned)n_blocks), per_block / kRouteTokensPerWave * 64, 0, s>>>(logits, ids, wts, slot_of, block_counts, (int)n_tokens,
                                                            n_experts, top_k);
-  moe_plan_kernel<<<1, 256, 0, s>>>(plan, block_counts, groups, n_experts, n_blocks, tile_rows);
+  if (n_blocks <= kFusedPlanBlocks)
+    moe_plan_index_kernel<<<dim3((unsigned)n_blocks), 1024, 0, s>>>(ids, block_counts, slot_of, row_token, groups, (int)(n_tokens * top_k),
+                                                                    top_k, n_experts, n_blocks, per_block, tile_rows);
+  else
+    moe_plan_kernel<<<1, 256, 0, s>>>(plan, block_counts, groups, n_experts, n_blocks, tile_rows);
 }
 
 void launch_moe_index(const int32_t* ids, const int32_t* plan, const int32_t* block_counts,
                       int32_t* slot_of, int32_t* row_token, int64_t n_tokens, int top_k, int n_experts,
                       hipStream_t s) {
+  if (moe_route_blocks(n_tokens) <= kFusedPlanBlocks) return;    // done with the plan
   const int64_t pairs = n_tokens * top_k;
   moe_index_kernel<<<dim3((unsigned)((pairs + 255) / 256)), 256, 0, s>>>(ids, plan, block_counts, slot_of, row_token,
                                                                         (int)pairs, top_k, n_experts,

@@ -155,7 +155,7 @@ fp_status launch_op(fp_prefill* t, int32_t index) {
     switch (op) {
       case 6:   // gate: router logits (fp32), selection, row plan
         fp::launch_router_gemm(t->h, w.w_router, t->moe_logits, T, E, d, s);
-        fp::launch_moe_route(t->moe_logits, ids, wts, t->moe_slot, t->moe_plan, t->moe_blocks, t->moe_groups, T, E, k,
+        fp::launch_moe_route(t->moe_logits, ids, wts, t->moe_slot, t->moe_plan, t->moe_blocks, t->moe_groups, t->moe_rows, T, E, k,
                              t->moe_tile_rows, s);
         break;
       case 7:   // experts, first half: gather per expert, gate/up projection + SiLU*up

@@ -262,3 +262,38 @@ def test_what_experts_add_to_each_token(n, ffn, seed):
     assert (off.view(blocks).norm(dim=2) / ref.view(blocks).norm(dim=2)).max().item() <= 1.6e-2
     task.end()
     model.close()
+
+
+@pytest.mark.parametrize("experts,top_k", [(8, 2), (256, 8)])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 1040, 2047, 2048, 2049, 16384, 16385])
+def test_every_pair_has_its_row(n, experts, top_k):
+    """Route workgroups of 16 and 64 tokens, the last of one token, of all but one and full; their counts added up by every workgroup
+    of the plan, or (16385 tokens and more) by one: what the layer adds to every token is its experts' weighted sum."""
+    B, R = _mods()
+    spec = I.ShapeSpec(1, 192, 2, 1, 64, 64, 1e-5, 10000.0, n_experts=experts, top_k=top_k)
+    weights = I.make_weights(spec, 63, torch.bfloat16, "cuda")
+    w = weights[0]
+    w["w_o"].zero_()
+    w["w_router"] *= torch.linspace(0.5, 1.5, experts, device="cuda")[:, None].to(torch.bfloat16)
+    x = I.make_hidden(n, spec.hidden, 63, torch.bfloat16, "cuda")
+    lengths = [512] * (n // 512) + ([n % 512] if n % 512 else [])
+    model = R.PrefillModel(spec, weights, B.FP_DTYPE_BF16, n // 16 + len(lengths) + 8, 512)
+    print(f"pairs' rows n={n} experts={experts}", flush=True)
+    task = model.begin(x, lengths)
+    task.run_to_completion()
+    ids, wts = task.moe_routing(0)
+    h, x32 = torch.empty_like(x), x.float()
+    torch.cuda.synchronize()
+    B.fp_op_rmsnorm(1, x32.data_ptr(), w["mlp_norm"].data_ptr(), h.data_ptr(), n, spec.hidden, spec.rms_eps)
+    torch.cuda.synchronize()
+    ref = torch.zeros(n, spec.hidden, dtype=torch.float64, device="cuda")
+    for e in range(experts):
+        token, slot = (ids == e).nonzero(as_tuple=True)
+        g, u = (h[token].double() @ w["w_gate_up"][e].double().T).split(spec.ffn, dim=1)
+        ref.index_add_(0, token, wts[token, slot, None].double() * ((torch.nn.functional.silu(g) * u) @ w["w_down"][e].double().T))
+    off = task.hidden().double() - x.double() - ref
+    # Four roundings to bf16, 2^-8 / sqrt(3) in the mean square each, the gate's up to doubled, over 64 products: 1.2e-2 of a token's
+    # contribution at most; a pair on a row that is not its own is 0.3 of it or more.
+    assert (off.norm(dim=1) / ref.norm(dim=1)).max().item() <= 2.4e-2
+    task.end()
+    model.close()
