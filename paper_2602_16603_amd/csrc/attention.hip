@@ -4,6 +4,7 @@
 // online softmax.  (The fp32 path has a file of its own.)
 #include "common.h"
 #include "kernels.h"
+#include "launch.h"
 
 namespace fp {
 
@@ -460,17 +461,17 @@ static void launch_attn_bf16(const void* qkv, const void* k_pool, const void* v_
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)D);
   dim3 grid((unsigned)((int64_t)m.n_attn_items * g.n_q_heads));
   if (m.n_attn_merges > 0)
-    attn_bf16_kernel<D, NW, true><<<grid, NW * 64, 0, s>>>(
+    launch_kernel(attn_bf16_kernel<D, NW, true>, grid, NW * 64, 0, s,
         (const bf16*)qkv, (const bf16*)k_pool, (const bf16*)v_pool, (bf16*)o, m.attn_part, g.n_q_heads,
         g.n_kv_heads, g.kv_num_blocks, layer, m.cu_seqlens, m.cached_lens, m.block_tables,
         m.max_blocks, m.attn_items, scale_log2);
   else
-    attn_bf16_kernel<D, NW, false><<<grid, NW * 64, 0, s>>>(
+    launch_kernel(attn_bf16_kernel<D, NW, false>, grid, NW * 64, 0, s,
         (const bf16*)qkv, (const bf16*)k_pool, (const bf16*)v_pool, (bf16*)o, nullptr, g.n_q_heads,
         g.n_kv_heads, g.kv_num_blocks, layer, m.cu_seqlens, m.cached_lens, m.block_tables,
         m.max_blocks, m.attn_items, scale_log2);
   if (m.n_attn_merges > 0)
-    attn_merge_kernel<D><<<dim3((unsigned)((int64_t)m.n_attn_merges * g.n_q_heads * 8)), 256, 0, s>>>(
+    launch_kernel(attn_merge_kernel<D>, dim3((unsigned)((int64_t)m.n_attn_merges * g.n_q_heads * 8)), 256, 0, s,
         m.attn_part, (bf16*)o, g.n_q_heads, m.cu_seqlens, m.attn_merges);
 }
 

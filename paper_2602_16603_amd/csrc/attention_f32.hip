@@ -3,6 +3,7 @@
 // semantics, unlike the bf16 kernel: this is the path on which a NaN is looked for.
 #include "common.h"
 #include "kernels.h"
+#include "launch.h"
 
 namespace fp {
 
@@ -144,7 +145,7 @@ template <int D>
 static void launch_attn_f32(const float* qkv, const float* k_pool, const float* v_pool, float* o,
                             const Geometry& g, const BatchMeta& m, int layer, hipStream_t s) {
   dim3 grid((unsigned)((int64_t)m.n_attn_items * 4 * g.n_q_heads));   // 64 of an item's 256 query rows each
-  attn_f32_kernel<D><<<grid, 256, 0, s>>>(qkv, k_pool, v_pool, o, g.n_q_heads, g.n_kv_heads, g.kv_num_blocks, layer,
+  launch_kernel(attn_f32_kernel<D>, grid, 256, 0, s, qkv, k_pool, v_pool, o, g.n_q_heads, g.n_kv_heads, g.kv_num_blocks, layer,
                                           m.cu_seqlens, m.cached_lens, m.block_tables, m.max_blocks, m.attn_items,
                                           1.0f / sqrtf((float)D));
 }

@@ -4,6 +4,7 @@
 // between the five core operators of Section 5.1).
 #include "common.h"
 #include "kernels.h"
+#include "launch.h"
 
 namespace fp {
 
@@ -80,9 +81,9 @@ void launch_rmsnorm(int dtype, const float* x, const void* gain, void* out, int6
   if (t == 0) return;
   dim3 grid((unsigned)t);
   if (dtype == 1)
-    rmsnorm_kernel<bf16><<<grid, 256, 0, s>>>(x, (const bf16*)gain, (bf16*)out, d, eps);
+    launch_kernel(rmsnorm_kernel<bf16>, grid, 256, 0, s, x, (const bf16*)gain, (bf16*)out, d, eps);
   else
-    rmsnorm_kernel<float><<<grid, 256, 0, s>>>(x, (const float*)gain, (float*)out, d, eps);
+    launch_kernel(rmsnorm_kernel<float>, grid, 256, 0, s, x, (const float*)gain, (float*)out, d, eps);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -113,10 +114,10 @@ void launch_task_start(int dtype, const void* in, float* x, const void* gain, vo
   dim3 grid((unsigned)(meta_blocks + t));
   if (grid.x == 0) return;
   if (dtype == 1)
-    task_start_kernel<bf16><<<grid, 256, 0, s>>>((const bf16*)in, x, (const bf16*)gain, (bf16*)out, d, eps,
+    launch_kernel(task_start_kernel<bf16>, grid, 256, 0, s, (const bf16*)in, x, (const bf16*)gain, (bf16*)out, d, eps,
                                                  (const u32x4*)meta_in, (u32x4*)meta_out, n_meta, meta_blocks);
   else
-    task_start_kernel<float><<<grid, 256, 0, s>>>((const float*)in, x, (const float*)gain, (float*)out, d, eps,
+    launch_kernel(task_start_kernel<float>, grid, 256, 0, s, (const float*)in, x, (const float*)gain, (float*)out, d, eps,
                                                   (const u32x4*)meta_in, (u32x4*)meta_out, n_meta, meta_blocks);
 }
 
@@ -144,9 +145,9 @@ void launch_silu_mul(int dtype, const void* gu, void* out, int64_t t, int64_t f,
   if (n == 0) return;
   dim3 grid((unsigned)((n + 255) / 256));
   if (dtype == 1)
-    silu_mul_kernel<bf16><<<grid, 256, 0, s>>>((const bf16*)gu, (bf16*)out, t, f);
+    launch_kernel(silu_mul_kernel<bf16>, grid, 256, 0, s, (const bf16*)gu, (bf16*)out, t, f);
   else
-    silu_mul_kernel<float><<<grid, 256, 0, s>>>((const float*)gu, (float*)out, t, f);
+    launch_kernel(silu_mul_kernel<float>, grid, 256, 0, s, (const float*)gu, (float*)out, t, f);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -324,17 +325,17 @@ void launch_rope_kvwrite(int dtype, void* qkv, const float* rope_cos, const floa
   if (m.n_tokens == 0) return;
   dim3 grid((unsigned)(m.n_tokens + m.n_kv_items));
   if (dtype == 1 && parts > 0)
-    rope_kvwrite_kernel<bf16, true><<<grid, 256, 0, s>>>(
+    launch_kernel(rope_kvwrite_kernel<bf16, true>, grid, 256, 0, s,
         (bf16*)qkv, rope_cos, rope_sin, g.n_q_heads, g.n_kv_heads, g.head_dim, g.kv_num_blocks,
         layer, (bf16*)k_pool, (bf16*)v_pool, m.n_tokens, m.tok_seq, m.tok_pos, m.cu_seqlens,
         m.cached_lens, m.block_tables, m.max_blocks, m.kv_items, part, parts);
   else if (dtype == 1)
-    rope_kvwrite_kernel<bf16, false><<<grid, 256, 0, s>>>(
+    launch_kernel(rope_kvwrite_kernel<bf16, false>, grid, 256, 0, s,
         (bf16*)qkv, rope_cos, rope_sin, g.n_q_heads, g.n_kv_heads, g.head_dim, g.kv_num_blocks,
         layer, (bf16*)k_pool, (bf16*)v_pool, m.n_tokens, m.tok_seq, m.tok_pos, m.cu_seqlens,
         m.cached_lens, m.block_tables, m.max_blocks, m.kv_items, nullptr, 0);
   else
-    rope_kvwrite_kernel<float, false><<<grid, 256, 0, s>>>(
+    launch_kernel(rope_kvwrite_kernel<float, false>, grid, 256, 0, s,
         (float*)qkv, rope_cos, rope_sin, g.n_q_heads, g.n_kv_heads, g.head_dim, g.kv_num_blocks,
         layer, (float*)k_pool, (float*)v_pool, m.n_tokens, m.tok_seq, m.tok_pos, m.cu_seqlens,
         m.cached_lens, m.block_tables, m.max_blocks, m.kv_items, nullptr, 0);
@@ -399,11 +400,11 @@ void launch_kv_gather(int dtype, const void* k_pool, const void* v_pool, void* k
   const int64_t n = (int64_t)((len + kKvBlock - 1) / kKvBlock) * g.n_kv_heads * (g.head_dim / 4);
   dim3 grid((unsigned)((n + 255) / 256), 2);
   if (dtype == 1)
-    kv_gather_kernel<bf16><<<grid, 256, 0, s>>>((const bf16*)k_pool, (const bf16*)v_pool,
+    launch_kernel(kv_gather_kernel<bf16>, grid, 256, 0, s, (const bf16*)k_pool, (const bf16*)v_pool,
                                                 (bf16*)k_out, (bf16*)v_out, len, g.n_kv_heads,
                                                 g.head_dim, g.kv_num_blocks, layer, table_dev);
   else
-    kv_gather_kernel<float><<<grid, 256, 0, s>>>((const float*)k_pool, (const float*)v_pool,
+    launch_kernel(kv_gather_kernel<float>, grid, 256, 0, s, (const float*)k_pool, (const float*)v_pool,
                                                  (float*)k_out, (float*)v_out, len, g.n_kv_heads,
                                                  g.head_dim, g.kv_num_blocks, layer, table_dev);
 }

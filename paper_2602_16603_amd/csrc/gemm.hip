@@ -9,6 +9,7 @@
 #include "common.h"
 #include "gemm_plan.h"
 #include "kernels.h"
+#include "launch.h"
 
 namespace fp {
 
@@ -1205,7 +1206,7 @@ static void launch_bf16_any(const bf16* a, const bf16* w, void* c, int m, int n,
       hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WGM, WGN, RESID, SWIGLU>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   (void)attr_set;
-  gemm_bf16_kernel<BM, BN, WGM, WGN, RESID, SWIGLU><<<dim3((unsigned)(tiles_m * tiles_n)), WGM * WGN * 64, smem, s>>>(
+  launch_kernel(gemm_bf16_kernel<BM, BN, WGM, WGN, RESID, SWIGLU>, dim3((unsigned)(tiles_m * tiles_n)), WGM * WGN * 64, smem, s,
       a, w, c, m, n, k, tiles_m, tiles_n);
 }
 
@@ -1258,7 +1259,7 @@ static int launch_ring(const bf16* a, const bf16* w, void* c, int m, int n, int 
   using T = RingTile<MI, EPI == kEpiSwiGLU, LONG_K>;
   const int tiles_m = (m + 16 * MI - 1) / (16 * MI), tiles_n = (n + T::BN - 1) / T::BN;
   const KRanges r = ring_ranges<MI, EPI>(n, k, splits);
-  gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, EPI, false, STREAM><<<dim3((unsigned)(tiles_m * tiles_n * r.used)), 256, 0, s>>>(
+  launch_kernel(gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, EPI, false, STREAM>, dim3((unsigned)(tiles_m * tiles_n * r.used)), 256, 0, s,
       a, w, c, m, n, k, tiles_m, tiles_n, r.per, start_groups, nullptr, nullptr);
   return r.used;
 }
@@ -1304,7 +1305,7 @@ void launch_router_gemm(const void* a, const void* w, float* logits, int64_t m, 
 template <int EPI, int ROWS>
 static void launch_large_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int tiles_n, hipStream_t s) {
   const int tiles_m = (m + ROWS - 1) / ROWS;
-  gemm_bf16_w4_kernel<EPI, false, 8, false, ROWS><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(
+  launch_kernel(gemm_bf16_w4_kernel<EPI, false, 8, false, ROWS>, dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s,
       a, w, c, m, n, k, tiles_m, tiles_n, k / kBK, 0, nullptr, nullptr);
 }
 template <int EPI>
@@ -1333,10 +1334,10 @@ static void launch_even_rows(const bf16* a, const bf16* w, void* c, int m, int n
   auto launch = [&](auto rows) {
     constexpr int ROWS = decltype(rows)::value;
     if (kUncut && tiles_m == 1)
-      gemm_bf16_w4_kernel<EPI, false, NJ, false, ROWS, kUncut><<<dim3((unsigned)tiles_n), 256, 0, s>>>(
+      launch_kernel(gemm_bf16_w4_kernel<EPI, false, NJ, false, ROWS, kUncut>, dim3((unsigned)tiles_n), 256, 0, s,
           a, w, c, m, n, k, 1, tiles_n, kt_per_split, starts, nullptr, nullptr);
     else
-      gemm_bf16_w4_kernel<EPI, false, NJ, false, ROWS><<<dim3((unsigned)(tiles_m * tiles_n * splits)), 256, 0, s>>>(
+      launch_kernel(gemm_bf16_w4_kernel<EPI, false, NJ, false, ROWS>, dim3((unsigned)(tiles_m * tiles_n * splits)), 256, 0, s,
           a, w, c, m, n, k, tiles_m, tiles_n, kt_per_split, starts, nullptr, nullptr);
   };
   const int rows = (m + tiles_m - 1) / tiles_m;
@@ -1397,9 +1398,8 @@ static void launch_grouped_ring(const bf16* a, const bf16* w, void* c, int n, in
   constexpr bool SWIGLU = EPI == kEpiSwiGLU;
   constexpr int NJ = 2, KT = 64, S = MI == 8 ? 2 : MI == 4 ? 3 : 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
   const int tiles_n = (n + BN - 1) / BN;
-  gemm_bf16_ring_kernel<MI, NJ, KT, S, EPI, true>
-      <<<dim3((unsigned)((max_row_tiles + kXcds - 1) / kXcds * kXcds * tiles_n)), 256, 0, s>>>(
-          a, w, c, m_arg, n, k, max_row_tiles, tiles_n, k / kBK, 0, groups, a_rows);
+  launch_kernel(gemm_bf16_ring_kernel<MI, NJ, KT, S, EPI, true>, dim3((unsigned)((max_row_tiles + kXcds - 1) / kXcds * kXcds * tiles_n)), 256, 0, s,
+      a, w, c, m_arg, n, k, max_row_tiles, tiles_n, k / kBK, 0, groups, a_rows);
 }
 
 void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64_t k, int swiglu,
@@ -1421,10 +1421,10 @@ void launch_gemm_grouped(const void* a, const void* w, void* c, int64_t n, int64
   const dim3 grid((unsigned)((max_row_tiles + kXcds - 1) / kXcds * kXcds * tiles_n));   // a whole number of row tiles per XCD
   const int m_arg = a_rows ? (int)a_total_rows : 0;
   if (swiglu)
-    gemm_bf16_w4_kernel<kEpiSwiGLU, true><<<grid, 256, 0, s>>>((const bf16*)a, (const bf16*)w, c, m_arg, (int)n,
+    launch_kernel(gemm_bf16_w4_kernel<kEpiSwiGLU, true>, grid, 256, 0, s, (const bf16*)a, (const bf16*)w, c, m_arg, (int)n,
                                                               (int)k, max_row_tiles, tiles_n, (int)(k / kBK), 0, groups, a_rows);
   else
-    gemm_bf16_w4_kernel<kEpiBf16, true><<<grid, 256, 0, s>>>((const bf16*)a, (const bf16*)w, c, m_arg, (int)n,
+    launch_kernel(gemm_bf16_w4_kernel<kEpiBf16, true>, grid, 256, 0, s, (const bf16*)a, (const bf16*)w, c, m_arg, (int)n,
                                                             (int)k, max_row_tiles, tiles_n, (int)(k / kBK), 0, groups, a_rows);
 }
 
@@ -1454,13 +1454,13 @@ static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, 
   if (tail.kind == kTailLeave) return;               // (gemm_left_ranges tells the caller how many ranges)
   const int64_t mn = (int64_t)m * n;
   if (RESID && tail.kind == kTailRmsNorm)
-    splitk_reduce_norm_kernel<<<dim3((unsigned)m), 256, 0, s>>>(workspace, (float*)c, (const bf16*)tail.gain,
+    launch_kernel(splitk_reduce_norm_kernel, dim3((unsigned)m), 256, 0, s, workspace, (float*)c, (const bf16*)tail.gain,
                                                                (bf16*)tail.out, mn, n, used, tail.eps);
   else if (!RESID && tail.kind == kTailSwiGLU)
-    splitk_reduce_swiglu_kernel<<<dim3((unsigned)(((int64_t)m * (n / 2) / 8 + 255) / 256)), 256, 0, s>>>(
+    launch_kernel(splitk_reduce_swiglu_kernel, dim3((unsigned)(((int64_t)m * (n / 2) / 8 + 255) / 256)), 256, 0, s,
         workspace, (bf16*)tail.out, m, n / 2, used);
   else
-    splitk_reduce_kernel<RESID><<<dim3((unsigned)((mn / 8 + 255) / 256)), 256, 0, s>>>(workspace, c, mn / 8,
+    launch_kernel(splitk_reduce_kernel<RESID>, dim3((unsigned)((mn / 8 + 255) / 256)), 256, 0, s, workspace, c, mn / 8,
                                                                                      mn, used);
 }
 
@@ -1624,7 +1624,8 @@ template <int TM, int TN, int WM, bool RESID>
 static void launch_f32_mfma(const float* a, const float* w, float* c, int m, int n, int k, hipStream_t s) {
   constexpr int BM = 16 * TM * WM, BN = 16 * TN * (4 / WM);
   const int tiles_m = (m + BM - 1) / BM, tiles_n = (n + BN - 1) / BN;
-  gemm_f32_mfma_kernel<TM, TN, WM, RESID><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(a, w, c, m, n, k, tiles_m, tiles_n);
+  launch_kernel(gemm_f32_mfma_kernel<TM, TN, WM, RESID>, dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s,
+      a, w, c, m, n, k, tiles_m, tiles_n);
 }
 
 template <bool RESID>
@@ -1746,7 +1747,7 @@ static void launch_small_problem(const bf16* a, const bf16* w, void* c, int m, i
     case GemmTile::kAny128: launch_bf16_any<RESID>(a, w, c, m, n, k, s); break;
     case GemmTile::kLarge: {
       const int tiles_m = (m + 255) / 256, tiles_n = (n + 255) / 256;
-      gemm_bf16_w4_kernel<EPI, false, 8, true><<<dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s>>>(
+      launch_kernel(gemm_bf16_w4_kernel<EPI, false, 8, true>, dim3((unsigned)(tiles_m * tiles_n)), 256, 0, s,
           a, w, c, m, n, k, tiles_m, tiles_n, k / kBK, 0, nullptr, nullptr);
       break;
     }
@@ -1766,10 +1767,10 @@ void launch_gemm(int dtype, const void* a, const void* w, void* c, int64_t m, in
     }
     dim3 grid((unsigned)((n + 63) / 64), (unsigned)((m + 63) / 64));
     if (residual)
-      gemm_f32_kernel<true><<<grid, 256, 0, s>>>((const float*)a, (const float*)w, (float*)c,
+      launch_kernel(gemm_f32_kernel<true>, grid, 256, 0, s, (const float*)a, (const float*)w, (float*)c,
                                                   (int)m, (int)n, (int)k);
     else
-      gemm_f32_kernel<false><<<grid, 256, 0, s>>>((const float*)a, (const float*)w, (float*)c,
+      launch_kernel(gemm_f32_kernel<false>, grid, 256, 0, s, (const float*)a, (const float*)w, (float*)c,
                                                    (int)m, (int)n, (int)k);
     return;
   }

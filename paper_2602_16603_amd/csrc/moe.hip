@@ -8,6 +8,7 @@
 // results.
 #include "common.h"
 #include "kernels.h"
+#include "launch.h"
 
 namespace fp {
 
@@ -265,13 +266,15 @@ void launch_moe_route(const float* logits, int32_t* ids, float* wts, int32_t* sl
                       int32_t* block_counts, int32_t* groups, int32_t* row_token, int64_t n_tokens, int n_experts, int top_k,
                       int tile_rows, hipStream_t s) {
   const int n_blocks = moe_route_blocks(n_tokens), per_block = route_tokens_per_block(n_tokens);
-  moe_route_kernel<<<dim3((unsigned)n_blocks), per_block / kRouteTokensPerWave * 64, 0, s>>>(logits, ids, wts, slot_of, block_counts, (int)n_tokens,
+  launch_kernel(moe_route_kernel, dim3((unsigned)n_blocks), per_block / kRouteTokensPerWave * 64, 0, s,
+      logits, ids, wts, slot_of, block_counts, (int)n_tokens,
                                                            n_experts, top_k);
   if (n_blocks <= kFusedPlanBlocks)
-    moe_plan_index_kernel<<<dim3((unsigned)n_blocks), 1024, 0, s>>>(ids, block_counts, slot_of, row_token, groups, (int)(n_tokens * top_k),
+    launch_kernel(moe_plan_index_kernel, dim3((unsigned)n_blocks), 1024, 0, s,
+        ids, block_counts, slot_of, row_token, groups, (int)(n_tokens * top_k),
                                                                     top_k, n_experts, n_blocks, per_block, tile_rows);
   else
-    moe_plan_kernel<<<1, 256, 0, s>>>(plan, block_counts, groups, n_experts, n_blocks, tile_rows);
+    launch_kernel(moe_plan_kernel, 1, 256, 0, s, plan, block_counts, groups, n_experts, n_blocks, tile_rows);
 }
 
 void launch_moe_index(const int32_t* ids, const int32_t* plan, const int32_t* block_counts,
@@ -279,7 +282,7 @@ void launch_moe_index(const int32_t* ids, const int32_t* plan, const int32_t* bl
                       hipStream_t s) {
   if (moe_route_blocks(n_tokens) <= kFusedPlanBlocks) return;    // done with the plan
   const int64_t pairs = n_tokens * top_k;
-  moe_index_kernel<<<dim3((unsigned)((pairs + 255) / 256)), 256, 0, s>>>(ids, plan, block_counts, slot_of, row_token,
+  launch_kernel(moe_index_kernel, dim3((unsigned)((pairs + 255) / 256)), 256, 0, s, ids, plan, block_counts, slot_of, row_token,
                                                                         (int)pairs, top_k, n_experts,
                                                                         route_tokens_per_block(n_tokens));
 }
@@ -287,7 +290,7 @@ void launch_moe_index(const int32_t* ids, const int32_t* plan, const int32_t* bl
 void launch_moe_combine(float* x, const void* y, const int32_t* slot_of, const float* wts,
                         int64_t n_tokens, int top_k, int d, hipStream_t s) {
   const int64_t n = n_tokens * (d / 8);
-  moe_combine_kernel<<<dim3((unsigned)((n + 255) / 256)), 256, 0, s>>>(x, (const bf16*)y, slot_of, wts, n_tokens,
+  launch_kernel(moe_combine_kernel, dim3((unsigned)((n + 255) / 256)), 256, 0, s, x, (const bf16*)y, slot_of, wts, n_tokens,
                                                                        top_k, d);
 }
 

@@ -26,6 +26,7 @@
 #include "common.h"
 #include "gemm_plan.h"
 #include "kernels.h"
+#include "launch.h"
 #include "task_core.h"
 
 namespace {
@@ -119,6 +120,7 @@ struct fp_prefill : fp::OpBackend {
   fp::TaskCore core;
   hipEvent_t ring[kMarkRing] = {};      // the task's own completion markers (from the model's pool)
   hipEvent_t slot_ev[kMarkRing] = {};   // event standing for marker slot i (ring[i], or a timing event)
+  bool carried = false;                 // the last operator's kernels carry its marker
   // per-op timing
   bool timing = false;
   std::vector<hipEvent_t> tev;          // timing events of the most recent advance call, in order
@@ -127,6 +129,7 @@ struct fp_prefill : fp::OpBackend {
 
   // ---- fp::OpBackend: what the state machine asks of the device ----
   void begin_call() override;
+  void expect_mark(int slot) override;
   int launch(int32_t index, bool* launched) override;
   int mark(int slot) override;
   int wait_mark(int slot) override;
@@ -312,6 +315,11 @@ void release_events(fp_model* m, bool with_timing, int n, hipEvent_t* ev) {
 
 }  // namespace
 
+fp::CarriedEvent& fp::carried_event() {
+  static thread_local CarriedEvent c;
+  return c;
+}
+
 // ---- the task as the state machine's device backend ----
 hipEvent_t fp_prefill::timing_event() {
   hipEvent_t ev = nullptr;
@@ -334,7 +342,15 @@ int fp_prefill::launch(int32_t index, bool* launched) {
   const int op = index % FP_OPS_PER_LAYER;
   *launched = !((swiglu_fused && op == 7) || (norm_after_o && op == 5) ||
                 index == 0 || (norm_after_down && op == 0));
-  return launch_op(this, index) == FP_OK ? 0 : -1;
+  const bool ok = launch_op(this, index) == FP_OK;
+  carried = fp::carried_event().taken;
+  fp::carried_event() = {};
+  return ok ? 0 : -1;
+}
+
+// The operator's own kernels carry its marker.  Timing reads the time between events, which is defined for recorded ones.
+void fp_prefill::expect_mark(int slot) {
+  if (!timing) fp::carried_event() = {ring[slot], false};
 }
 
 // One event per operator serves both the launch-ahead bound and the timing read-out (an event
@@ -344,7 +360,7 @@ int fp_prefill::mark(int slot) {
   if (timing) {
     ev = timing_event();
     if (!ev) return -1;
-  } else {
+  } else if (!carried) {
     hipError_t e = hipEventRecord(ev, model->stream);
     if (e != hipSuccess) { fail(FP_ERR_DEVICE, "event record: %s", hipGetErrorString(e)); return -1; }
   }

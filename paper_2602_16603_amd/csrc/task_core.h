@@ -30,6 +30,8 @@ struct OpBackend {
   virtual void begin_call() {}
   // Enqueues operator `index` (0 .. total-1).  *launched = false when the operator had no device work.
   virtual int launch(int32_t index, bool* launched) = 0;
+  // The next launch will be followed by mark(slot) if it has device work.
+  virtual void expect_mark(int /*slot*/) {}
   // Places completion marker `slot` (0 .. kMarkRing-1) behind everything enqueued so far.
   virtual int mark(int slot) = 0;
   // Blocks the host until marker `slot` has completed on the device.
@@ -80,10 +82,12 @@ class TaskCore {
       }
       if (issued == 0) be.begin_call();
       bool launched = true;
+      const bool marks = launch_ahead_ > 0 || be.wants_marks();
+      if (marks) be.expect_mark(marked % kMarkRing);
       if (be.launch(cur, &launched) != 0) { result = kTaskErrDevice; break; }
       // One marker per operator serves the launch-ahead bound (and the backend's timing); an
       // operator without device work places none and completes with its predecessor.
-      if (launched && (launch_ahead_ > 0 || be.wants_marks())) {
+      if (launched && marks) {
         if (be.mark(marked % kMarkRing) != 0) { result = kTaskErrDevice; break; }
         ++marked;
       }
