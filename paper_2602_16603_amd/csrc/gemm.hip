@@ -875,7 +875,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // experts' projections of the 30B-A3B shape, cold, us: 16 tokens 87 -> 80 and 55 -> 49, 590 tokens 164 -> 147 and 97 -> 92 (with the
 // combine).  Not the experts' gate_up on 128 rows, which loses by the hint from 70 rows per expert on (96 rows of 8 experts [4096 14336]
 // 390 us, 377 without; of 64 [4096 1536] 345 and 331) and gains less below (50 rows: 367 and 371, 314 and 320).
-// K ranges start at different k as it is, and gain nothing.
+// K ranges start at different k as it is, and gain nothing by more starts (50 x 5120 x 27648 57 us, 73 with them); by the hint, of up to 64 rows: 16 rows of
+// 4096 x 14336 24.6 -> 22.3, 6144 x 4096 14.3 -> 13.1, 50 rows of 4096 x 14336 27.1 -> 25.5, 5120 x 27648 57 -> 53.8, short K no change.  (Not the large
+// kernel's: 256 x 4096 x 14336 45 -> 44, but 100 x 4096 x 4096 16 -> 19, 256 x 5120 x 2048 19.5 -> 23.)
 // STREAM (uncut launches of one row tile, the W of all of them read once): the same two, the start by start_groups, which
 // keeps the fused projection and the plain one on one order of sums.  The hint by itself: 50 rows of [14336 outputs 4096]
 // 52.5 -> 49.3 us, 27648 x 5120 110 -> 103; with the starts 41.2, and 256 rows on the 128-column tile 68.2 -> 60.4.  Not on 128 rows here: 27648 x 5120
@@ -941,7 +943,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_ring_kernel(const bf16* __restr
     A += (int64_t)m0 * K;
     Cout = reinterpret_cast<char*>(Cout) + ((int64_t)m0 * N + slab) * (EPI == kEpiBf16 || SWIGLU ? 2 : 4);
     M = min(BM, M - m0);
-    if (STREAM) rot = k_start(tile_n * BN, K, start_groups) / KT;
+    if (STREAM && EPI != kEpiPartial) rot = k_start(tile_n * BN, K, start_groups) / KT;
   }
   const int n0 = tile_n * BN;
   const int k_first = split * kt_per_split * kBK;    // (K ranges are counted in k-tiles of 64)
@@ -1266,8 +1268,8 @@ static int launch_ring(const bf16* a, const bf16* w, void* c, int m, int n, int 
 // Returns the number of K ranges launched (at most `splits`).
 template <int EPI>
 static int launch_few_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
-  constexpr bool SWIGLU = EPI == kEpiSwiGLU, STREAM = SWIGLU || EPI == kEpiBf16;
-  const int starts = STREAM ? start_groups(m, SWIGLU ? 2 * (int64_t)n : n, k) : 0;
+  constexpr bool SWIGLU = EPI == kEpiSwiGLU, STREAM = EPI != kEpiResidual;
+  const int starts = STREAM && EPI != kEpiPartial ? start_groups(m, SWIGLU ? 2 * (int64_t)n : n, k) : 0;
   if (SWIGLU && k >= 3072) {
     if (m <= 32) return launch_ring<2, EPI, STREAM, SWIGLU>(a, w, c, m, n, k, splits, s, starts);
     if (m <= 64) return launch_ring<4, EPI, STREAM, SWIGLU>(a, w, c, m, n, k, splits, s, starts);
