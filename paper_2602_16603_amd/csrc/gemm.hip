@@ -254,9 +254,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t panel_rsrc(const void* base, u
 }
 
 // NT: non-temporal, for lines that one workgroup reads and nobody after it.
+constexpr int kAuxNonTemporal = 2;                 // of a buffer instruction: the nt bit
 template <bool NT = false>
 __device__ __forceinline__ void w4_dma(__amdgpu_buffer_rsrc_t r, bf16* lds_rows, uint32_t voff, int kbyte) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_rows, 16, voff, kbyte, 0, NT ? 2 : 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_rows, 16, voff, kbyte, 0, NT ? kAuxNonTemporal : 0);
 }
 
 // One k-step: MI NJ MFMAs from `cur` (A block s against the NJ W blocks, s = 0 .. MI - 1; MI = 8: the 256-row
@@ -764,6 +765,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
     }
   } else if (EPI == kEpiBf16) {
     // [128 rows][CH = 2 NJ chunks of 8 bf16], chunk c of row r at position c ^ (r & (CH-1)).
+    // The experts' outputs go past the L2, which the neighbours' panels want: with the combine, 30B-A3B shape, us, 1700 tokens 129 -> 125,
+    // 8192 336.5 -> 331, 16000 596 -> 577.  (Not those of gate_up, which the next kernel reads: 1700 tokens 183 -> 177, but 4096 272 -> 275;
+    // nor a dense projection's: no change.)
     constexpr int CH = 2 * NJ;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
@@ -787,7 +791,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
       const int idx = lane_out + it * 64;
       const int row = idx / CH, ch = idx % CH;
       const u32x4 v = *reinterpret_cast<const u32x4*>(region + row * (CH * 8) + ((ch ^ (row & (CH - 1))) << 3));
-      __builtin_amdgcn_raw_buffer_store_b128(v, rc, cbyte, it * (64 / CH) * N * 2, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(v, rc, cbyte, it * (64 / CH) * N * 2, GROUPED ? kAuxNonTemporal : 0);
     }
   } else {
     // fp32 residual (read-modify-write) or split-K partial (plain store into this split's [M][N]
