@@ -12,19 +12,20 @@
 
 namespace fp {
 
-// Router: four tokens per wave: probabilities, top_k selection, renormalised weights.  n_experts <= 256 (lane l holds experts l, l+64, l+128, l+192), top_k <= 8.  A selection step is
+// Router: Q tokens per wave: probabilities, top_k selection, renormalised weights.  n_experts <= 256 (lane l holds experts l, l+64, l+128, l+192), top_k <= 8.  A selection step is
 // a chain -- the wave's maximum by DPP, then the first lane that holds it by ballot (ties: lower index) -- so a
-// wave runs the chains of its four tokens side by side (29 us with one after the other on LDS-shuffle reductions).
+// wave runs the chains of its tokens side by side (29 us with one after the other on LDS-shuffle reductions).
 // Every chosen (token, expert) pair also takes a rank among the workgroup's pairs of
 // that expert (an LDS counter), and the workgroup leaves its per-expert counts in
 // block_counts[block][expert]: the row plan below needs no global atomics (65536 of them on 128
 // addresses cost more than the rest of the operator).
-// The selections are bound by instruction issue, so a short request takes workgroups of 16 tokens (590 tokens: 16 us on
-// ten workgroups of 64, 7 on 37); from 2048 tokens on 64 tokens each fill the chip and keep the plan's walk over
-// the workgroups short.
+// The selections are bound by instruction issue, so they are spread over the CUs as far as the plan's walk over the workgroups'
+// counts allows (kFusedPlanBlocks of them): below 2048 tokens workgroups of 8, two per wave, up to 8192 of 32, four per wave, then 64.  The gate
+// operator, us, against workgroups of 16 and 64, four tokens per wave: 16 tokens 22.2 -> 19.2, 200 25.6 -> 21.5, 590 26 -> 22.8, 1000 27.9 -> 25.2,
+// 1700 30 -> 28.3, 2100 35.3 -> 31.8, 4096 37.5 -> 33.8, 8192 47.6 -> 45.
 constexpr int kMaxChoices = 8;                     // of a token
-constexpr int kRouteTokensPerWave = 4;
-__host__ __device__ inline int route_tokens_per_block(int64_t n_tokens) { return n_tokens < 2048 ? 16 : 64; }
+__host__ __device__ inline int route_tokens_per_block(int64_t n_tokens) { return n_tokens < 2048 ? 8 : n_tokens <= 8192 ? 32 : 64; }
+inline int route_tokens_per_wave(int64_t n_tokens) { return n_tokens < 2048 ? 2 : 4; }   // (four waves or more)
 
 template <int CTRL, int ROWS> __device__ __forceinline__ float max_dpp(float v) {   // lanes without a source keep v
   const int u = __builtin_bit_cast(int, v);
@@ -40,13 +41,13 @@ __device__ __forceinline__ float wave_max_dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
+template <int Q>
 __global__ __launch_bounds__(1024) void moe_route_kernel(const float* __restrict__ logits,
                                                          int32_t* __restrict__ ids,
                                                          float* __restrict__ wts,
                                                          int32_t* __restrict__ rank_in_block,
                                                          int32_t* __restrict__ block_counts,
                                                          int n_tokens, int n_experts, int top_k) {
-  constexpr int Q = kRouteTokensPerWave;
   __shared__ int hist[256];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (threadIdx.x < 256) hist[threadIdx.x] = 0;     // (256 threads or more)
@@ -239,8 +240,8 @@ __global__ __launch_bounds__(1024) void moe_plan_index_kernel(const int32_t* __r
 
 // x[t] += sum_j wts[t][j] * y[slot_of[t][j]], j ascending, fp32.  Bound by its bytes (8192 tokens of 2048, 8 choices: 402 MB);
 // a thread requests the rows of all choices together instead of slot, weight and row one after the other, and
-// past the caches, since nobody reads them again.  experts_down with it, us, 30B-A3B shape: 16 tokens 46.6 -> 44.9, 590 90 -> 88.8,
-// 8192 331 -> 325.6, 16000 572 -> 560 (the order alone 44.9, 88.6, 327.5, 573).
+// past the caches, since nobody reads them again.  experts_down with it, us, 30B-A3B shape: 16 tokens 46.6 -> 45.2, 590 90 -> 88.8,
+// 8192 331 -> 326.5, 16000 572 -> 566.
 __global__ __launch_bounds__(256) void moe_combine_kernel(float* __restrict__ x,
                                                           const bf16* __restrict__ y,
                                                           const int32_t* __restrict__ slot_of,
@@ -278,9 +279,9 @@ void launch_moe_route(const float* logits, int32_t* ids, float* wts, int32_t* sl
                       int32_t* block_counts, int32_t* groups, int32_t* row_token, int64_t n_tokens, int n_experts, int top_k,
                       int tile_rows, hipStream_t s) {
   const int n_blocks = moe_route_blocks(n_tokens), per_block = route_tokens_per_block(n_tokens);
-  launch_kernel(moe_route_kernel, dim3((unsigned)n_blocks), per_block / kRouteTokensPerWave * 64, 0, s,
-      logits, ids, wts, slot_of, block_counts, (int)n_tokens,
-                                                           n_experts, top_k);
+  const int q = route_tokens_per_wave(n_tokens);
+  launch_kernel(q == 2 ? moe_route_kernel<2> : moe_route_kernel<4>, dim3((unsigned)n_blocks), per_block / q * 64, 0, s,
+      logits, ids, wts, slot_of, block_counts, (int)n_tokens, n_experts, top_k);
   if (n_blocks <= kFusedPlanBlocks)
     launch_kernel(moe_plan_index_kernel, dim3((unsigned)n_blocks), 1024, 0, s,
         ids, block_counts, slot_of, row_token, groups, (int)(n_tokens * top_k),

@@ -265,9 +265,9 @@ def test_what_experts_add_to_each_token(n, ffn, seed):
 
 
 @pytest.mark.parametrize("experts,top_k", [(8, 2), (256, 8)])
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 1040, 2047, 2048, 2049, 16384, 16385])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 15, 16, 17, 1040, 2047, 2048, 2049, 8192, 8193, 16384, 16385])
 def test_every_pair_has_its_row(n, experts, top_k):
-    """Route workgroups of 16 and 64 tokens, the last of one token, of all but one and full; their counts added up by every workgroup
+    """Route workgroups of 8, 32 and 64 tokens, the last of one token, of all but one and full; their counts added up by every workgroup
     of the plan, or (16385 tokens and more) by one: what the layer adds to every token is its experts' weighted sum."""
     B, R = _mods()
     spec = I.ShapeSpec(1, 192, 2, 1, 64, 64, 1e-5, 10000.0, n_experts=experts, top_k=top_k)
