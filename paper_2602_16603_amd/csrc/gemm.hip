@@ -501,10 +501,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   // for every other row of it, and nobody where the expert has one tile; gathered rows of A have an address each, and
   // their shares do not rotate (8192 tokens of the 30B-A3B shape: experts_up 409 -> 396 us, experts_down 335 -> 329).
   const int w_shares = warm_shares(w_sharers);
-  // Three stages hide what sharers wait for each other, and the extra requests then cost 2 to 5 % -- but not where rows lie an odd multiple
-  // of a power of two apart, whose lines crowd a few sets: 1900 x 7168 on 160 rows, without / with, K = 5120 172 / 153 us, 10240 338 / 299, 6144
-  // 186 / 179, 14336 426 / 397; 4096 113 / 116, 8192 216 / 224, 4160 118 / 121.
-  const bool warm_up = GROUPED ? shared : !kThree || (K % 512 == 0 && (K & (K - 1)) != 0);
+  const bool warm_up = GROUPED ? shared : !kThree || warm_three_stages(K, SWIGLU);
   const __amdgpu_buffer_rsrc_t rsrc_warm = !warm_up ? rsrc_none
                                            : wave == 0 ? (gathered ? rsrc_a : rsrc_warm_a)
                                            : w_shares > 0 && (wave == 1 || (w_shares == 2 && wave == 2)) ? rsrc_warm_w : rsrc_none;

@@ -36,6 +36,25 @@ inline int moe_tile_rows(int64_t mean_rows, int64_t ffn, int64_t hidden) {
 // 160 column tiles and more 0 to 10 % faster than with eight, 1 % slower at most.
 constexpr int warm_shares(int row_tiles) { return row_tiles >= 8 ? 8 : row_tiles >= 4 ? 4 : row_tiles >= 2 ? 2 : 0; }
 
+// Whether the large tile on three stages (128 and 160 rows) asks for the L2 warm-up as well.  Three stages hide most of what
+// sharers wait for each other, and the extra requests then cost 1 to 6 %; but where K is a small odd number of times a power
+// of two from 512 on they gain more than that.  1259 problems of 257 to 3000 rows, 44 K from 320 to 28672, cold weights; time
+// with the warm-up over time without it, mean per K (powers of two times the factor):
+//   factor        bf16 and residual                       SwiGLU
+//   1             1.011 to 1.051                          1.021 to 1.078
+//   3  (x 512 up) 0.952 0.956 0.970 0.978, 24576 1.010    0.987 1.008 1.019 1.019, 24576 1.025
+//   5             0.936 0.923 0.953, 20480 1.033          0.971 0.952 1.003, 20480 1.019
+//   7             1.000 1.008 0.994 0.945                 1.010 1.015 1.019 0.967
+//   9 to 15       0.983 to 1.003                          1.019 to 1.049
+//   27, 37        1.014 1.018 1.060                       1.064 1.074 1.077
+//   x 256         0.987 to 1.019                          1.001 to 1.041
+//   less          0.971 to 1.034                          1.004 to 1.040
+// (Single problems differ from these means by up to 10 %: which lines crowd one another depends on all three sizes.)
+constexpr bool warm_three_stages(int k, bool swiglu) {
+  const int power = k & -k;
+  return power >= 512 && k > power && k < (swiglu ? 6 : 16) * power;
+}
+
 // Column tiles of 256 from which on a launch of one row tile is not cut over K and does not take the 128-column tile.
 constexpr int64_t kWideTiles = 160;
 

@@ -5,6 +5,7 @@
 //   f32 m n k residual            -> rows of the fp32 tile
 //   few m n k                     -> 1 if the problem runs on the few-rows kernel
 //   warm row_tiles                -> shares of a W panel in the large tile's L2 warm-up
+//   warm3 k swiglu                -> 1 if the large tile on three stages asks for the warm-up
 //   swiglu m f k                  -> rows per tile of its fused gate_up projection (0: two operators)
 #include <iostream>
 #include <sstream>
@@ -44,6 +45,10 @@ int main() {
       int row_tiles;
       in >> row_tiles;
       std::cout << fp::warm_shares(row_tiles) << "\n";
+    } else if (kind == "warm3") {
+      int k, swiglu;
+      in >> k >> swiglu;
+      std::cout << fp::warm_three_stages(k, swiglu != 0) << "\n";
     } else if (kind == "rows") {
       long long m, n, k;
       std::string epilogue;

@@ -92,6 +92,22 @@ def test_the_l2_warm_up_asks_for_shared_lines_only(rules):
     assert shares[0] == 0 and all(n / 2 < s <= n for n, s in enumerate(shares[1:], 2)), shares
 
 
+def test_three_stages_ask_for_the_warm_up_where_it_was_measured_to_gain(rules):
+    """Time with over time without it, measured means: 0.92 to 0.98 for 3 and 5 times 512 to 4096 (SwiGLU 0.95 to 1.02), 0.98 to
+    1.00 for 9 to 15 times (SwiGLU 1.02 to 1.05); 1.01 to 1.08 for powers of two, larger odd factors and smaller powers.  The
+    GPU tests run both sides of the rule."""
+    small, larger = (1536, 2560, 3072, 5120, 6144, 10240, 12288), (4608, 5632, 6656, 7680, 9216, 11264)
+    never = (64, 832, 896, 1024, 4096, 8192, 16384, 13824, 18944, 27648, 1280, 2304, 3328, 4160, 4480)
+    assert rules([f"warm3 {k} 0" for k in small + larger + never]) == ["1"] * 13 + ["0"] * len(never)
+    assert rules([f"warm3 {k} 1" for k in small + larger + never]) == ["1"] * 7 + ["0"] * (6 + len(never))
+    from tests.test_gpu_ops import LARGE_TILE_SIZES
+    three = {(rows, epilogue, k) for rows, epilogue, _, _, k in LARGE_TILE_SIZES if rows <= 160}
+    for rows in (128, 160):
+        for epilogue in ("bf16", "residual", "swiglu"):
+            # k-tiles behind the last whole turn of six: one and two (832, 896), none and a half with the warm-up (1536, 2560)
+            assert {(rows, epilogue, k) for k in (64, 576, 832, 896, 1536, 2560)} <= three
+
+
 def test_wide_projections_of_65_to_128_rows_stay_on_the_few_rows_kernel(rules):
     """Measured, us, few-rows kernel / large kernel: 110 / 137, 244 / 288, 107 / 131, 124 / 130, 128 / 135 -- and, a short K
     in one round of large tiles, the other way round."""
