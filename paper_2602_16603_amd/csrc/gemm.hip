@@ -228,11 +228,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
 // k-tile for both projections).  The pad load is the last VMEM instruction before the wave's
 // wait, which therefore asks for "all but one" and never blocks on it.
 // ------------------------------------------------------------------------------------------
-// Where a workgroup whose columns begin at `col` starts in K (start_groups of gemm_plan.h: 0 = at its beginning).
-__device__ __forceinline__ int k_start(int col, int K, int groups) {
-  return groups ? (col / 128 % groups) * (K / 128) / groups * 128 : 0;
-}
-
 constexpr int kWaitVm0 = 0x0F70;   // s_waitcnt vmcnt(0)           (expcnt/lgkmcnt untouched)
 constexpr int kWaitVm1 = 0x0F71;   // s_waitcnt vmcnt(1)
 template <int N> constexpr int wait_vm() { return 0x0F70 | (N & 15) | ((N >> 4) << 14); }   // s_waitcnt vmcnt(N)
@@ -1213,26 +1208,6 @@ static void launch_bf16_any(const bf16* a, const bf16* w, void* c, int m, int n,
       a, w, c, m, n, k, tiles_m, tiles_n);
 }
 
-// Tile width and number of K ranges for a problem.  Enough 256-column tiles to occupy the chip, or
-// more than two row tiles (then the MFMAs bound the launch and the wide tile's operand reuse
-// counts: measured at 768 tokens and up): the 256-column tile.  Otherwise the 128-column tile.
-// Either is cut over K only as far as it takes to reach about one workgroup per CU, and never
-// below 8 k-tiles (512 columns) per range.
-struct W4Shape {
-  int nj;       // W blocks per wave tile: 8 (256-column tile) or 4 (128-column tile)
-  int splits;   // 1 = no split
-};
-static W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
-  const int64_t tiles_m = (m + 255) / 256;
-  const int64_t wide = tiles_m * ((n + 255) / 256);
-  if (wide >= kWideTiles) return {8, 1};
-  const bool narrow = tiles_m <= 2;
-  const int64_t tiles = std::max<int64_t>(1, narrow ? tiles_m * ((n + 127) / 128) : wide);
-  int s = (int)std::max<int64_t>(1, std::min<int64_t>(16, 256 / tiles));
-  while (s > 1 && (k / kBK) / s < 8) --s;
-  return {narrow ? 4 : 8, s};
-}
-
 // Few rows (gemm_plan.h's few_rows): columns per tile, k-tiles and stages by
 // row count and epilogue, as measured on cold weights of the 8B shape (us, against the two-stage 256-row tile): up to
 // 64 rows 64-column tiles of 128 k (256 bytes of a weight row at a time: HBM gives 4.9 TB/s to such pieces where 128-byte
@@ -1258,19 +1233,18 @@ static KRanges ring_ranges(int n, int k, int splits) {
   return k_ranges(k, splits > 1 ? std::max(2, std::min(splits, 256 / ((n + T::BN - 1) / T::BN))) : 1);
 }
 template <int MI, int EPI, bool STREAM = false, bool LONG_K = false>
-static int launch_ring(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s, int start_groups = 0) {
+static int launch_ring(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s, int starts = 0) {
   using T = RingTile<MI, EPI == kEpiSwiGLU, LONG_K>;
   const int tiles_m = (m + 16 * MI - 1) / (16 * MI), tiles_n = (n + T::BN - 1) / T::BN;
   const KRanges r = ring_ranges<MI, EPI>(n, k, splits);
   launch_kernel(gemm_bf16_ring_kernel<MI, T::NJ, T::KT, T::S, EPI, false, STREAM>, dim3((unsigned)(tiles_m * tiles_n * r.used)), 256, 0, s,
-      a, w, c, m, n, k, tiles_m, tiles_n, r.per, start_groups, nullptr, nullptr);
+      a, w, c, m, n, k, tiles_m, tiles_n, r.per, starts, nullptr, nullptr);
   return r.used;
 }
-// Returns the number of K ranges launched (at most `splits`).
+// starts: uncut_starts.  Returns the number of K ranges launched (at most `splits`).
 template <int EPI>
-static int launch_few_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, hipStream_t s) {
+static int launch_few_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits, int starts, hipStream_t s) {
   constexpr bool SWIGLU = EPI == kEpiSwiGLU, STREAM = EPI != kEpiResidual;
-  const int starts = STREAM && EPI != kEpiPartial ? start_groups(m, SWIGLU ? 2 * (int64_t)n : n, k) : 0;
   if (SWIGLU && k >= 3072) {
     if (m <= 32) return launch_ring<2, EPI, STREAM, SWIGLU>(a, w, c, m, n, k, splits, s, starts);
     if (m <= 64) return launch_ring<4, EPI, STREAM, SWIGLU>(a, w, c, m, n, k, splits, s, starts);
@@ -1329,11 +1303,11 @@ static void launch_large(const bf16* a, const bf16* w, void* c, int m, int n, in
 // fetches less: 8B shape, cold, us: 140 tokens gate_up 58 -> 55.5, 270 tokens qkv 33 -> 28.5, down 55 -> 49, 560 tokens qkv 43.5 -> 41,
 // down 84 -> 75; 300 tokens of the 32B shape down 145 -> 112.
 template <int EPI, int NJ>
-static void launch_even_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int kt_per_split, int splits, hipStream_t s) {
+static void launch_even_rows(const bf16* a, const bf16* w, void* c, int m, int n, int k, int kt_per_split, int splits, int starts,
+                             hipStream_t s) {
   constexpr int BN = EPI == kEpiSwiGLU ? 16 * NJ : 32 * NJ;
   const int tiles_m = (m + 255) / 256, tiles_n = (n + BN - 1) / BN;
   constexpr bool kUncut = NJ == 4 && (EPI == kEpiBf16 || EPI == kEpiSwiGLU);
-  const int starts = kUncut ? start_groups(m, EPI == kEpiSwiGLU ? 2 * (int64_t)n : n, k) : 0;
   auto launch = [&](auto rows) {
     constexpr int ROWS = decltype(rows)::value;
     if (kUncut && tiles_m == 1)
@@ -1353,19 +1327,7 @@ static void launch_even_rows(const bf16* a, const bf16* w, void* c, int m, int n
   else launch(std::integral_constant<int, 256>{});
 }
 
-// Tile of the fused gate_up projection: 128 FFN columns when that occupies the chip or the
-// request has more than two row tiles, else 64.
-static int swiglu_nj(int64_t m, int64_t f) {
-  const int64_t tiles_m = (m + 255) / 256;
-  return tiles_m <= 2 && tiles_m * ((f + 127) / 128) < 160 ? 4 : 8;
-}
-
-bool gemm_swiglu_fusable(int dtype, int64_t m, int64_t f, int64_t k) {
-  if (dtype != 1 || k % kBK != 0 || f % 8 != 0 || m <= 0) return false;
-  if ((f + 256) * k * 2 >= (int64_t)kOffOutOfRange) return false;   // the kernel's 32-bit offsets into the [gate | up] panel
-  const int cols = swiglu_nj(m, f) * 16;
-  return ((m + 255) / 256) * ((f + cols - 1) / cols) >= 96;
-}
+bool gemm_swiglu_fusable(int dtype, int64_t m, int64_t f, int64_t k) { return dtype == 1 && swiglu_fusable(m, f, k); }
 
 void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t m, int64_t f,
                         int64_t k, hipStream_t s) {
@@ -1374,15 +1336,16 @@ void launch_gemm_swiglu(const void* a, const void* w_gate_up, void* out, int64_t
     return;
   }
   const int nj = swiglu_nj(m, f);
-  const bool few = m <= kFewRows || (m <= 2 * kFewRows && nj == 8);
-  if (few && aligned_to(16, a, w_gate_up, out)) {
-    launch_few_rows<kEpiSwiGLU>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, 1, s);
+  const bool few = swiglu_few_rows(m, f) && aligned_to(16, a, w_gate_up, out);
+  const int starts = uncut_starts(m, 2 * f, k, nj, few);
+  if (few) {
+    launch_few_rows<kEpiSwiGLU>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, 1, starts, s);
     return;
   }
   if (nj == 8)
     launch_large<kEpiSwiGLU>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, s);
   else
-    launch_even_rows<kEpiSwiGLU, 4>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, (int)(k / kBK), 1, s);
+    launch_even_rows<kEpiSwiGLU, 4>((const bf16*)a, (const bf16*)w_gate_up, out, (int)m, (int)f, (int)k, (int)(k / kBK), 1, starts, s);
 }
 
 size_t gemm_workspace_bytes(int dtype, int64_t m, int64_t n, int64_t k) {
@@ -1436,8 +1399,9 @@ template <bool RESID, int NJ>
 static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, int k, int splits,
                            float* workspace, const GemmTail& tail, hipStream_t s) {
   const bool few = few_rows(m, n, k) && aligned_to(16, a, w, c);
+  const int starts = RESID || splits > 1 ? 0 : uncut_starts(m, n, k, NJ, few);
   if (splits <= 1 && few) {
-    launch_few_rows<RESID ? kEpiResidual : kEpiBf16>(a, w, c, m, n, k, 1, s);
+    launch_few_rows<RESID ? kEpiResidual : kEpiBf16>(a, w, c, m, n, k, 1, starts, s);
     return;
   }
   if (splits <= 1) {
@@ -1445,15 +1409,15 @@ static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, 
     if constexpr (NJ == 8)
       launch_large<EPI>(a, w, c, m, n, k, s);
     else
-      launch_even_rows<EPI, NJ>(a, w, c, m, n, k, k / kBK, 1, s);
+      launch_even_rows<EPI, NJ>(a, w, c, m, n, k, k / kBK, 1, starts, s);
     return;
   }
   const KRanges r = k_ranges(k, splits);
   int used = r.used;
   if (few)
-    used = launch_few_rows<kEpiPartial>(a, w, workspace, m, n, k, splits, s);
+    used = launch_few_rows<kEpiPartial>(a, w, workspace, m, n, k, splits, 0, s);
   else
-    launch_even_rows<kEpiPartial, NJ>(a, w, workspace, m, n, k, r.per, used, s);
+    launch_even_rows<kEpiPartial, NJ>(a, w, workspace, m, n, k, r.per, used, 0, s);
   if (tail.kind == kTailLeave) return;               // (gemm_left_ranges tells the caller how many ranges)
   const int64_t mn = (int64_t)m * n;
   if (RESID && tail.kind == kTailRmsNorm)
@@ -1693,34 +1657,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     }
 }
 
-// Tile and number of K ranges launch_gemm uses with that much workspace (splits 1 = uncut; 0 = the
-// problem does not run on the fast kernel at all).
-static W4Shape w4_plan(int dtype, int64_t m, int64_t n, int64_t k, size_t workspace_bytes) {
-  if (dtype != 1 || k % kBK != 0 || n % 8 != 0 || n > (1 << 21) || k > (1 << 21)) return {8, 0};
-  // (the size limits keep the fast kernel's 32-bit buffer offsets below kOffOutOfRange)
-  W4Shape p = w4_shape(m, n, k);
-  if (p.splits > 1 && (size_t)p.splits * m * n * sizeof(float) > workspace_bytes) p.splits = 1;
-  const int64_t tiles = ((m + 255) / 256) * ((n + 32 * p.nj - 1) / (32 * p.nj));
-  if (tiles * p.splits < 96) p.splits = 0;
-  return p;
-}
-
 // Problems whose tile small_problem_tile chooses.
 static bool takes_small_tiles(int64_t m, int64_t n, int64_t k, size_t workspace_bytes) {
   return w4_plan(1, m, n, k, workspace_bytes).splits == 0;
-}
-
-// What a problem that w4_plan cuts over K runs as.  Three or four row tiles and a short K: the 128-column
-// tile in fewer ranges (possibly one: nothing is cut then), if that occupies the chip -- fewer partial sums
-// against more operand reads per MFMA, which a long K would pay for too often.  With the reduction, us:
-// 777 x 6144 x 4096 54 -> 45, 777 x 4096 x 4096 44 -> 40, 590 x 5120 x 2048 30 -> 24, but x 14336 110 -> 115; 600 x 6144 x
-// 4096 has 144 tiles and stays (47.7, 49).  Of 80 drawn problems of 513 to 1024 rows and K up to 6144 none was more than 3 %
-// slower than without this rule.  Residual projections stay cut (their tail rides on the reduction).
-static W4Shape w4_cut(int64_t m, int64_t n, int64_t k, bool residual, W4Shape p) {
-  const int64_t tiles_m = (m + 255) / 256, tiles = tiles_m * ((n + 127) / 128);
-  if (p.nj != 8 || tiles_m > 4 || k > 6144 || tiles > 256) return p;
-  const int s = (int)std::min<int64_t>(p.splits, 256 / tiles);
-  return tiles * s >= 184 && s >= (residual ? 2 : 1) ? W4Shape{4, s} : p;
 }
 
 bool gemm_tail_fusable(int dtype, int64_t m, int64_t n, int64_t k, size_t workspace_bytes, int tail_kind) {

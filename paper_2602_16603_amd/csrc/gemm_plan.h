@@ -1,5 +1,7 @@
 // Which tile a GEMM runs on.  Plain C++17 with no GPU dependency: the rules can be built and checked on the CPU.
 #pragma once
+#include <algorithm>
+#include <cstddef>
 #include <cstdint>
 
 namespace fp {
@@ -76,6 +78,71 @@ inline bool few_rows(int64_t m, int64_t n, int64_t k) {
   return tiles >= kWideTiles ? tiles > 256 || k > 1152 : k > 16384;
 }
 
+// Tile width and number of K ranges for a problem.  Enough 256-column tiles to occupy the chip, or
+// more than two row tiles (then the MFMAs bound the launch and the wide tile's operand reuse
+// counts: measured at 768 tokens and up): the 256-column tile.  Otherwise the 128-column tile.
+// Either is cut over K only as far as it takes to reach about one workgroup per CU, and never
+// below 8 k-tiles (512 columns) per range.
+struct W4Shape {
+  int nj;       // W blocks per wave tile: 8 (256-column tile) or 4 (128-column tile)
+  int splits;   // 1 = no split
+};
+inline W4Shape w4_shape(int64_t m, int64_t n, int64_t k) {
+  const int64_t tiles_m = (m + 255) / 256;
+  const int64_t wide = tiles_m * ((n + 255) / 256);
+  if (wide >= kWideTiles) return {8, 1};
+  const bool narrow = tiles_m <= 2;
+  const int64_t tiles = std::max<int64_t>(1, narrow ? tiles_m * ((n + 127) / 128) : wide);
+  int s = (int)std::max<int64_t>(1, std::min<int64_t>(16, 256 / tiles));
+  while (s > 1 && (k / kBK) / s < 8) --s;
+  return {narrow ? 4 : 8, s};
+}
+
+// Tile and number of K ranges launch_gemm uses with that much workspace (splits 1 = uncut; 0 = the
+// problem does not run on the fast kernel at all).
+inline W4Shape w4_plan(int dtype, int64_t m, int64_t n, int64_t k, size_t workspace_bytes) {
+  if (dtype != 1 || k % kBK != 0 || n % 8 != 0 || n > (1 << 21) || k > (1 << 21)) return {8, 0};
+  // (the size limits keep the fast kernel's 32-bit buffer offsets below kOffOutOfRange)
+  W4Shape p = w4_shape(m, n, k);
+  if (p.splits > 1 && (size_t)p.splits * m * n * sizeof(float) > workspace_bytes) p.splits = 1;
+  const int64_t tiles = ((m + 255) / 256) * ((n + 32 * p.nj - 1) / (32 * p.nj));
+  if (tiles * p.splits < 96) p.splits = 0;
+  return p;
+}
+
+// What a problem that w4_plan cuts over K runs as.  Three or four row tiles and a short K: the 128-column
+// tile in fewer ranges (possibly one: nothing is cut then), if that occupies the chip -- fewer partial sums
+// against more operand reads per MFMA, which a long K would pay for too often.  With the reduction, us:
+// 777 x 6144 x 4096 54 -> 45, 777 x 4096 x 4096 44 -> 40, 590 x 5120 x 2048 30 -> 24, but x 14336 110 -> 115; 600 x 6144 x
+// 4096 has 144 tiles and stays (47.7, 49).  Of 80 drawn problems of 513 to 1024 rows and K up to 6144 none was more than 3 %
+// slower than without this rule.  Residual projections stay cut (their tail rides on the reduction).
+inline W4Shape w4_cut(int64_t m, int64_t n, int64_t k, bool residual, W4Shape p) {
+  const int64_t tiles_m = (m + 255) / 256, tiles = tiles_m * ((n + 127) / 128);
+  if (p.nj != 8 || tiles_m > 4 || k > 6144 || tiles > 256) return p;
+  const int s = (int)std::min<int64_t>(p.splits, 256 / tiles);
+  return tiles * s >= 184 && s >= (residual ? 2 : 1) ? W4Shape{4, s} : p;
+}
+
+// Tile of the fused gate_up projection: 128 FFN columns when that occupies the chip or the
+// request has more than two row tiles, else 64.
+inline int swiglu_nj(int64_t m, int64_t f) {
+  const int64_t tiles_m = (m + 255) / 256;
+  return tiles_m <= 2 && tiles_m * ((f + 127) / 128) < 160 ? 4 : 8;
+}
+
+// Whether the fused gate_up projection (f outputs, W of 2 f rows) runs on the large and the few-rows tiles: the others' W
+// offsets are 32 bits wide and reach both halves of the [gate | up] panel.
+inline bool swiglu_fusable(int64_t m, int64_t f, int64_t k) {
+  if (k % kBK != 0 || f % 8 != 0 || m <= 0) return false;
+  if ((f + 256) * k * 2 >= (int64_t)kOffOutOfRange) return false;
+  const int cols = swiglu_nj(m, f) * 16;
+  return ((m + 255) / 256) * ((f + cols - 1) / cols) >= 96;
+}
+
+// Whether it runs on the few-rows kernel (which wants 16-byte aligned operands): where its own tile would be 256 columns wide, up
+// to 128 rows (few_rows has the figures).
+inline bool swiglu_few_rows(int64_t m, int64_t f) { return m <= kFewRows || (m <= 2 * kFewRows && swiglu_nj(m, f) == 8); }
+
 // A launch of one or two row tiles on the 128-column or the few-rows tile reads every line of W for one or two workgroups only,
 // and workgroups in step ask for the same 128 or 256 bytes of every row.  Where rows lie a power of two or three of them apart those
 // fall on few HBM channels, on fewer or more of them with where the allocation lies; so the columns' starts in K are spread evenly
@@ -89,6 +156,15 @@ inline int start_groups(int64_t m, int64_t n, int64_t k) {
   const bool narrow = m <= 512 && (m + 255) / 256 * ((n + 255) / 256) < kWideTiles;
   return narrow && n % 256 == 0 && k % 128 == 0 && k >= 2048 && k <= 16384 ? (int)(n / 256) : 0;
 }
+
+// The starts an uncut bf16 projection runs with (of n columns of W, gate and up ones together if fused): its tile is `nj` W
+// blocks per wave wide, or the few-rows kernel's, which starts elsewhere on 32 and 64 rows only.
+inline int uncut_starts(int64_t m, int64_t n, int64_t k, int nj, bool few) {
+  return few ? (m <= kFewRows ? start_groups(m, n, k) : 0) : nj == 4 ? start_groups(m, n, k) : 0;
+}
+
+// The k at which a workgroup whose columns begin at `col` starts.
+constexpr int k_start(int col, int k, int groups) { return groups ? (col / 128 % groups) * (k / 128) / groups * 128 : 0; }
 
 // Rows of the large tile (256 columns; SwiGLU 128 outputs; K % 64 == 0, not cut).  A CU works off its tiles one after the other;
 // a launch of a few rounds loses what its last round leaves empty and the padding of its last row tile, a smaller tile

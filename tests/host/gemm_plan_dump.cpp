@@ -4,6 +4,10 @@
 //   rows m n k bf16|swiglu|residual -> rows of the large tile for an uncut problem (swiglu: n outputs)
 //   f32 m n k residual            -> rows of the fp32 tile
 //   few m n k                     -> 1 if the problem runs on the few-rows kernel
+//   starts m n k                  -> groups of columns that start at different k (0: all at the beginning)
+//   forms m f k workspace aligned -> the starts that the plain projection of 2 f columns and the fused one of f outputs run with
+//                                    (operands on the 16-byte grid or only on the dword grid), whether all of their columns
+//                                    start alike (1), and whether the plain one is cut (1) or there is no fused one (2)
 //   warm row_tiles                -> shares of a W panel in the large tile's L2 warm-up
 //   warm3 k swiglu                -> 1 if the large tile on three stages asks for the warm-up
 //   swiglu m f k                  -> rows per tile of its fused gate_up projection (0: two operators)
@@ -41,6 +45,20 @@ int main() {
       long long m, n, k;
       in >> m >> n >> k;
       std::cout << fp::start_groups(m, n, k) << "\n";
+    } else if (kind == "forms") {
+      long long m, f, k, workspace;
+      int aligned;
+      in >> m >> f >> k >> workspace >> aligned;
+      fp::W4Shape p = fp::w4_plan(1, m, 2 * f, k, (size_t)workspace);
+      if (p.splits > 1) p = fp::w4_cut(m, 2 * f, k, false, p);
+      const bool fusable = fp::swiglu_fusable(m, f, k);
+      // (splits 0: the tiles of small problems, which start at the beginning)
+      const int plain = p.splits == 1 ? fp::uncut_starts(m, 2 * f, k, p.nj, fp::few_rows(m, 2 * f, k) && aligned) : 0;
+      const int fused = fusable ? fp::uncut_starts(m, 2 * f, k, fp::swiglu_nj(m, f), fp::swiglu_few_rows(m, f) && aligned) : 0;
+      bool alike = true;
+      for (long long col = 0; col < f; col += 8)
+        for (long long half : {0LL, f}) alike &= fp::k_start((int)(half + col), (int)k, plain) == fp::k_start((int)col, (int)k, fused);
+      std::cout << plain << " " << fused << " " << alike << " " << (fusable ? p.splits > 1 : 2) << "\n";
     } else if (kind == "warm") {
       int row_tiles;
       in >> row_tiles;

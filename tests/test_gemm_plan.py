@@ -125,3 +125,21 @@ def test_columns_start_elsewhere_only_where_either_form_does(rules):
         assert int(groups) == (n // 256 if narrow and 2048 <= k <= 16384 else 0), (m, n, k, groups)
         assert int(groups) == 0 or m <= 64 or few == "0", (m, n, k)
     assert rules(["starts 50 28680 4096", "starts 50 28672 4160", "starts 50 128 4096"]) == ["0", "0", "0"]
+
+
+@pytest.mark.parametrize("aligned", [1, 0])
+def test_the_fused_and_the_plain_form_start_alike_on_the_tiles_they_take(rules, aligned):
+    """The dispatch itself, operands on the 16-byte grid or off it (then nothing runs on the few-rows kernel): wherever the fused
+    projection exists and the plain one is not cut, every output's gate, up and fused column start at one k."""
+    outputs = [128 * g + 8 * d for g in (15, 47, 48, 49, 50, 56, 63, 64, 79, 80, 81, 95, 96, 110, 111, 112, 127, 128, 159, 160, 161, 319, 320) for d in (0, 1, 8)]
+    # Workspace: none, and enough to cut whatever the rules cut (three and four row tiles may come out uncut of that).
+    asked = [(m, f, k, ws, aligned) for m in (1, 32, 33, 64, 65, 96, 128, 129, 256, 257, 384, 512, 513, 768, 1024) for f in outputs
+             for k in (64, 1024, 1920, 2048, 2112, 3072, 4096, 6144, 16384, 16512, 17408) for ws in (0, 1 << 40)]
+    answers = rules([f"forms {m} {f} {k} {ws} {a}" for m, f, k, ws, a in asked])
+    answers = [tuple(map(int, answers[i:i + 4])) for i in range(0, len(answers), 4)]
+    compared = 0
+    for case, (plain, fused, alike, form) in zip(asked, answers):
+        if form == 0:
+            assert plain == fused and alike, (case, plain, fused)
+            compared += fused > 0
+    assert compared > 500
