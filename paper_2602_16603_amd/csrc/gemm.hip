@@ -861,7 +861,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // stream is all there is to it; it also takes most of what has too few 256-row tiles to occupy the chip,
 // and of odd K (gemm_plan.h).
 // 256 threads = 4 waves side by side along N; every wave multiplies all rows by its 16 NJ columns with
-// v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits, unless grouped or cut).  K is consumed KT at a
+// v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits, unless grouped or cut; both start columns at the same k).  K is consumed KT at a
 // time through a ring of S LDS stages, separate arrays filled by DMA S - 1 k-tiles ahead; the loop body has no
 // branch and always runs a multiple of S k-tiles (behind the last one there is nothing to fetch and
 // zeros to multiply), since with a branch between stages the compiler waits for all DMA before a read.

@@ -149,7 +149,8 @@ inline bool swiglu_few_rows(int64_t m, int64_t f) { return m <= kFewRows || (m <
 // over it, in groups of 128 columns.  Returns the number of such groups, 0: all start at the beginning.  A projection fused with SiLU*up
 // and the plain one of the same matrix have to add up their products in the same order whatever kernel takes them: the start
 // depends on the column modulo half the columns (gate and up of one output start alike) and nothing else, and
-// where either form could be on a tile that does not start elsewhere (kWideTiles, few_rows of a long K) neither does.
+// where either form could be on a tile that does not start elsewhere (kWideTiles, few_rows of a long K) neither does.  So a row's
+// bits are the same in all calls that have these starts, and differ from those of a larger call in the order of the sums.
 // us, cold, five allocations each, gate_up of [14336 outputs 4096]: 50 rows 52.5 (45..57) -> 43.0 (42.7..43.4), 256 rows 69.3 -> 63.1;
 // [14336 6144] 50 rows 82.3 -> 65.6, 200 rows 102.6 -> 89.1; [8192 2048] 23.7 -> 23.6, 31.8 -> 30.7; [18944 3584] 73.7 -> 73.4, 98.9 -> 98.1.  Other spreads are worse or no better: 8 or 16 starts in turn 44 to 68, a random one 46.6.
 inline int start_groups(int64_t m, int64_t n, int64_t k) {

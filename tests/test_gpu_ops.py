@@ -384,7 +384,8 @@ def test_gemm_of_few_rows(m, n, k, residual):
     """The kernel of up to 128 rows on its three row tiles (one row, a row less, a row more, all), uncut
     where the columns alone occupy the chip and cut over K otherwise, k-tiles behind the end of K (one and
     three of 64: the ring holds more) and a last column tile of eight columns: against the definition, and
-    the uncut form bit for bit against the kernel of larger requests (the same sums in the same order)."""
+    the uncut form bit for bit against the kernel of larger requests (the same sums in the same order, as for every
+    projection whose columns all start at the beginning of K)."""
     B = _binding()
     print(f"few rows m={m} n={n} k={k} residual={residual}", flush=True)
     a = torch.zeros((200, k), dtype=torch.bfloat16, device="cuda")
@@ -459,6 +460,41 @@ def test_gate_up_whose_columns_start_at_different_k(m, f, k):
     err = (gu[:m].double() - ref).norm(dim=1) / ref.norm(dim=1)
     assert err.max().item() <= 4e-3, (err.argmax().item(), err.max().item())
     assert max_rel_err(fused[:m], torch.nn.functional.silu(ref[:, :f]) * ref[:, f:]) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("n,k,last", [(12544, 2048, 512), (12544, 3200, 512), (14336, 4096, 512), (20736, 2048, 256)])
+def test_a_row_has_one_result_for_all_sizes_that_start_alike(n, k, last):
+    """An uncut projection whose columns start at different k (49, 49, 56 and 81 groups) adds a row's products up in one order for
+    all sizes that do so (up to two row tiles, up to one where two fill the chip with wide tiles), whatever tile they run on: the
+    same bits from 1 to 512 or 256 rows.  Larger ones start at the beginning, and so does a residual one of any size: another
+    order of the same sums."""
+    B = _binding()
+    a = I.normal_tensor((600, k), 1.0, 106, torch.bfloat16, "cuda")
+    w = I.normal_tensor((n, k), 0.02, 107, torch.bfloat16, "cuda")
+    ref = a.double() @ w.double().T
+    rows = {}
+    for m in (last, last + 1, 1, 20, 32, 50, 64, 65, 100, 128, 200, 256, 300, 512, 600):
+        print(f"one result m={m} n={n} k={k}", flush=True)
+        rows[m] = torch.full((m + 1, n), 7.0, dtype=torch.bfloat16, device="cuda")
+        torch.cuda.synchronize()
+        B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), rows[m].data_ptr(), m, n, k, False)
+        torch.cuda.synchronize()
+        assert torch.all(rows[m][m] == 7.0)
+        alike = rows[last if m <= last else last + 1]
+        both = min(m, alike.shape[0] - 1)
+        assert torch.equal(rows[m][:both], alike[:both]), m
+    # Sums of up to 4096 products in fp32, 32 at a time: a random walk of 128 roundings of 2^-24 of the running sum, 7e-7 of a row;
+    # at bf16's 2^-9 that moves one value in a thousand or so to the neighbouring one.
+    assert (rows[600][:last] != rows[last][:last]).float().mean().item() <= 4e-3
+    for m in (last, 600):
+        err = (rows[m][:m].double() - ref[:m]).norm(dim=1) / ref[:m].norm(dim=1)
+        assert err.max().item() <= 4e-3                # bf16 rounding: 2^-9 at most of a value, 2^-9 / sqrt(3) in the mean square
+    one, many = (torch.zeros((m, n), device="cuda") for m in (50, 600))
+    torch.cuda.synchronize()
+    B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), one.data_ptr(), 50, n, k, True)
+    B.fp_op_gemm(1, a.data_ptr(), w.data_ptr(), many.data_ptr(), 600, n, k, True)
+    torch.cuda.synchronize()
+    assert torch.equal(one, many[:50]) and torch.equal(many.bfloat16()[:600], rows[600][:600])
 
 
 @pytest.mark.parametrize("m,n,k", [(777, 6144, 1088), (513, 7824, 2048), (1024, 4096, 1600), (600, 5136, 1024)])
