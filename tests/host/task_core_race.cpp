@@ -5,6 +5,7 @@
 // polls the cursor -- the calls the C ABI allows to run concurrently (FlowPrefill Section 5.1: the
 // scheduler signals, the worker acknowledges at an operator boundary).  Exit code 0 = every
 // invariant held; ThreadSanitizer adds its own report and exit code on a data race.
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cstdio>
@@ -34,13 +35,30 @@ struct FakeDevice : fp::OpBackend {
   Clock::time_point free_at = Clock::now();
   Clock::time_point mark_at[fp::kMarkRing];
   int32_t mark_op[fp::kMarkRing];
+  bool waited[fp::kMarkRing];            // since it was last placed, or never placed in this call
+  int32_t expected = -1;                 // slot announced for the operator that is launched next
+  bool pending = false;                  // that operator had device work and its marker has not been placed yet
   int32_t last = -1, calls = 0, first_of_call = 0;
   std::mt19937 rng;
   FakeDevice(int32_t n, int32_t ahead, uint32_t seed) : total(n), launch_ahead(ahead), runs(n, 0), end_of(n), rng(seed) {}
 
   std::vector<Clock::time_point> work_ends;   // completion times of this call's operators with device work
-  void begin_call() override { ++calls; first_of_call = last + 1; work_ends.clear(); }
+  void begin_call() override {
+    ++calls;
+    first_of_call = last + 1;
+    work_ends.clear();
+    std::fill(waited, waited + fp::kMarkRing, true);   // (the last call drained)
+  }
+  // A backend may hand the marker to the operator's own work, so the slot must be the one mark() names, must be announced before
+  // that work exists, and must not stand for an operator that may still run.
+  void expect_mark(int slot) override {
+    CHECK(launch_ahead > 0);
+    CHECK(slot >= 0 && slot < fp::kMarkRing && waited[slot]);
+    CHECK(!pending);                                // the operator before has its marker
+    expected = slot;
+  }
   int launch(int32_t index, bool* launched) override {
+    CHECK((expected >= 0) == (launch_ahead > 0));
     CHECK(index == last + 1);                       // in order, none skipped, none repeated
     CHECK(index < total);
     *launched = index % 9 != 7;                     // one operator per layer has no device work
@@ -56,11 +74,30 @@ struct FakeDevice : fp::OpBackend {
     end_of[index] = free_at;
     runs[index]++;
     last = index;
+    pending = launch_ahead > 0 && *launched;
+    if (!*launched) expected = -1;                  // dropped: an operator without device work leaves no marker
     return 0;
   }
-  int mark(int slot) override { mark_at[slot] = free_at; mark_op[slot] = last; return 0; }
-  int wait_mark(int slot) override { std::this_thread::sleep_until(mark_at[slot]); return 0; }
-  int drain() override { std::this_thread::sleep_until(free_at); return 0; }
+  int mark(int slot) override {
+    CHECK(pending && slot == expected);             // one marker per operator with work, where it was announced
+    pending = false;
+    expected = -1;
+    waited[slot] = false;
+    mark_at[slot] = free_at;
+    mark_op[slot] = last;
+    return 0;
+  }
+  int wait_mark(int slot) override {
+    CHECK(mark_at[slot] == work_ends[work_ends.size() - launch_ahead]);   // of the operator the bound asks for
+    std::this_thread::sleep_until(mark_at[slot]);
+    waited[slot] = true;
+    return 0;
+  }
+  int drain() override {
+    CHECK(!pending);
+    std::this_thread::sleep_until(free_at);
+    return 0;
+  }
   bool drained() const { return free_at <= Clock::now(); }
 };
 
@@ -71,7 +108,8 @@ int main(int argc, char** argv) {
   for (int it = 0; it < n_tasks; ++it) {
     const int32_t layers = 2 + it % 3, total = layers * 9;
     const uint32_t mask = masks[it % 4];
-    const int32_t ahead = it % 3;                   // 0 = unbounded, 1, 2
+    static const int32_t kAhead[] = {0, 1, 2, fp::kMarkRing - 1, fp::kMarkRing};
+    const int32_t ahead = kAhead[it % 5];           // 0 = unbounded; the last one uses every slot
     fp::TaskCore core(total, 9, mask);
     FakeDevice dev(total, ahead, 1234u + it);
     CHECK(core.set_launch_ahead(ahead) == fp::kTaskOk);
