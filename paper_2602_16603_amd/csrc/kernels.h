@@ -118,8 +118,11 @@ void launch_kv_gather(int dtype, const void* k_pool, const void* v_pool, void* k
                       int len, const Geometry& g, int layer, const int32_t* table_dev,
                       hipStream_t s);
 
-// Mixture-of-experts FFN (bf16 path).  plan = device int32 [n_experts] (row offset of every
-// expert); block_counts = device int32 [moe_route_blocks(T)][n_experts]; slot_of = device int32
+// Mixture-of-experts FFN (bf16 path).  Bounds of a model: the route kernel's wave holds up to kMaxExperts probabilities and the
+// combine kernel a thread's kMaxChoices rows.
+constexpr int kMaxExperts = 256, kMaxChoices = 8;
+// plan = device int32 [n_experts] (row offset of every expert; written only where the index is left to launch_moe_index);
+// block_counts = device int32 [moe_route_blocks(T)][n_experts]; slot_of = device int32
 // [T*top_k] and row_token = the token of every row (final after launch_moe_index, which has something left to do only
 // where launch_moe_route's plan does not place the pairs itself); groups = device int32 [1 + 3 * (T*top_k/tile_rows + n_experts)]: the row-tile
 // table launch_gemm_grouped reads.

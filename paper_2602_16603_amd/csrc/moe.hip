@@ -23,7 +23,6 @@ namespace fp {
 // counts allows (kFusedPlanBlocks of them): below 2048 tokens workgroups of 8, two per wave, up to 8192 of 32, four per wave, then 64.  The gate
 // operator, us, against workgroups of 16 and 64, four tokens per wave: 16 tokens 22.2 -> 19.2, 200 25.6 -> 21.5, 590 26 -> 22.8, 1000 27.9 -> 25.2,
 // 1700 30 -> 28.3, 2100 35.3 -> 31.8, 4096 37.5 -> 33.8, 8192 47.6 -> 45.
-constexpr int kMaxChoices = 8;                     // of a token
 __host__ __device__ inline int route_tokens_per_block(int64_t n_tokens) { return n_tokens < 2048 ? 8 : n_tokens <= 8192 ? 32 : 64; }
 inline int route_tokens_per_wave(int64_t n_tokens) { return n_tokens < 2048 ? 2 : 4; }   // (four waves or more)
 
@@ -83,7 +82,7 @@ __global__ __launch_bounds__(1024) void moe_route_kernel(const float* __restrict
 #pragma unroll
   for (int q = 0; q < Q; ++q) { my_p[q] = 0.f; my_e[q] = 0; }
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
+  for (int j = 0; j < kMaxChoices; ++j) {
     if (j >= top_k) break;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {

@@ -414,7 +414,8 @@ fp_status fp_model_create(const fp_shape* shape, const fp_layer_weights* layers,
     return fail(FP_ERR_INVALID, "n_experts and top_k must both be zero (dense) or both positive");
   if (s.n_experts > 0) {
     if (s.dtype != FP_DTYPE_BF16) return fail(FP_ERR_INVALID, "mixture-of-experts models are bf16 only");
-    if (s.n_experts > 256 || s.n_experts % 8 || s.top_k > 8 || s.top_k > s.n_experts)
+    static_assert(fp::kMaxExperts == 256 && fp::kMaxChoices == 8, "the message below");
+    if (s.n_experts > fp::kMaxExperts || s.n_experts % 8 || s.top_k > fp::kMaxChoices || s.top_k > s.n_experts)
       return fail(FP_ERR_INVALID, "n_experts must be a multiple of 8 up to 256, top_k at most 8 and n_experts");
     if (s.hidden % 64 || s.ffn % 64)
       return fail(FP_ERR_INVALID, "mixture-of-experts models need hidden and ffn multiples of 64");
