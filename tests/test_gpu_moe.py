@@ -297,3 +297,48 @@ def test_every_pair_has_its_row(n, experts, top_k):
     assert (off.norm(dim=1) / ref.norm(dim=1)).max().item() <= 2.4e-2
     task.end()
     model.close()
+
+
+def test_a_marker_stands_for_the_last_kernel_of_its_operator():
+    """One operator in flight: when operator i is launched, all kernels of operator i - 1 are done.  experts_down's second kernel, the
+    combine, takes most of its time here (16384 tokens of 8 choices over 16 narrow experts), and layer 1's qkv projection, which
+    does not touch the residual, long enough to look at it: once the cursor says that the operator behind experts_down has been
+    launched, the residual's rows, read on another stream, are those of a task that stopped there.  (Read one operator earlier,
+    with experts_down in flight, they were not in any of 39 looks.)"""
+    import ctypes
+    import threading
+    B, R = _mods()
+    spec = I.ShapeSpec(2, 2048, 32, 32, 128, 64, 1e-5, 10000.0, n_experts=16, top_k=8)
+    n, rows = 16384, 64
+    stream, side = torch.cuda.Stream(), torch.cuda.Stream()
+    model = R.PrefillModel(spec, I.make_weights(spec, 71, torch.bfloat16, "cuda"), B.FP_DTYPE_BF16, n // 16 + 8, 512, stream)
+    x = I.make_hidden(n, spec.hidden, 71, torch.bfloat16, "cuda")
+    lengths = [512] * (n // 512)
+    task = model.begin(x, lengths)
+    assert task.advance(9) == (B.FP_OK, 9)
+    want = task.hidden()[-rows:].clone()
+    task.end()
+    hip = ctypes.CDLL("libamdhip64.so")
+    hip.hipMemcpyAsync.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int, ctypes.c_void_p]
+    looked = 0
+    for attempt in range(20):
+        got = torch.zeros_like(want)
+        torch.cuda.synchronize()
+        task = model.begin(x, lengths)
+        B.fp_prefill_set_launch_ahead(task.handle, 1)
+        at = B.fp_prefill_hidden(task.handle) + (n - rows) * spec.hidden * 4
+        th = threading.Thread(target=task.run_to_completion)
+        th.start()
+        while th.is_alive() and task.cursor() < (1, 1):
+            pass
+        rc = hip.hipMemcpyAsync(got.data_ptr(), at, got.numel() * 4, 3, side.cuda_stream)
+        side.synchronize()
+        in_time = task.cursor() <= (1, 3)              # (the o_proj, which adds to the residual, is operator 4)
+        th.join()
+        assert rc == 0 and task.cursor() == (2, 0)
+        task.end()
+        if in_time:
+            looked += 1
+            assert torch.equal(got, want), f"attempt {attempt}"
+    model.close()
+    assert looked >= 5
