@@ -223,8 +223,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16* _
 // queues behind that miss (measured: 480 cycles average L2 read latency in gate_up_proj, 3300
 // cycles per k-tile in down_proj).  Instead each workgroup asks for its share of the lines three
 // k-tiles ahead of the DMA -- every 4th row of its A panel (wave 0) and every 8th row of its W
-// panel (wave 1; every 4th or 2nd where fewer row tiles share it), the shares rotating with the k-tile -- with a one-dword-per-lane load into a
-// dummy LDS pad, so the DMA requests of all sharers find the line resident (2180-2240 cycles per
+// panel (wave 1; every 4th or 2nd where fewer row tiles share it), the shares rotating with the k-tile -- with a
+// one-dword-per-lane load into a dummy LDS pad, so the DMA requests of all sharers find the line resident (2180-2240 cycles per
 // k-tile for both projections).  The pad load is the last VMEM instruction before the wave's
 // wait, which therefore asks for "all but one" and never blocks on it.
 // ------------------------------------------------------------------------------------------
@@ -361,8 +361,9 @@ enum { kEpiBf16 = 0, kEpiResidual = 1, kEpiPartial = 2, kEpiSwiGLU = 3 };
 //
 // KTAIL (256-column tile, not cut): K is not a multiple of 64; its last K % 64 columns (a multiple of 8) follow the
 // main loop as one more k-tile, not pipelined, whose missing 16-byte chunks are fetched from outside the
-// descriptors (K < 64: there is nothing else; the prologue's k-tile 0 is overwritten unread).  K rows then start at odd multiples of 16 bytes, which the DMA does not mind.  8192 x 8192 x 2056:
-// 408 us on register-staged 128x128 tiles, 265 here (1.04 PFLOP/s; rows that straddle lines cost the rest).
+// descriptors (K < 64: there is nothing else; the prologue's k-tile 0 is overwritten unread).  K rows then start at odd multiples
+// of 16 bytes, which the DMA does not mind.  8192 x 8192 x 2056: 408 us on register-staged 128x128 tiles, 265 here (1.04 PFLOP/s;
+// rows that straddle lines cost the rest).
 template <int EPI, bool GROUPED = false, int NJ = 8, bool KTAIL = false, int ROWS = 256, bool STREAM = false>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restrict__ A,
                                                            const bf16* __restrict__ W,
@@ -758,8 +759,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
   } else if (EPI == kEpiBf16) {
     // [128 rows][CH = 2 NJ chunks of 8 bf16], chunk c of row r at position c ^ (r & (CH-1)).
     // The experts' outputs go past the L2, which the neighbours' panels want: with the combine, 30B-A3B shape, us, 1700 tokens 129 -> 125,
-    // 8192 336.5 -> 331, 16000 596 -> 577.  (Not those of gate_up, which the next kernel reads: 1700 tokens 183 -> 177, but 4096 272 -> 275;
-    // nor a dense projection's: no change.)
+    // 8192 336.5 -> 331, 16000 596 -> 577.  (Not those of gate_up, which the next kernel reads: 1700 tokens 183 -> 177, but 4096
+    // 272 -> 275; nor a dense projection's: no change.)
     constexpr int CH = 2 * NJ;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
@@ -861,9 +862,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // stream is all there is to it; it also takes most of what has too few 256-row tiles to occupy the chip,
 // and of odd K (gemm_plan.h).
 // 256 threads = 4 waves side by side along N; every wave multiplies all rows by its 16 NJ columns with
-// v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits, unless grouped or cut; both start columns at the same k).  K is consumed KT at a
-// time through a ring of S LDS stages, separate arrays filled by DMA S - 1 k-tiles ahead; the loop body has no
-// branch and always runs a multiple of S k-tiles (behind the last one there is nothing to fetch and
+// v_mfma_f32_16x16x32_bf16, in the k order of the kernel above (the same bits, unless grouped or cut; both start columns at the
+// same k).  K is consumed KT at a time through a ring of S LDS stages, separate arrays filled by DMA S - 1 k-tiles ahead; the loop
+// body has no branch and always runs a multiple of S k-tiles (behind the last one there is nothing to fetch and
 // zeros to multiply), since with a branch between stages the compiler waits for all DMA before a read.
 // LDS rows hold KT bf16, 16-byte chunk c of row r at c ^ ((r >> 1) & 7) (KT = 64) or c ^ (r & 15)
 // (KT = 128): a half-wave's 16 rows x 2 chunks put two lanes on every bank group.
@@ -871,13 +872,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const bf16* __restric
 // experts' projections of the 30B-A3B shape, cold, us: 16 tokens 87 -> 80 and 55 -> 49, 590 tokens 164 -> 147 and 97 -> 92 (with the
 // combine).  Not the experts' gate_up on 128 rows, which loses by the hint from 70 rows per expert on (96 rows of 8 experts [4096 14336]
 // 390 us, 377 without; of 64 [4096 1536] 345 and 331) and gains less below (50 rows: 367 and 371, 314 and 320).
-// K ranges start at different k as it is, and gain nothing by more starts (50 x 5120 x 27648 57 us, 73 with them); by the hint, of up to 64 rows: 16 rows of
-// 4096 x 14336 24.6 -> 22.3, 6144 x 4096 14.3 -> 13.1, 50 rows of 4096 x 14336 27.1 -> 25.5, 5120 x 27648 57 -> 53.8, short K no change.  (Not the large
-// kernel's: 256 x 4096 x 14336 45 -> 44, but 100 x 4096 x 4096 16 -> 19, 256 x 5120 x 2048 19.5 -> 23.)
+// K ranges start at different k as it is, and gain nothing by more starts (50 x 5120 x 27648 57 us, 73 with them); by the hint, of
+// up to 64 rows: 16 rows of 4096 x 14336 24.6 -> 22.3, 6144 x 4096 14.3 -> 13.1, 50 rows of 4096 x 14336 27.1 -> 25.5, 5120 x
+// 27648 57 -> 53.8, short K no change.  (Not the large kernel's: 256 x 4096 x 14336 45 -> 44, but 100 x 4096 x 4096 16 -> 19, 256
+// x 5120 x 2048 19.5 -> 23.)
 // STREAM (uncut launches of one row tile, the W of all of them read once): the same two, the start by start_groups, which
 // keeps the fused projection and the plain one on one order of sums.  The hint by itself: 50 rows of [14336 outputs 4096]
-// 52.5 -> 49.3 us, 27648 x 5120 110 -> 103; with the starts 41.2, and 256 rows on the 128-column tile 68.2 -> 60.4.  Not on 128 rows here: 27648 x 5120
-// 125 -> 126.7.
+// 52.5 -> 49.3 us, 27648 x 5120 110 -> 103; with the starts 41.2, and 256 rows on the 128-column tile 68.2 -> 60.4.
+// Not on 128 rows here: 27648 x 5120 125 -> 126.7.
 // ------------------------------------------------------------------------------------------
 template <int KT> __device__ __forceinline__ int ring_chunk(int chunk, int row) {
   return KT == 128 ? chunk ^ (row & 15) : chunk ^ ((row >> 1) & 7);
@@ -1212,9 +1214,9 @@ static void launch_bf16_any(const bf16* a, const bf16* w, void* c, int m, int n,
 // row count and epilogue, as measured on cold weights of the 8B shape (us, against the two-stage 256-row tile): up to
 // 64 rows 64-column tiles of 128 k (256 bytes of a weight row at a time: HBM gives 4.9 TB/s to such pieces where 128-byte
 // pieces get 4.2) -- 50 rows: qkv 22 -> 17, o 17 -> 12.6, down 40 -> 28; from 65 rows on the A tile weighs more and 128-column
-// tiles of 64 k read it half as often.  SwiGLU: 128 W rows of 64 k, 75 -> 52 at 50 rows; from 3072 k on (LONG_K) 128 k at a time there too, through
-// three stages for 64 rows (50 rows, outputs x k: 8192 x 3072 32.1 -> 29.8, 14336 x 6144 61.9 -> 59.5, 8192 x 8192 73 -> 69; 8192 x 2048
-// 23.5 -> 23.8, 14336 x 1024 15.8 -> 16.7).
+// tiles of 64 k read it half as often.  SwiGLU: 128 W rows of 64 k, 75 -> 52 at 50 rows; from 3072 k on (LONG_K) 128 k at a time
+// there too, through three stages for 64 rows (50 rows, outputs x k: 8192 x 3072 32.1 -> 29.8, 14336 x 6144 61.9 -> 59.5, 8192 x
+// 8192 73 -> 69; 8192 x 2048 23.5 -> 23.8, 14336 x 1024 15.8 -> 16.7).
 template <int MI, bool SWIGLU, bool LONG_K = false> struct RingTile {
   static constexpr bool kWide = SWIGLU || MI > 4;
   static constexpr int NJ = kWide ? 2 : 1, KT = kWide && !LONG_K ? 64 : 128, S = LONG_K && MI == 4 ? 3 : 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
@@ -1358,9 +1360,9 @@ template <int MI, int EPI>
 static void launch_grouped_ring(const bf16* a, const bf16* w, void* c, int n, int k, const int32_t* groups,
                                     int max_row_tiles, const int32_t* a_rows, int m_arg, hipStream_t s) {
   // Stages such that two workgroups share a CU (up to 32 rows: no fewer than four), so that one's prologue and stores lie under the
-  // other's k-tiles: worth more than a stage more.  30B-A3B shape, cold, us, experts_up on four stages: 64-row tiles (350 to 720 tokens) 140 ->
-  // 132, 160 -> 151, 128-row ones (850, 1200 tokens) 185 -> 171.5, 188 -> 175; experts_down (with the combine) on 32-row tiles 49.2 -> 46 with four
-  // stages instead of three (16 tokens), 64-row ones 87 -> 81 with three instead of four.
+  // other's k-tiles: worth more than a stage more.  30B-A3B shape, cold, us, experts_up on four stages: 64-row tiles (350 to 720
+  // tokens) 140 -> 132, 160 -> 151, 128-row ones (850, 1200 tokens) 185 -> 171.5, 188 -> 175; experts_down (with the combine) on
+  // 32-row tiles 49.2 -> 46 with four stages instead of three (16 tokens), 64-row ones 87 -> 81 with three instead of four.
   constexpr bool SWIGLU = EPI == kEpiSwiGLU;
   constexpr int NJ = 2, KT = 64, S = MI == 8 ? 2 : MI == 4 ? 3 : 4, BN = SWIGLU ? 32 * NJ : 64 * NJ;
   const int tiles_n = (n + BN - 1) / BN;
@@ -1439,11 +1441,12 @@ static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, 
 // instruction takes one k per lane quarter; a lane reads four consecutive k of its row with one
 // ds_read_b128 and step j of four multiplies the j-th of each quarter -- A and W are permuted over k
 // alike.  Chunks past K are fetched from outside the descriptor, so they read as zero (K % 4 == 0).
-// The matrix pipes bound it (157 TFLOP/s at 2.4 GHz; under this load the clock is 2.1): 300 rows of the 8B shape's gate_up projection
-// 2040 -> 568 us (132 TFLOP/s, row padding included), down 2476 -> 317 us, against the plain FMA kernel below; f32_tile_rows chooses
-// the tile.  Half a k-tile's fragments are read, and the next DMA issued, while the other half is multiplied: with both in front
-// of their MFMAs, us, 16-row tiles 67 x 4096 x 14336 179 -> 161, 80-row ones 300 x 4096 x 14336 330 -> 317, 64-row ones 300 x 28672 x 4096
-// 580 -> 568, 128-row ones 1000 x 4096 x 4096 273 -> 261.  Waves side by side along N (WM = 1) for heights that are no multiple of 32.
+// The matrix pipes bound it: 300 rows of the 8B shape's gate_up projection, several workgroups per CU, keep them busy 85 % of its
+// cycles (at 2.3 GHz), down and o, one per CU, 76 %.  Against the plain FMA kernel below gate_up 2040 -> 568 us (132 TFLOP/s of
+// 157, row padding included), down 2476 -> 317 us; f32_tile_rows chooses the tile.  Half a k-tile's fragments are read, and the
+// next DMA issued, while the other half is multiplied: with both in front of their MFMAs, us, 16-row tiles 67 x 4096 x 14336 179
+// -> 161, 80-row ones 300 x 4096 x 14336 330 -> 317, 64-row ones 300 x 28672 x 4096 580 -> 568, 128-row ones 1000 x 4096 x 4096
+// 273 -> 261.  Waves side by side along N (WM = 1) for heights that are no multiple of 32.
 // ------------------------------------------------------------------------------------------
 constexpr int kFK = 32;
 
@@ -1516,9 +1519,9 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restr
     const int row = i < TM ? wm * 16 * TM + i * 16 : RA + wn * 16 * TN + (i - TM) * 16;
     h.f[i] = *reinterpret_cast<const f32x4*>(s + (row + frag_row) * kFK + at);
   };
-  // The MFMAs of one half, and behind each of them, inside the cycles it takes, one of `n` reads and DMA instructions (in front of the MFMAs
-  // 300 x 4096 x 14336 323 us, so 317).  Up to two accumulators, whose MFMAs wait for each other anyway: in front of them (67 x 6144 x
-  // 4096 52.9 us, between them 57).
+  // The MFMAs of one half, and behind each of them, inside the cycles it takes, one of `n` reads and DMA instructions (in front of
+  // the MFMAs 300 x 4096 x 14336 323 us, so 317).  Up to two accumulators, whose MFMAs wait for each other anyway: in front of
+  // them (67 x 6144 x 4096 52.9 us, between them 57).
   auto multiply = [&](const Half& h, int n, auto&& other) __attribute__((always_inline)) {
     constexpr int kMfmas = 4 * TM * TN;
     constexpr bool kBetween = TM * TN > 2;
@@ -1608,7 +1611,8 @@ static void launch_f32(const float* a, const float* w, float* c, int64_t m, int6
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 GEMM for operands that are not 16-byte aligned or too long for 32-bit offsets: 64x64 tile, 256 threads, 4x4 outputs per thread, K step 16, plain FMAs.
+// fp32 GEMM for operands that are not 16-byte aligned or too long for 32-bit offsets: 64x64 tile, 256 threads, 4x4 outputs per
+// thread, K step 16, plain FMAs.
 // ------------------------------------------------------------------------------------------
 template <bool RESID>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A,

@@ -16,14 +16,17 @@ constexpr uint32_t kOffOutOfRange = 0x80000000u;   // a byte offset no buffer de
 // counts spread by about the root of their mean, hence the lines below 64 and 128.  experts_up + experts_down (with the combine), us,
 // on tiles of 32, 64, 128 and 256 rows, [hidden, ffn, experts, top_k]:
 //   rows per expert   [2048 768 128 8]      [4096 1536 64 8]      [4096 14336 8 2]        [2048 1408 64 6]
-//   16                207  215  259  245    398  404  450  469    445   447   604   666   193  205  238  231
-//   44                365  240  270  260    747  433  480  479    884   469   610   676   348  224  250  238
-//   52                381  262  275  266    802  478  488  487    887   483   613   680   372  252  254  242
-//   86                574  433  297  289    1227 845  516  518    1518  926   629   719   573  403  271  260
-//   100               684  449  309  301    1384 854  528  528    1596  939   637   730   640  410  278  268
-//   130               844  583  444  323    1770 1118 834  554    2014  1299  1074  735   812  551  403  284
-// (Between 52 and 96 rows the 256-row tile is up to 5 % ahead of the 128-row one on the narrow experts and 10 to 14 % behind on the
-// wide ones.)
+//   16                200  201              380  386              428  428                182  185
+//   22                215  209              421  395              427  432                201  189
+//   44                     230  244  247         425  458  468         452   576   651         205  224  229
+//   52                     256  256  260         472  468  476         464   587   659         234  223  227
+//   86                          280  281              503  504               613   700              250  250
+//   92                          284  284              509  510               628   703              249  253
+//   100                         325  290              521  521               640   709              257  260
+//   110                         334  295              616  528               660   718              307  266
+//   130                         398  315              790  553              1020   738              380  275
+// (Tiles that are left out are slower by more.  At the line of 96 rows some of the narrow experts have a second 128-row tile already, 325
+// against 288 us, and on the widest ones the 128-row tile stays 9 to 11 % ahead up to 110.)
 // The smaller tiles reach an expert's gate and up rows through one 32-bit offset, as the dense fused kernel does
 // ([2 ffn][hidden] below 2 GiB); the 256-row tile has a base for each.
 inline int moe_tile_rows(int64_t mean_rows, int64_t ffn, int64_t hidden) {
@@ -152,7 +155,8 @@ inline bool swiglu_few_rows(int64_t m, int64_t f) { return m <= kFewRows || (m <
 // where either form could be on a tile that does not start elsewhere (kWideTiles, few_rows of a long K) neither does.  So a row's
 // bits are the same in all calls that have these starts, and differ from those of a larger call in the order of the sums.
 // us, cold, five allocations each, gate_up of [14336 outputs 4096]: 50 rows 52.5 (45..57) -> 43.0 (42.7..43.4), 256 rows 69.3 -> 63.1;
-// [14336 6144] 50 rows 82.3 -> 65.6, 200 rows 102.6 -> 89.1; [8192 2048] 23.7 -> 23.6, 31.8 -> 30.7; [18944 3584] 73.7 -> 73.4, 98.9 -> 98.1.  Other spreads are worse or no better: 8 or 16 starts in turn 44 to 68, a random one 46.6.
+// [14336 6144] 50 rows 82.3 -> 65.6, 200 rows 102.6 -> 89.1; [8192 2048] 23.7 -> 23.6, 31.8 -> 30.7; [18944 3584] 73.7 -> 73.4,
+// 98.9 -> 98.1.  Other spreads are worse or no better: 8 or 16 starts in turn 44 to 68, a random one 46.6.
 inline int start_groups(int64_t m, int64_t n, int64_t k) {
   const bool narrow = m <= 512 && (m + 255) / 256 * ((n + 255) / 256) < kWideTiles;
   return narrow && n % 256 == 0 && k % 128 == 0 && k >= 2048 && k <= 16384 ? (int)(n / 256) : 0;
@@ -171,8 +175,9 @@ constexpr int k_start(int col, int k, int groups) { return groups ? (col / 128 %
 // a launch of a few rounds loses what its last round leaves empty and the padding of its last row tile, a smaller tile
 // reads W more often.  The rule is an estimate in ns fitted to 700 problems on all five heights (257-9000 rows, the dense
 // shapes' projections and drawn ones, cold weights): a round costs a fixed part and a part per k, a partly filled one at
-// least 0.66 of that.  Its choice is 0.2 % slower than the best of the five and 9.0 % faster than 256 rows on average, more than 1 %
-// slower than those on 4 problems, by 1.04 at most.  us, 256 rows against the choice: 600 x 14336 x 4096 SwiGLU 139 -> 121 (160 rows),
+// least 0.66 of that.  On 239 other problems (with the warm-up rule above) its choice is 0.06 % slower than the best of the five and
+// 10.2 % faster than 256 rows on average, more than 1 % slower than the best on 6, by 4.5 % at most (1567 x 7168 x 5120, 93.0 us on 224
+// rows), and than 256 rows on 2, by 1.3 %.  us, 256 rows against the choice: 600 x 14336 x 4096 SwiGLU 139 -> 121 (160 rows),
 // 1300 x 6144 x 4096 73 -> 57 (160), 3001 x 27648 x 5120 SwiGLU 1255 -> 1204 (224), 3000 x 14336 x 4096 SwiGLU 514 -> 492 (192).
 enum class LargeEpilogue { kBf16, kSwiGLU, kResidual };
 
@@ -257,9 +262,10 @@ inline int swiglu_tile_rows(int64_t m, int64_t f, int64_t k) {
 // Rows of the fp32 tile (64 columns; 128 rows: 128 columns).  128 rows where the busiest of 256 CUs then has no more outputs
 // than with 64 or 32, padding included; else an estimate in ns.  The tiles of a CU share its matrix pipes, and small ones hide
 // each other's latencies, so it has a part per tile of the busiest CU and one per tile on average; fitted to 250 problems of
-// 1 to 1024 rows (the 8B shape's projections, the tiny shape's, drawn ones).  us, against the tile of 32, 64 or 128 rows whose busiest CU
-// has the fewest outputs: 300 x 4096 x 4096 110 -> 100 and 300 x 4096 x 14336 373 -> 338 (80 rows), 67 x 6144 x 4096 77 -> 53, 56 x
-// 4096 x 4096 50 -> 43 and 15 x 1832 x 2600 30 -> 21 (16 rows); 150 other problems 9 to 10 % on average.
+// 1 to 1024 rows (the 8B shape's projections, the tiny shape's, drawn ones) on the kernel as it was before its reads went between the
+// MFMAs.  On the present one its choice is 0.1 % slower than the best of the six on 90 other problems, 3.2 % at most (37 x 5560 x
+// 648, 10.0 against 9.7 us).  us on 16, 32, 48, 64, 80 and 128 rows: 300 x 4096 x 4096 101, 103, 100, 128, 91, 247; 300 x 4096 x
+// 14336 376, 368, 360, 438, 328, 843; 300 x 28672 x 4096 698, 612, 621, 562, 576, 771; 67 x 6144 x 4096 50, 73, 57, 73, 91, 256.
 inline double f32_tile_ns(int rows, int64_t m, int64_t n, int64_t k, bool residual) {
   struct Cost { int rows; double launch, tile, residual, busiest_k, average_k; };
   constexpr Cost costs[] = {{16, 4200, 0, 242, 5.06, 0.21}, {32, 3210, 265, 289, 6.38, 2.94}, {48, 2877, 554, 450, 8.63, 4.90},

@@ -124,8 +124,8 @@ constexpr int kMaxExperts = 256, kMaxChoices = 8;
 // plan = device int32 [n_experts] (row offset of every expert; written only where the index is left to launch_moe_index);
 // block_counts = device int32 [moe_route_blocks(T)][n_experts]; slot_of = device int32
 // [T*top_k] and row_token = the token of every row (final after launch_moe_index, which has something left to do only
-// where launch_moe_route's plan does not place the pairs itself); groups = device int32 [1 + 3 * (T*top_k/tile_rows + n_experts)]: the row-tile
-// table launch_gemm_grouped reads.
+// where launch_moe_route's plan does not place the pairs itself); groups = device int32 [1 + 3 * (T*top_k/tile_rows + n_experts)]:
+// the row-tile table launch_gemm_grouped reads.
 int moe_route_blocks(int64_t n_tokens);
 void launch_moe_route(const float* logits, int32_t* ids, float* wts, int32_t* slot_of, int32_t* plan,
                       int32_t* block_counts, int32_t* groups, int32_t* row_token, int64_t n_tokens, int n_experts, int top_k,

@@ -3,8 +3,8 @@
 // Router: softmax over all experts of h W_r^T, the top_k most probable experts per token (ties:
 // lower index), probabilities renormalised over the selected ones.  The expert FFNs run as two
 // grouped GEMMs over per-expert row ranges (the first gathers the routed tokens' activations by
-// index; the second one's rows are then combined, weighted, into the residual stream).  The arithmetic of a token never depends on where in an
-// expert's row range it lands, so the (atomic, run-to-run varying) slot order does not reach the
+// index; the second one's rows are then combined, weighted, into the residual stream).  The arithmetic of a token never depends on
+// where in an expert's row range it lands, so the (atomic, run-to-run varying) slot order does not reach the
 // results.
 #include "common.h"
 #include "kernels.h"
@@ -12,17 +12,18 @@
 
 namespace fp {
 
-// Router: Q tokens per wave: probabilities, top_k selection, renormalised weights.  n_experts <= 256 (lane l holds experts l, l+64, l+128, l+192), top_k <= 8.  A selection step is
-// a chain -- the wave's maximum by DPP, then the first lane that holds it by ballot (ties: lower index) -- so a
-// wave runs the chains of its tokens side by side (29 us with one after the other on LDS-shuffle reductions).
-// Every chosen (token, expert) pair also takes a rank among the workgroup's pairs of
+// Router: Q tokens per wave: probabilities, top_k selection, renormalised weights.  n_experts <= 256 (lane l holds experts l,
+// l+64, l+128, l+192), top_k <= 8.  A selection step is a chain -- the wave's maximum by DPP, then the first lane that holds it by
+// ballot (ties: lower index) -- so a wave runs the chains of its tokens side by side (29 us with one after the other on
+// LDS-shuffle reductions).  Every chosen (token, expert) pair also takes a rank among the workgroup's pairs of
 // that expert (an LDS counter), and the workgroup leaves its per-expert counts in
 // block_counts[block][expert]: the row plan below needs no global atomics (65536 of them on 128
 // addresses cost more than the rest of the operator).
 // The selections are bound by instruction issue, so they are spread over the CUs as far as the plan's walk over the workgroups'
-// counts allows (kFusedPlanBlocks of them): below 2048 tokens workgroups of 8, two per wave, up to 8192 of 32, four per wave, then 64.  The gate
-// operator, us, against workgroups of 16 and 64, four tokens per wave: 16 tokens 22.2 -> 19.2, 200 25.6 -> 21.5, 590 26 -> 22.8, 1000 27.9 -> 25.2,
-// 1700 30 -> 28.3, 2100 35.3 -> 31.8, 4096 37.5 -> 33.8, 8192 47.6 -> 45.
+// counts allows (kFusedPlanBlocks of them): below 2048 tokens workgroups of 8, two per wave, up to 8192 of 32, four per wave, then
+// 64.  The gate operator, us, against workgroups of 16 and 64, four tokens per wave: 16 tokens 22.2 -> 19.2, 200 25.6 -> 21.5, 590
+// 26 -> 22.8, 1000 27.9 -> 25.2, 1700 30 -> 28.3, 2100 35.3 -> 31.8, 4096 37.5 -> 33.8, 8192 47.6 -> 45.  (Workgroups of 16 from
+// 2048 to 4096 tokens: not measured.)
 __host__ __device__ inline int route_tokens_per_block(int64_t n_tokens) { return n_tokens < 2048 ? 8 : n_tokens <= 8192 ? 32 : 64; }
 inline int route_tokens_per_wave(int64_t n_tokens) { return n_tokens < 2048 ? 2 : 4; }   // (four waves or more)
 
@@ -196,8 +197,8 @@ __global__ __launch_bounds__(256) void moe_index_kernel(const int32_t* __restric
 
 // Both of the above in one launch for up to kFusedPlanBlocks route workgroups: workgroup b adds up the counts itself (four threads per
 // expert, each a quarter of the route workgroups) and places the pairs of route workgroup b; the first one writes the table.  A launch
-// and the gap before it less: gate and experts_up together, us, 16 tokens 101 -> 98, 590 tokens 162 -> 160, 4096 299 -> 296, 16000 741 -> 733.
-// Every workgroup reads all counts, so their number squared bounds it: beyond the line the two kernels.
+// and the gap before it less: gate and experts_up together, us, 16 tokens 101 -> 98, 590 tokens 162 -> 160, 4096 299 -> 296, 16000
+// 741 -> 733.  Every workgroup reads all counts, so their number squared bounds it: beyond the line the two kernels.
 constexpr int kFusedPlanBlocks = 256;
 __global__ __launch_bounds__(1024) void moe_plan_index_kernel(const int32_t* __restrict__ ids,
                                                               const int32_t* __restrict__ block_counts,

@@ -64,8 +64,8 @@ def test_sizes_beyond_32_bit_offsets_run_on_the_kernel_without_them(rules, k):
 
 def test_expert_tiles_leave_room_for_uneven_counts(rules):
     """Counts spread by about the root of their mean: a tile is chosen only where two such deviations still fit it, since an
-    expert with a second tile reads its weights twice (52 rows on 64-row tiles, 8 experts of 14336 x 4096: 790 us, 613 on
-    128-row ones, 747 on 256)."""
+    expert with a second tile reads its weights twice (130 rows on 128-row tiles, 8 experts of 14336 x 4096: 1020 us, 738 on
+    256-row ones; 52 rows on 64-row tiles, 64 experts of 1408 x 2048: 234 us, 223 on 128-row ones)."""
     means = list(range(1, 400))
     for mean, tile in zip(means, map(int, rules([f"moe {m} 14336 4096" for m in means]))):
         assert tile == 256 or mean + 2 * mean ** 0.5 <= tile, (mean, tile)
