@@ -1442,7 +1442,7 @@ static void launch_bf16_w4(const bf16* a, const bf16* w, void* c, int m, int n, 
 // ds_read_b128 and step j of four multiplies the j-th of each quarter -- A and W are permuted over k
 // alike.  Chunks past K are fetched from outside the descriptor, so they read as zero (K % 4 == 0).
 // The matrix pipes bound it: 300 rows of the 8B shape's gate_up projection, several workgroups per CU, keep them busy 85 % of its
-// cycles (at 2.3 GHz), down and o, one per CU, 76 %.  Against the plain FMA kernel below gate_up 2040 -> 568 us (132 TFLOP/s of
+// cycles (at 2.3 GHz), down and o, one per CU, 75 %.  Against the plain FMA kernel below gate_up 2040 -> 568 us (132 TFLOP/s of
 // 157, row padding included), down 2476 -> 317 us; f32_tile_rows chooses the tile.  Half a k-tile's fragments are read, and the
 // next DMA issued, while the other half is multiplied: with both in front of their MFMAs, us, 16-row tiles 67 x 4096 x 14336 179
 // -> 161, 80-row ones 300 x 4096 x 14336 330 -> 317, 64-row ones 300 x 28672 x 4096 580 -> 568, 128-row ones 1000 x 4096 x 4096
