@@ -42,9 +42,9 @@ inline int moe_tile_rows(int64_t mean_rows, int64_t ffn, int64_t hidden) {
 constexpr int warm_shares(int row_tiles) { return row_tiles >= 8 ? 8 : row_tiles >= 4 ? 4 : row_tiles >= 2 ? 2 : 0; }
 
 // Whether the large tile on three stages (128 and 160 rows) asks for the L2 warm-up as well.  Three stages hide most of what
-// sharers wait for each other, and the extra requests then cost 1 to 6 %; but where K is a small odd number of times a power
-// of two from 512 on they gain more than that.  1259 problems of 257 to 3000 rows, 44 K from 320 to 28672, cold weights; time
-// with the warm-up over time without it, mean per K (powers of two times the factor):
+// sharers wait for each other, and the extra requests then cost 1 to 6 %; but where K is an odd number of times a power of two
+// from 512 on they gain more than that on average, with SwiGLU up to 7 times.  1259 problems of 257 to 3000 rows, 44 K from 320
+// to 28672, cold weights; time with the warm-up over time without it, mean per K (powers of two times the factor):
 //   factor        bf16 and residual                       SwiGLU
 //   1             1.011 to 1.051                          1.021 to 1.078
 //   3  (x 512 up) 0.952 0.956 0.970 0.978, 24576 1.010    0.987 1.008 1.019 1.019, 24576 1.025
@@ -54,10 +54,12 @@ constexpr int warm_shares(int row_tiles) { return row_tiles >= 8 ? 8 : row_tiles
 //   27, 37        1.014 1.018 1.060                       1.064 1.074 1.077
 //   x 256         0.987 to 1.019                          1.001 to 1.041
 //   less          0.971 to 1.034                          1.004 to 1.040
-// (Single problems differ from these means by up to 10 %: which lines crowd one another depends on all three sizes.)
+// Single problems differ from these means by up to 10 %: which lines crowd one another depends on all three sizes.  So the large
+// factors stay in for bf16 and residual: 18944 would gain 6 % without, but 5120 columns of 27648, nine row counts from 1885 to
+// 3846, lose 2 % on average and up to 5.
 constexpr bool warm_three_stages(int k, bool swiglu) {
   const int power = k & -k;
-  return power >= 512 && k > power && k < (swiglu ? 6 : 16) * power;
+  return power >= 512 && k > power && (!swiglu || k < 8 * power);
 }
 
 // Column tiles of 256 from which on a launch of one row tile is not cut over K and does not take the 128-column tile.
