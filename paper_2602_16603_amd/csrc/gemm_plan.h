@@ -177,9 +177,9 @@ constexpr int k_start(int col, int k, int groups) { return groups ? (col / 128 %
 // a launch of a few rounds loses what its last round leaves empty and the padding of its last row tile, a smaller tile
 // reads W more often.  The rule is an estimate in ns fitted to 700 problems on all five heights (257-9000 rows, the dense
 // shapes' projections and drawn ones, cold weights): a round costs a fixed part and a part per k, a partly filled one at
-// least 0.66 of that.  On 239 other problems (with the warm-up rule above) its choice is 0.06 % slower than the best of the five and
-// 10.2 % faster than 256 rows on average, more than 1 % slower than the best on 6, by 4.5 % at most (1567 x 7168 x 5120, 93.0 us on 224
-// rows), and than 256 rows on 2, by 1.3 %.  us, 256 rows against the choice: 600 x 14336 x 4096 SwiGLU 139 -> 121 (160 rows),
+// least 0.66 of that.  On 239 other problems (with the warm-up rule above) its choice is 0.04 % slower than the best of the five and
+// 10.1 % faster than 256 rows on average, more than 1 % slower than the best on 2, by 4.7 % at most (1217 x 13816 x 9024 SwiGLU, 524
+// us on 192 rows, 500 on 224), and nowhere more than 0.8 % slower than 256 rows.  us, 256 rows against the choice: 600 x 14336 x 4096 SwiGLU 139 -> 121 (160 rows),
 // 1300 x 6144 x 4096 73 -> 57 (160), 3001 x 27648 x 5120 SwiGLU 1255 -> 1204 (224), 3000 x 14336 x 4096 SwiGLU 514 -> 492 (192).
 enum class LargeEpilogue { kBf16, kSwiGLU, kResidual };
 
