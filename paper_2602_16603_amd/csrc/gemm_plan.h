@@ -179,8 +179,9 @@ constexpr int k_start(int col, int k, int groups) { return groups ? (col / 128 %
 // shapes' projections and drawn ones, cold weights): a round costs a fixed part and a part per k, a partly filled one at
 // least 0.66 of that.  On 239 other problems (with the warm-up rule above) its choice is 0.04 % slower than the best of the five and
 // 10.1 % faster than 256 rows on average, more than 1 % slower than the best on 2, by 4.7 % at most (1217 x 13816 x 9024 SwiGLU, 524
-// us on 192 rows, 500 on 224), and nowhere more than 0.8 % slower than 256 rows.  us, 256 rows against the choice: 600 x 14336 x 4096 SwiGLU 139 -> 121 (160 rows),
-// 1300 x 6144 x 4096 73 -> 57 (160), 3001 x 27648 x 5120 SwiGLU 1255 -> 1204 (224), 3000 x 14336 x 4096 SwiGLU 514 -> 492 (192).
+// us on 192 rows, 500 on 224), and nowhere more than 0.8 % slower than 256 rows.  us, 256 rows against the choice: 600 x 14336 x
+// 4096 SwiGLU 139 -> 121 (160 rows), 1300 x 6144 x 4096 73 -> 57 (160), 3001 x 27648 x 5120 SwiGLU 1255 -> 1204 (224), 3000 x 14336
+// x 4096 SwiGLU 514 -> 492 (192).
 enum class LargeEpilogue { kBf16, kSwiGLU, kResidual };
 
 inline double large_tile_ns(int rows, int64_t m, int64_t tiles_n, int64_t k, LargeEpilogue epilogue) {
